@@ -66,10 +66,10 @@ typedef enum { MXQ_SCALE_E8M0 = 0, MXQ_SCALE_E4M3 = 1, MXQ_SCALE_UE5M3 = 2 } mxq
  *              minimal SSE is kept (brute-force paragraph, Section 2).  126 candidates for
  *              E4M3, 254 for UE5M3, the 255 powers of two 2^(byte-127), byte 0 .. 254, for E8M0.
  *   BRUTE_PRUNED  the same result as BRUTE, bit for bit, but candidates that provably cannot
- *              win are skipped: scales so large that the elements certain to quantise to zero
- *              alone cost more than the abs-max scale's whole SSE, and scales so small that the
- *              clipping error of the abs-max element alone does.  2 to 5 times faster than
- *              BRUTE.  A step toward cheaper near-optimal selection (Conclusion).
+ *              win are skipped: scales whose half is a scale code too and fits the block at least
+ *              as well, and scales so small that the clipping error of the abs-max element alone
+ *              costs more than the best candidate so far.  4 to 12 times faster than BRUTE.  A step
+ *              toward cheaper near-optimal selection (Conclusion).
  * 4OVER6* and BRUTE_PRUNED with E8M0 return MXQ_ERR_UNSUPPORTED (Eq. 4 rounds amax / M to the
  * scale format, which the floor rule of Eq. 1 does not define). */
 typedef enum {

@@ -43,8 +43,7 @@ struct BruteState {
 // the wavefront improved is the position of the minimum looked up (the first position that
 // equals it: the lowest code on a tie inside the group; between groups "strictly less" keeps
 // the earlier, lower code).  A candidate costs half an instruction here; measured against a
-// compare and two selects per candidate it is faster also when most groups improve (the
-// pruned search).
+// compare and two selects per candidate it is faster also when most groups improve.
 template <int B>
 struct GroupArgMin {
     static constexpr int NBLK = BruteState<B>::NBLK;
@@ -59,19 +58,7 @@ struct GroupArgMin {
     }
     template <int POS>
     __device__ __forceinline__ void put(int k, float sse) { s[k][POS] = sse; }
-    // Take position 7 of block slot k out of this group (the code there is not a number).
-    __device__ __forceinline__ void drop_last(int k, bool drop) { s[k][7] = drop ? __builtin_inff() : s[k][7]; }
-
     __device__ __forceinline__ void end(BruteState<B>& st, uint32_t code0) const
-    {
-        uint32_t c0[NBLK];
-        bool ok[NBLK];
-#pragma unroll
-        for (int k = 0; k < NBLK; ++k) { c0[k] = code0; ok[k] = true; }
-        end(st, c0, ok);
-    }
-    // code0 per block slot; a slot with ok == false takes no part in this group
-    __device__ __forceinline__ void end(BruteState<B>& st, const uint32_t (&code0)[NBLK], const bool (&ok)[NBLK]) const
     {
         float gmin[NBLK];
         bool any = false;
@@ -80,7 +67,7 @@ struct GroupArgMin {
             const float a = fminf(fminf(s[k][0], s[k][1]), s[k][2]);
             const float b = fminf(fminf(s[k][3], s[k][4]), s[k][5]);
             gmin[k] = fminf(fminf(a, b), fminf(s[k][6], s[k][7]));
-            any |= ok[k] && gmin[k] < st.best_sse[k];
+            any |= gmin[k] < st.best_sse[k];
         }
         if (__builtin_amdgcn_ballot_w64(any) == 0ull) return;           // wave-uniform
 #pragma unroll
@@ -88,8 +75,8 @@ struct GroupArgMin {
             uint32_t pos = 7u;
 #pragma unroll
             for (int i = 6; i >= 0; --i) pos = (s[k][i] == gmin[k]) ? (uint32_t)i : pos;
-            const bool better = ok[k] && gmin[k] < st.best_sse[k];
-            st.best_code[k] = better ? code0[k] + pos : st.best_code[k];
+            const bool better = gmin[k] < st.best_sse[k];
+            st.best_code[k] = better ? code0 + pos : st.best_code[k];
             st.best_sse[k] = better ? gmin[k] : st.best_sse[k];
         }
     }
@@ -149,213 +136,155 @@ __device__ __forceinline__ void try_binade(const float (&v)[8], const float (&w)
 }
 
 // ---------------------------------------------------------------------------------------
-// Pruned search (recipe BRUTE_PRUNED): same result as the full enumeration, bit for bit,
-// fewer candidates.  Three facts bound the useful codes of a block with abs-max `amax`:
-//   (hi) S >= 4*amax quantises every element to zero, so all such candidates share one SSE
-//        (sum of squares); the first of them has the lowest code, the others can only tie.
-//   (hi2) under any scale S >= S0 an element with |v| < S0/2 quantises to 0 or to S/2, with a
-//        residual of |v| or of S/2 - |v| >= S0/2 - |v| > 0, so its square in the SSE is at least
-//        min(fl(v^2), fl(fl(S0/2 - |v|)^2)) (for |v| < S0/4, where it is certain to vanish, that is
-//        fl(v^2) itself); the other elements contribute >= +0, and an fp32 sum of non-negative
-//        terms does not fall when a term grows.  The tree sum of these terms is therefore a lower
-//        bound of the SSE of every scale >= S0; it grows with S0, and once it exceeds U (below)
-//        every higher code loses.  On weights this ends the window two binades above the abs-max
-//        scale, where (hi) alone lets it run to five or six.
-//   (lo) while 6*S < amax the abs-max element saturates and alone contributes
-//        fl(fl(amax - 6S)^2); fp32 sums of non-negative terms never fall below a term, so that
-//        is a lower bound of the candidate's SSE.  Once it exceeds U, the SSE of a reference
-//        candidate (the abs-max scale), the candidate cannot win; the bound falls with S, so
-//        the losers form a prefix of the code range (tested per binade, bisection as fall-back).
-// Windows of different blocks sit at different places of the code range (wherever the block's
-// abs-max puts them) but have nearly the same width, about one binade below the abs-max scale to
-// two or three above ((hi) alone: five to six).  So the scan is wave-uniform in RELATIVE terms:
-// in step t every block tries the t-th binade of its OWN window (the power of two handed to the
-// conversion instruction is a per-lane register, the mantissa stays uniform), t running up to
-// the widest window of the wavefront.  A wavefront with 128 small blocks then visits hardly more
-// candidates than its widest block alone would, where a scan of the union of the absolute
-// windows degrades with the number of blocks per wavefront and with the spread of their
-// magnitudes.  Lanes whose window has ended are masked out; the sub-normal codes are one uniform
-// group in front.  Every block visits its own window in ascending code order.  (A second scan
-// over the union of the absolute windows, chosen per wavefront when it has no more steps, was
-// measured: at best 3 % faster on weights at b = 4, slower everywhere else.)
+// Pruned search (recipe BRUTE_PRUNED): same result as the full enumeration, bit for bit, from about
+// ten candidates per block.  Two facts bound the codes that can win a block with abs-max `amax`:
+//   (hi) A scale S >= amax / 3.5 is never better than S / 2 where S / 2 is itself a code.  The grid
+//        of S / 2 is {0, .25, .5, .75, 1, 1.5, 2, 3} S: it holds every point of the grid of S up to
+//        3 S, and no element lies beyond 3.5 S, so none is nearer to 4 S or 6 S than to 3 S (at
+//        exactly 3.5 S the two are equally far).  Every residual under S / 2 is therefore no larger
+//        than under S; fp32 rounding, squaring and the sum tree are monotone, so the same holds for
+//        the pinned fp32 SSE, and on a tie the lower code S / 2 wins.  S / 2 is a code for every
+//        code from 16 on and for the even ones below; what is left above amax / 3.5 are the odd
+//        codes below 16 (the sub-normals and the first binade, spaced by eps), and of those none
+//        above the first S >= 4 amax, from which on everything quantises to zero.
+//   (lo) While 6 S < amax the abs-max element saturates and alone contributes fl(fl(amax - 6 S)^2);
+//        fp32 sums of non-negative terms never fall below a term, so that is a lower bound of the
+//        candidate's SSE.  Once it exceeds the best SSE found so far, this code loses and, because the
+//        bound grows as S falls, so do all lower ones.
+// So the scan starts at the abs-max code (Eq. 2), walks up to amax / 3.5 (five to seven codes; odd
+// codes to 15 beyond that where the scales are that small), then down until (lo) stops it (one to
+// three codes).  Every block walks from its OWN code: scale and reciprocal are per-lane registers,
+// the wavefront takes as many steps as its longest block, and blocks of very different magnitude
+// cost each other nothing.  Bound by vector issue: about 220 cycles a step, ten or eleven steps.
+// Measured on 4096 x 14336 bf16 weights, against a scan of whole binades in a window closed by a
+// weaker upper bound: E4M3 b = 16 236 -> 127 us, b = 4 346 -> 160 us; UE5M3 b = 16 277 -> 132 us,
+// b = 4 373 -> 160 us.
 // ---------------------------------------------------------------------------------------
+
+// Value of a scale code, sub-normal codes included: the code's bits moved into the fp32 exponent and
+// mantissa are off by a power of two only, and the multiplication is exact.  (Beyond the last code
+// the value is meaningless but harmless.)
 template <int FMT>
-__device__ __forceinline__ uint32_t ceil_code(float y)      // smallest code >= 1 with value >= y
+__device__ __forceinline__ float walk_scale(uint32_t code)
 {
-    uint32_t c = sf_encode_rne<FMT>(y);
-    if (sf_decode<FMT>(c) < y) c = min(c + 1u, (uint32_t)ScaleFmt<FMT>::kMaxCode);
-    return max(c, 1u);
+    return u2f(code << 20) * u2f((uint32_t)(127 + 127 - ScaleFmt<FMT>::kBias) << 23);
 }
 
-// Per block of the lane: the window [lo, hi] of codes that can win.
+// Codes and SSE of the lane's blocks under the scales S.
+template <int B>
+__device__ __forceinline__ void walk_step(const float (&v)[8], const float (&S)[BruteState<B>::NBLK], uint32_t& packed,
+                                          float (&sse)[4])
+{
+    constexpr int NBLK = BruteState<B>::NBLK;
+    constexpr int EPB = (B < 8) ? B : 8;
+    float y[8];
+#pragma unroll
+    for (int k = 0; k < NBLK; ++k) {
+        const Recip r = make_recip_from(S[k], __builtin_amdgcn_rcpf(S[k]));
+#pragma unroll
+        for (int i = 0; i < EPB; ++i) y[k * EPB + i] = quot(v[k * EPB + i], r);
+    }
+    packed = e2m1_pack8(y, 1.0f);
+    float q[8], sq[8];
+    e2m1_unpack8(packed, 1.0f, q);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) { const float e = __builtin_fmaf(-q[j], S[j / EPB], v[j]); sq[j] = e * e; }
+    block_sse<B>(sq, sse);
+}
+
+// Keep the blocks in which this step was better (a take-over of codes, SSE and packed nibbles).
+template <int B>
+__device__ __forceinline__ void walk_keep(const bool (&better)[BruteState<B>::NBLK],
+                                          const uint32_t (&code)[BruteState<B>::NBLK], const float (&sse)[4],
+                                          uint32_t packed_now, uint32_t& packed, BruteState<B>& st)
+{
+    constexpr int NBLK = BruteState<B>::NBLK;
+#pragma unroll
+    for (int k = 0; k < NBLK; ++k) {
+        st.best_code[k] = better[k] ? code[k] : st.best_code[k];
+        st.best_sse[k] = better[k] ? sse[k] : st.best_sse[k];
+    }
+    if constexpr (NBLK == 1) packed = better[0] ? packed_now : packed;
+}
+
 template <int B, int FMT>
-__device__ __forceinline__ void prune_window(const float (&v)[8], uint32_t (&lo_k)[BruteState<B>::NBLK],
-                                             uint32_t (&hi_k)[BruteState<B>::NBLK])
+__device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_t& packed, BruteState<B>& st)
 {
     constexpr int NBLK = BruteState<B>::NBLK;
     constexpr int LANES = (B < 8) ? 1 : B / 8;
     constexpr int EPB = (B < 8) ? B : 8;
-    float amax[NBLK], y[8], S[NBLK];
-    uint32_t cref[NBLK];
+    constexpr int kMax = ScaleFmt<FMT>::kMaxCode;
+    const float inv_eps4 = 4.0f * u2f((uint32_t)(127 + ScaleFmt<FMT>::kBias + 2) << 23);      // 4 / eps
+
+    float amax[NBLK], S[NBLK], sse[4];
+    uint32_t start[NBLK], code[NBLK], halved[NBLK], last_odd[NBLK];
+    block_amax<NBLK, EPB, LANES>(v, amax);
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) {
-        float a = 0.0f;
-#pragma unroll
-        for (int i = 0; i < EPB; ++i) a = fmaxf(a, __builtin_fabsf(v[k * EPB + i]));
-        amax[k] = group_max<LANES>(a);
-        cref[k] = max(sf_encode_rne<FMT>(sixth_of(amax[k])), 1u);
-        S[k] = sf_decode<FMT>(cref[k]);
-        const Recip r = make_recip(S[k]);
-#pragma unroll
-        for (int i = 0; i < EPB; ++i) y[k * EPB + i] = quot(v[k * EPB + i], r);
+        start[k] = max(sf_encode_rne<FMT>(sixth_of(amax[k])), 1u);
+        // the first code with 3.5 S >= amax (3.5 S is exact), one past the last code if there is none
+        const uint32_t h = sf_encode_rne<FMT>(amax[k] * (float)(1.0 / 3.5));
+        halved[k] = h + ((3.5f * walk_scale<FMT>(h) < amax[k]) ? 1u : 0u);
+        // the first code >= 1 with S >= 4 amax if that is below 16, else 15
+        last_odd[k] = (uint32_t)fminf(fmaxf(__builtin_ceilf(amax[k] * inv_eps4), 1.0f), 15.0f);
+        S[k] = walk_scale<FMT>(start[k]);
+        code[k] = start[k];
+        st.best_sse[k] = __builtin_inff();
+        st.best_code[k] = 1u;
     }
-    const uint32_t packed = e2m1_pack8(y, 1.0f);
-    float q[8], sq[8], U[4];
-    e2m1_unpack8(packed, 1.0f, q);
+    uint32_t now;
+    walk_step<B>(v, S, now, sse);
+    {
+        bool better[NBLK];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) { const float e = __builtin_fmaf(-q[j], S[j / EPB], v[j]); sq[j] = e * e; }
-    const float p0 = sq[0] + sq[1], p1 = sq[2] + sq[3], p2 = sq[4] + sq[5], p3 = sq[6] + sq[7];
-    if constexpr (B == 2) { U[0] = p0; U[1] = p1; U[2] = p2; U[3] = p3; }
-    else if constexpr (B == 4) { U[0] = p0 + p1; U[1] = p2 + p3; }
-    else U[0] = group_sum<B / 8>((p0 + p1) + (p2 + p3));
+        for (int k = 0; k < NBLK; ++k) better[k] = sse[k] < st.best_sse[k];
+        packed = now;
+        walk_keep<B>(better, code, sse, now, packed, st);
+    }
 
-    // (hi2): first binade above the reference binade whose lowest scale S0 = 2^(ef - bias) already
-    // loses.  thr = S0 / 4; the sum uses the tree of the block SSE.
-    constexpr int kMaxUp = 5;                                            // (hi) ends the window at five or six anyway
-    constexpr uint32_t kNone = 1u << 20;
-    uint32_t dz[NBLK];
-#pragma unroll
-    for (int k = 0; k < NBLK; ++k) dz[k] = kNone;
-    float vsq[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) vsq[j] = v[j] * v[j];
-    // Only the widest window of a wavefront costs steps, so the search is for the first binade d at
-    // which EVERY block of the wavefront loses (a block is given the lowest tested d at which it
-    // loses: never too low).  With 32 blocks per wavefront that is two or three binades up and the
-    // tests simply ascend from 2; with 128 or more (b <= 4) it is usually four or five, so d = 4 is
-    // probed first, then 5 if some block survives it, else 3 and 2 as long as all blocks lose.
-    int d = (B <= 4) ? 4 : 2;
-    bool descending = false;
-#pragma unroll 1
-    for (int it = 0; it < 4; ++it) {                                     // uniform
-        float thr[NBLK], zs[8], Z[4];
-#pragma unroll
-        for (int k = 0; k < NBLK; ++k)
-            thr[k] = u2f(((cref[k] >> 3) + (uint32_t)(d + 127 - ScaleFmt<FMT>::kBias - 2)) << 23);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float half = 2.0f * thr[j / EPB];                      // S0 / 2
-            const float gap = half - __builtin_fabsf(v[j]);
-            zs[j] = (gap > 0.0f) ? fminf(vsq[j], gap * gap) : 0.0f;     // |v| < S0/4: the minimum is v^2
-        }
-        const float z0 = zs[0] + zs[1], z1 = zs[2] + zs[3], z2 = zs[4] + zs[5], z3 = zs[6] + zs[7];
-        if constexpr (B == 2) { Z[0] = z0; Z[1] = z1; Z[2] = z2; Z[3] = z3; }
-        else if constexpr (B == 4) { Z[0] = z0 + z1; Z[1] = z2 + z3; }
-        else Z[0] = group_sum<B / 8>((z0 + z1) + (z2 + z3));
-        bool survives = false;
+    while (true) {                                                      // upwards: a strictly lower SSE wins
+        bool alive[NBLK], any = false;
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) {
-            if (Z[k] > U[k]) dz[k] = min(dz[k], (uint32_t)d);
-            else survives = true;
+            code[k] += 1u;
+            const bool below = code[k] < halved[k];
+            code[k] = below ? code[k] : (code[k] | 1u);
+            alive[k] = below || code[k] <= last_odd[k];
+            any |= alive[k];
+            S[k] = walk_scale<FMT>(code[k]);
         }
-        const bool all_lose = __builtin_amdgcn_ballot_w64(survives) == 0ull;
-        if constexpr (B <= 4) {
-            if (it == 0) descending = all_lose;
-            if (descending) { if (!all_lose || d == 2) break; --d; }
-            else { if (all_lose || d == kMaxUp) break; ++d; }
-        } else {
-            if (all_lose || d == kMaxUp) break;
-            ++d;
-        }
+        if (__builtin_amdgcn_ballot_w64(any) == 0ull) break;            // uniform
+        walk_step<B>(v, S, now, sse);
+        bool better[NBLK];
+#pragma unroll
+        for (int k = 0; k < NBLK; ++k) better[k] = alive[k] && sse[k] < st.best_sse[k];
+        walk_keep<B>(better, code, sse, now, packed, st);
     }
 
-    // (lo) at the granularity the scan has anyway: the highest code of a binade saturates least, so
-    // a binade whose highest code loses is lost as a whole, with everything below it.  Nearly every
-    // block settles in the first or second binade below its reference; the bisection over the
-    // codes runs only if some block of the wavefront has not settled after three.
-    uint32_t lo_b[NBLK];
-    bool unsettled = false;
 #pragma unroll
-    for (int k = 0; k < NBLK; ++k) {
-        const uint32_t er = cref[k] >> 3;
-        lo_b[k] = kNone;
+    for (int k = 0; k < NBLK; ++k) code[k] = start[k];
+    while (true) {                                                      // downwards: the lower code wins a tie
+        bool alive[NBLK], any = false;
 #pragma unroll
-        for (int t = 1; t <= 3; ++t) {
-            // highest code of binade er - t: 1.875 * 2^(er - t - bias); the sub-normal "binade" 0
-            // ends with 0.875 * 2^(1 - bias)
-            const int ef = (int)er - t;
-            const float top_scale = (ef >= 1) ? 1.875f * u2f((uint32_t)(ef + 127 - ScaleFmt<FMT>::kBias) << 23)
-                                              : 0.875f * u2f((uint32_t)(1 + 127 - ScaleFmt<FMT>::kBias) << 23);
-            const float lim = 6.0f * top_scale;
-            const float dd = amax[k] - lim;
-            const bool loser = ef < 0 || ((lim < amax[k]) && (dd * dd > U[k]));
-            if (lo_b[k] == kNone && loser) lo_b[k] = (uint32_t)max(ef + 1, 0) << 3;
+        for (int k = 0; k < NBLK; ++k) {
+            code[k] = (code[k] != 0u) ? code[k] - 1u : 0u;
+            S[k] = walk_scale<FMT>(code[k]);
+            const float over = amax[k] - 6.0f * S[k];
+            alive[k] = code[k] != 0u && !(over > 0.0f && over * over > st.best_sse[k]);
+            any |= alive[k];
         }
-        unsettled |= lo_b[k] == kNone;
-    }
-    const bool bisect = __builtin_amdgcn_ballot_w64(unsettled) != 0ull;  // uniform
-
+        if (__builtin_amdgcn_ballot_w64(any) == 0ull) break;            // uniform
+        walk_step<B>(v, S, now, sse);
+        bool better[NBLK];
 #pragma unroll
-    for (int k = 0; k < NBLK; ++k) {
-        uint32_t lo = 1u, hi = cref[k];                 // the bound at cref is <= U: not a loser
-        if (bisect) {
-#pragma unroll 1
-            for (int it = 0; it < 8; ++it) {
-                if (lo < hi) {
-                    const uint32_t mid = (lo + hi) >> 1;
-                    const float lim = 6.0f * sf_decode<FMT>(mid);
-                    const float d = amax[k] - lim;
-                    const bool loser = (lim < amax[k]) && (d * d > U[k]);
-                    if (loser) lo = mid + 1u; else hi = mid;
-                }
-            }
-        } else {
-            lo = max(lo_b[k], 1u);
-        }
-        lo_k[k] = lo;
-        hi_k[k] = ceil_code<FMT>(4.0f * amax[k]);
-        if (dz[k] != kNone) hi_k[k] = min(hi_k[k], (((cref[k] >> 3) + dz[k]) << 3) - 1u);
+        for (int k = 0; k < NBLK; ++k) better[k] = alive[k] && sse[k] <= st.best_sse[k];
+        walk_keep<B>(better, code, sse, now, packed, st);
     }
-}
 
-// One candidate of the relative scan: mantissa MI (uniform), power of two per block.
-template <int B, int MI, int POS, class G>
-__device__ __forceinline__ void try_candidate_rel(const float (&v)[8], const float (&w)[8],
-                                                  const float (&scale2)[BruteState<B>::NBLK], G& g)
-{
-    constexpr int EPB = (B < 8) ? B : 8;
-    const uint32_t packed = e2m1_pack8_scales<EPB>(w, scale2);
-    float q2[8], sq[8];
-    e2m1_unpack2<0>(packed, scale2[0 / EPB], q2[0], q2[1]);
-    e2m1_unpack2<1>(packed, scale2[2 / EPB], q2[2], q2[3]);
-    e2m1_unpack2<2>(packed, scale2[4 / EPB], q2[4], q2[5]);
-    e2m1_unpack2<3>(packed, scale2[6 / EPB], q2[6], q2[7]);
+    if constexpr (NBLK > 1) {                                           // several blocks: the codes of the winners once
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        float e;
-        if constexpr (MI == 0) e = v[j] - q2[j];
-        else e = __builtin_fmaf(-q2[j], mant_value(MI), v[j]);
-        sq[j] = e * e;
-    }
-    const float p0 = sq[0] + sq[1], p1 = sq[2] + sq[3], p2 = sq[4] + sq[5], p3 = sq[6] + sq[7];
-    if constexpr (B == 2) {
-        g.template put<POS>(0, p0); g.template put<POS>(1, p1);
-        g.template put<POS>(2, p2); g.template put<POS>(3, p3);
-    } else if constexpr (B == 4) {
-        g.template put<POS>(0, p0 + p1); g.template put<POS>(1, p2 + p3);
-    } else {
-        g.template put<POS>(0, group_sum<B / 8>((p0 + p1) + (p2 + p3)));
-    }
-    __builtin_amdgcn_sched_barrier(0);
-}
-
-template <int B, int MI, class G>
-__device__ __forceinline__ void try_binade_rel_from(const float (&v)[8], const float (&w)[8][8],
-                                                    const float (&scale2)[BruteState<B>::NBLK], G& g)
-{
-    if constexpr (MI < 8) {
-        try_candidate_rel<B, MI, MI>(v, w[MI], scale2, g);
-        try_binade_rel_from<B, MI + 1>(v, w, scale2, g);
+        for (int k = 0; k < NBLK; ++k) S[k] = walk_scale<FMT>(st.best_code[k]);
+        walk_step<B>(v, S, packed, sse);
     }
 }
 
@@ -376,16 +305,13 @@ __device__ __forceinline__ void try_pow2_from(const float (&v)[8], uint32_t code
 }
 
 // Search for the lane's 8 values (already divided by T): winner codes, packed nibbles, SSE.
-template <int B, int FMT, bool PRUNE>
+template <int B, int FMT>
 __device__ __forceinline__ void brute_search(const float (&v)[8], uint32_t& packed, BruteState<B>& st)
 {
     constexpr int NBLK = BruteState<B>::NBLK;
     constexpr int EPB = (B < 8) ? B : 8;
     constexpr int bias = ScaleFmt<FMT>::kBias;
     constexpr int emin = 1 - bias;                                      // exponent of the first binade
-
-    constexpr uint32_t lo_w = 1u, hi_w = (uint32_t)ScaleFmt<FMT>::kMaxCode;
-    static_assert(!PRUNE, "the pruned search is brute_search_pruned");
 
     float w[8][8];
 #pragma unroll
@@ -402,7 +328,7 @@ __device__ __forceinline__ void brute_search(const float (&v)[8], uint32_t& pack
     const float s1 = u2f((uint32_t)(127 + emin - 3) << 23);
     const float s2 = u2f((uint32_t)(127 + emin - 2) << 23);
     const float s4 = u2f((uint32_t)(127 + emin - 1) << 23);
-    if (lo_w < 8u) {                                                    // uniform
+    {
         GroupArgMin<B> g;
         g.begin();
         try_candidate<B, 0, 0>(v, w[0], s1, g);
@@ -416,94 +342,9 @@ __device__ __forceinline__ void brute_search(const float (&v)[8], uint32_t& pack
     }
 
     // normal codes: exponent field ef = 1 .. kMaxCode >> 3, value (1 + mi/8) * 2^(ef - bias)
-    for (uint32_t ef = max(lo_w >> 3, 1u); ef <= (hi_w >> 3); ++ef) {
+    for (uint32_t ef = 1u; ef <= (uint32_t)(ScaleFmt<FMT>::kMaxCode >> 3); ++ef) {
         const float scale2 = u2f((ef + (uint32_t)(127 - bias)) << 23);
         try_binade<B, FMT>(v, w, scale2, ef << 3, st);
-    }
-
-    // codes of the winners
-    float y[8];
-#pragma unroll
-    for (int k = 0; k < NBLK; ++k) {
-        const Recip r = make_recip(sf_decode<FMT>(st.best_code[k]));
-#pragma unroll
-        for (int i = 0; i < EPB; ++i) y[k * EPB + i] = quot(v[k * EPB + i], r);
-    }
-    packed = e2m1_pack8(y, 1.0f);
-}
-
-// Pruned search: windows, then the relative scan described above.
-template <int B, int FMT>
-__device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_t& packed, BruteState<B>& st)
-{
-    constexpr int NBLK = BruteState<B>::NBLK;
-    constexpr int EPB = (B < 8) ? B : 8;
-    constexpr int bias = ScaleFmt<FMT>::kBias;
-    constexpr int emin = 1 - bias;
-    constexpr int top = ScaleFmt<FMT>::kMaxCode >> 3;                   // last binade; its position 7 is not a number
-
-    uint32_t lo_k[NBLK], hi_k[NBLK];
-    prune_window<B, FMT>(v, lo_k, hi_k);
-    // Steps of the scan: every block starts at the first binade of its OWN window, so the
-    // wavefront needs as many steps as its widest window has binades.
-    int w_max = -1;
-    bool sub = false;
-#pragma unroll
-    for (int k = 0; k < NBLK; ++k) {
-        w_max = max(w_max, (int)(hi_k[k] >> 3) - max((int)(lo_k[k] >> 3), 1));
-        sub |= lo_k[k] < 8u;
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) w_max = max(w_max, __shfl_xor(w_max, off, 64));
-    w_max = __builtin_amdgcn_readfirstlane(w_max);
-    const bool any_sub = __builtin_amdgcn_ballot_w64(sub) != 0ull;
-
-    float w[8][8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) w[0][j] = v[j];
-#pragma unroll
-    for (int i = 1; i < 8; ++i) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) w[i][j] = quot(v[j], Recip{mant_rhi(i), mant_rlo(i)});
-    }
-#pragma unroll
-    for (int k = 0; k < NBLK; ++k) { st.best_sse[k] = __builtin_inff(); st.best_code[k] = 1u; }
-
-    if (any_sub) {                                                      // uniform: codes 1 .. 7
-        const float s1 = u2f((uint32_t)(127 + emin - 3) << 23);
-        const float s2 = u2f((uint32_t)(127 + emin - 2) << 23);
-        const float s4 = u2f((uint32_t)(127 + emin - 1) << 23);
-        GroupArgMin<B> g;
-        g.begin();
-        try_candidate<B, 0, 0>(v, w[0], s1, g);
-        try_candidate<B, 0, 1>(v, w[0], s2, g);
-        try_candidate<B, 4, 2>(v, w[4], s2, g);
-        try_candidate<B, 0, 3>(v, w[0], s4, g);
-        try_candidate<B, 2, 4>(v, w[2], s4, g);
-        try_candidate<B, 4, 5>(v, w[4], s4, g);
-        try_candidate<B, 6, 6>(v, w[6], s4, g);
-        g.end(st, 1u);
-    }
-
-    for (int t = 0; t <= w_max; ++t) {                                  // uniform
-        float scale2[NBLK];
-        uint32_t code0[NBLK];
-        bool ok[NBLK], last[NBLK];
-#pragma unroll
-        for (int k = 0; k < NBLK; ++k) {
-            const int ef = max((int)(lo_k[k] >> 3), 1) + t;             // this block's binade in step t
-            ok[k] = ef <= (int)(hi_k[k] >> 3);
-            const int efc = min(ef, top);
-            last[k] = efc == top;
-            scale2[k] = u2f((uint32_t)(efc + 127 - bias) << 23);
-            code0[k] = (uint32_t)efc << 3;
-        }
-        GroupArgMin<B> g;
-        g.begin();
-        try_binade_rel_from<B, 0>(v, w, scale2, g);
-#pragma unroll
-        for (int k = 0; k < NBLK; ++k) g.drop_last(k, last[k]);
-        g.end(st, code0, ok);
     }
 
     // codes of the winners
@@ -602,7 +443,7 @@ brute_kernel(const void* __restrict__ x, int64_t n_full, float T_arg,
         BruteState<B> st;
         if constexpr (FMT == kE8M0) brute_search_pow2<B>(v, packed, st);
         else if constexpr (PRUNE) brute_search_pruned<B, FMT>(v, packed, st);
-        else brute_search<B, FMT, false>(v, packed, st);
+        else brute_search<B, FMT>(v, packed, st);
         float clip[4];
         if (clip_out) {                                                 // uniform
             float S_best[NBLK];
@@ -659,7 +500,7 @@ brute_tail_kernel(const void* __restrict__ x, int64_t first, int count, float T_
     BruteState<B> st;
     if constexpr (FMT == kE8M0) brute_search_pow2<B>(v, packed, st);
     else if constexpr (PRUNE) brute_search_pruned<B, FMT>(v, packed, st);
-    else brute_search<B, FMT, false>(v, packed, st);
+    else brute_search<B, FMT>(v, packed, st);
     float S_best[NBLK], clip[4];
     for (int k = 0; k < NBLK; ++k) S_best[k] = brute_scale_value<FMT>(st.best_code[k]);
     brute_clip_sse<B>(v, S_best, clip);

@@ -83,6 +83,17 @@ MXQ_HD Recip make_recip(float d)
     return r;
 }
 
+// The same from a hardware reciprocal: `approx` is 1/d to within one ulp.  Scaled down by 2^-22 it
+// is certainly below 1/d, so rho > 0; rho < 2^-21 and has at most 7 significant bits (hi*d ends at
+// 2^-28), so the fma is exact; hi + lo = 1/d to within 2^-41.
+MXQ_HD Recip make_recip_from(float d, float approx)
+{
+    Recip r;
+    r.hi = approx * (1.0f - 0x1p-22f);
+    r.lo = __builtin_fmaf(-r.hi, d, 1.0f) * r.hi;
+    return r;
+}
+
 MXQ_HD float quot(float v, Recip r)
 {
     return __builtin_fmaf(v, r.hi, v * r.lo);

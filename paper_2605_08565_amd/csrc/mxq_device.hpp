@@ -200,6 +200,67 @@ __device__ __forceinline__ float group_sum(float v)
     return v;
 }
 
+// Block SSE: balanced tree in index order, inside the lane and then across the block's lanes.
+// For b < 8 the lane holds 8/b blocks; their sums come back in sse[0 .. 8/b).
+template <int B>
+__device__ __forceinline__ void block_sse(const float (&sq)[8], float (&sse)[4])
+{
+    const float p0 = sq[0] + sq[1], p1 = sq[2] + sq[3], p2 = sq[4] + sq[5], p3 = sq[6] + sq[7];
+    if constexpr (B == 2) {
+        sse[0] = p0; sse[1] = p1; sse[2] = p2; sse[3] = p3;
+    } else if constexpr (B == 4) {
+        sse[0] = p0 + p1; sse[1] = p2 + p3;
+    } else {
+        sse[0] = group_sum<B / 8>((p0 + p1) + (p2 + p3));
+    }
+}
+
+// Division by the per-tensor scale T of hierarchical scaling: div_by_T (reciprocal + one FMA
+// refinement, exact inside the range fast_division_ok / fast_division_unsafe_amax delimit) or the
+// plain IEEE division.
+enum : int { kNoT = 0, kFastT = 1, kSlowT = 2, kDynT = 3 };   // kDynT: T comes from device memory, one of
+                                                              // the other three is chosen at run time
+
+template <int NBLK, int EPB, int LANES>
+__device__ __forceinline__ void block_amax(const float (&v)[8], float (&amax)[NBLK])
+{
+#pragma unroll
+    for (int k = 0; k < NBLK; ++k) {
+        float a = 0.0f;
+#pragma unroll
+        for (int i = 0; i < EPB; ++i) a = fmaxf(a, __builtin_fabsf(v[k * EPB + i]));
+        amax[k] = group_max<LANES>(a);
+    }
+}
+
+// Division by the per-tensor scale (MODE: none / reciprocal-refined / plain) and the block
+// abs-max of the adjusted values.
+template <int MODE, int NBLK, int EPB, int LANES>
+__device__ __forceinline__ void adjust_and_amax(float (&v)[8], float T, float rT, float (&amax)[NBLK])
+{
+    if constexpr (MODE == kSlowT) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = v[i] / T;            // IEEE division
+        block_amax<NBLK, EPB, LANES>(v, amax);
+    } else if constexpr (MODE == kFastT) {
+        float raw[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { raw[i] = v[i]; v[i] = div_by_T(raw[i], T, rT); }
+        block_amax<NBLK, EPB, LANES>(v, amax);
+        bool unsafe = false;
+#pragma unroll
+        for (int k = 0; k < NBLK; ++k)                  // 0 < amax < 2^-40  or  amax > 2^90
+            unsafe |= fast_division_unsafe_amax(amax[k]);
+        if (__builtin_amdgcn_ballot_w64(unsafe) != 0ull) {       // rare, wave-uniform
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = raw[i] / T;
+            block_amax<NBLK, EPB, LANES>(v, amax);
+        }
+    } else {
+        block_amax<NBLK, EPB, LANES>(v, amax);
+    }
+}
+
 // ---------------------------------------------------------------------------------------
 // Loads: 8 consecutive elements per lane, widened to fp32.
 // ---------------------------------------------------------------------------------------

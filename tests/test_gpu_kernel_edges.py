@@ -1,0 +1,57 @@
+"""GPU results at the sizes and values where a kernel's own branches meet: window edges of the
+pruned scale search, tile and tail edges.  Everything is compared bit for bit with the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_08565_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mxq():
+    from paper_2605_08565_amd import mxq as M
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    M.lib()
+    return M
+
+
+def same(gpu, ref):
+    torch.cuda.synchronize()
+    for g, r, name in zip(gpu, ref, ("codes", "scales", "sse")):
+        g = g.cpu().numpy()
+        assert (g.view(np.uint32) == r.view(np.uint32)).all() if name == "sse" else (g == r).all(), name
+
+
+def window_edge_blocks(oracle, fmt, block, seed):
+    """fp32 blocks whose abs-max sits on, just below and just above 3.5, 4, 5, 6 and 1/4 times a scale,
+    the other elements on grid points and rounding ties of that scale, for codes over the whole range."""
+    rng = np.random.default_rng(seed)
+    top = oracle.scale_max_code(fmt)
+    codes = sorted(set(range(1, 34)) | {top - 9, top - 8, top - 1, top} | set(rng.integers(34, top, 24).tolist()))
+    grid = np.array([0, .25, .5, .75, 1, 1.25, 1.5, 1.75, 2, 2.5, 3, 3.5], np.float32)
+    rows = []
+    for c in codes:
+        s = np.float32(oracle.scale_decode(fmt, c))
+        for f in (3.5, 4.0, 5.0, 6.0, 0.25, 40.0):
+            a = np.float32(f) * s
+            for amax in (a, np.nextafter(a, np.float32(0)), np.nextafter(a, np.float32(np.inf))):
+                v = rng.choice(grid, block) * s if rng.random() < 0.5 else rng.random(block).astype(np.float32) * amax
+                v = np.minimum(v.astype(np.float32), amax) * rng.choice([-1, 1], block)
+                v[rng.integers(block)] = amax
+                rows.append(v.astype(np.float32))
+    return np.stack(rows)
+
+
+@pytest.mark.parametrize("fmt", [1, 2])
+@pytest.mark.parametrize("block", [2, 4, 8, 16, 128])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_pruned_search_window_edges(oracle, mxq, fmt, block, dtype):
+    x = window_edge_blocks(oracle, fmt, block, seed=31 * block + fmt)
+    if dtype == "bf16":
+        x = W.f32_to_bf16_bits(x)
+    print(f"[edges] pruned fmt={fmt} b={block} {dtype} blocks={x.shape[0]}", flush=True)
+    for T in (1.0, 0.7):
+        ref = oracle.quantize(x, block, fmt, 4, tensor_scale=T)
+        same(mxq.quantize(mxq.from_bits(x), block, fmt, mxq.RECIPE_BRUTE_PRUNED, tensor_scale=T), ref)

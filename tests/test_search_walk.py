@@ -1,0 +1,72 @@
+"""What the pruned scale search rests on, checked on the CPU.
+
+A scale S with 3.5 S >= amax never has a lower block SSE than S / 2 where S / 2 is a scale code too
+(from code 16 on, and for the even codes below), so the search stops there.  Checked against the
+oracle's SSE of every code, in its pinned fp32 arithmetic, together with the set of codes the search
+visits: the lowest code of minimal SSE must always be among them.  And the element quotient the search
+forms from the hardware reciprocal."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CLANG = shutil.which("amdclang++") or "/opt/rocm/llvm/bin/clang++"
+
+
+def blocks(kind, b, n, rng):
+    if kind == "student":
+        return (rng.standard_t(4, size=(n, b)) * 0.02).astype(np.float32)
+    if kind == "tiny":                                     # scales in the sub-normal codes
+        return (rng.standard_normal((n, b)) * 2.0 ** rng.integers(-18, -4, (n, 1))).astype(np.float32)
+    # abs-max and elements on grid points and ties of some scale
+    s = (1 + rng.integers(0, 8, (n, 1)) / 8.0) * 2.0 ** rng.integers(-10, 4, (n, 1))
+    v = rng.integers(0, 15, (n, b)) * 0.25 * s
+    v[:, 0] = rng.choice([3.5, 4.0, 5.0, 6.0], n) * s[:, 0]
+    return v.astype(np.float32)
+
+
+@pytest.mark.parametrize("fmt", [1, 2])
+@pytest.mark.parametrize("b", [2, 4, 16])
+@pytest.mark.parametrize("kind", ["student", "tiny", "grid"])
+def test_half_scale_dominates_and_walk_finds_the_winner(oracle, fmt, b, kind):
+    rng = np.random.default_rng(17 * fmt + b + len(kind))
+    top = oracle.scale_max_code(fmt)
+    scale = np.array([oracle.scale_decode(fmt, c) for c in range(top + 1)])
+    for v in blocks(kind, b, 40, rng):
+        sse = np.array([oracle.block_sse(v, fmt, c)[1] for c in range(top + 1)], np.float32)
+        amax = float(np.abs(v).max())
+        codes = np.arange(1, top + 1)
+        has_half = (codes >= 16) | (codes % 2 == 0)
+        half = np.where(codes >= 16, codes - 8, codes // 2)
+        dominated = has_half & (3.5 * scale[codes] >= amax)
+        assert (scale[half[has_half]] * 2 == scale[codes[has_half]]).all()
+        assert (sse[half[dominated]] <= sse[codes[dominated]]).all()
+
+        start = max(int(oracle.quantize(v.reshape(1, b), b, fmt, 0)[1][0, 0]), 1)
+        best = sse[start]
+        seen = {start}
+        for c in codes[start:]:                            # upwards: what is not dominated, up to 4 amax
+            if not dominated[c - 1] and (c < 16 or 3.5 * scale[c] < amax) and scale[c - 1] < 4 * amax:
+                seen.add(int(c))
+                best = min(best, sse[c])
+        for c in range(start - 1, 0, -1):                  # downwards until the clipping bound exceeds the best
+            over = np.float32(amax) - np.float32(6.0) * np.float32(scale[c])
+            if over > 0 and np.float32(over * over) > best:
+                break
+            seen.add(c)
+            best = min(best, sse[c])
+        assert 1 + int(np.argmin(sse[1:])) in seen, (kind, b, fmt)
+
+
+def test_quotient_from_hardware_reciprocal(tmp_path):
+    if "fma" not in open("/proc/cpuinfo").read():
+        pytest.skip("host CPU has no FMA instruction")
+    exe = str(tmp_path / "reciprocal_check")
+    subprocess.run([CLANG, "-O2", "-std=c++17", "-ffp-contract=off", "-mfma", "-Wall", "-Werror",
+                    os.path.join(HERE, "host", "reciprocal_check.cpp"), "-o", exe, "-lm"], check=True)
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    print(res.stdout)
+    assert res.returncode == 0 and "bad=0" in res.stdout
