@@ -201,7 +201,8 @@ MXQ_API int mxq_dequantize_hier(const uint8_t* codes, const uint8_t* scales,
 /*
  * mxq_tensor_absmax -- first stage of hierarchical scaling (Section 2): max |x_i| over the
  * whole tensor, written as one float to absmax_out (device, 4-byte aligned).  x 16-byte
- * aligned.  An empty tensor writes 0.
+ * aligned.  An empty tensor writes 0.  One launch up to 160 KiB of input, two beyond (the first
+ * clears the word).
  */
 MXQ_API int mxq_tensor_absmax(const void* x, int64_t rows, int64_t cols, int x_dtype,
                       float* absmax_out, void* stream);
@@ -226,7 +227,7 @@ MXQ_API int mxq_tensor_absmax_acc(const void* x, int64_t rows, int64_t cols, int
 
 /*
  * mxq_tensor_absmax_ws -- mxq_tensor_absmax in ONE launch (that one needs a second, tiny launch
- * that clears the output word first) and without a precondition on the output word (unlike
+ * that clears the output word first, except for small tensors) and without a precondition on the output word (unlike
  * mxq_tensor_absmax_acc): the workgroups meet in a caller-owned workspace, and the one that
  * arrives last writes the output.  One graph node instead of two; the tail of the kernel is
  * longer than that of the other two forms (three dependent device-scope atomics), so on large

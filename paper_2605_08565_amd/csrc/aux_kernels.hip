@@ -167,7 +167,8 @@ hipError_t launch_dequant(const DequantArgs& a)
 
 // Tensor abs-max.  |x| of finite fp32 values orders like the unsigned integer bits & 0x7fffffff,
 // so the reduction is an integer max; the workgroups' partial results meet in one 32-bit atomic
-// max on a device word.  Two closing schemes:
+// max on a device word.  Two closing schemes (and a third for tensors small enough for one workgroup,
+// further down):
 //   * no workspace: the word is the caller's output, which a one-thread kernel clears first (a
 //     kernel, not a memset node, so the pair can be captured in a graph) -- two launches -- or
 //     which the caller guarantees to hold zero (or a maximum to be continued) -- one launch; that
@@ -185,12 +186,10 @@ constexpr int kAbsItems = 4;
 constexpr int kAbsThreads = 1024;
 constexpr int kAbsMaxGrid = 256;
 
-template <int DT, bool TICKET>
-__global__ void __launch_bounds__(kAbsThreads)
-absmax_kernel(const void* __restrict__ x, int64_t n, uint32_t* __restrict__ out, uint32_t* __restrict__ ws,
-              uint32_t* __restrict__ clear_word)
+// Maximum over the workgroup's tiles (bit pattern); valid in thread 0.
+template <int DT>
+__device__ __forceinline__ uint32_t workgroup_absmax(const void* __restrict__ x, int64_t n)
 {
-    if (clear_word && blockIdx.x == 0 && threadIdx.x == 0) *clear_word = 0u;      // for a LATER launch
     constexpr int64_t kVec = (DT == kBF16) ? 1 : 2;               // 128-bit vectors per chunk
     const int64_t n_vec = (n >> 3) * kVec;                         // complete vectors
     const int64_t tile = (int64_t)kAbsThreads * kAbsItems;
@@ -236,9 +235,22 @@ absmax_kernel(const void* __restrict__ x, int64_t n, uint32_t* __restrict__ out,
     __shared__ uint32_t part[kAbsThreads / 64];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
     __syncthreads();
+    uint32_t w = 0u;
     if (threadIdx.x == 0) {
-        uint32_t w = part[0];
+        w = part[0];
         for (int i = 1; i < kAbsThreads / 64; ++i) w = max(w, part[i]);
+    }
+    return w;
+}
+
+template <int DT, bool TICKET>
+__global__ void __launch_bounds__(kAbsThreads)
+absmax_kernel(const void* __restrict__ x, int64_t n, uint32_t* __restrict__ out, uint32_t* __restrict__ ws,
+              uint32_t* __restrict__ clear_word)
+{
+    if (clear_word && blockIdx.x == 0 && threadIdx.x == 0) *clear_word = 0u;      // for a LATER launch
+    const uint32_t w = workgroup_absmax<DT>(x, n);
+    if (threadIdx.x == 0) {
         if constexpr (!TICKET) {
             // The word only grows during a call, so a workgroup whose maximum does not exceed the
             // value it reads (at device scope, past the per-CU cache) has nothing to add: after
@@ -261,6 +273,22 @@ absmax_kernel(const void* __restrict__ x, int64_t n, uint32_t* __restrict__ out,
     }
 }
 
+// A tensor that one workgroup reads in the time a second launch costs: no word to clear, no atomic,
+// no workspace -- one launch for every form but the running maximum (whose word other streams may be
+// raising at the same time; it is one launch anyway).  One compute unit draws about 50 GB/s, two
+// launches cost about 5 us on the GPU whatever the size (graph replay, bf16): 16 KiB 2.6 against
+// 4.6 us, 128 KiB 4.4 against 5.2 us, 256 KiB 6.6 against 5.2 us, so the line lies at 160 KiB.
+// Launched one by one from Python the second launch costs another 3.5 us of host time.
+constexpr int64_t kAbsSmallBytes = 160 << 10;
+
+template <int DT>
+__global__ void __launch_bounds__(kAbsThreads)
+absmax_small_kernel(const void* __restrict__ x, int64_t n, uint32_t* __restrict__ out)
+{
+    const uint32_t w = workgroup_absmax<DT>(x, n);
+    if (threadIdx.x == 0) *out = w;
+}
+
 // `ws`: the two-word workspace of the ticket scheme, or NULL.  `accumulate` (without ws): the output
 // word is not cleared first; `clear_word` (accumulate only, may be NULL) is set to zero instead.
 hipError_t launch_absmax(const void* x, int64_t n, int dtype, float* out, uint32_t* ws, bool accumulate,
@@ -269,6 +297,12 @@ hipError_t launch_absmax(const void* x, int64_t n, int dtype, float* out, uint32
     if (accumulate && n == 0) {
         if (!clear_word) return hipSuccess;
         hipLaunchKernelGGL(absmax_clear_kernel, dim3(1), dim3(1), 0, stream, (uint32_t*)clear_word);
+        return hipGetLastError();
+    }
+    if (!accumulate && n > 0 && n * (dtype == kBF16 ? 2 : 4) <= kAbsSmallBytes) {
+        const dim3 one(1), block(kAbsThreads);
+        if (dtype == kBF16) hipLaunchKernelGGL(absmax_small_kernel<kBF16>, one, block, 0, stream, x, n, (uint32_t*)out);
+        else hipLaunchKernelGGL(absmax_small_kernel<kF32>, one, block, 0, stream, x, n, (uint32_t*)out);
         return hipGetLastError();
     }
     if ((!ws && !accumulate) || n == 0) {

@@ -55,3 +55,22 @@ def test_pruned_search_window_edges(oracle, mxq, fmt, block, dtype):
     for T in (1.0, 0.7):
         ref = oracle.quantize(x, block, fmt, 4, tensor_scale=T)
         same(mxq.quantize(mxq.from_bits(x), block, fmt, mxq.RECIPE_BRUTE_PRUNED, tensor_scale=T), ref)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tensor_absmax_around_the_one_workgroup_limit(oracle, mxq, dtype):
+    """One workgroup up to 160 KiB, two launches beyond; the maximum first, last and in between; all forms."""
+    limit = (160 << 10) // (4 if dtype == "f32" else 2)
+    ws, words = mxq.absmax_workspace(), torch.full((3,), 7.0, device="cuda")
+    for n in (1, 7, 8, 9, 8 * 1024, 4 * 8 * 1024 + 3, limit - 8, limit, limit + 1, limit + 8):
+        for at in {0, n // 2, n - 1}:
+            x = np.linspace(-1, 1, n, dtype=np.float32).reshape(1, n)
+            x[0, at] = -3.0
+            x = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+            print(f"[edges] absmax {dtype} n={n} at={at}", flush=True)
+            g = mxq.from_bits(x)
+            mxq.tensor_absmax(g, out=words[0:1])
+            mxq.tensor_absmax(g, out=words[1:2], workspace=ws)
+            mxq.tensor_absmax_static(g, words[2:3])
+            assert words.cpu().tolist() == [3.0] * 3
+    assert int(ws.sum()) == 0
