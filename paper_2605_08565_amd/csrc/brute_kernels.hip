@@ -409,7 +409,7 @@ __device__ __forceinline__ void brute_clip_sse(const float (&v)[8], const float 
 
 template <int DT, int B, int FMT, bool HAS_T, bool PRUNE>
 __global__ void __launch_bounds__(kThreads)
-brute_kernel(const void* __restrict__ x, int64_t n_full, float T_arg,
+brute_kernel(const void* __restrict__ x, int64_t n_full, int tail, float T_arg,
              const float* __restrict__ absmax_dev, float* __restrict__ t_out,
              uint32_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ sse_out,
              float* __restrict__ clip_out)
@@ -427,10 +427,14 @@ brute_kernel(const void* __restrict__ x, int64_t n_full, float T_arg,
     const int64_t stride = (int64_t)gridDim.x * kThreads;
     int64_t chunk = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     int64_t base = chunk - (threadIdx.x & 63);
+    // n not a multiple of 8 (b = 2 or 4 only): one more chunk, of `tail` elements, read and written
+    // element-wise by the lane it falls to
+    const int64_t n_chunks = n_full + ((B < 8 && tail != 0) ? 1 : 0);
 
-    for (; base < n_full; base += stride, chunk += stride) {
+    for (; base < n_chunks; base += stride, chunk += stride) {
         float v[8];
         if (chunk < n_full) load8<DT>(x, chunk << 3, v);
+        else if (B < 8 && chunk < n_chunks) load_partial<DT>(x, chunk << 3, tail, v);
         else {
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[i] = 0.0f;
@@ -470,47 +474,16 @@ brute_kernel(const void* __restrict__ x, int64_t n_full, float T_arg,
                     if (clip_out) clip_out[blk0 + k] = clip[k];
                 }
             }
-        }
-    }
-}
-
-// Ragged tail (n not a multiple of 8; b = 2 or 4 only): lane 0 of one wavefront.
-template <int DT, int B, int FMT, bool HAS_T, bool PRUNE>
-__global__ void __launch_bounds__(64)
-brute_tail_kernel(const void* __restrict__ x, int64_t first, int count, float T_arg,
-                  const float* __restrict__ absmax_dev, float* __restrict__ t_out,
-                  uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ sse_out,
-                  float* __restrict__ clip_out)
-{
-    constexpr int NBLK = BruteState<B>::NBLK;
-    float T = T_arg;
-    if constexpr (HAS_T) {
-        if (absmax_dev) {
-            T = tensor_scale_of<FMT>(*absmax_dev);
-            if (t_out && threadIdx.x == 0) *t_out = T;      // t_out is passed only when no main kernel runs
-        }
-    }
-    float v[8];
-    load_partial<DT>(x, first, (threadIdx.x == 0) ? count : 0, v);
-    if constexpr (HAS_T) {
+        } else if (B < 8 && chunk < n_chunks) {
+            for (int i = 0; i < tail / 2; ++i) reinterpret_cast<uint8_t*>(codes)[chunk * 4 + i] = (uint8_t)(packed >> (8 * i));
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = v[i] / T;
-    }
-    uint32_t packed;
-    BruteState<B> st;
-    if constexpr (FMT == kE8M0) brute_search_pow2<B>(v, packed, st);
-    else if constexpr (PRUNE) brute_search_pruned<B, FMT>(v, packed, st);
-    else brute_search<B, FMT>(v, packed, st);
-    float S_best[NBLK], clip[4];
-    for (int k = 0; k < NBLK; ++k) S_best[k] = brute_scale_value<FMT>(st.best_code[k]);
-    brute_clip_sse<B>(v, S_best, clip);
-    if (threadIdx.x != 0) return;
-    for (int i = 0; i < count / 2; ++i) codes[first / 2 + i] = (uint8_t)(packed >> (8 * i));
-    for (int k = 0; k < NBLK; ++k) {
-        if (k < count / B) {
-            scales[first / B + k] = (uint8_t)st.best_code[k];
-            if (sse_out) sse_out[first / B + k] = st.best_sse[k];
-            if (clip_out) clip_out[first / B + k] = clip[k];
+            for (int k = 0; k < NBLK; ++k) {
+                if (k < tail / B) {
+                    scales[chunk * NBLK + k] = (uint8_t)st.best_code[k];
+                    if (sse_out) sse_out[chunk * NBLK + k] = st.best_sse[k];
+                    if (clip_out) clip_out[chunk * NBLK + k] = clip[k];
+                }
+            }
         }
     }
 }
@@ -521,29 +494,14 @@ static hipError_t launch_f(const StreamArgs& a)
     const int64_t n_full = a.n / 8;
     const int count = (int)(a.n - n_full * 8);
     const bool has_t = (a.absmax_dev != nullptr) || (a.T != 1.0f);
-    if (n_full > 0) {
-        const int64_t need = (n_full + kThreads - 1) / kThreads;
-        const dim3 grid((unsigned)(need < 256 * 8 ? need : 256 * 8)), block(kThreads);
-        if (has_t)
-            hipLaunchKernelGGL((brute_kernel<DT, B, FMT, true, PRUNE>), grid, block, 0, a.stream,
-                               a.x, n_full, a.T, a.absmax_dev, a.t_out, (uint32_t*)a.codes, a.scales, a.sse, a.clip);
-        else
-            hipLaunchKernelGGL((brute_kernel<DT, B, FMT, false, PRUNE>), grid, block, 0, a.stream,
-                               a.x, n_full, a.T, a.absmax_dev, a.t_out, (uint32_t*)a.codes, a.scales, a.sse, a.clip);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if constexpr (B < 8) {
-        if (count > 0) {
-            float* t_out_tail = (n_full > 0) ? nullptr : a.t_out;
-            if (has_t)
-                hipLaunchKernelGGL((brute_tail_kernel<DT, B, FMT, true, PRUNE>), dim3(1), dim3(64), 0, a.stream,
-                                   a.x, n_full * 8, count, a.T, a.absmax_dev, t_out_tail, a.codes, a.scales, a.sse, a.clip);
-            else
-                hipLaunchKernelGGL((brute_tail_kernel<DT, B, FMT, false, PRUNE>), dim3(1), dim3(64), 0, a.stream,
-                                   a.x, n_full * 8, count, a.T, a.absmax_dev, t_out_tail, a.codes, a.scales, a.sse, a.clip);
-        }
-    }
+    const int64_t need = (n_full + (count != 0 ? 1 : 0) + kThreads - 1) / kThreads;
+    const dim3 grid((unsigned)(need < 256 * 8 ? need : 256 * 8)), block(kThreads);
+    if (has_t)
+        hipLaunchKernelGGL((brute_kernel<DT, B, FMT, true, PRUNE>), grid, block, 0, a.stream, a.x, n_full, count, a.T,
+                           a.absmax_dev, a.t_out, (uint32_t*)a.codes, a.scales, a.sse, a.clip);
+    else
+        hipLaunchKernelGGL((brute_kernel<DT, B, FMT, false, PRUNE>), grid, block, 0, a.stream, a.x, n_full, count, a.T,
+                           a.absmax_dev, a.t_out, (uint32_t*)a.codes, a.scales, a.sse, a.clip);
     return hipGetLastError();
 }
 

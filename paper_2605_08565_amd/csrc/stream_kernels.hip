@@ -223,6 +223,10 @@ struct Slices {
     uint32_t count;        // number of slices
     uint32_t last;         // chunks in the last slice, 1 .. 256
     __device__ __forceinline__ uint32_t chunks(uint32_t s) const { return (s + 1u == count) ? last : (uint32_t)kThreads; }
+    __device__ __forceinline__ uint64_t elements() const                             // in all complete chunks
+    {
+        return (count == 0u) ? 0u : ((uint64_t)(count - 1u) * kThreads + last) * 8u;
+    }
 };
 
 // Stores of one slice.
@@ -312,11 +316,37 @@ __device__ __forceinline__ void stream_step(RawChunk<DT> (&cur)[kItems], RawChun
                                                   out[i].clip);
 }
 
+// Ragged tail: when n is not a multiple of 8 (only possible for b = 2 or 4) the last `count` < 8
+// elements are handled by one lane of an extra workgroup of the same launch, reading and writing
+// element-wise.  (A launch of its own, as it was, cost more than it does on any tensor that fits in a
+// few microseconds: 2563 x 4110 elements, b = 2, 18.4 us against 14.9 us for 2563 x 4112.)
+template <int DT, int B, int FMT, bool FOUR6, int TMODE, bool CLIP>
+__device__ __forceinline__ void stream_tail(const void* __restrict__ x, uint64_t first, uint32_t count, float T, float rT,
+                                            int tdyn, bool pz, const ScaleEntry* tab, uint8_t* __restrict__ codes,
+                                            uint8_t* __restrict__ scales, float* __restrict__ sse_out,
+                                            float* __restrict__ clip_out)
+{
+    if (threadIdx.x >= 64u) return;                                  // one wavefront, its first lane stores
+    TileOut<B> o;
+    float v[8];
+    load_partial<DT>(x, (int64_t)first, (threadIdx.x == 0) ? (int)count : 0, v);
+    process_chunk<B, FMT, FOUR6, TMODE, CLIP>(v, T, rT, tdyn, pz, tab, o.packed, o.code, o.sse, o.clip);
+    if (threadIdx.x != 0) return;
+    for (uint32_t i = 0; i < count / 2u; ++i) codes[first / 2u + i] = (uint8_t)(o.packed >> (8u * i));
+    for (uint32_t k = 0; k < (uint32_t)TileOut<B>::NBLK; ++k) {
+        if (k < count / (uint32_t)B) {
+            scales[first / B + k] = (uint8_t)o.code[k];
+            if (sse_out) sse_out[first / B + k] = o.sse[k];
+            if constexpr (CLIP) { if (clip_out) clip_out[first / B + k] = o.clip[k]; }
+        }
+    }
+}
+
 // Main kernel: the complete chunks, grid-stride over workgroup tiles with two register buffers
 // alternating between "being processed" and "in flight".
 template <int DT, int B, int FMT, bool FOUR6, int TMODE, bool CLIP>
 __global__ void __launch_bounds__(kThreads)
-stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunks, float T_arg, int pz,
+stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunks, uint32_t tail, float T_arg, int pz,
               const float* __restrict__ absmax_dev, float* __restrict__ t_out,
               uint32_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ sse_out,
               float* __restrict__ clip_out)
@@ -326,9 +356,9 @@ stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunk
     u32x4* wave_lds = xpose + ((DT == kF32) ? 2u * (threadIdx.x & ~63u) : 0u);
 
     const Slices sl{n_slices, last_chunks};
-    const uint32_t stride = gridDim.x * (uint32_t)kItems;
+    const uint32_t workers = gridDim.x - ((B < 8 && tail != 0u) ? 1u : 0u);       // the last workgroup takes the tail
+    const uint32_t stride = workers * (uint32_t)kItems;
     uint32_t s0 = blockIdx.x * (uint32_t)kItems;
-    if (s0 >= sl.count) return;                                      // whole workgroup
     float T = T_arg;
     int tdyn = TMODE;
     if constexpr (TMODE == kDynT) {                  // T from the abs-max left in device memory, if there is one
@@ -337,6 +367,15 @@ stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunk
         if (t_out && blockIdx.x == 0 && threadIdx.x == 0) *t_out = T;
     }
     const float rT = 1.0f / T;                                       // correctly rounded
+    if constexpr (B < 8) {
+        if (tail != 0u && blockIdx.x == workers) {
+            if constexpr (FMT != kE8M0) fill_scale_table<FMT>(tab);
+            stream_tail<DT, B, FMT, FOUR6, TMODE, CLIP>(x, sl.elements(), tail, T, rT, tdyn, pz != 0, tab,
+                                                        reinterpret_cast<uint8_t*>(codes), scales, sse_out, clip_out);
+            return;
+        }
+    }
+    if (s0 >= sl.count) return;                                      // whole workgroup
 
     // the first tile's loads are in flight while the scale table is built
     RawChunk<DT> bufA[kItems], bufB[kItems];
@@ -379,7 +418,9 @@ struct BatchArgs {
     float* sse[kMaxBatch];
     uint32_t first[kMaxBatch + 1];        // first global slice of tensor t; first[count] = total
     uint32_t last[kMaxBatch];             // chunks in tensor t's last slice, 1 .. 256
+    uint32_t tail[kMaxBatch];             // elements behind the complete chunks, 0 .. 7 (b = 2, 4)
     uint32_t count;
+    uint32_t tails;                       // workgroups behind the workers, one per tensor, or 0
 };
 
 struct TileRef {                          // one tile = one slice of one tensor
@@ -425,8 +466,19 @@ stream_batch_kernel(const BatchArgs a, int pz)
     u32x4* wave_lds = xpose + ((DT == kF32) ? 2u * (threadIdx.x & ~63u) : 0u);
 
     const uint32_t total = a.first[a.count];
-    const uint32_t stride = gridDim.x;
+    const uint32_t stride = gridDim.x - ((B < 8) ? a.tails : 0u);
     uint32_t g = blockIdx.x;
+    if constexpr (B < 8) {
+        if (g >= stride) {
+            const uint32_t t = g - stride;
+            if (a.tail[t] == 0u) return;
+            if constexpr (FMT != kE8M0) fill_scale_table<FMT>(tab);
+            stream_tail<DT, B, FMT, FOUR6, kNoT, false>(a.x[t], Slices{a.first[t + 1] - a.first[t], a.last[t]}.elements(),
+                                                        a.tail[t], 1.0f, 1.0f, kNoT, pz != 0, tab,
+                                                        reinterpret_cast<uint8_t*>(a.codes[t]), a.scales[t], a.sse[t], nullptr);
+            return;
+        }
+    }
     if (g >= total) return;                                          // whole workgroup
 
     RawChunk<DT> bufA[kItems], bufB[kItems];
@@ -457,43 +509,6 @@ stream_batch_kernel(const BatchArgs a, int pz)
     store_slice<B>(out[0], prev.s, prev.sl, a.codes[prev.t], a.scales[prev.t], a.sse[prev.t], nullptr);
 }
 
-// Ragged tail: when n is not a multiple of 8 (only possible for b = 2 or 4) the last
-// `count` < 8 elements are handled by lane 0 of one wavefront, reading and writing element-wise.
-template <int DT, int B, int FMT, bool FOUR6, int TMODE>
-__global__ void __launch_bounds__(64)
-stream_tail_kernel(const void* __restrict__ x, int64_t first, int count, float T_arg, int pz,
-                   const float* __restrict__ absmax_dev, float* __restrict__ t_out,
-                   uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ sse_out,
-                   float* __restrict__ clip_out)
-{
-    constexpr int NBLK = (B < 8) ? 8 / B : 1;
-    __shared__ ScaleEntry tab[(FMT == kE8M0) ? 1 : 256];
-    if constexpr (FMT != kE8M0) fill_scale_table<FMT>(tab);
-
-    float v[8], sse_sel[4], clip_sel[4];
-    uint32_t packed, code_out[NBLK];
-    load_partial<DT>(x, first, (threadIdx.x == 0) ? count : 0, v);
-    float T = T_arg;
-    int tdyn = TMODE;
-    if constexpr (TMODE == kDynT) {
-        if (absmax_dev) T = tensor_scale_of<FMT>(*absmax_dev);
-        tdyn = (T == 1.0f) ? kNoT : kSlowT;
-        if (t_out && threadIdx.x == 0) *t_out = T;      // t_out is passed only when no main kernel runs
-    }
-    process_chunk<B, FMT, FOUR6, TMODE, true>(v, T, 1.0f / T, tdyn, pz != 0, tab, packed, code_out, sse_sel, clip_sel);
-    if (threadIdx.x != 0) return;
-    for (int i = 0; i < count / 2; ++i) codes[first / 2 + i] = (uint8_t)(packed >> (8 * i));
-    if constexpr (B < 8) {
-        for (int k = 0; k < NBLK; ++k) {
-            if (k < count / B) {
-                scales[first / B + k] = (uint8_t)code_out[k];
-                if (sse_out) sse_out[first / B + k] = sse_sel[k];
-                if (clip_out) clip_out[first / B + k] = clip_sel[k];
-            }
-        }
-    }
-}
-
 // ------------------------------------------------------------------------------ dispatch
 
 template <int DT, int B, int FMT, bool FOUR6>
@@ -505,36 +520,22 @@ static hipError_t launch_recipe(const StreamArgs& a, int pz)
     // device memory the kernel makes the same choice itself
     // the variant that also writes the clipping-only SSE exists for the run-time mode only
     const int tmode = (a.absmax_dev || a.clip) ? kDynT : (a.T == 1.0f) ? kNoT : (fast_division_ok(a.T) ? kFastT : kSlowT);
-    if (n_full > 0) {
-        const int64_t slices = (n_full + kThreads - 1) / kThreads;
-        const uint32_t n_slices = (uint32_t)slices;
-        const uint32_t last = (uint32_t)(n_full - (slices - 1) * kThreads);
-        const dim3 grid(stream_grid(((slices + kItems - 1) / kItems) * kThreads)), block(kThreads);
-        uint32_t* codes = reinterpret_cast<uint32_t*>(a.codes);
+    const int64_t slices = (n_full + kThreads - 1) / kThreads;
+    const uint32_t n_slices = (uint32_t)slices;
+    const uint32_t last = (uint32_t)(n_full - (slices - 1) * kThreads);              // not read when there is no slice
+    const uint32_t tail = (B < 8) ? (uint32_t)count : 0u;
+    const int workers = (n_slices == 0u) ? 0 : stream_grid(((slices + kItems - 1) / kItems) * kThreads);
+    const dim3 grid((unsigned)workers + (tail != 0u ? 1u : 0u)), block(kThreads);
+    uint32_t* codes = reinterpret_cast<uint32_t*>(a.codes);
 #define MXQ_LAUNCH_STREAM(MODE, CLIP)                                                                 \
     hipLaunchKernelGGL((stream_kernel<DT, B, FMT, FOUR6, MODE, CLIP>), grid, block, 0, a.stream, a.x,       \
-                       n_slices, last, a.T, pz, a.absmax_dev, a.t_out, codes, a.scales, a.sse, a.clip)
-        if (a.clip) MXQ_LAUNCH_STREAM(kDynT, true);
-        else if (tmode == kNoT) MXQ_LAUNCH_STREAM(kNoT, false);
-        else if (tmode == kFastT) MXQ_LAUNCH_STREAM(kFastT, false);
-        else if (tmode == kSlowT) MXQ_LAUNCH_STREAM(kSlowT, false);
-        else MXQ_LAUNCH_STREAM(kDynT, false);
+                       n_slices, last, tail, a.T, pz, a.absmax_dev, a.t_out, codes, a.scales, a.sse, a.clip)
+    if (a.clip) MXQ_LAUNCH_STREAM(kDynT, true);
+    else if (tmode == kNoT) MXQ_LAUNCH_STREAM(kNoT, false);
+    else if (tmode == kFastT) MXQ_LAUNCH_STREAM(kFastT, false);
+    else if (tmode == kSlowT) MXQ_LAUNCH_STREAM(kSlowT, false);
+    else MXQ_LAUNCH_STREAM(kDynT, false);
 #undef MXQ_LAUNCH_STREAM
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if constexpr (B < 8) {
-        if (count > 0) {
-            float* t_out_tail = (n_full > 0) ? nullptr : a.t_out;
-#define MXQ_LAUNCH_TAIL(MODE)                                                                         \
-    hipLaunchKernelGGL((stream_tail_kernel<DT, B, FMT, FOUR6, MODE>), dim3(1), dim3(64), 0, a.stream, a.x,   \
-                       n_full * 8, count, a.T, pz, a.absmax_dev, t_out_tail, a.codes, a.scales, a.sse, a.clip)
-            if (tmode == kDynT) MXQ_LAUNCH_TAIL(kDynT);
-            else if (tmode != kNoT) MXQ_LAUNCH_TAIL(kSlowT);
-            else MXQ_LAUNCH_TAIL(kNoT);
-#undef MXQ_LAUNCH_TAIL
-        }
-    }
     return hipGetLastError();
 }
 
@@ -579,14 +580,14 @@ static hipError_t launch_dt(const StreamArgs& a)
 template <int DT, int B, int FMT, bool FOUR6>
 static hipError_t launch_batch_recipe(const StreamArgs* t, int count, int pz, hipStream_t stream)
 {
-    // complete chunks of up to kMaxBatch tensors per launch; ragged tails (b = 2, 4) one small launch each
+    // up to kMaxBatch tensors per launch, ragged tails (b = 2, 4) included
     for (int i0 = 0; i0 < count; i0 += kMaxBatch) {
         BatchArgs a{};
         uint32_t n_t = 0u;
         uint64_t total = 0u;
+        bool tails = false;
         for (int i = i0; i < count && i < i0 + kMaxBatch; ++i) {
             const int64_t n_full = t[i].n / 8;
-            if (n_full == 0) continue;
             const int64_t slices = (n_full + kThreads - 1) / kThreads;
             a.x[n_t] = t[i].x;
             a.codes[n_t] = reinterpret_cast<uint32_t*>(t[i].codes);
@@ -594,29 +595,21 @@ static hipError_t launch_batch_recipe(const StreamArgs* t, int count, int pz, hi
             a.sse[n_t] = t[i].sse;
             a.first[n_t] = (uint32_t)total;
             a.last[n_t] = (uint32_t)(n_full - (slices - 1) * kThreads);
+            a.tail[n_t] = (uint32_t)(t[i].n - n_full * 8);
+            tails |= a.tail[n_t] != 0u;
             total += (uint64_t)slices;
             ++n_t;
         }
-        if (n_t > 0u) {
-            a.first[n_t] = (uint32_t)total;                      // the host has bounded the sum below 2^32
-            a.count = n_t;
-            const dim3 grid(stream_grid((int64_t)total * kThreads)), block(kThreads);
-            hipLaunchKernelGGL((stream_batch_kernel<DT, B, FMT, FOUR6>), grid, block, 0, stream, a, pz);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
+        a.first[n_t] = (uint32_t)total;                          // the host has bounded the sum below 2^32
+        a.count = n_t;
+        a.tails = tails ? n_t : 0u;
+        const int workers = (total == 0u) ? 0 : stream_grid((int64_t)total * kThreads);
+        hipLaunchKernelGGL((stream_batch_kernel<DT, B, FMT, FOUR6>), dim3((unsigned)workers + a.tails), dim3(kThreads), 0,
+                           stream, a, pz);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    if constexpr (B < 8) {
-        for (int i = 0; i < count; ++i) {
-            const int64_t n_full = t[i].n / 8;
-            const int cnt = (int)(t[i].n - n_full * 8);
-            if (cnt > 0)
-                hipLaunchKernelGGL((stream_tail_kernel<DT, B, FMT, FOUR6, kNoT>), dim3(1), dim3(64), 0, stream, t[i].x,
-                                   n_full * 8, cnt, 1.0f, pz, (const float*)nullptr, (float*)nullptr, t[i].codes,
-                                   t[i].scales, t[i].sse, (float*)nullptr);
-        }
-    }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 template <int DT, int B>

@@ -57,6 +57,33 @@ def test_pruned_search_window_edges(oracle, mxq, fmt, block, dtype):
         same(mxq.quantize(mxq.from_bits(x), block, fmt, mxq.RECIPE_BRUTE_PRUNED, tensor_scale=T), ref)
 
 
+@pytest.mark.parametrize("block", [2, 4])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_ragged_tail_beside_full_slices(oracle, mxq, block, dtype):
+    """n = 8 * 256 * k + r: the tail of r < 8 elements is handled inside the main launch, alone (k = 0),
+    behind exactly full slices and behind a part-filled one; single calls, batches, all outputs."""
+    rng = np.random.default_rng(5 * block)
+    xs = []
+    for n in [n0 + r for n0 in (0, 8, 2048, 6 * 2048, 6 * 2048 + 1000) for r in (block, 8 - block)]:
+        x = (rng.standard_normal((1, n)) * 0.05).astype(np.float32)
+        xs.append(W.f32_to_bf16_bits(x) if dtype == "bf16" else x)
+    for x in xs:
+        print(f"[edges] tail b={block} {dtype} n={x.size}", flush=True)
+        g = mxq.from_bits(x)
+        for fmt, rec, T in [(0, 0, 1.0), (1, 2, 0.7), (2, 3, 1.0), (1, 4, 1.0), (2, 5, 0.7)]:
+            ref = oracle.quantize(x, block, fmt, min(rec, 4), tensor_scale=T)
+            same(mxq.quantize(g, block, fmt, rec, tensor_scale=T), ref)
+            clip = torch.full(ref[2].shape, -1.0, device="cuda")
+            same(mxq.quantize(g, block, fmt, rec, tensor_scale=T, clip_sse_out=clip), ref)
+            want = oracle.clip_sse(x, ref[1], block, fmt, tensor_scale=T)
+            assert (clip.cpu().numpy().view(np.uint32) == want.view(np.uint32)).all()
+        amax = mxq.tensor_absmax(g)
+        *out, t = mxq.quantize_hier(g, block, 1, 2, amax)
+        same(out, oracle.quantize(x, block, 1, 2, tensor_scale=float(t.cpu()[0])))
+    for out, x in zip(mxq.quantize_batch([mxq.from_bits(x) for x in xs], block, 1, 3), xs):
+        same(out, oracle.quantize(x, block, 1, 3))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_tensor_absmax_around_the_one_workgroup_limit(oracle, mxq, dtype):
     """One workgroup up to 160 KiB, two launches beyond; the maximum first, last and in between; all forms."""
