@@ -68,7 +68,7 @@ typedef enum { MXQ_SCALE_E8M0 = 0, MXQ_SCALE_E4M3 = 1, MXQ_SCALE_UE5M3 = 2 } mxq
  *   BRUTE_PRUNED  the same result as BRUTE, bit for bit, but candidates that provably cannot
  *              win are skipped: scales whose half is a scale code too and fits the block at least
  *              as well, and scales so small that the clipping error of the abs-max element alone
- *              costs more than the best candidate so far.  4 to 12 times faster than BRUTE.  A step
+ *              costs more than the best candidate so far.  4 to 14 times faster than BRUTE.  A step
  *              toward cheaper near-optimal selection (Conclusion).
  * 4OVER6* and BRUTE_PRUNED with E8M0 return MXQ_ERR_UNSUPPORTED (Eq. 4 rounds amax / M to the
  * scale format, which the floor rule of Eq. 1 does not define). */

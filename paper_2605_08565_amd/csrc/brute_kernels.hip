@@ -155,10 +155,15 @@ __device__ __forceinline__ void try_binade(const float (&v)[8], const float (&w)
 // codes to 15 beyond that where the scales are that small), then down until (lo) stops it (one to
 // three codes).  Every block walks from its OWN code: scale and reciprocal are per-lane registers,
 // the wavefront takes as many steps as its longest block, and blocks of very different magnitude
-// cost each other nothing.  Bound by vector issue: about 220 cycles a step, ten or eleven steps.
-// Measured on 4096 x 14336 bf16 weights, against a scan of whole binades in a window closed by a
-// weaker upper bound: E4M3 b = 16 236 -> 127 us, b = 4 346 -> 160 us; UE5M3 b = 16 277 -> 132 us,
-// b = 4 373 -> 160 us.
+// cost each other nothing.  A block that is done goes on trying codes: a code that cannot win changes
+// nothing, and masking it out would cost more.  Where every block of a wavefront starts at code 16 or
+// above (all of UE5M3 in practice), the way up is seven unrolled steps without the odd-code rule.
+// Bound by vector issue, ten or eleven steps.  What an instruction costs here, measured in a loop of
+// independent ones over 8 wavefronts per SIMD, cycles per wavefront: fp32 add, multiply, FMA and logic
+// on vector registers 2.5; the same with a scalar-register operand, minimum, maximum, compare, shift,
+// DPP and unpacking 4.3; packing to E2M1 and the reciprocal 8.5.
+// Measured on 4096 x 14336 bf16 weights with the exact quotient and masks in every step -> as it is:
+// E4M3 b = 16 127 -> 113 us, b = 4 160 -> 151 us; UE5M3 b = 16 132 -> 111 us, b = 4 157 -> 126 us.
 // ---------------------------------------------------------------------------------------
 
 // Value of a scale code, sub-normal codes included: the code's bits moved into the fp32 exponent and
@@ -170,21 +175,31 @@ __device__ __forceinline__ float walk_scale(uint32_t code)
     return u2f(code << 20) * u2f((uint32_t)(127 + 127 - ScaleFmt<FMT>::kBias) << 23);
 }
 
-// Codes and SSE of the lane's blocks under the scales S.
-template <int B>
-__device__ __forceinline__ void walk_step(const float (&v)[8], const float (&S)[BruteState<B>::NBLK], uint32_t& packed,
-                                          float (&sse)[4])
+// SSE of the lane's blocks under the scales S.  ONE_MUL (bf16 input, no per-tensor scale): the
+// quotient is one product with the hardware reciprocal.  With 8 significant bits in v and 4 in S an
+// element that is not exactly half way between two grid points is at least 2^-9 (relative) away from
+// the mid-point, far more than the 2^-22 that the product is off, so it rounds to the right side; an
+// element exactly half way may round to either neighbour, but both leave the same |residual| and
+// hence the same SSE.  (The codes come from the exact quotient, once, in walk_codes.)
+template <int B, bool ONE_MUL>
+__device__ __forceinline__ void walk_sse(const float (&v)[8], const float (&S)[BruteState<B>::NBLK], float (&sse)[4])
 {
     constexpr int NBLK = BruteState<B>::NBLK;
     constexpr int EPB = (B < 8) ? B : 8;
     float y[8];
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) {
-        const Recip r = make_recip_from(S[k], __builtin_amdgcn_rcpf(S[k]));
+        const float approx = __builtin_amdgcn_rcpf(S[k]);
+        if constexpr (ONE_MUL) {
 #pragma unroll
-        for (int i = 0; i < EPB; ++i) y[k * EPB + i] = quot(v[k * EPB + i], r);
+            for (int i = 0; i < EPB; ++i) y[k * EPB + i] = v[k * EPB + i] * approx;
+        } else {
+            const Recip r = make_recip_from(S[k], approx);
+#pragma unroll
+            for (int i = 0; i < EPB; ++i) y[k * EPB + i] = quot(v[k * EPB + i], r);
+        }
     }
-    packed = e2m1_pack8(y, 1.0f);
+    const uint32_t packed = e2m1_pack8(y, 1.0f);
     float q[8], sq[8];
     e2m1_unpack8(packed, 1.0f, q);
 #pragma unroll
@@ -192,32 +207,49 @@ __device__ __forceinline__ void walk_step(const float (&v)[8], const float (&S)[
     block_sse<B>(sq, sse);
 }
 
-// Keep the blocks in which this step was better (a take-over of codes, SSE and packed nibbles).
+// Codes of the lane's blocks under the scales S.
 template <int B>
-__device__ __forceinline__ void walk_keep(const bool (&better)[BruteState<B>::NBLK],
-                                          const uint32_t (&code)[BruteState<B>::NBLK], const float (&sse)[4],
-                                          uint32_t packed_now, uint32_t& packed, BruteState<B>& st)
+__device__ __forceinline__ uint32_t walk_codes(const float (&v)[8], const float (&S)[BruteState<B>::NBLK])
 {
-    constexpr int NBLK = BruteState<B>::NBLK;
+    constexpr int EPB = (B < 8) ? B : 8;
+    float y[8];
 #pragma unroll
-    for (int k = 0; k < NBLK; ++k) {
-        st.best_code[k] = better[k] ? code[k] : st.best_code[k];
-        st.best_sse[k] = better[k] ? sse[k] : st.best_sse[k];
+    for (int k = 0; k < BruteState<B>::NBLK; ++k) {
+        const Recip r = make_recip_from(S[k], __builtin_amdgcn_rcpf(S[k]));
+#pragma unroll
+        for (int i = 0; i < EPB; ++i) y[k * EPB + i] = quot(v[k * EPB + i], r);
     }
-    if constexpr (NBLK == 1) packed = better[0] ? packed_now : packed;
+    return e2m1_pack8(y, 1.0f);
 }
 
-template <int B, int FMT>
+// One step upwards: a strictly lower SSE wins.  Trying a code that cannot win, or the last code again,
+// changes nothing, so no block needs to be masked.
+template <int B, bool ONE_MUL>
+__device__ __forceinline__ void walk_up(const float (&v)[8], const float (&S)[BruteState<B>::NBLK],
+                                        const uint32_t (&code)[BruteState<B>::NBLK], BruteState<B>& st)
+{
+    float sse[4];
+    walk_sse<B, ONE_MUL>(v, S, sse);
+#pragma unroll
+    for (int k = 0; k < BruteState<B>::NBLK; ++k) {
+        const bool better = sse[k] < st.best_sse[k];
+        st.best_code[k] = better ? code[k] : st.best_code[k];
+        st.best_sse[k] = better ? sse[k] : st.best_sse[k];
+    }
+}
+
+template <int B, int FMT, bool ONE_MUL>
 __device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_t& packed, BruteState<B>& st)
 {
     constexpr int NBLK = BruteState<B>::NBLK;
     constexpr int LANES = (B < 8) ? 1 : B / 8;
     constexpr int EPB = (B < 8) ? B : 8;
-    constexpr int kMax = ScaleFmt<FMT>::kMaxCode;
+    constexpr uint32_t kMax = (uint32_t)ScaleFmt<FMT>::kMaxCode;
     const float inv_eps4 = 4.0f * u2f((uint32_t)(127 + ScaleFmt<FMT>::kBias + 2) << 23);      // 4 / eps
 
     float amax[NBLK], S[NBLK], sse[4];
-    uint32_t start[NBLK], code[NBLK], halved[NBLK], last_odd[NBLK];
+    uint32_t start[NBLK], code[NBLK], halved[NBLK];
+    bool low = false;
     block_amax<NBLK, EPB, LANES>(v, amax);
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) {
@@ -225,67 +257,86 @@ __device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_
         // the first code with 3.5 S >= amax (3.5 S is exact), one past the last code if there is none
         const uint32_t h = sf_encode_rne<FMT>(amax[k] * (float)(1.0 / 3.5));
         halved[k] = h + ((3.5f * walk_scale<FMT>(h) < amax[k]) ? 1u : 0u);
-        // the first code >= 1 with S >= 4 amax if that is below 16, else 15
-        last_odd[k] = (uint32_t)fminf(fmaxf(__builtin_ceilf(amax[k] * inv_eps4), 1.0f), 15.0f);
+        low |= start[k] - 16u > kMax - 7u - 16u;                        // start < 16 or start + 7 > kMax
         S[k] = walk_scale<FMT>(start[k]);
-        code[k] = start[k];
         st.best_sse[k] = __builtin_inff();
-        st.best_code[k] = 1u;
+        st.best_code[k] = start[k];
     }
-    uint32_t now;
-    walk_step<B>(v, S, now, sse);
-    {
-        bool better[NBLK];
+    walk_sse<B, ONE_MUL>(v, S, sse);
 #pragma unroll
-        for (int k = 0; k < NBLK; ++k) better[k] = sse[k] < st.best_sse[k];
-        packed = now;
-        walk_keep<B>(better, code, sse, now, packed, st);
+    for (int k = 0; k < NBLK; ++k) {
+        const bool better = sse[k] < __builtin_inff();                  // nothing wins where every SSE overflows
+        st.best_code[k] = better ? start[k] : 1u;
+        st.best_sse[k] = better ? sse[k] : __builtin_inff();
     }
 
-    while (true) {                                                      // upwards: a strictly lower SSE wins
-        bool alive[NBLK], any = false;
+    if (__builtin_amdgcn_ballot_w64(low) == 0ull) {
+        // Every code the blocks try is a normal number with a code at half its value: neighbouring codes
+        // are 2^20 apart as floats, and amax / 3.5 lies five to seven codes above the start.
+#pragma unroll
+        for (uint32_t i = 1u; i <= 7u; ++i) {
+            if (i > 4u) {
+                bool any = false;
+#pragma unroll
+                for (int k = 0; k < NBLK; ++k) any |= start[k] + i < halved[k];
+                if (__builtin_amdgcn_ballot_w64(any) == 0ull) break;    // uniform
+            }
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) {
+                code[k] = start[k] + i;
+                S[k] = u2f(f2u(S[k]) + (1u << 20));
+            }
+            walk_up<B, ONE_MUL>(v, S, code, st);
+        }
+    } else {
+        uint32_t last_odd[NBLK];
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) {
-            code[k] += 1u;
-            const bool below = code[k] < halved[k];
-            code[k] = below ? code[k] : (code[k] | 1u);
-            alive[k] = below || code[k] <= last_odd[k];
-            any |= alive[k];
-            S[k] = walk_scale<FMT>(code[k]);
+            // the first code >= 1 with S >= 4 amax if that is below 16, else 15
+            last_odd[k] = (uint32_t)fminf(fmaxf(__builtin_ceilf(amax[k] * inv_eps4), 1.0f), 15.0f);
+            code[k] = start[k];
         }
-        if (__builtin_amdgcn_ballot_w64(any) == 0ull) break;            // uniform
-        walk_step<B>(v, S, now, sse);
-        bool better[NBLK];
+        while (true) {
+            bool any = false;
 #pragma unroll
-        for (int k = 0; k < NBLK; ++k) better[k] = alive[k] && sse[k] < st.best_sse[k];
-        walk_keep<B>(better, code, sse, now, packed, st);
+            for (int k = 0; k < NBLK; ++k) {
+                code[k] += 1u;
+                const bool below = code[k] < halved[k];
+                code[k] = below ? code[k] : (code[k] | 1u);
+                any |= below || code[k] <= last_odd[k];
+                code[k] = min(code[k], kMax);
+                S[k] = walk_scale<FMT>(code[k]);
+            }
+            if (__builtin_amdgcn_ballot_w64(any) == 0ull) break;        // uniform
+            walk_up<B, ONE_MUL>(v, S, code, st);
+        }
     }
 
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) code[k] = start[k];
     while (true) {                                                      // downwards: the lower code wins a tie
-        bool alive[NBLK], any = false;
+        bool any = false;
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) {
-            code[k] = (code[k] != 0u) ? code[k] - 1u : 0u;
+            const bool first = code[k] <= 1u;                           // nothing below: code 1 once more
+            code[k] = max(code[k], 2u) - 1u;
             S[k] = walk_scale<FMT>(code[k]);
             const float over = amax[k] - 6.0f * S[k];
-            alive[k] = code[k] != 0u && !(over > 0.0f && over * over > st.best_sse[k]);
-            any |= alive[k];
+            any |= !first && !(over > 0.0f && over * over > st.best_sse[k]);
         }
         if (__builtin_amdgcn_ballot_w64(any) == 0ull) break;            // uniform
-        walk_step<B>(v, S, now, sse);
-        bool better[NBLK];
+        walk_sse<B, ONE_MUL>(v, S, sse);
 #pragma unroll
-        for (int k = 0; k < NBLK; ++k) better[k] = alive[k] && sse[k] <= st.best_sse[k];
-        walk_keep<B>(better, code, sse, now, packed, st);
+        for (int k = 0; k < NBLK; ++k) {
+            const bool better = sse[k] <= st.best_sse[k];
+            st.best_code[k] = better ? code[k] : st.best_code[k];
+            st.best_sse[k] = better ? sse[k] : st.best_sse[k];
+        }
     }
 
-    if constexpr (NBLK > 1) {                                           // several blocks: the codes of the winners once
 #pragma unroll
-        for (int k = 0; k < NBLK; ++k) S[k] = walk_scale<FMT>(st.best_code[k]);
-        walk_step<B>(v, S, packed, sse);
-    }
+    for (int k = 0; k < NBLK; ++k) S[k] = walk_scale<FMT>(st.best_code[k]);
+    packed = walk_codes<B>(v, S);
 }
 
 // Value of a power-of-two scale byte (0 .. 254); 2^-127 is a sub-normal float.
@@ -446,7 +497,7 @@ brute_kernel(const void* __restrict__ x, int64_t n_full, int tail, float T_arg,
         uint32_t packed;
         BruteState<B> st;
         if constexpr (FMT == kE8M0) brute_search_pow2<B>(v, packed, st);
-        else if constexpr (PRUNE) brute_search_pruned<B, FMT>(v, packed, st);
+        else if constexpr (PRUNE) brute_search_pruned<B, FMT, DT == kBF16 && !HAS_T>(v, packed, st);
         else brute_search<B, FMT>(v, packed, st);
         float clip[4];
         if (clip_out) {                                                 // uniform

@@ -61,6 +61,24 @@ def test_half_scale_dominates_and_walk_finds_the_winner(oracle, fmt, b, kind):
         assert 1 + int(np.argmin(sse[1:])) in seen, (kind, b, fmt)
 
 
+@pytest.mark.parametrize("off", [-2, -1, 0, 1, 2])
+def test_one_product_gives_the_sse_of_8_bit_inputs(off):
+    """bf16 elements without a per-tensor scale: rounding v * r, r within two ulps of 1 / S, leaves the
+    residual of the exact quotient, for every significand of v and S (sub-normal codes included)."""
+    grid = np.array([0, .5, 1, 1.5, 2, 3, 4, 6])
+    mids = (grid[1:] + grid[:-1]) / 2
+    v = (np.arange(128, 256)[:, None] * 2.0 ** np.arange(-14, 0)).ravel()
+    for s in [1, 3, 5, 7, *range(8, 16)]:
+        S = s / 8.0
+        r = np.float32(1 / S)
+        r = (r.view(np.uint32) + np.uint32(off & 0xFFFFFFFF)).view(np.float32)
+        y = (v.astype(np.float32) * r).astype(np.float64)
+        for k in (1.0, -1.0):                              # an exact tie may fall either way
+            near = np.searchsorted(mids, y + k * 2.0 ** -40, side="left")
+            exact = np.min(np.abs(v[:, None] - grid * S), axis=1)
+            assert (np.abs(v - grid[near] * S) == exact).all(), (s, off)
+
+
 def test_quotient_from_hardware_reciprocal(tmp_path):
     if "fma" not in open("/proc/cpuinfo").read():
         pytest.skip("host CPU has no FMA instruction")
