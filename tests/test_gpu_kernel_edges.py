@@ -101,3 +101,22 @@ def test_tensor_absmax_around_the_one_workgroup_limit(oracle, mxq, dtype):
             mxq.tensor_absmax_static(g, words[2:3])
             assert words.cpu().tolist() == [3.0] * 3
     assert int(ws.sum()) == 0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tensor_absmax_at_group_edges(mxq, dtype):
+    """Eight workgroups share a group of 512 KiB slice by slice, 32 groups are in flight: the maximum in the
+    first and last element of slices, groups and the tensor, sizes around one, two and 32 groups."""
+    size = 4 if dtype == "f32" else 2
+    per = (512 << 10) // size
+    word = torch.empty(1, device="cuda")
+    ws = mxq.absmax_workspace()
+    for n in (per // 2 + 5, per - 8, per, per + 8, 2 * per + 2048 * 3 + 1, 32 * per, 33 * per + 13):
+        x = torch.zeros((1, n), dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+        at = {0, 2047, 2048, 8 * 2048 - 1, 8 * 2048, per // 2, per - 1, per, n // 8 * 8 - 1, n - 1}
+        print(f"[edges] absmax groups {dtype} n={n}", flush=True)
+        for value, i in enumerate(sorted(i for i in at if i < n), start=1):
+            x[0, i] = -float(value)                        # the latest one is the largest
+            assert float(mxq.tensor_absmax(x, out=word).cpu()[0]) == value
+            assert float(mxq.tensor_absmax(x, workspace=ws).cpu()[0]) == value
+            assert float(mxq.tensor_absmax_acc(x, torch.zeros(1, device="cuda")).cpu()[0]) == value
