@@ -120,3 +120,29 @@ def test_tensor_absmax_at_group_edges(mxq, dtype):
             assert float(mxq.tensor_absmax(x, out=word).cpu()[0]) == value
             assert float(mxq.tensor_absmax(x, workspace=ws).cpu()[0]) == value
             assert float(mxq.tensor_absmax_acc(x, torch.zeros(1, device="cuda")).cpu()[0]) == value
+
+
+@pytest.mark.parametrize("block", [2, 4, 8, 128])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_dequantize_at_tile_edges(oracle, mxq, block, dtype):
+    """One chunk per lane up to 2048 workgroups, four beyond: remainders of a chunk, of a workgroup's tile and
+    the line between the two, T by value and from device memory."""
+    rng = np.random.default_rng(block)
+    per = 8 if dtype == "bf16" else 4
+    line = 2048 * 256 * per
+    out_dtype = torch.bfloat16 if dtype == "bf16" else torch.float32
+    for n in (block, 256 * per - block, 256 * per + block, 1024 * per + 8, line - block, line, line + block, line + 1024 * per - block):
+        n = n // block * block
+        if n == 0:
+            continue
+        codes = rng.integers(0, 256, (1, n // 2), dtype=np.uint8)
+        scales = rng.integers(0, 0x7F, (1, n // block), dtype=np.uint8)
+        print(f"[edges] dequantize {dtype} b={block} n={n}", flush=True)
+        want = oracle.dequantize(codes, scales, block, 1, 0.75)
+        c, s = torch.from_numpy(codes).cuda(), torch.from_numpy(scales).cuda()
+        for t in (0.75, torch.full((1,), 0.75, device="cuda")):
+            out = torch.full((1, n + 8), 7.0, dtype=out_dtype, device="cuda")     # nothing beyond n may change
+            mxq.dequantize(c, s, block, 1, t, out_dtype, out=out)
+            got = out.float().cpu().numpy()
+            ref = want if dtype == "f32" else torch.from_numpy(want).to(torch.bfloat16).float().numpy()
+            assert (got[:, :n] == ref).all() and (got[:, n:] == 7.0).all()
