@@ -31,8 +31,7 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 constexpr int kDqItems = 4;
 constexpr int64_t kDqResident = 256 * 8;                            // workgroups
 template <int B, int ITEMS>
-__global__ void __launch_bounds__(kThreads)
-dequant_bf16_kernel(const uint32_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n,
+__device__ __forceinline__ void dequant_bf16_tile(const uint32_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n,
                     int fmt, float T_arg, const float* __restrict__ t_dev, uint16_t* __restrict__ out)
 {
     const float T = t_dev ? *t_dev : T_arg;                         // per-tensor scale by value or from device memory
@@ -86,13 +85,28 @@ dequant_bf16_kernel(const uint32_t* __restrict__ codes, const uint8_t* __restric
     }
 }
 
+template <int B>
+__global__ void __launch_bounds__(kThreads)
+dequant_bf16_kernel(const uint32_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n, int fmt, float T,
+                      const float* __restrict__ t_dev, uint16_t* __restrict__ out)
+{
+    dequant_bf16_tile<B, kDqItems>(codes, scales, n, fmt, T, t_dev, out);
+}
+
+template <int B>
+__global__ void __launch_bounds__(kThreads)
+dequant_bf16_one_kernel(const uint32_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n, int fmt, float T,
+                          const float* __restrict__ t_dev, uint16_t* __restrict__ out)
+{
+    dequant_bf16_tile<B, 1>(codes, scales, n, fmt, T, t_dev, out);
+}
+
 // fp32 output: one lane = 4 consecutive elements = 16 bits of codes = one 128-bit store, so a
 // store instruction of a wavefront covers 1 KiB without gaps (with 8 elements per lane its two
 // stores would each leave every other 16 bytes untouched).  n is even, so at most 2 elements are
 // left behind the complete quads.
 template <int B, int ITEMS>
-__global__ void __launch_bounds__(kThreads)
-dequant_f32_kernel(const uint16_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n,
+__device__ __forceinline__ void dequant_f32_tile(const uint16_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n,
                    int fmt, float T_arg, const float* __restrict__ t_dev, float* __restrict__ out)
 {
     const float T = t_dev ? *t_dev : T_arg;
@@ -139,13 +153,29 @@ dequant_f32_kernel(const uint16_t* __restrict__ codes, const uint8_t* __restrict
     }
 }
 
-template <int ITEMS>
+template <int B>
+__global__ void __launch_bounds__(kThreads)
+dequant_f32_kernel(const uint16_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n, int fmt, float T,
+                     const float* __restrict__ t_dev, float* __restrict__ out)
+{
+    dequant_f32_tile<B, kDqItems>(codes, scales, n, fmt, T, t_dev, out);
+}
+
+template <int B>
+__global__ void __launch_bounds__(kThreads)
+dequant_f32_one_kernel(const uint16_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n, int fmt, float T,
+                         const float* __restrict__ t_dev, float* __restrict__ out)
+{
+    dequant_f32_tile<B, 1>(codes, scales, n, fmt, T, t_dev, out);
+}
+
 static void launch_dequant_f32(const DequantArgs& a)
 {
-    const int64_t tile = 4 * (int64_t)kThreads * ITEMS;
+    const bool one = a.n <= kDqResident * kThreads * 4;
+    const int64_t tile = 4 * (int64_t)kThreads * (one ? 1 : kDqItems);
     const unsigned grid = (unsigned)((a.n + tile - 1) / tile);
 #define MXQ_DQF(BB)                                                                                  \
-    hipLaunchKernelGGL((dequant_f32_kernel<BB, ITEMS>), dim3(grid), dim3(kThreads), 0, a.stream,    \
+    hipLaunchKernelGGL((one ? dequant_f32_one_kernel<BB> : dequant_f32_kernel<BB>), dim3(grid), dim3(kThreads), 0, a.stream,    \
                        (const uint16_t*)a.codes, a.scales, (uint64_t)a.n, a.scale_fmt, a.T, a.t_dev, (float*)a.out)
     switch (a.block) {
         case 2: MXQ_DQF(2); break;
@@ -159,13 +189,13 @@ static void launch_dequant_f32(const DequantArgs& a)
 #undef MXQ_DQF
 }
 
-template <int ITEMS>
 static void launch_dequant_bf16(const DequantArgs& a)
 {
-    const int64_t tile = 8 * (int64_t)kThreads * ITEMS;
+    const bool one = a.n <= kDqResident * kThreads * 8;
+    const int64_t tile = 8 * (int64_t)kThreads * (one ? 1 : kDqItems);
     const unsigned grid = (unsigned)((a.n + tile - 1) / tile);
 #define MXQ_DQ(BB)                                                                                   \
-    hipLaunchKernelGGL((dequant_bf16_kernel<BB, ITEMS>), dim3(grid), dim3(kThreads), 0, a.stream,   \
+    hipLaunchKernelGGL((one ? dequant_bf16_one_kernel<BB> : dequant_bf16_kernel<BB>), dim3(grid), dim3(kThreads), 0, a.stream,   \
                        (const uint32_t*)a.codes, a.scales, (uint64_t)a.n, a.scale_fmt, a.T, a.t_dev, (uint16_t*)a.out)
     switch (a.block) {
         case 2: MXQ_DQ(2); break;
@@ -181,9 +211,8 @@ static void launch_dequant_bf16(const DequantArgs& a)
 
 hipError_t launch_dequant(const DequantArgs& a)
 {
-    const bool resident = a.n <= kDqResident * kThreads * (a.dtype == kBF16 ? 8 : 4);
-    if (a.dtype == kBF16) { if (resident) launch_dequant_bf16<1>(a); else launch_dequant_bf16<kDqItems>(a); }
-    else { if (resident) launch_dequant_f32<1>(a); else launch_dequant_f32<kDqItems>(a); }
+    if (a.dtype == kBF16) launch_dequant_bf16(a);
+    else launch_dequant_f32(a);
     return hipGetLastError();
 }
 
