@@ -99,10 +99,57 @@ MXQ_HD float quot(float v, Recip r)
     return __builtin_fmaf(v, r.hi, v * r.lo);
 }
 
-// A single multiplication by a rounded reciprocal is NOT enough, not even for bf16 inputs with
+// A single multiplication by a rounded reciprocal is NOT enough for the code, not even for bf16 inputs with
 // their 8 significant bits: an input that sits exactly on a tie (v = t*d) must produce exactly t
 // for the ties-to-even rule of the E2M1 rounding, and t*d*fl(1/d) misses t by an ulp for most d
-// (the host-side check shows the failures when quot is replaced by one product).
+// (the host-side check shows the failures when quot is replaced by one product).  Where only the
+// residual is needed and not the code, one product does for 8 significant bits: an exact tie leaves the
+// same |residual| on either side, and every other quotient is 2^-9 away from a mid-point (walk_sse).
+
+// ---------------------------------------------------------------------------------------
+// Scalar rules of the pruned scale search (the walk itself is brute_search_pruned; the host check
+// tests/host/search_walk_check.cpp walks single blocks with these same functions).
+// ---------------------------------------------------------------------------------------
+
+// Value of a scale code, sub-normal codes included: the code's bits moved into the fp32 exponent and
+// mantissa are off by a power of two only, and the multiplication is exact.  (Beyond the last code
+// the value is meaningless but harmless.)
+template <int BIAS>
+MXQ_HD float walk_scale_bias(uint32_t code)
+{
+    return u2f(code << 20) * u2f((uint32_t)(127 + 127 - BIAS) << 23);
+}
+
+// The first code with 3.5 S >= amax, one past the last code if there is none; `h` is the code that
+// amax * kHalvedAt rounds to, at most one too low (3.5 S is exact).
+constexpr float kHalvedAt = (float)(1.0 / 3.5);
+template <int BIAS>
+MXQ_HD uint32_t walk_halved(uint32_t h, float amax)
+{
+    return h + ((3.5f * walk_scale_bias<BIAS>(h) < amax) ? 1u : 0u);
+}
+
+// Below code 16 (spacing eps, half of an odd code is no code): the first code >= 1 with S >= 4 amax,
+// 15 if there is none.  From S = 4 amax on every element quantises to zero.
+template <int BIAS>
+MXQ_HD uint32_t walk_last_odd(float amax)
+{
+    const float inv_eps4 = 4.0f * u2f((uint32_t)(127 + BIAS + 2) << 23);      // 4 / eps
+    return (uint32_t)__builtin_fminf(__builtin_fmaxf(__builtin_ceilf(amax * inv_eps4), 1.0f), 15.0f);
+}
+
+// An element with |v| > 6 S saturates and leaves fl(fl(|v| - 6 S)^2) in the SSE (6 S is exact); this is
+// that term, +0 for every other element.  It does not grow with S.
+MXQ_HD float saturation_loss(float v, float S)
+{
+    const float over = __builtin_fmaxf(__builtin_fabsf(v) - 6.0f * S, 0.0f);
+    return over * over;
+}
+
+// Steps down after which the walk looks for its floor: a few more than ordinary wavefronts take, whose
+// number grows with the block.  (With three, b = 16 took 47 instead of 36 us on 4096 x 4096 and b = 128
+// 59 instead of 44; with twelve at b = 2, values beyond the format 107 instead of 62.)
+MXQ_HD constexpr uint32_t walk_patience(int b) { return b <= 4 ? 3u : b == 8 ? 4u : b == 16 ? 6u : b == 32 ? 10u : 16u; }
 
 // amax / 6 and amax / 4 in front of Round_SF (Eq. 2, M = 6; Eq. 4, M = 4): the first by the
 // two-part reciprocal above (6 has 2 significant bits), the second is exact.

@@ -57,6 +57,36 @@ def test_pruned_search_window_edges(oracle, mxq, fmt, block, dtype):
         same(mxq.quantize(mxq.from_bits(x), block, fmt, mxq.RECIPE_BRUTE_PRUNED, tensor_scale=T), ref)
 
 
+@pytest.mark.parametrize("fmt", [1, 2])
+@pytest.mark.parametrize("block", [2, 4, 8, 128])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_pruned_search_beyond_the_format(oracle, mxq, fmt, block, dtype):
+    """Blocks whose abs-max lies above 6 times the largest scale, alone in their wavefront and beside
+    ordinary ones, up to magnitudes at which the codes no longer differ and at which every SSE overflows;
+    NaN and infinity, whose codes are not specified but whose scale byte and SSE are the full search's."""
+    rng = np.random.default_rng(block + 7 * fmt)
+    top = 6 * oracle.scale_decode(fmt, oracle.scale_max_code(fmt))
+    n = 4 * 512 // block                                    # four wavefronts of each kind
+    rows = []
+    for e in (0, 0.1, 1, 3, 8, 16, 24, 26, 28, 40):
+        x = rng.standard_normal((n, block)) * top * 2.0 ** e
+        rows += [x, np.where(rng.random((n, 1)) < 0.1, x, rng.standard_normal((n, block)) * 0.02),
+                 np.sign(x) * top * 2.0 ** e * (1 + 0.05 * rng.random((n, block)))]
+    x = np.concatenate(rows).astype(np.float32)
+    x = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    print(f"[edges] beyond fmt={fmt} b={block} {dtype} blocks={x.shape[0]}", flush=True)
+    same(mxq.quantize(mxq.from_bits(x), block, fmt, mxq.RECIPE_BRUTE_PRUNED), oracle.quantize(x, block, fmt, 4))
+    x = (rng.standard_normal((n, block)) * 0.02).astype(np.float32)
+    for i, bad in enumerate((np.nan, np.inf, -np.inf, 3e38, 1.8e19, 1.9e19)):
+        x[7 * i::61, i % block] = bad
+    g = mxq.from_bits(W.f32_to_bf16_bits(x) if dtype == "bf16" else x)
+    full, pruned = mxq.quantize(g, block, fmt, mxq.RECIPE_BRUTE), mxq.quantize(g, block, fmt, mxq.RECIPE_BRUTE_PRUNED)
+    torch.cuda.synchronize()
+    assert torch.equal(full[1], pruned[1]) and torch.equal(full[2], pruned[2])
+    ok = torch.isfinite(g.float()).all(dim=1)
+    assert torch.equal(full[0][ok], pruned[0][ok])
+
+
 @pytest.mark.parametrize("block", [2, 4])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_ragged_tail_beside_full_slices(oracle, mxq, block, dtype):

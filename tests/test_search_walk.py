@@ -88,3 +88,31 @@ def test_quotient_from_hardware_reciprocal(tmp_path):
     res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
     print(res.stdout)
     assert res.returncode == 0 and "bad=0" in res.stdout
+
+
+def test_walk_over_single_blocks_with_the_kernels_rules(tmp_path):
+    """The kernel's order of steps over the scalar rules it includes (mxq_arith.hpp): same winner and same
+    SSE bits as all codes tried, and never many candidates -- also for blocks beyond the format, which
+    the clipping bound of one element alone would send through every code (126 and 254), and for NaN and
+    infinity.  The longest way down before a floor is looked for is 16 steps; with the start and the floor
+    itself that is 18 candidates for such a block, and no ordinary block needs more than 15."""
+    if "fma" not in open("/proc/cpuinfo").read():
+        pytest.skip("host CPU has no FMA instruction")
+    exe = str(tmp_path / "search_walk_check")
+    subprocess.run([CLANG, "-O2", "-std=c++17", "-ffp-contract=off", "-mfma", "-Wall", "-Werror",
+                    os.path.join(HERE, "host", "search_walk_check.cpp"), "-o", exe, "-lm"], check=True)
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    print(res.stdout)
+    rows = [dict(t.split("=") for t in l.split()[1:]) for l in res.stdout.splitlines() if "cases=" in l]
+    assert res.returncode == 0 and len(rows) == 16
+    for r in rows:
+        assert int(r["cases"]) > 100 and int(r["bad"]) == 0 and int(r["most"]) <= 18, r
+
+
+def test_search_rules_are_defined_once():
+    """In the header that the host check compiles, not a second time in a kernel file."""
+    csrc = os.path.join(os.path.dirname(HERE), "paper_2605_08565_amd", "csrc")
+    names = ("walk_scale_bias(uint32_t", "walk_halved(uint32_t", "walk_last_odd(float", "saturation_loss(float", "walk_patience(int", "make_recip_from(float")
+    for f in os.listdir(csrc):
+        text = open(os.path.join(csrc, f)).read()
+        assert all((n in text) == (f == "mxq_arith.hpp") for n in names), f
