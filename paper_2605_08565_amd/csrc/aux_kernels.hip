@@ -247,43 +247,53 @@ __global__ void absmax_clear_kernel(uint32_t* out) { *out = 0u; }
 constexpr int kAbsItems = 4;
 constexpr int kAbsThreads = 1024;
 constexpr int kAbsMaxGrid = 256;
+constexpr int kAbsTile = kAbsThreads * kAbsItems;                    // vectors a workgroup has in flight
 
-// Maximum over the workgroup's tiles (bit pattern); valid in thread 0.
+// Maximum over the lane's vectors of one group (bit pattern); `left` vectors of the tensor from `base` on.
 template <int DT>
+__device__ __forceinline__ uint32_t group_absmax(const u32x4* base, uint32_t left, uint32_t off, uint32_t step)
+{
+    u32x4 r[kAbsItems];
+#pragma unroll
+    for (int i = 0; i < kAbsItems; ++i) {
+        r[i] = base[min(off + (uint32_t)i * step, left - 1u)];                // lanes beyond it read the last vector again
+    }
+    uint32_t m = 0u;
+#pragma unroll
+    for (int i = 0; i < kAbsItems; ++i) {
+        if constexpr (DT == kBF16) {
+            // two bf16 per dword: compare the high halves and the low halves separately
+            const uint32_t hi = max(max(r[i].x & 0x7FFF0000u, r[i].y & 0x7FFF0000u),
+                                    max(r[i].z & 0x7FFF0000u, r[i].w & 0x7FFF0000u));
+            const uint32_t lo = max(max(r[i].x & 0x7FFFu, r[i].y & 0x7FFFu),
+                                    max(r[i].z & 0x7FFFu, r[i].w & 0x7FFFu));
+            m = max(m, max(hi, lo << 16));
+        } else {
+            m = max(m, max(max(r[i].x & 0x7FFFFFFFu, r[i].y & 0x7FFFFFFFu),
+                           max(r[i].z & 0x7FFFFFFFu, r[i].w & 0x7FFFFFFFu)));
+        }
+    }
+    return m;
+}
+
+// Maximum over the workgroup's share (bit pattern); valid in thread 0.  ALONE: one workgroup, tile by
+// tile.  Else the grid is a multiple of 8, or less than 8 for a tensor of no more tiles than workgroups.
+template <int DT, bool ALONE>
 __device__ __forceinline__ uint32_t workgroup_absmax(const void* __restrict__ x, int64_t n)
 {
     constexpr int64_t kVec = (DT == kBF16) ? 1 : 2;               // 128-bit vectors per chunk
     const int64_t n_vec = (n >> 3) * kVec;                         // complete vectors
     const u32x4* xv = static_cast<const u32x4*>(x);
     constexpr uint32_t kSlice = kThreads * (uint32_t)kVec;         // vectors of a slice of the streaming kernels
+    constexpr int64_t kGroup = kAbsTile * (ALONE ? 1 : 8);         // vectors; powers of two, no division
     uint32_t m = 0u;
-    const uint32_t members = min(gridDim.x, 8u), member = blockIdx.x & 7u;      // the grid is 1 or a multiple of 8
-    const uint32_t teams = (gridDim.x + 7u) >> 3;
-    const int64_t group = (int64_t)members * kAbsThreads * kAbsItems;
-    const int64_t n_groups = (n_vec + group - 1) / group;
+    const uint32_t members = ALONE ? 1u : min(gridDim.x, 8u), member = ALONE ? 0u : blockIdx.x & 7u;
+    const uint32_t teams = ALONE ? 1u : (gridDim.x + 7u) >> 3;
     const uint32_t off = (member + threadIdx.x / kSlice * members) * kSlice + threadIdx.x % kSlice;
     const uint32_t step = members * kAbsThreads;
-    for (int64_t g = n_groups - 1 - (int64_t)(blockIdx.x >> 3); g >= 0; g -= teams) {            // uniform
-        const u32x4* base = xv + g * group;
-        const uint32_t last = (uint32_t)min(group, n_vec - g * group) - 1u;      // lanes beyond it read the last vector again
-        u32x4 r[kAbsItems];
-#pragma unroll
-        for (int i = 0; i < kAbsItems; ++i) r[i] = base[min(off + (uint32_t)i * step, last)];
-#pragma unroll
-        for (int i = 0; i < kAbsItems; ++i) {
-            if constexpr (DT == kBF16) {
-                // two bf16 per dword: compare the high halves and the low halves separately
-                const uint32_t hi = max(max(r[i].x & 0x7FFF0000u, r[i].y & 0x7FFF0000u),
-                                        max(r[i].z & 0x7FFF0000u, r[i].w & 0x7FFF0000u));
-                const uint32_t lo = max(max(r[i].x & 0x7FFFu, r[i].y & 0x7FFFu),
-                                        max(r[i].z & 0x7FFFu, r[i].w & 0x7FFFu));
-                m = max(m, max(hi, lo << 16));
-            } else {
-                m = max(m, max(max(r[i].x & 0x7FFFFFFFu, r[i].y & 0x7FFFFFFFu),
-                               max(r[i].z & 0x7FFFFFFFu, r[i].w & 0x7FFFFFFFu)));
-            }
-        }
-    }
+    int64_t g = (n_vec + kGroup - 1) / kGroup - 1 - (int64_t)(ALONE ? 0u : blockIdx.x >> 3);
+    for (; g >= 0; g -= teams)                                                                          // uniform
+        m = max(m, group_absmax<DT>(xv + g * kGroup, (uint32_t)min(kGroup, n_vec - g * kGroup), off, step));
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         for (int64_t i = (n >> 3) << 3; i < n; ++i) {
             uint32_t b;
@@ -337,9 +347,11 @@ absmax_kernel(const void* __restrict__ x, int64_t n, uint32_t* __restrict__ out,
 
 // A tensor that one workgroup reads in the time a second launch costs: no word to clear, no atomic,
 // no workspace -- one launch for every form but the running maximum (whose word other streams may be
-// raising at the same time; it is one launch anyway).  One compute unit draws about 50 GB/s, two
-// launches cost about 5 us on the GPU whatever the size (graph replay, bf16): 16 KiB 2.6 against
-// 4.6 us, 128 KiB 4.4 against 5.2 us, 256 KiB 6.6 against 5.2 us, so the line lies at 160 KiB.
+// raising at the same time; it is one launch anyway).  One workgroup against several, graph replay, bf16:
+// with the clearing launch 16 KiB 2.3 against 4.1 us, 128 KiB 2.9 against 4.3, 160 KiB 3.3 against 4.2; with
+// the ticket 16 KiB 2.3 against 3.2 to 3.6, 128 KiB 2.9 against 3.4, 160 KiB 3.3 against 3.3 -- so the line
+// lies at 160 KiB for all of them.  (A division by the number of workgroups that share a group cost every
+// call of this size 0.3 us; groups are powers of two now.)
 // Launched one by one from Python the second launch costs another 3.5 us of host time.
 constexpr int64_t kAbsSmallBytes = 160 << 10;
 
@@ -347,8 +359,19 @@ template <int DT>
 __global__ void __launch_bounds__(kAbsThreads)
 absmax_small_kernel(const void* __restrict__ x, int64_t n, uint32_t* __restrict__ out)
 {
-    const uint32_t w = workgroup_absmax<DT>(x, n);
+    const uint32_t w = workgroup_absmax<DT, true>(x, n);
     if (threadIdx.x == 0) *out = w;
+}
+
+// Workgroups for `tiles` tiles: one each up to 8 (a team reads its group of 8 at once), then whole teams up
+// to one workgroup per compute unit.  A ticket costs a workgroup three dependent accesses to one place, so
+// with tickets it reads at least two tiles as soon as there are 64 workgroups (16 MiB: 10.3 -> 7.2 us).
+static unsigned absmax_grid(int64_t tiles, bool ticket)
+{
+    if (tiles <= 8) return (unsigned)tiles;
+    int64_t teams = tiles / 8 + (tiles % 8 != 0 ? 1 : 0);
+    if (ticket && teams > 8) teams = (teams < 16) ? 8 : (teams + 1) / 2;
+    return 8u * (unsigned)(teams < kAbsMaxGrid / 8 ? teams : kAbsMaxGrid / 8);
 }
 
 // `ws`: the two-word workspace of the ticket scheme, or NULL.  `accumulate` (without ws): the output
@@ -372,9 +395,8 @@ hipError_t launch_absmax(const void* x, int64_t n, int dtype, float* out, uint32
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess || n == 0) return e;
     }
-    const int64_t group_bytes = 8 * (int64_t)kAbsThreads * kAbsItems * 16;
-    const int64_t groups = (n * (dtype == kBF16 ? 2 : 4) + group_bytes - 1) / group_bytes;
-    const dim3 grid((unsigned)(8 * (groups < kAbsMaxGrid / 8 ? groups : kAbsMaxGrid / 8))), block(kAbsThreads);
+    const int64_t per_tile = kAbsTile * (dtype == kBF16 ? 8 : 4);                    // elements
+    const dim3 grid(absmax_grid(n / per_tile + (n % per_tile != 0 ? 1 : 0), ws != nullptr)), block(kAbsThreads);
     uint32_t* o = (uint32_t*)out;
     uint32_t* cw = (uint32_t*)clear_word;
     if (dtype == kBF16) {

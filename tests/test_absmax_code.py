@@ -1,0 +1,29 @@
+"""What the compiler makes of the tensor abs-max (CPU only, gfx950 assembly of aux_kernels.hip).
+
+A division by a run-time group size costs a small call a tenth of its time."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_08565_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def bodies(tmp_path_factory):
+    from paper_2605_08565_amd.build import FLAGS
+    out = str(tmp_path_factory.mktemp("asm") / "aux.s")
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    subprocess.run([hipcc, *FLAGS, "--offload-device-only", "-S", os.path.join(CSRC, "aux_kernels.hip"), "-o", out], check=True,
+                   capture_output=True)
+    text = open(out).read()
+    found = dict(re.findall(r"^(_ZN3mxq\w*absmax\w*kernelI\w+):(.*?)s_endpgm", text, re.S | re.M))
+    assert sum("absmax_kernel" in k for k in found) == 4 and sum("absmax_small_kernel" in k for k in found) == 2
+    return found
+
+
+def test_no_division_by_a_run_time_number(bodies):
+    for name, body in bodies.items():
+        assert not re.search(r"v_rcp_|v_cvt_f32_u32", body), name

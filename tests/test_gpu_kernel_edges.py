@@ -152,6 +152,27 @@ def test_tensor_absmax_at_group_edges(mxq, dtype):
             assert float(mxq.tensor_absmax_acc(x, torch.zeros(1, device="cuda")).cpu()[0]) == value
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tensor_absmax_with_few_tiles(mxq, dtype):
+    """One workgroup per tile of 64 KiB up to eight tiles, whole teams beyond, two tiles a workgroup with
+    tickets beyond 64 of them."""
+    size = 4 if dtype == "f32" else 2
+    tile = (64 << 10) // size
+    word, ws = torch.empty(1, device="cuda"), mxq.absmax_workspace()
+    sizes = [1, 8, tile - 8, tile, tile + 1, 3 * tile + 9, 7 * tile, 8 * tile, 8 * tile + 1, 9 * tile + 8, 64 * tile, 65 * tile, 129 * tile + 3]
+    for n in sizes:
+        x = torch.zeros((1, n), dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+        at = {0, 255, tile - 1, tile, 5 * tile + 77, 8 * tile - 1, 8 * tile, n // 2, n // 8 * 8 - 1, n - 1}
+        print(f"[edges] absmax tiles {dtype} n={n}", flush=True)
+        for value, i in enumerate(sorted(i for i in at if 0 <= i < n), start=1):
+            x[0, i] = -float(value)                        # the latest one is the largest
+            assert float(mxq.tensor_absmax(x, out=word).cpu()[0]) == value
+            assert float(mxq.tensor_absmax(x, workspace=ws).cpu()[0]) == value
+            assert float(mxq.tensor_absmax_static(x, word).cpu()[0]) == value
+            assert float(mxq.tensor_absmax_acc(x, torch.zeros(1, device="cuda")).cpu()[0]) == value
+    assert int(ws.sum()) == 0
+
+
 @pytest.mark.parametrize("block", [2, 4, 8, 128])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_dequantize_at_tile_edges(oracle, mxq, block, dtype):
