@@ -321,7 +321,7 @@ absmax_kernel(const void* __restrict__ x, int64_t n, uint32_t* __restrict__ out,
               uint32_t* __restrict__ clear_word)
 {
     if (clear_word && blockIdx.x == 0 && threadIdx.x == 0) *clear_word = 0u;      // for a LATER launch
-    const uint32_t w = workgroup_absmax<DT>(x, n);
+    const uint32_t w = workgroup_absmax<DT, false>(x, n);
     if (threadIdx.x == 0) {
         if constexpr (!TICKET) {
             // The word only grows during a call, so a workgroup whose maximum does not exceed the
