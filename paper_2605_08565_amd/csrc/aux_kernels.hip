@@ -239,24 +239,29 @@ __global__ void absmax_clear_kernel(uint32_t* out) { *out = 0u; }
 // here what it will read there: workgroups go to the dies in turn, the streaming kernels give slice s
 // (256 chunks) to a workgroup on die s mod 8, and the eight workgroups of a team share a group of
 // 512 KiB slice by slice in the same way.  Groups are walked from the last to the first, because the
-// quantise pass begins at the first, and the loads are ordinary ones, which stay in the caches.
-// Abs-max and abs-max quantisation of b = 16 in a graph, against contiguous tiles in ascending order
-// with non-temporal loads: bf16 1024 x 4096 12.4 -> 11.6 us, 4096 x 4096 21.4 -> 19.0 us, 8192 x 4096
-// 33.0 -> 30.7 us, 4096 x 14336 52.0 -> 47.3 us; fp32 4096 x 8192 54.0 -> 47.1 us.  (The abs-max
-// alone: 14.8 -> 13.5 us on 64 MiB; on 112 MiB, more than the caches can pass on whole, 22.1 -> 23.8.)
+// quantise pass begins at the first.  The first 64 MiB are read with ordinary loads, which stay in the
+// caches, what lies behind them (and is read before them) with non-temporal ones.  Abs-max and abs-max
+// quantisation (b = 16) in a graph, contiguous ascending tiles and non-temporal loads throughout -> this
+// order, ordinary loads throughout -> as it is: bf16 64 MiB 30.9 -> 27.2 -> 26.6 us, 112 MiB 49.2 -> 46.0
+// -> 45.2, 384 MiB 153 -> 164 -> 149; fp32 128 MiB 52.5 -> 46.7 -> 46.8.  The abs-max alone: 64 MiB 13.7 ->
+// 14.8 -> 14.5, 112 MiB 21.1 -> 22.8 -> 21.8, 224 MiB 39.1 -> 41.6 -> 38.7.  With 32 MiB kept instead of 64
+// it is as fast as with none (13.9, 20.9, 38.1), but the pair loses 3 us at 64 MiB and 2 to 9 us on fp32.
 constexpr int kAbsItems = 4;
 constexpr int kAbsThreads = 1024;
 constexpr int kAbsMaxGrid = 256;
 constexpr int kAbsTile = kAbsThreads * kAbsItems;                    // vectors a workgroup has in flight
+constexpr int64_t kAbsKeepVectors = (64 << 20) / 16;
 
 // Maximum over the lane's vectors of one group (bit pattern); `left` vectors of the tensor from `base` on.
-template <int DT>
+template <int DT, bool STREAM>
 __device__ __forceinline__ uint32_t group_absmax(const u32x4* base, uint32_t left, uint32_t off, uint32_t step)
 {
     u32x4 r[kAbsItems];
 #pragma unroll
     for (int i = 0; i < kAbsItems; ++i) {
-        r[i] = base[min(off + (uint32_t)i * step, left - 1u)];                // lanes beyond it read the last vector again
+        const u32x4* p = base + min(off + (uint32_t)i * step, left - 1u);      // lanes beyond it read the last vector again
+        if constexpr (STREAM) r[i] = __builtin_nontemporal_load(p);
+        else r[i] = *p;
     }
     uint32_t m = 0u;
 #pragma unroll
@@ -292,8 +297,13 @@ __device__ __forceinline__ uint32_t workgroup_absmax(const void* __restrict__ x,
     const uint32_t off = (member + threadIdx.x / kSlice * members) * kSlice + threadIdx.x % kSlice;
     const uint32_t step = members * kAbsThreads;
     int64_t g = (n_vec + kGroup - 1) / kGroup - 1 - (int64_t)(ALONE ? 0u : blockIdx.x >> 3);
+    if constexpr (!ALONE) {
+        // (A loop of its own: of two loads in the branches of one the compiler makes a single ordinary one.)
+        for (; g >= kAbsKeepVectors / kGroup; g -= teams)                                               // uniform
+            m = max(m, group_absmax<DT, true>(xv + g * kGroup, (uint32_t)min(kGroup, n_vec - g * kGroup), off, step));
+    }
     for (; g >= 0; g -= teams)                                                                          // uniform
-        m = max(m, group_absmax<DT>(xv + g * kGroup, (uint32_t)min(kGroup, n_vec - g * kGroup), off, step));
+        m = max(m, group_absmax<DT, false>(xv + g * kGroup, (uint32_t)min(kGroup, n_vec - g * kGroup), off, step));
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         for (int64_t i = (n >> 3) << 3; i < n; ++i) {
             uint32_t b;

@@ -1,6 +1,9 @@
 """What the compiler makes of the tensor abs-max (CPU only, gfx950 assembly of aux_kernels.hip).
 
-A division by a run-time group size costs a small call a tenth of its time."""
+The kernel reads the part of a large tensor that the quantise pass will find in the caches with
+ordinary loads and the rest with non-temporal ones.  Written as two branches of one loop the compiler
+merges the two loads and drops the hint, without a word; and a division by a run-time group size costs
+a small call a tenth of its time."""
 import os
 import re
 import shutil
@@ -22,6 +25,16 @@ def bodies(tmp_path_factory):
     found = dict(re.findall(r"^(_ZN3mxq\w*absmax\w*kernelI\w+):(.*?)s_endpgm", text, re.S | re.M))
     assert sum("absmax_kernel" in k for k in found) == 4 and sum("absmax_small_kernel" in k for k in found) == 2
     return found
+
+
+def test_large_tensors_are_read_with_both_kinds_of_load(bodies):
+    for name, body in bodies.items():
+        loads = re.findall(r"global_load_dwordx4.*", body)
+        hinted = sum(l.rstrip().endswith(" nt") for l in loads)
+        if "small" in name:
+            assert len(loads) >= 4 and hinted == 0, name
+        else:
+            assert hinted >= 4 and len(loads) - hinted >= 4, (name, loads)
 
 
 def test_no_division_by_a_run_time_number(bodies):

@@ -153,16 +153,16 @@ def test_tensor_absmax_at_group_edges(mxq, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_tensor_absmax_with_few_tiles(mxq, dtype):
+def test_tensor_absmax_with_few_tiles_and_at_the_change_of_loads(mxq, dtype):
     """One workgroup per tile of 64 KiB up to eight tiles, whole teams beyond, two tiles a workgroup with
-    tickets beyond 64 of them."""
+    tickets beyond 64 of them; and both sides of the 64 MiB where the kind of load changes."""
     size = 4 if dtype == "f32" else 2
-    tile = (64 << 10) // size
+    tile, keep = (64 << 10) // size, (64 << 20) // size
     word, ws = torch.empty(1, device="cuda"), mxq.absmax_workspace()
     sizes = [1, 8, tile - 8, tile, tile + 1, 3 * tile + 9, 7 * tile, 8 * tile, 8 * tile + 1, 9 * tile + 8, 64 * tile, 65 * tile, 129 * tile + 3]
-    for n in sizes:
+    for n in sizes + [keep, keep + 8, keep + 8 * tile + 1, keep + 300 * tile]:
         x = torch.zeros((1, n), dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
-        at = {0, 255, tile - 1, tile, 5 * tile + 77, 8 * tile - 1, 8 * tile, n // 2, n // 8 * 8 - 1, n - 1}
+        at = {0, 255, tile - 1, tile, 5 * tile + 77, 8 * tile - 1, 8 * tile, keep - 1, keep, n // 2, n // 8 * 8 - 1, n - 1}
         print(f"[edges] absmax tiles {dtype} n={n}", flush=True)
         for value, i in enumerate(sorted(i for i in at if 0 <= i < n), start=1):
             x[0, i] = -float(value)                        # the latest one is the largest
