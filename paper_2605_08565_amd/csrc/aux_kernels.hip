@@ -25,8 +25,14 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 // all workgroups of the tensor are resident at once (the shortest path through the kernel), else four:
 // 4096 x 14336, b = 16, against a loop over single chunks in 2048 workgroups: bf16 28.2 -> 25.9 us
 // (5.8 TB/s), fp32 56.5 -> 47.3 us (5.7 TB/s); two chunks 26.7 / 48.5 us, eight 26.9 / 50.0 us, one 31.0
-// us.  16 x 4096 in a graph: one chunk 2.4 us, four 2.9 us.  For b = 2 the loop was as good between
-// 24 and 34 M elements (15.1 against 15.3 us) and worse on either side of that.
+// us.  16 x 4096 in a graph: one chunk 2.4 us, four 2.9 us.
+// bf16 with b < 8, whose scales are half as many bytes as its codes or as many, takes three chunks a lane
+// once four no longer leave all workgroups resident.  b = 2, loop -> four chunks with non-temporal scale
+// loads -> as it is: 4096 x 4096 10.9 -> 11.4 -> 9.4 us (three chunks 10.5), 5000 x 4096 12.7 -> 14.1 ->
+// 12.3 (four 13.4), 8192 x 4096 19.2 -> 20.2 -> 18.2 (19.6), 14336 x 4096 31.5 -> 31.7 -> 28.8 (30.1);
+// b = 4 10.4 -> 10.3 -> 9.7, 11.9 -> 12.7 -> 10.9 (12.1), 18.4 -> 18.1 -> 16.8 (17.5), 29.4 -> 29.0 -> 27.3
+// (27.8).  (With eight such tensors in turn, none of it found in the Infinity Cache, b = 2 stays up to 6 %
+// behind the loop between 14 and 17 M elements.)
 // (A grid counts fewer than 2^32 threads: enough for every tensor that the memory can hold.)
 constexpr int kDqItems = 4;
 constexpr int64_t kDqResident = 256 * 8;                            // workgroups
@@ -50,8 +56,8 @@ __device__ __forceinline__ void dequant_bf16_tile(const uint32_t* __restrict__ c
         for (int i = 0; i < ITEMS; ++i) {
             const uint32_t c = min((uint32_t)threadIdx.x + (uint32_t)i * kThreads, valid - 1u);
             packed[i] = __builtin_nontemporal_load(cp + c);
-            if constexpr (NBLK == 4) sb[i] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(sp) + c);
-            else if constexpr (NBLK == 2) sb[i] = __builtin_nontemporal_load(reinterpret_cast<const uint16_t*>(sp) + c);
+            if constexpr (NBLK == 4) sb[i] = reinterpret_cast<const uint32_t*>(sp)[c];
+            else if constexpr (NBLK == 2) sb[i] = reinterpret_cast<const uint16_t*>(sp)[c];
             else sb[i] = sp[c / LANES];
         }
 #pragma unroll
@@ -99,6 +105,14 @@ dequant_bf16_one_kernel(const uint32_t* __restrict__ codes, const uint8_t* __res
                           const float* __restrict__ t_dev, uint16_t* __restrict__ out)
 {
     dequant_bf16_tile<B, 1>(codes, scales, n, fmt, T, t_dev, out);
+}
+
+template <int B>
+__global__ void __launch_bounds__(kThreads)
+dequant_bf16_three_kernel(const uint32_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n, int fmt, float T,
+                          const float* __restrict__ t_dev, uint16_t* __restrict__ out)
+{
+    dequant_bf16_tile<B, 3>(codes, scales, n, fmt, T, t_dev, out);
 }
 
 // fp32 output: one lane = 4 consecutive elements = 16 bits of codes = one 128-bit store, so a
@@ -191,12 +205,17 @@ static void launch_dequant_f32(const DequantArgs& a)
 
 static void launch_dequant_bf16(const DequantArgs& a)
 {
-    const bool one = a.n <= kDqResident * kThreads * 8;
-    const int64_t tile = 8 * (int64_t)kThreads * (one ? 1 : kDqItems);
+    const int64_t resident = kDqResident * kThreads * 8;                 // elements, one chunk per lane
+    const int items = a.n <= resident ? 1 : (a.block < 8 && a.n > resident * kDqItems) ? 3 : kDqItems;
+    const int64_t tile = 8 * (int64_t)kThreads * items;
     const unsigned grid = (unsigned)((a.n + tile - 1) / tile);
+#define MXQ_DQ_LAUNCH(KERNEL)                                                                         \
+    hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(kThreads), 0, a.stream, (const uint32_t*)a.codes, a.scales, (uint64_t)a.n,       \
+                       a.scale_fmt, a.T, a.t_dev, (uint16_t*)a.out)
 #define MXQ_DQ(BB)                                                                                   \
-    hipLaunchKernelGGL((one ? dequant_bf16_one_kernel<BB> : dequant_bf16_kernel<BB>), dim3(grid), dim3(kThreads), 0, a.stream,   \
-                       (const uint32_t*)a.codes, a.scales, (uint64_t)a.n, a.scale_fmt, a.T, a.t_dev, (uint16_t*)a.out)
+    if (items == 1) MXQ_DQ_LAUNCH((dequant_bf16_one_kernel<BB>));                                     \
+    else if (BB >= 8 || items != 3) MXQ_DQ_LAUNCH((dequant_bf16_kernel<BB>));                         \
+    else MXQ_DQ_LAUNCH((dequant_bf16_three_kernel<(BB < 8) ? BB : 2>))
     switch (a.block) {
         case 2: MXQ_DQ(2); break;
         case 4: MXQ_DQ(4); break;
@@ -207,6 +226,7 @@ static void launch_dequant_bf16(const DequantArgs& a)
         default: MXQ_DQ(128); break;
     }
 #undef MXQ_DQ
+#undef MXQ_DQ_LAUNCH
 }
 
 hipError_t launch_dequant(const DequantArgs& a)

@@ -182,7 +182,10 @@ def test_dequantize_at_tile_edges(oracle, mxq, block, dtype):
     per = 8 if dtype == "bf16" else 4
     line = 2048 * 256 * per
     out_dtype = torch.bfloat16 if dtype == "bf16" else torch.float32
-    for n in (block, 256 * per - block, 256 * per + block, 1024 * per + 8, line - block, line, line + block, line + 1024 * per - block):
+    beyond = [line + k * 256 * per + d for k in (3, 4) for d in (-block, block)]
+    if dtype == "bf16" and block < 8:                      # three chunks per lane beyond 2048 workgroups of four
+        beyond += [4 * line + d for d in (-block, 0, block, 3 * 256 * per - block, 3 * 256 * per + block)]
+    for n in (block, 256 * per - block, 256 * per + block, 1024 * per + 8, line - block, line, line + block, *beyond):
         n = n // block * block
         if n == 0:
             continue
