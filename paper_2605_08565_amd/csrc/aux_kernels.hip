@@ -33,7 +33,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 // b = 4 10.4 -> 10.3 -> 9.7, 11.9 -> 12.7 -> 10.9 (12.1), 18.4 -> 18.1 -> 16.8 (17.5), 29.4 -> 29.0 -> 27.3
 // (27.8).  (With eight such tensors in turn, none of it found in the Infinity Cache, b = 2 stays up to 6 %
 // behind the loop between 14 and 17 M elements.)
-// (A grid counts fewer than 2^32 threads: enough for every tensor that the memory can hold.)
 constexpr int kDqItems = 4;
 constexpr int64_t kDqResident = 256 * 8;                            // workgroups
 template <int B, int ITEMS>
@@ -229,11 +228,24 @@ static void launch_dequant_bf16(const DequantArgs& a)
 #undef MXQ_DQ_LAUNCH
 }
 
+// A grid counts fewer than 2^32 threads of 16 to 32 elements: larger tensors (codes or output may lie in
+// host memory that the GPU can address) are taken in pieces.
+constexpr int64_t kDqPiece = (int64_t)1 << 35;
+
 hipError_t launch_dequant(const DequantArgs& a)
 {
-    if (a.dtype == kBF16) launch_dequant_bf16(a);
-    else launch_dequant_f32(a);
-    return hipGetLastError();
+    DequantArgs piece = a;
+    for (int64_t done = 0; done < a.n; done += kDqPiece) {
+        piece.codes = a.codes + done / 2;
+        piece.scales = a.scales + done / a.block;
+        piece.out = static_cast<char*>(a.out) + done * (a.dtype == kBF16 ? 2 : 4);
+        piece.n = a.n - done < kDqPiece ? a.n - done : kDqPiece;
+        if (a.dtype == kBF16) launch_dequant_bf16(piece);
+        else launch_dequant_f32(piece);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // Tensor abs-max.  |x| of finite fp32 values orders like the unsigned integer bits & 0x7fffffff,

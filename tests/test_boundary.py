@@ -215,3 +215,17 @@ def test_header_is_plain_c_and_links(tmp_path, mxq):
                     str(src), "-o", str(exe), "-L", libdir, "-lmxq", f"-Wl,-rpath,{libdir}"], check=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout.split()
     assert out == ["126", "254", "448", "MXQ_ERR_ALIGNMENT"]
+
+
+def test_dequantize_takes_tensors_beyond_one_grid_in_pieces(tmp_path):
+    """The launcher's own code with a recording stand-in for the runtime's kernel launch."""
+    import shutil
+    import subprocess
+    from paper_2605_08565_amd.build import FLAGS
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    exe = str(tmp_path / "launch_pieces_check")
+    subprocess.run([hipcc, *FLAGS, os.path.join(ROOT, "tests", "host", "launch_pieces_check.hip"),
+                    os.path.join(ROOT, "paper_2605_08565_amd", "csrc", "aux_kernels.hip"), "-o", exe], check=True, capture_output=True)
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    print(res.stdout)
+    assert res.returncode == 0 and "cases=196 bad=0" in res.stdout
