@@ -95,12 +95,19 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError("libmxq takes bfloat16 or float32 tensors")
 
 
+# Not part of torch's public interface: without them the public calls are used.
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream) -> int:
-    """The hipStream_t of `stream`, by default the current one.  The raw handle is asked for directly:
-    building a torch.cuda.Stream object to read it from costs 2.8 us a call against 0.2 us, more than
-    the rest of a small call's argument handling."""
+    """The hipStream_t of `stream`, by default the current one.  The raw handle is asked for directly
+    where torch offers that: building a torch.cuda.Stream object to read it from costs 2.8 us a call
+    against 0.2 us, more than the rest of a small call's argument handling."""
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _current_device is not None and _current_raw_stream is not None:
+            return _current_raw_stream(_current_device())
+        stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
 

@@ -98,3 +98,29 @@ def test_binding_checks_arguments_before_any_launch():
         mxq.quantize(x, 16, mxq.SCALE_E4M3, mxq.RECIPE_ABSMAX)
     with pytest.raises(ValueError):
         mxq.quantize_batch([x], 16, mxq.SCALE_E4M3, mxq.RECIPE_ABSMAX)
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getDevice", "_cuda_getCurrentRawStream"])
+def test_stream_of_a_torch_without_the_raw_handle(monkeypatch, missing):
+    """The raw stream handle comes from functions that torch does not promise; without one of them the
+    public call answers."""
+    import importlib.util
+    from types import SimpleNamespace
+
+    from paper_2605_08565_amd import mxq
+
+    monkeypatch.delattr(torch._C, missing, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: SimpleNamespace(cuda_stream=0x1234))
+    spec = importlib.util.spec_from_file_location("mxq_without_raw_handle", mxq.__file__)
+    fresh = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(fresh)
+    assert fresh._stream_ptr(None) == 0x1234
+    assert fresh._stream_ptr(SimpleNamespace(cuda_stream=7)) == 7
+
+
+def test_stream_is_the_raw_handle_of_the_current_device(monkeypatch):
+    from paper_2605_08565_amd import mxq
+
+    monkeypatch.setattr(mxq, "_current_device", lambda: 3)
+    monkeypatch.setattr(mxq, "_current_raw_stream", lambda d: 0x5000 + d)
+    assert mxq._stream_ptr(None) == 0x5003
