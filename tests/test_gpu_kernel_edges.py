@@ -57,6 +57,51 @@ def test_pruned_search_window_edges(oracle, mxq, fmt, block, dtype):
         same(mxq.quantize(mxq.from_bits(x), block, fmt, mxq.RECIPE_BRUTE_PRUNED, tensor_scale=T), ref)
 
 
+@pytest.mark.parametrize("T", [1.0, 0.7])
+@pytest.mark.parametrize("fmt", [1, 2])
+@pytest.mark.parametrize("block", [2, 4, 8, 16])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_pruned_search_in_wavefronts_of_normal_scales(oracle, mxq, fmt, block, dtype, T):
+    """The unrolled way up runs only where EVERY block of a wavefront (512 elements) starts at a code from
+    16 to top - 7, so whole wavefronts of such blocks are made: all codes of that range, its two ends in
+    every wavefront, the abs-max on and beside 3.5, 4, 5 and 6 times a scale.  Behind them wavefronts
+    with a single block one code too low and one too high, which send it the general way."""
+    rng = np.random.default_rng(100 * block + 10 * fmt + (dtype == "bf16"))
+    top, per_wave = oracle.scale_max_code(fmt), 512 // block
+    grid = np.array([0, .25, .5, .75, 1, 1.25, 1.5, 1.75, 2, 2.5, 3, 3.5], np.float32)
+
+    def make(codes, factors):
+        """One block per (code, factor, neighbour) and the codes that the abs-max rule gives them."""
+        c, f, d = (a.ravel() for a in np.meshgrid(codes, factors, (-1, 0, 1), indexing="ij"))
+        s = np.array([oracle.scale_decode(fmt, int(i)) for i in c], np.float32) * np.float32(T)
+        step = 1 if dtype == "f32" else 1 << 16
+        amax = (((s * f.astype(np.float32)).view(np.uint32) // step + d.astype(np.uint32)) * step).astype(np.uint32).view(np.float32)
+        v = np.where(rng.random((len(c), 1)) < 0.5, rng.choice(grid, (len(c), block)) * s[:, None], rng.random((len(c), block)) * amax[:, None])
+        v = np.minimum(v, amax[:, None]) * rng.choice([-1, 1], (len(c), block))
+        v[np.arange(len(c)), rng.integers(block, size=len(c))] = amax
+        x = v.astype(np.float32)
+        x = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+        return x, oracle.quantize(x, block, fmt, 0, tensor_scale=T)[1][:, 0].astype(int)
+
+    x, start = make(np.arange(16, top + 1), (3.5, 4.0, 5.0, 6.0))
+    x, start = x[(start >= 16) & (start <= top - 7)], start[(start >= 16) & (start <= top - 7)]
+    ends = np.concatenate([x[start == 16][:1], x[start == top - 7][:1]])
+    out, out_start = make([15, top - 6], (6.0,))
+    low, high = out[out_start < 16][:1], out[out_start > top - 7][:1]
+    x = x[rng.permutation(len(x))]
+    body = per_wave - 3
+    waves = [np.concatenate([ends, x[i:i + body], x[:1]]) for i in range(0, len(x) - body, body)]
+    waves[-2][-1], waves[-1][-1] = low[0], high[0]
+    x = np.concatenate(waves)
+    start = oracle.quantize(x, block, fmt, 0, tensor_scale=T)[1][:, 0].astype(int).reshape(len(waves), per_wave)
+    inside = ((start >= 16) & (start <= top - 7))
+    assert inside.all(axis=1).sum() == len(waves) - 2 >= 2 and (inside.sum(axis=1)[-2:] == per_wave - 1).all()
+    assert (start[:-2].min(axis=1) == 16).all() and (start[:-2].max(axis=1) == top - 7).all()
+    print(f"[edges] fast wavefronts fmt={fmt} b={block} {dtype} T={T} wavefronts={len(waves)}", flush=True)
+    same(mxq.quantize(mxq.from_bits(x), block, fmt, mxq.RECIPE_BRUTE_PRUNED, tensor_scale=T),
+         oracle.quantize(x, block, fmt, 4, tensor_scale=T))
+
+
 @pytest.mark.parametrize("fmt", [1, 2])
 @pytest.mark.parametrize("block", [2, 4, 8, 128])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
