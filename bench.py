@@ -158,7 +158,7 @@ KERNEL_OF_PASS = {
     "brute_ue5m3_b16": "mxq::brute_kernel<0, 16, 2, false, false>",
     "brute_e4m3_b4": "mxq::brute_kernel<0, 4, 1, false, false>",
     "brute_ue5m3_b4": "mxq::brute_kernel<0, 4, 2, false, false>",
-    "dequantize_e4m3_b16_bf16": "mxq::dequant_bf16_kernel<16>",
+    "dequantize_e4m3_b16_bf16": "mxq::dequant_bf16_kernel<16, 4>",
     "tensor_absmax": "mxq::absmax_kernel<0, false>",
 }
 PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "hbm_traffic_bf16_4096x14336.md")

@@ -33,10 +33,11 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 // b = 4 10.4 -> 10.3 -> 9.7, 11.9 -> 12.7 -> 10.9 (12.1), 18.4 -> 18.1 -> 16.8 (17.5), 29.4 -> 29.0 -> 27.3
 // (27.8).  (With eight such tensors in turn, none of it found in the Infinity Cache, b = 2 stays up to 6 %
 // behind the loop between 14 and 17 M elements.)
-constexpr int kDqItems = 4;
+constexpr int kDqItems = 4, kDqItemsLarge = 3;
 constexpr int64_t kDqResident = 256 * 8;                            // workgroups
 template <int B, int ITEMS>
-__device__ __forceinline__ void dequant_bf16_tile(const uint32_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n,
+__global__ void __launch_bounds__(kThreads)
+dequant_bf16_kernel(const uint32_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n,
                     int fmt, float T_arg, const float* __restrict__ t_dev, uint16_t* __restrict__ out)
 {
     const float T = t_dev ? *t_dev : T_arg;                         // per-tensor scale by value or from device memory
@@ -90,37 +91,13 @@ __device__ __forceinline__ void dequant_bf16_tile(const uint32_t* __restrict__ c
     }
 }
 
-template <int B>
-__global__ void __launch_bounds__(kThreads)
-dequant_bf16_kernel(const uint32_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n, int fmt, float T,
-                      const float* __restrict__ t_dev, uint16_t* __restrict__ out)
-{
-    dequant_bf16_tile<B, kDqItems>(codes, scales, n, fmt, T, t_dev, out);
-}
-
-template <int B>
-__global__ void __launch_bounds__(kThreads)
-dequant_bf16_one_kernel(const uint32_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n, int fmt, float T,
-                          const float* __restrict__ t_dev, uint16_t* __restrict__ out)
-{
-    dequant_bf16_tile<B, 1>(codes, scales, n, fmt, T, t_dev, out);
-}
-
-template <int B>
-__global__ void __launch_bounds__(kThreads)
-dequant_bf16_three_kernel(const uint32_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n, int fmt, float T,
-                          const float* __restrict__ t_dev, uint16_t* __restrict__ out)
-{
-    dequant_bf16_tile<B, 3>(codes, scales, n, fmt, T, t_dev, out);
-}
-
 // fp32 output: one lane = 4 consecutive elements = 16 bits of codes = one 128-bit store, so a
 // store instruction of a wavefront covers 1 KiB without gaps (with 8 elements per lane its two
 // stores would each leave every other 16 bytes untouched).  n is even, so at most 2 elements are
 // left behind the complete quads.
 template <int B, int ITEMS>
-__device__ __forceinline__ void dequant_f32_tile(const uint16_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n,
-                   int fmt, float T_arg, const float* __restrict__ t_dev, float* __restrict__ out)
+__global__ void __launch_bounds__(kThreads)
+dequant_f32_kernel(const uint16_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n, int fmt, float T_arg, const float* __restrict__ t_dev, float* __restrict__ out)
 {
     const float T = t_dev ? *t_dev : T_arg;
     constexpr int EPB = (B < 4) ? B : 4;
@@ -166,29 +143,13 @@ __device__ __forceinline__ void dequant_f32_tile(const uint16_t* __restrict__ co
     }
 }
 
-template <int B>
-__global__ void __launch_bounds__(kThreads)
-dequant_f32_kernel(const uint16_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n, int fmt, float T,
-                     const float* __restrict__ t_dev, float* __restrict__ out)
-{
-    dequant_f32_tile<B, kDqItems>(codes, scales, n, fmt, T, t_dev, out);
-}
-
-template <int B>
-__global__ void __launch_bounds__(kThreads)
-dequant_f32_one_kernel(const uint16_t* __restrict__ codes, const uint8_t* __restrict__ scales, uint64_t n, int fmt, float T,
-                         const float* __restrict__ t_dev, float* __restrict__ out)
-{
-    dequant_f32_tile<B, 1>(codes, scales, n, fmt, T, t_dev, out);
-}
-
 static void launch_dequant_f32(const DequantArgs& a)
 {
     const bool one = a.n <= kDqResident * kThreads * 4;
     const int64_t tile = 4 * (int64_t)kThreads * (one ? 1 : kDqItems);
     const unsigned grid = (unsigned)((a.n + tile - 1) / tile);
 #define MXQ_DQF(BB)                                                                                  \
-    hipLaunchKernelGGL((one ? dequant_f32_one_kernel<BB> : dequant_f32_kernel<BB>), dim3(grid), dim3(kThreads), 0, a.stream,    \
+    hipLaunchKernelGGL((one ? dequant_f32_kernel<BB, 1> : dequant_f32_kernel<BB, kDqItems>), dim3(grid), dim3(kThreads), 0, a.stream,    \
                        (const uint16_t*)a.codes, a.scales, (uint64_t)a.n, a.scale_fmt, a.T, a.t_dev, (float*)a.out)
     switch (a.block) {
         case 2: MXQ_DQF(2); break;
@@ -205,16 +166,13 @@ static void launch_dequant_f32(const DequantArgs& a)
 static void launch_dequant_bf16(const DequantArgs& a)
 {
     const int64_t resident = kDqResident * kThreads * 8;                 // elements, one chunk per lane
-    const int items = a.n <= resident ? 1 : (a.block < 8 && a.n > resident * kDqItems) ? 3 : kDqItems;
+    const int items = a.n <= resident ? 1 : (a.block < 8 && a.n > resident * kDqItems) ? kDqItemsLarge : kDqItems;
     const int64_t tile = 8 * (int64_t)kThreads * items;
     const unsigned grid = (unsigned)((a.n + tile - 1) / tile);
-#define MXQ_DQ_LAUNCH(KERNEL)                                                                         \
-    hipLaunchKernelGGL(KERNEL, dim3(grid), dim3(kThreads), 0, a.stream, (const uint32_t*)a.codes, a.scales, (uint64_t)a.n,       \
-                       a.scale_fmt, a.T, a.t_dev, (uint16_t*)a.out)
 #define MXQ_DQ(BB)                                                                                   \
-    if (items == 1) MXQ_DQ_LAUNCH((dequant_bf16_one_kernel<BB>));                                     \
-    else if (BB >= 8 || items != 3) MXQ_DQ_LAUNCH((dequant_bf16_kernel<BB>));                         \
-    else MXQ_DQ_LAUNCH((dequant_bf16_three_kernel<(BB < 8) ? BB : 2>))
+    hipLaunchKernelGGL((items == 1 ? dequant_bf16_kernel<BB, 1> : items == kDqItems ? dequant_bf16_kernel<BB, kDqItems>         \
+                        : dequant_bf16_kernel<BB, (BB < 8) ? kDqItemsLarge : kDqItems>), dim3(grid), dim3(kThreads), 0,         \
+                       a.stream, (const uint32_t*)a.codes, a.scales, (uint64_t)a.n, a.scale_fmt, a.T, a.t_dev, (uint16_t*)a.out)
     switch (a.block) {
         case 2: MXQ_DQ(2); break;
         case 4: MXQ_DQ(4); break;
@@ -225,7 +183,6 @@ static void launch_dequant_bf16(const DequantArgs& a)
         default: MXQ_DQ(128); break;
     }
 #undef MXQ_DQ
-#undef MXQ_DQ_LAUNCH
 }
 
 // A grid counts fewer than 2^32 threads of 16 to 32 elements: larger tensors (codes or output may lie in
