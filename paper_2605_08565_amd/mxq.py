@@ -95,9 +95,14 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError("libmxq takes bfloat16 or float32 tensors")
 
 
-# Not part of torch's public interface: without them the public calls are used.
-_current_device = getattr(torch._C, "_cuda_getDevice", None)
-_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+try:
+    _current_device, _current_raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+except AttributeError:                  # not part of torch's public interface: the public call instead
+    def _current_device() -> int:
+        return torch.cuda.current_device()
+
+    def _current_raw_stream(device: int) -> int:
+        return int(torch.cuda.current_stream(device).cuda_stream)
 
 
 def _stream_ptr(stream) -> int:
@@ -105,9 +110,7 @@ def _stream_ptr(stream) -> int:
     where torch offers that: building a torch.cuda.Stream object to read it from costs 2.8 us a call
     against 0.2 us, more than the rest of a small call's argument handling."""
     if stream is None:
-        if _current_device is not None and _current_raw_stream is not None:
-            return _current_raw_stream(_current_device())
-        stream = torch.cuda.current_stream()
+        return _current_raw_stream(_current_device())
     return int(stream.cuda_stream)
 
 

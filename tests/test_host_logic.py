@@ -110,11 +110,12 @@ def test_stream_of_a_torch_without_the_raw_handle(monkeypatch, missing):
     from paper_2605_08565_amd import mxq
 
     monkeypatch.delattr(torch._C, missing, raising=False)
-    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: SimpleNamespace(cuda_stream=0x1234))
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 2)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: SimpleNamespace(cuda_stream=0x1234 + (device or 0)))
     spec = importlib.util.spec_from_file_location("mxq_without_raw_handle", mxq.__file__)
     fresh = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(fresh)
-    assert fresh._stream_ptr(None) == 0x1234
+    assert fresh._stream_ptr(None) == 0x1236
     assert fresh._stream_ptr(SimpleNamespace(cuda_stream=7)) == 7
 
 
