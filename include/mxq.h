@@ -67,9 +67,12 @@ typedef enum { MXQ_SCALE_E8M0 = 0, MXQ_SCALE_E4M3 = 1, MXQ_SCALE_UE5M3 = 2 } mxq
  *              E4M3, 254 for UE5M3, the 255 powers of two 2^(byte-127), byte 0 .. 254, for E8M0.
  *   BRUTE_PRUNED  the same result as BRUTE, bit for bit, but candidates that provably cannot
  *              win are skipped: scales whose half is a scale code too and fits the block at least
- *              as well, and scales so small that the clipping error of the abs-max element alone
- *              costs more than the best candidate so far.  4 to 14 times faster than BRUTE.  A step
- *              toward cheaper near-optimal selection (Conclusion).
+ *              as well, and scales so small that the clipping error of the abs-max element alone,
+ *              or of all saturated elements, costs more than the best candidate so far.  A step
+ *              toward cheaper near-optimal selection (Conclusion).  Time of BRUTE over time of
+ *              BRUTE_PRUNED, 16 M elements, both dtypes, all block sizes, with and without the
+ *              per-tensor scale: E4M3 3.4 to 6.4, UE5M3 6.5 to 12.5 (b = 2 and values beyond the
+ *              format the least); up to 17 where the scales are tiny.
  * 4OVER6* and BRUTE_PRUNED with E8M0 return MXQ_ERR_UNSUPPORTED (Eq. 4 rounds amax / M to the
  * scale format, which the floor rule of Eq. 1 does not define). */
 typedef enum {
@@ -226,9 +229,9 @@ MXQ_API int mxq_tensor_absmax_acc(const void* x, int64_t rows, int64_t cols, int
                           float* absmax_inout, float* clear_word, void* stream);
 
 /*
- * mxq_tensor_absmax_ws -- mxq_tensor_absmax in ONE launch (that one needs a second, tiny launch
- * that clears the output word first, except for small tensors) and without a precondition on the output word (unlike
- * mxq_tensor_absmax_acc): the workgroups meet in a caller-owned workspace, and the one that
+ * mxq_tensor_absmax_ws -- mxq_tensor_absmax in ONE launch (beyond 160 KiB that one needs a second,
+ * tiny launch that clears the output word first) and without a precondition on the output word
+ * (unlike mxq_tensor_absmax_acc): the workgroups meet in a caller-owned workspace, and the one that
  * arrives last writes the output.  One graph node instead of two; the tail of the kernel is
  * longer than that of the other two forms (three dependent device-scope atomics), so on large
  * tensors it is the slowest of the three (first stage of hierarchical scaling, Section 2).

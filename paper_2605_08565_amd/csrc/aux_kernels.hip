@@ -234,7 +234,9 @@ __global__ void absmax_clear_kernel(uint32_t* out) { *out = 0u; }
 // order, ordinary loads throughout -> as it is: bf16 64 MiB 30.9 -> 27.2 -> 26.6 us, 112 MiB 49.2 -> 46.0
 // -> 45.2, 384 MiB 153 -> 164 -> 149; fp32 128 MiB 52.5 -> 46.7 -> 46.8.  The abs-max alone: 64 MiB 13.7 ->
 // 14.8 -> 14.5, 112 MiB 21.1 -> 22.8 -> 21.8, 224 MiB 39.1 -> 41.6 -> 38.7.  With 32 MiB kept instead of 64
-// it is as fast as with none (13.9, 20.9, 38.1), but the pair loses 3 us at 64 MiB and 2 to 9 us on fp32.
+// it is as fast as with none (13.9, 20.9, 38.1), but the pair on re-used outputs loses 1 us at 64 MiB, up to 4 on fp32.
+// (Ordinary loads also push out what others have written: eight fills of 64 MiB and eight abs-max take 30.5
+// us a pair instead of 24.3, and quantising with b <= 4 into fresh buffers loses 5 to 10 %.)
 constexpr int kAbsItems = 4;
 constexpr int kAbsThreads = 1024;
 constexpr int kAbsMaxGrid = 256;
