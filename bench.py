@@ -14,10 +14,11 @@ Infinity Cache and one event pair brackets eight launches of the same kernel.
 Prints ONE JSON line: whole-step throughput in GElem/s (element-passes quantised per second),
 a per-recipe breakdown, the roofline of the kernel that dominates the step (measured with
 events around every launch inside the timed region), the HBM roofline of the streaming
-kernels, the attainable HBM ceilings measured in the same run (read-only, copy, fill), a
-`configs` object with one timed row per configuration / block size of the other workloads
-(fp32 matrix, activation tensor with hierarchical scaling, the 32-layer model sweep, the
-appendix diagnostics), and the CPU oracle timed on a bounded sample of the step's workload.
+kernels, the attainable HBM ceilings measured in the same run (read-only, copy, fill), and the CPU
+oracle timed on a bounded sample of the step's workload.  The line is about 3 KB; one more JSON
+line, on stderr, holds the rows of every pass (`kernels`) and a `configs` object with one timed row
+per configuration / block size of the other workloads (fp32 matrix, activation tensor with
+hierarchical scaling, the 32-layer model sweep, the appendix diagnostics).
 """
 from __future__ import annotations
 
@@ -204,6 +205,15 @@ def recorded(pass_name):
         out["wait_issue_pct"] = float(w[kern][4].rstrip(" %"))
         out["wait_data_pct"] = float(w[kern][5].rstrip(" %"))
     return out
+
+
+def split_output(out):
+    """(the result line for stdout, the tables for stderr): the rows of every pass and configuration are
+    30 KB, more than a reader that keeps the end of stdout can be expected to hold."""
+    details = {k: out[k] for k in ("kernels", "configs") if k in out}
+    line = {k: v for k, v in out.items() if k not in details}
+    line["details"] = "per-pass and per-configuration rows: a JSON line on stderr"
+    return line, details
 
 
 def cpu_baseline(x_np, passes, T, rows):
@@ -663,7 +673,9 @@ def main():
         out["roofline_4over6"] = roof(f6[0], {"bytes_per_elem": 2.8125})
     if not args.no_cpu and not profiling:
         out["cpu_baseline"] = cpu_baseline(w2.x_np, passes, T, args.cpu_rows)
-    print(json.dumps(out))
+    line, details = split_output(out)
+    print(json.dumps({"details": details}), file=sys.stderr, flush=True)
+    print(json.dumps(line), flush=True)
 
 
 if __name__ == "__main__":

@@ -89,6 +89,21 @@ def test_benchmark_pass_list():
     assert not set(extra) & set(names)
 
 
+def test_benchmark_result_line_is_short():
+    """The tables of passes and configurations go to stderr; what is left fits the last few KB of stdout."""
+    import json
+
+    import bench
+
+    rows = [{"name": p[1], "ms": 0.12345, "gelem_s": 1234.5} for p in bench.step_passes()]
+    out = {"metric": "m", "value": 1.0, "config": {"workload": "w" * 300}, "per_recipe_gelem_s": {r["name"]: r["gelem_s"] for r in rows},
+           "roofline": {"note": "n" * 900}, "kernels": rows * 10, "configs": {"config3": rows * 50}}
+    line, details = bench.split_output(out)
+    assert len(json.dumps(line)) < 4000
+    assert set(line) - {"details"} == set(out) - {"kernels", "configs"}
+    assert details == {"kernels": out["kernels"], "configs": out["configs"]}
+
+
 def test_binding_checks_arguments_before_any_launch():
     """Wrong devices, shapes and dtypes are refused by the binding itself."""
     from paper_2605_08565_amd import mxq
