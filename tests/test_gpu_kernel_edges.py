@@ -221,7 +221,7 @@ def test_tensor_absmax_with_few_tiles_and_at_the_change_of_loads(mxq, dtype):
 @pytest.mark.parametrize("block", [2, 4, 8, 128])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_dequantize_at_tile_edges(oracle, mxq, block, dtype):
-    """One chunk per lane up to 2048 workgroups, four beyond: remainders of a chunk, of a workgroup's tile and
+    """One chunk per lane up to 2048 workgroups, four (or three) beyond: remainders of a chunk, of a workgroup's tile and
     the line between the two, T by value and from device memory."""
     rng = np.random.default_rng(block)
     per = 8 if dtype == "bf16" else 4

@@ -95,7 +95,7 @@ def test_walk_over_single_blocks_with_the_kernels_rules(tmp_path):
     SSE bits as all codes tried, and never many candidates -- also for blocks beyond the format, which
     the clipping bound of one element alone would send through every code (126 and 254), and for NaN and
     infinity.  The longest way down before a floor is looked for is 16 steps; with the start and the floor
-    itself that is 18 candidates for such a block, and no ordinary block needs more than 15."""
+    itself that is 18 candidates; ordinary blocks end well before (15 on these inputs)."""
     if "fma" not in open("/proc/cpuinfo").read():
         pytest.skip("host CPU has no FMA instruction")
     exe = str(tmp_path / "search_walk_check")
