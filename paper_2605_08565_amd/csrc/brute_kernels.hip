@@ -253,7 +253,8 @@ __device__ __forceinline__ void walk_loss(const float (&v)[8], const float (&S)[
 // Called when a wavefront has gone walk_patience steps down.
 // 4096 x 4096 bf16 Student-t values, with the walk alone -> with the floor: E4M3, values times 2^16, b = 2
 // 653 -> 69 us, b = 16 357 -> 44, b = 128 392 -> 76 (full enumeration 251 to 278); UE5M3, times 2^30, b = 2
-// 1287 -> 63 us, b = 16 735 -> 46, b = 128 711 -> 77 (457 to 530); values inside the formats within 2 %.
+// 1287 -> 63 us, b = 16 735 -> 46, b = 128 711 -> 77 (457 to 530); values inside the formats within 2 %, for
+// which the compiler has to be told that this is the rare path (b = 128 with a tensor scale 177 -> 175 us).
 template <int B, int FMT, bool ONE_MUL>
 __device__ __forceinline__ void walk_saturated(const float (&v)[8], uint32_t (&code)[BruteState<B>::NBLK],
                                                uint32_t (&floor)[BruteState<B>::NBLK], BruteState<B>& st)
@@ -320,7 +321,7 @@ __device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_
         floor[k] = 1u;
         none |= !better;
     }
-    if (__builtin_amdgcn_ballot_w64(none) != 0ull) {                    // uniform, rare
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(none) != 0ull, 0)) {                    // uniform
         // Under every code a NaN stays a NaN, and where the saturated elements alone overflow here they
         // do under every lower code (there is none above).  Such a block walks like one of zeros: not at
         // all, with code 1 as the full enumeration has it.
@@ -379,7 +380,7 @@ __device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) code[k] = start[k];
     for (uint32_t step = 0u;; ++step) {                                 // downwards: the lower code wins a tie
-        if (step == walk_patience(B)) walk_saturated<B, FMT, ONE_MUL>(v, code, floor, st);
+        if (__builtin_expect(step == walk_patience(B), 0)) walk_saturated<B, FMT, ONE_MUL>(v, code, floor, st);
         bool any = false;
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) {
