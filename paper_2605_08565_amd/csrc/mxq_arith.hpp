@@ -99,12 +99,26 @@ MXQ_HD float quot(float v, Recip r)
     return __builtin_fmaf(v, r.hi, v * r.lo);
 }
 
-// A single multiplication by a rounded reciprocal is NOT enough for the code, not even for bf16 inputs with
-// their 8 significant bits: an input that sits exactly on a tie (v = t*d) must produce exactly t
-// for the ties-to-even rule of the E2M1 rounding, and t*d*fl(1/d) misses t by an ulp for most d
+// A single multiplication by a rounded reciprocal, rounded to nearest, is NOT enough for the code, not even
+// for bf16 inputs with their 8 significant bits: an input that sits exactly on a tie (v = t*d) must produce
+// exactly t for the ties-to-even rule of the E2M1 rounding, and t*d*fl(1/d) misses t by an ulp for most d
 // (the host-side check shows the failures when quot is replaced by one product).  Where only the
 // residual is needed and not the code, one product does for 8 significant bits: an exact tie leaves the
-// same |residual| on either side, and every other quotient is 2^-9 away from a mid-point (walk_sse).
+// same |residual| on either side, and every other quotient is 2^-8 away from a mid-point (walk_sse).
+//
+// One product that is TRUNCATED does for the code too.  The float nearest to 1/d is (1/d)*(1 + e*2^-24) with
+// e = 0, .125, .25 .. .875 for the eight scale mantissas 1, 1.125 .. 1.875: never below 1/d.  An exact
+// tie gives t*(1 + e*2^-24), less than an ulp (2^-23) above t, which truncates to t; every other quotient is
+// 2^-8 away from a mid-point.  quot_truncated() says what the kernels' products compute (quot8_truncated in
+// mxq_device.hpp switches the rounding mode around them).
+#if !defined(__HIP_DEVICE_COMPILE__)
+inline float quot_truncated(float v, float nearest_reciprocal)
+{
+    const double exact = (double)v * (double)nearest_reciprocal;                // at most 48 bits
+    const float f = (float)exact;
+    return __builtin_fabs((double)f) > __builtin_fabs(exact) ? u2f(f2u(f) - 1u) : f;      // away from zero: one step back
+}
+#endif
 
 // ---------------------------------------------------------------------------------------
 // Scalar rules of the pruned scale search (the walk itself is brute_search_pruned; the host check

@@ -10,6 +10,8 @@
 #include "mxq_device.hpp"
 #include "mxq_launch.hpp"
 
+#include <type_traits>
+
 #ifndef MXQ_STREAM_ITEMS
 #define MXQ_STREAM_ITEMS 1
 #endif
@@ -37,22 +39,24 @@ __device__ __forceinline__ void absmax_codes(float amax, uint32_t floor_code, ui
     }
 }
 
-// Quantise the lane's 8 values (NBLK blocks of EPB elements, one scale code each) under
-// table scales: packed nibbles and the 8 squared residuals.
-template <int NBLK, int EPB>
-__device__ __forceinline__ void quant_lane(const float (&v)[8], const uint32_t (&code)[NBLK],
-                                           const ScaleEntry* tab, uint32_t& packed, float (&sq)[8], float (&S)[NBLK])
+// Quantise the lane's 8 values (NBLK blocks of EPB elements, one table entry each): packed nibbles and
+// the 8 squared residuals.  The quotient is one truncated product with 1/S (ScalePair) or the
+// two-part product (ScaleEntry).
+template <int NBLK, int EPB, class Entry>
+__device__ __forceinline__ void quant_lane(const float (&v)[8], const Entry (&entry)[NBLK], uint32_t& packed, float (&sq)[8],
+                                           float (&S)[NBLK])
 {
     float y[8];
 #pragma unroll
-    for (int k = 0; k < NBLK; ++k) {
-        const ScaleEntry se = tab[code[k]];
-        S[k] = se.S;
+    for (int k = 0; k < NBLK; ++k) S[k] = entry[k].S;
+    if constexpr (Entry::kOneProduct) {
+        float r[NBLK];
 #pragma unroll
-        for (int i = 0; i < EPB; ++i) {
-            const int j = k * EPB + i;
-            y[j] = quot(v[j], Recip{se.rhi, se.rlo});
-        }
+        for (int k = 0; k < NBLK; ++k) r[k] = entry[k].r;
+        quot8_truncated<NBLK>(v, r, y);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) y[j] = quot(v[j], Recip{entry[j / EPB].rhi, entry[j / EPB].rlo});
     }
     packed = e2m1_pack8(y, 1.0f);
     float q[8];
@@ -101,9 +105,9 @@ __device__ __forceinline__ void block_clip_sse(const float (&v)[8], const float 
 
 // Everything between the load and the store for one lane's 8 values.  `tdyn` (one of kNoT,
 // kFastT, kSlowT; wave-uniform) is read only when TMODE == kDynT.
-template <int B, int FMT, bool FOUR6, int TMODE, bool CLIP>
+template <int B, int FMT, bool FOUR6, int TMODE, bool CLIP, class Entry>
 __device__ __forceinline__ void process_chunk(float (&v)[8], float T, float rT, int tdyn, bool pz,
-                                              const ScaleEntry* tab, uint32_t& packed,
+                                              const Entry* tab, uint32_t& packed,
                                               uint32_t (&code_out)[(B < 8) ? 8 / B : 1], float (&sse_sel)[4],
                                               float (&clip_sel)[4])
 {
@@ -132,13 +136,18 @@ __device__ __forceinline__ void process_chunk(float (&v)[8], float T, float rT, 
         const uint32_t floor_code = pz ? 1u : 0u;
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) absmax_codes<FMT, FOUR6>(amax[k], floor_code, code_out[k], c4[k]);
-        quant_lane<NBLK, EPB>(v, code_out, tab, packed, sq, S);
+        Entry entry[NBLK];
+#pragma unroll
+        for (int k = 0; k < NBLK; ++k) entry[k] = tab[code_out[k]];
+        quant_lane<NBLK, EPB>(v, entry, packed, sq, S);
         block_sse<B>(sq, sse_sel);
         if constexpr (CLIP) block_clip_sse<B, NBLK, EPB>(v, sq, S, clip_sel);
         if constexpr (FOUR6) {
             uint32_t packed4;
             float sse4[4], clip4[4];
-            quant_lane<NBLK, EPB>(v, c4, tab, packed4, sq, S);
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) entry[k] = tab[c4[k]];
+            quant_lane<NBLK, EPB>(v, entry, packed4, sq, S);
             block_sse<B>(sq, sse4);
             if constexpr (CLIP) block_clip_sse<B, NBLK, EPB>(v, sq, S, clip4);
             // Eq. 4: M = 4 only when its SSE is strictly lower
@@ -266,6 +275,11 @@ __device__ __forceinline__ void store_slice(const TileOut<B>& o, uint32_t s, Sli
     }
 }
 
+// Scale table of a kernel.  One truncated product does for bf16 values that nothing has divided (8 significant
+// bits); fp32 values and quotients by a tensor scale have 24 and need both parts.
+template <int DT, int TMODE>
+using TableEntry = std::conditional_t<DT == kBF16 && TMODE == kNoT, ScalePair, ScaleEntry>;
+
 // A workgroup tile is kItems consecutive slices; every lane owns one chunk of each slice.
 constexpr int kItems = MXQ_STREAM_ITEMS;
 
@@ -290,11 +304,11 @@ __device__ __forceinline__ void load_tile(RawChunk<DT> (&buf)[kItems], const voi
 // On gfx9 loads and stores share one in-order counter, so the wait at the top covers every
 // memory operation still in flight; with this order all of them were issued a whole compute
 // phase earlier and the wait is short.
-template <int DT, int B, int FMT, bool FOUR6, int TMODE, bool CLIP>
+template <int DT, int B, int FMT, bool FOUR6, int TMODE, bool CLIP, class Entry>
 __device__ __forceinline__ void stream_step(RawChunk<DT> (&cur)[kItems], RawChunk<DT> (&nxt)[kItems],
                                             TileOut<B> (&out)[kItems], bool have_prev, uint32_t s_prev,
                                             const void* __restrict__ x, uint32_t s0, uint32_t stride,
-                                            Slices sl, float T, float rT, int tdyn, bool pz, const ScaleEntry* tab,
+                                            Slices sl, float T, float rT, int tdyn, bool pz, const Entry* tab,
                                             u32x4* wave_lds, uint32_t* __restrict__ codes, uint8_t* __restrict__ scales,
                                             float* __restrict__ sse_out, float* __restrict__ clip_out)
 {
@@ -320,9 +334,9 @@ __device__ __forceinline__ void stream_step(RawChunk<DT> (&cur)[kItems], RawChun
 // elements are handled by one lane of an extra workgroup of the same launch, reading and writing
 // element-wise.  (A launch of its own, as it was, cost more than it does on any tensor that fits in a
 // few microseconds: 2563 x 4110 elements, b = 2, 18.4 us against 14.9 us for 2563 x 4112.)
-template <int DT, int B, int FMT, bool FOUR6, int TMODE, bool CLIP>
+template <int DT, int B, int FMT, bool FOUR6, int TMODE, bool CLIP, class Entry>
 __device__ __forceinline__ void stream_tail(const void* __restrict__ x, uint64_t first, uint32_t count, float T, float rT,
-                                            int tdyn, bool pz, const ScaleEntry* tab, uint8_t* __restrict__ codes,
+                                            int tdyn, bool pz, const Entry* tab, uint8_t* __restrict__ codes,
                                             uint8_t* __restrict__ scales, float* __restrict__ sse_out,
                                             float* __restrict__ clip_out)
 {
@@ -351,7 +365,8 @@ stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunk
               uint32_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ sse_out,
               float* __restrict__ clip_out)
 {
-    __shared__ ScaleEntry tab[(FMT == kE8M0) ? 1 : 256];
+    using Entry = TableEntry<DT, TMODE>;
+    __shared__ Entry tab[(FMT == kE8M0) ? 1 : 256];
     __shared__ u32x4 xpose[(DT == kF32) ? 2 * kThreads : 1];        // 2 KiB per wavefront, fp32 input only
     u32x4* wave_lds = xpose + ((DT == kF32) ? 2u * (threadIdx.x & ~63u) : 0u);
 
@@ -436,11 +451,11 @@ __device__ __forceinline__ TileRef locate(const BatchArgs& a, uint32_t g)
     return TileRef{t, g - a.first[t], Slices{a.first[t + 1] - a.first[t], a.last[t]}};
 }
 
-template <int DT, int B, int FMT, bool FOUR6>
+template <int DT, int B, int FMT, bool FOUR6, class Entry>
 __device__ __forceinline__ void batch_step(RawChunk<DT> (&cur)[kItems], RawChunk<DT> (&nxt)[kItems],
                                            TileOut<B> (&out)[kItems], bool have_prev, TileRef prev,
                                            bool have_next, TileRef next, const BatchArgs& a, bool pz,
-                                           const ScaleEntry* tab, u32x4* wave_lds)
+                                           const Entry* tab, u32x4* wave_lds)
 {
     static_assert(kItems == 1, "one slice per tile");
     float v[8];
@@ -461,7 +476,8 @@ template <int DT, int B, int FMT, bool FOUR6>
 __global__ void __launch_bounds__(kThreads)
 stream_batch_kernel(const BatchArgs a, int pz)
 {
-    __shared__ ScaleEntry tab[(FMT == kE8M0) ? 1 : 256];
+    using Entry = TableEntry<DT, kNoT>;
+    __shared__ Entry tab[(FMT == kE8M0) ? 1 : 256];
     __shared__ u32x4 xpose[(DT == kF32) ? 2 * kThreads : 1];
     u32x4* wave_lds = xpose + ((DT == kF32) ? 2u * (threadIdx.x & ~63u) : 0u);
 
