@@ -220,6 +220,41 @@ MXQ_HD bool fast_division_unsafe_amax(float a)
     return (f2u(a) - 0x2B800000u) > (0x6C800000u - 0x2B800000u) && f2u(a) != 0u;
 }
 
+// bf16 inputs have 128 mantissas only, so for one T it can be SEEN whether shorter sequences are exact:
+//   * the quotient x/T as quot(x, make_recip(T)), two instructions instead of three: tried on every mantissa
+//     (lean_division_exact).  About one T in 10^5 fails.
+//   * the quotient of v = fl(x/T) by a scale S as one truncated product with the float nearest to 1/S or the
+//     next one above: it is within 2^-21 of x/(T*S), so it can take a wrong decision only for an x that close
+//     to t*S*T, and there is at most one such mantissa for each of the 8 mantissas of S and the 4 of the
+//     mid-points t.  That one is tried with both reciprocals, and the nearer one taken for a mantissa of S
+//     unless it fails (lean_quotient_candidate; lean_T in mxq_device.hpp).  About one T in 10^4 is left without; of the 128 tensor
+//     scales that tensor_scale_from makes of a bf16 abs-max two need a reciprocal from above and four are left
+//     without.
+// Both hold for every exponent of x: below |x/T| = 2^-78 the small product of the first may lose bits, but
+// such an element quantises to a signed zero under every E4M3 or UE5M3 scale and its square underflows.
+// T beyond 2^+-60 or with an all-ones mantissa is not tried (the reference, div_by_T, is not exact for the
+// latter; within the range nothing on these mantissas over- or underflows).
+MXQ_HD bool lean_T_in_range(float T)
+{
+    return T >= 0x1p-60f && T <= 0x1p60f && (f2u(T) & 0x7FFFFFu) != 0x7FFFFFu;
+}
+
+MXQ_HD bool lean_division_exact(uint32_t mantissa, float T, float rT, Recip r)
+{
+    const float x = u2f(0x3F800000u | (mantissa << 16));
+    return quot(x, r) == div_by_T(x, T, rT);
+}
+
+// The bf16 value nearest to (t*d)*T, and whether it is close enough to matter.  (What is tried then: the
+// truncated product lies on the same side of t as fl(x/T) does of t*d, a quotient AT t counting as up
+// where the even code lies above.)
+MXQ_HD bool lean_quotient_candidate(float td, float T, float& x)
+{
+    const float p = td * T;
+    x = u2f((f2u(p) + 0x8000u) & 0xFFFF0000u);
+    return __builtin_fabsf(x - p) <= p * 0x1p-20f;
+}
+
 // Per-tensor scale of hierarchical scaling (Section 2, two-stage process) from the tensor
 // abs-max: the abs-max lands on (largest element magnitude) x (largest scale value); 1 for an
 // all-zero tensor or when the quotient vanishes or overflows.

@@ -71,28 +71,56 @@ __device__ __forceinline__ float tensor_scale_of(float absmax)
     return tensor_scale_from(absmax, sf_max);
 }
 
-// Entry of every scale byte, filled once per workgroup into LDS, one entry per thread.  Code 0 has S = 0
-// and a zero "reciprocal", so that every quotient is a signed 0.
-struct __align__(16) ScaleEntry {          // for quot(): reciprocal in two parts
+// Entry of every scale byte, copied once per workgroup into LDS, one entry per thread.  The entries are made by
+// the compiler (formed in the kernel, they cost every wavefront a division and 25 instructions in all).  Code 0
+// has S = 0 and a zero "reciprocal", so that every quotient is a signed 0.
+struct __align__(16) ScaleEntry {          // for quot(): reciprocal in two parts, as make_recip() has them
     static constexpr bool kOneProduct = false;
     float S, rhi, rlo, pad;
-    __device__ __forceinline__ static ScaleEntry of(float S)
+    static constexpr ScaleEntry of(float S)
     {
-        const Recip r = make_recip(S);
-        return ScaleEntry{S, r.hi, r.lo, 0.0f};
+        float hi = 1.0f / S;
+        if ((double)hi * S > 1.0) hi = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, hi) - 1u);      // exact product
+        return ScaleEntry{S, hi, (float)(1.0 - (double)hi * S) * hi, 0.0f};
     }
 };
 struct __align__(8) ScalePair {            // for quot_truncated(): the float nearest to 1/S
     static constexpr bool kOneProduct = true;
     float S, r;
-    __device__ __forceinline__ static ScalePair of(float S) { return ScalePair{S, 1.0f / S}; }
+    static constexpr ScalePair of(float S) { return ScalePair{S, 1.0f / S}; }
 };
+
+template <class Entry> struct ScaleTable { Entry of[256]; };
+template <int FMT, class Entry>
+constexpr ScaleTable<Entry> make_scale_table()
+{
+    ScaleTable<Entry> t{};
+    for (int c = 1; c <= ScaleFmt<FMT>::kMaxCode; ++c) {
+        float S = (c < 8) ? (float)c : (float)(8 + (c & 7));             // in units of the code's binade
+        for (int e = (c < 8) ? 0 : (c >> 3) - 1; e > 0; --e) S *= 2.0f;
+        for (int e = ScaleFmt<FMT>::kBias + 2; e > 0; --e) S *= 0.5f;
+        t.of[c] = Entry::of(S);
+    }
+    return t;
+}
+template <int FMT, class Entry>
+static __device__ constexpr ScaleTable<Entry> kScaleTable = make_scale_table<FMT, Entry>();
 
 template <int FMT, class Entry>
 __device__ __forceinline__ void fill_scale_table(Entry* tab)
 {
-    const uint32_t c = threadIdx.x;                                     // 256 threads, 256 codes
-    tab[c] = (c >= 1u && c <= (uint32_t)ScaleFmt<FMT>::kMaxCode) ? Entry::of(sf_decode<FMT>(c)) : Entry{};
+    tab[threadIdx.x] = kScaleTable<FMT, Entry>.of[threadIdx.x];         // 256 threads, 256 codes
+    __syncthreads();
+}
+
+// The same, where the scale mantissas 1 + i/8 with bit i of `above` set take the reciprocal above the nearest one.
+template <int FMT>
+__device__ __forceinline__ void fill_scale_table(ScalePair* tab, uint32_t above)
+{
+    ScalePair e = kScaleTable<FMT, ScalePair>.of[threadIdx.x];
+    const uint32_t up = (threadIdx.x == 0u) ? 0u : (above >> ((f2u(e.S) >> 20) & 7u)) & 1u;
+    e.r = u2f(f2u(e.r) + up);
+    tab[threadIdx.x] = e;
     __syncthreads();
 }
 
@@ -119,6 +147,47 @@ __device__ __forceinline__ void quot8_truncated(const float (&v)[8], const float
         : "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3]), "=&v"(y[4]), "=&v"(y[5]), "=&v"(y[6]), "=&v"(y[7])
         : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]),
           "v"(r0), "v"(r1), "v"(r2), "v"(r3));
+}
+
+// One of the 32 pairs of a scale mantissa d and a mid-point mantissa t that lean_T looks at.  The even code lies
+// above the mid-points .75 and 1.75: a quotient AT them goes up, so they are represented by the float below.
+struct __align__(16) LeanPair { float td, rd, y_at, v_at; };
+struct LeanPairs { LeanPair of[32]; };
+constexpr LeanPairs make_lean_pairs()
+{
+    LeanPairs p{};
+    for (int i = 0; i < 32; ++i) {
+        const float d = 1.0f + 0.125f * (float)(i & 7), t = 1.0f + 0.25f * (float)(i >> 3);
+        const uint32_t below = (i >> 3) >= 2 ? 1u : 0u;
+        p.of[i] = LeanPair{t * d, 1.0f / d, __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, t) - below),
+                           __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, t * d) - below)};
+    }
+    return p;
+}
+static __device__ constexpr LeanPairs kLeanPairs = make_lean_pairs();
+
+// Whether both shorter sequences are exact for every bf16 input under this T: two mantissas and one of the 32
+// pairs in every lane, so that no wavefront waits for another.  Bit i of `above`: the scale mantissa 1 + i/8
+// takes the reciprocal above the nearest one.
+__device__ __forceinline__ bool lean_T(LeanPair pair, float T, float rT, Recip r, uint32_t& above)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    float x, y, y_above;
+    const bool near = lean_quotient_candidate(pair.td, T, x);
+    const float v = div_by_T(x, T, rT);
+    asm("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 3\n\t"
+        "v_mul_f32 %0, %2, %3\n\t"
+        "v_mul_f32 %1, %2, %4\n\t"
+        "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 0"
+        : "=&v"(y), "=&v"(y_above) : "v"(v), "v"(pair.rd), "v"(u2f(f2u(pair.rd) + 1u)));
+    const bool up = v > pair.v_at;
+    const bool divides = lean_division_exact(lane, T, rT, r) && lean_division_exact(lane + 64u, T, rT, r);
+    auto of_mantissa = [](bool bad) {                                   // the four mid-points of a scale mantissa together
+        const uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64(bad);
+        return (m | (m >> 8) | (m >> 16) | (m >> 24)) & 0xFFu;
+    };
+    above = of_mantissa(near && (y > pair.y_at) != up);
+    return (above & of_mantissa(near && (y_above > pair.y_at) != up)) == 0u && __builtin_amdgcn_ballot_w64(!divides) == 0ull;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -249,8 +318,9 @@ __device__ __forceinline__ void block_sse(const float (&sq)[8], float (&sse)[4])
 // Division by the per-tensor scale T of hierarchical scaling: div_by_T (reciprocal + one FMA
 // refinement, exact inside the range fast_division_ok / fast_division_unsafe_amax delimit) or the
 // plain IEEE division.
-enum : int { kNoT = 0, kFastT = 1, kSlowT = 2, kDynT = 3 };   // kDynT: T comes from device memory, one of
+enum : int { kNoT = 0, kFastT = 1, kSlowT = 2, kDynT = 3,     // kDynT: T comes from device memory, one of
                                                               // the other three is chosen at run time
+             kLeanT = 4 };    // bf16, T for which lean_T holds: the two parts of 1/T in the place of (T, 1/T)
 
 template <int NBLK, int EPB, int LANES>
 __device__ __forceinline__ void block_amax(const float (&v)[8], float (&amax)[NBLK])
@@ -264,7 +334,7 @@ __device__ __forceinline__ void block_amax(const float (&v)[8], float (&amax)[NB
     }
 }
 
-// Division by the per-tensor scale (MODE: none / reciprocal-refined / plain) and the block
+// Division by the per-tensor scale (MODE: none / reciprocal-refined / plain / in two parts) and the block
 // abs-max of the adjusted values.
 template <int MODE, int NBLK, int EPB, int LANES>
 __device__ __forceinline__ void adjust_and_amax(float (&v)[8], float T, float rT, float (&amax)[NBLK])
@@ -272,6 +342,10 @@ __device__ __forceinline__ void adjust_and_amax(float (&v)[8], float T, float rT
     if constexpr (MODE == kSlowT) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = v[i] / T;            // IEEE division
+        block_amax<NBLK, EPB, LANES>(v, amax);
+    } else if constexpr (MODE == kLeanT) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = quot(v[i], Recip{T, rT});
         block_amax<NBLK, EPB, LANES>(v, amax);
     } else if constexpr (MODE == kFastT) {
         float raw[8];

@@ -356,8 +356,39 @@ __device__ __forceinline__ void stream_tail(const void* __restrict__ x, uint64_t
     }
 }
 
-// Main kernel: the complete chunks, grid-stride over workgroup tiles with two register buffers
-// alternating between "being processed" and "in flight".
+// The complete chunks of one workgroup, grid-stride over workgroup tiles with two register buffers
+// alternating between "being processed" and "in flight"; bufA holds the first tile's loads.
+template <int DT, int B, int FMT, bool FOUR6, int TMODE, bool CLIP, class Entry>
+__device__ __forceinline__ void stream_tiles(RawChunk<DT> (&bufA)[kItems], const void* __restrict__ x, uint32_t s0,
+                                             uint32_t stride, Slices sl, float T, float rT, int tdyn, bool pz, const Entry* tab,
+                                             u32x4* wave_lds, uint32_t* __restrict__ codes, uint8_t* __restrict__ scales,
+                                             float* __restrict__ sse_out, float* __restrict__ clip_out)
+{
+    RawChunk<DT> bufB[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) bufB[i] = RawChunk<DT>{};
+    TileOut<B> out[kItems];
+    bool have_prev = false;
+    uint32_t s_prev = s0;
+    while (true) {
+        stream_step<DT, B, FMT, FOUR6, TMODE, CLIP>(bufA, bufB, out, have_prev, s_prev, x, s0, stride, sl, T, rT, tdyn,
+                                                    pz, tab, wave_lds, codes, scales, sse_out, clip_out);
+        have_prev = true;
+        s_prev = s0;
+        s0 += stride;
+        if (s0 >= sl.count) break;
+        stream_step<DT, B, FMT, FOUR6, TMODE, CLIP>(bufB, bufA, out, true, s_prev, x, s0, stride, sl, T, rT, tdyn,
+                                                    pz, tab, wave_lds, codes, scales, sse_out, clip_out);
+        s_prev = s0;
+        s0 += stride;
+        if (s0 >= sl.count) break;
+    }
+#pragma unroll
+    for (int i = 0; i < kItems; ++i)
+        store_slice<B>(out[i], s_prev + (uint32_t)i, sl, codes, scales, sse_out, CLIP ? clip_out : nullptr);
+}
+
+// Main kernel.
 template <int DT, int B, int FMT, bool FOUR6, int TMODE, bool CLIP>
 __global__ void __launch_bounds__(kThreads)
 stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunks, uint32_t tail, float T_arg, int pz,
@@ -373,7 +404,7 @@ stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunk
     const Slices sl{n_slices, last_chunks};
     const uint32_t workers = gridDim.x - ((B < 8 && tail != 0u) ? 1u : 0u);       // the last workgroup takes the tail
     const uint32_t stride = workers * (uint32_t)kItems;
-    uint32_t s0 = blockIdx.x * (uint32_t)kItems;
+    const uint32_t s0 = blockIdx.x * (uint32_t)kItems;
     float T = T_arg;
     int tdyn = TMODE;
     if constexpr (TMODE == kDynT) {                  // T from the abs-max left in device memory, if there is one
@@ -392,31 +423,100 @@ stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunk
     }
     if (s0 >= sl.count) return;                                      // whole workgroup
 
-    // the first tile's loads are in flight while the scale table is built
-    RawChunk<DT> bufA[kItems], bufB[kItems];
+    RawChunk<DT> first[kItems];
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) { bufA[i] = RawChunk<DT>{}; bufB[i] = RawChunk<DT>{}; }
-    load_tile<DT>(bufA, x, s0, sl);
+    for (int i = 0; i < kItems; ++i) first[i] = RawChunk<DT>{};
+    load_tile<DT>(first, x, s0, sl);                                 // in flight while the scale table is built
     if constexpr (FMT != kE8M0) fill_scale_table<FMT>(tab);
-    TileOut<B> out[kItems];
-    bool have_prev = false;
-    uint32_t s_prev = s0;
-    while (true) {
-        stream_step<DT, B, FMT, FOUR6, TMODE, CLIP>(bufA, bufB, out, have_prev, s_prev, x, s0, stride, sl, T, rT, tdyn,
-                                                    pz != 0, tab, wave_lds, codes, scales, sse_out, clip_out);
-        have_prev = true;
-        s_prev = s0;
-        s0 += stride;
-        if (s0 >= sl.count) break;
-        stream_step<DT, B, FMT, FOUR6, TMODE, CLIP>(bufB, bufA, out, true, s_prev, x, s0, stride, sl, T, rT, tdyn,
-                                                    pz != 0, tab, wave_lds, codes, scales, sse_out, clip_out);
-        s_prev = s0;
-        s0 += stride;
-        if (s0 >= sl.count) break;
+    stream_tiles<DT, B, FMT, FOUR6, TMODE, CLIP>(first, x, s0, stride, sl, T, rT, tdyn, pz != 0, tab, wave_lds, codes, scales,
+                                                 sse_out, clip_out);
+}
+
+// bf16 under a tensor scale, T by value or from the abs-max in device memory, for tensors of several tiles a
+// workgroup: 29 vector instructions of 160 a chunk (4-over-6) go where lean_T finds the shorter sequences exact
+// for this T.  Every wavefront finds that out by itself in some 45 instructions.  The other T's go the general way,
+// with b = 2 in a plain loop, whose registers are few, without prefetch.
+// General kernel -> this one, T from device memory, E4M3: 4096 x 8192 4-over-6 b = 16 23.0 -> 21.1 us, b = 64 22.7
+// -> 20.4, b = 4 27.2 -> 24.8, abs-max b = 16 19.0 -> 18.2.
+// With fewer tiles a workgroup than these the test of T costs what it saves (two tiles, 2048 x 4096: 4-over-6
+// b = 16, T from the device 7.5 -> 7.1 us, by value b = 4 8.6 -> 9.2, abs-max b = 16 6.2 -> 6.7).  The abs-max recipes
+// with b < 16 are bound by memory, and by value, where no wavefront has to derive T, they are 1 to 2 % faster
+// in the general kernel while that has the short division.
+constexpr int64_t kScaledTiles = 4, kScaledTilesFour6 = 2, kScaledTilesFour6ByValue = 3;
+template <int B, bool FOUR6>
+static bool takes_scaled_kernel(const StreamArgs& a, int64_t slices, int64_t workers)
+{
+    if (a.clip || slices == 0) return false;
+    if (a.absmax_dev) return slices >= (FOUR6 ? kScaledTilesFour6 : kScaledTiles) * workers;
+    if (a.T == 1.0f || !lean_T_in_range(a.T)) return false;
+    if (!FOUR6 && B < 16 && fast_division_ok(a.T)) return false;
+    return slices >= (FOUR6 ? kScaledTilesFour6ByValue : kScaledTiles) * workers;
+}
+
+template <int B, int FMT, bool FOUR6>
+__global__ void __launch_bounds__(kThreads)
+stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunks, uint32_t tail, float T_arg, int pz,
+                     const float* __restrict__ absmax_dev, float* __restrict__ t_out,
+                     uint32_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ sse_out)
+{
+    static_assert(FMT != kE8M0 && kItems == 1, "scales from a table, one slice per tile");
+    __shared__ ScaleEntry tab[256];
+    const Slices sl{n_slices, last_chunks};
+    const uint32_t stride = gridDim.x - ((B < 8 && tail != 0u) ? 1u : 0u);        // the last workgroup takes the tail
+    uint32_t s0 = blockIdx.x;
+    // The first tile's loads are in flight while T is looked at, and both parts of 1/T live in vector registers
+    // (an instruction with a scalar operand costs more): not where the 64 registers that eight wavefronts a
+    // SIMD leave for each do not hold them.
+    constexpr bool kEarly = !(B == 2 && FOUR6);
+    RawChunk<kBF16> first[kItems];
+    if constexpr (kEarly) first[0] = RawChunk<kBF16>{};
+    if (kEarly && s0 < stride) load_tile<kBF16>(first, x, s0, sl);
+    const LeanPair pair = kLeanPairs.of[threadIdx.x & 31u];
+    if constexpr (kEarly) __builtin_amdgcn_sched_barrier(0);
+    float T = T_arg;
+    if (absmax_dev) T = tensor_scale_of<FMT>(*absmax_dev);
+    if (t_out && blockIdx.x == 0 && threadIdx.x == 0) *t_out = T;
+    const float rT = 1.0f / T;                                       // correctly rounded
+    Recip r = make_recip(T);
+    uint32_t above = 0u;
+    if (s0 < stride && lean_T_in_range(T) && lean_T(pair, T, rT, r, above)) {     // uniform: every wavefront finds the same
+        if constexpr (!kEarly) load_tile<kBF16>(first, x, s0, sl);
+        ScalePair* pairs = reinterpret_cast<ScalePair*>(tab);
+        fill_scale_table<FMT>(pairs, above);
+        if constexpr (kEarly) {
+            asm volatile("" : "+v"(r.hi), "+v"(r.lo));
+        } else {
+            r.hi = u2f((uint32_t)__builtin_amdgcn_readfirstlane((int)f2u(r.hi)));
+            r.lo = u2f((uint32_t)__builtin_amdgcn_readfirstlane((int)f2u(r.lo)));
+        }
+        stream_tiles<kBF16, B, FMT, FOUR6, kLeanT, false>(first, x, s0, stride, sl, r.hi, r.lo, kLeanT, pz != 0, pairs,
+                                                          (u32x4*)nullptr, codes, scales, sse_out, (float*)nullptr);
+        return;
     }
-#pragma unroll
-    for (int i = 0; i < kItems; ++i)
-        store_slice<B>(out[i], s_prev + (uint32_t)i, sl, codes, scales, sse_out, CLIP ? clip_out : nullptr);
+    const int tdyn = (T == 1.0f) ? kNoT : (fast_division_ok(T) ? kFastT : kSlowT);
+    fill_scale_table<FMT>(tab);
+    if constexpr (B < 8) {
+        if (s0 == stride) {
+            stream_tail<kBF16, B, FMT, FOUR6, kDynT, false>(x, sl.elements(), tail, T, rT, tdyn, pz != 0, tab,
+                                                            reinterpret_cast<uint8_t*>(codes), scales, sse_out, nullptr);
+            return;
+        }
+    }
+    if constexpr (B >= 4) {
+        load_tile<kBF16>(first, x, s0, sl);                          // (again: kept from above, it would cost registers)
+        stream_tiles<kBF16, B, FMT, FOUR6, kDynT, false>(first, x, s0, stride, sl, T, rT, tdyn, pz != 0, tab, (u32x4*)nullptr,
+                                                         codes, scales, sse_out, (float*)nullptr);
+    } else {
+#pragma unroll 1
+        for (; s0 < sl.count; s0 += stride) {                        // uniform
+            load_tile<kBF16>(first, x, s0, sl);
+            float v[8];
+            widen<kBF16>(first[0], v, nullptr);
+            TileOut<B> o;
+            process_chunk<B, FMT, FOUR6, kDynT, false>(v, T, rT, tdyn, pz != 0, tab, o.packed, o.code, o.sse, o.clip);
+            store_slice<B>(o, s0, sl, codes, scales, sse_out, nullptr);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -543,6 +643,13 @@ static hipError_t launch_recipe(const StreamArgs& a, int pz)
     const int workers = (n_slices == 0u) ? 0 : stream_grid(((slices + kItems - 1) / kItems) * kThreads);
     const dim3 grid((unsigned)workers + (tail != 0u ? 1u : 0u)), block(kThreads);
     uint32_t* codes = reinterpret_cast<uint32_t*>(a.codes);
+    if constexpr (DT == kBF16 && FMT != kE8M0) {
+        if (takes_scaled_kernel<B, FOUR6>(a, slices, workers)) {
+            hipLaunchKernelGGL((stream_scaled_kernel<B, FMT, FOUR6>), grid, block, 0, a.stream, a.x, n_slices, last, tail, a.T,
+                               pz, a.absmax_dev, a.t_out, codes, a.scales, a.sse);
+            return hipGetLastError();
+        }
+    }
 #define MXQ_LAUNCH_STREAM(MODE, CLIP)                                                                 \
     hipLaunchKernelGGL((stream_kernel<DT, B, FMT, FOUR6, MODE, CLIP>), grid, block, 0, a.stream, a.x,       \
                        n_slices, last, tail, a.T, pz, a.absmax_dev, a.t_out, codes, a.scales, a.sse, a.clip)

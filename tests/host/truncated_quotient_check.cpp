@@ -1,7 +1,8 @@
 /*
  * Element quotients by one truncated product (mxq_arith.hpp: quot_truncated) on the CPU: for every bf16 value
  * of both signs and every scale code of E4M3 and UE5M3 the E2M1 decision must be the exact one and the
- * quotient must keep the sign of the value.  Prints "<name> cases=<n> bad=<m>".
+ * quotient must keep the sign of the value.  Then bf16 values under a tensor scale, for every such scale that a
+ * bf16 abs-max gives and 3007 others.  Prints "<name> cases=<n> bad=<m>".
  */
 #include <math.h>
 #include <stdint.h>
@@ -36,8 +37,72 @@ static void bf16_values(void)
     printf("bf16_values cases=%ld bad=%ld\n", n, bad);
 }
 
+/* lean_T of mxq_device.hpp, lane by lane: 0 no, 1 yes, and which scale mantissas take the reciprocal above */
+static int lean(float T, mxq::Recip r, uint32_t* above)
+{
+    const float rT = 1.0f / T;
+    uint32_t near_bad = 0, above_bad = 0;
+    for (uint32_t m = 0; m < 128; ++m)
+        if (!mxq::lean_division_exact(m, T, rT, r)) return 0;
+    for (int i = 0; i < 32; ++i) {
+        const float d = 1.0f + 0.125f * (i & 7), t = 1.0f + 0.25f * (i >> 3), rd = 1.0f / d;
+        float x;
+        if (!mxq::lean_quotient_candidate(t * d, T, x)) continue;
+        const float v = mxq::div_by_T(x, T, rT);
+        const float y = mxq::quot_truncated(v, rd), z = mxq::quot_truncated(v, mxq::u2f(mxq::f2u(rd) + 1u));
+        const bool up = (i >> 3) >= 2 ? v >= t * d : v > t * d;
+        near_bad |= (uint32_t)(((i >> 3) >= 2 ? y >= t : y > t) != up) << (i & 7);
+        above_bad |= (uint32_t)(((i >> 3) >= 2 ? z >= t : z > t) != up) << (i & 7);
+    }
+    *above = near_bad;
+    return (near_bad & above_bad) == 0;
+}
+
+/* For every T that lean() accepts: quotient by T and decision under every scale mantissa, for every bf16
+ * mantissa at the exponents that contain a mid-point, equal to the IEEE quotient and the exact decision. */
+static long g_n, g_bad, g_refused;
+static void tensor_scale(float T)
+{
+    const mxq::Recip r = mxq::make_recip(T);
+    uint32_t above = 0;
+    if (!mxq::lean_T_in_range(T) || !lean(T, r, &above)) { ++g_refused; return; }
+    for (uint32_t m = 0; m < 128; ++m)
+        for (int e = -4; e <= 5; ++e) {
+            const float x = ldexpf(mxq::u2f(0x3F800000u | (m << 16)), e + ilogbf(T));
+            const float v = mxq::quot(x, r), w = x / T;
+            g_bad += v != w || mxq::quot(-x, r) != -w;
+            for (int i = 0; i < 8; ++i) {
+                const float S = 1.0f + 0.125f * i, rS = mxq::u2f(mxq::f2u(1.0f / S) + ((above >> i) & 1u));
+                const float y = mxq::quot_truncated(v, rS);
+                ++g_n;
+                g_bad += index_of(y, 1.0) != index_of(v, S) || mxq::quot_truncated(-v, rS) != -y;
+            }
+        }
+}
+
+static void tensor_scales(void)
+{
+    for (int f = 0; f < 2; ++f)                                  /* every T that a bf16 abs-max gives, four exponents */
+        for (uint32_t m = 0; m < 128; ++m)
+            for (int e = -20; e <= 16; e += 12)
+                tensor_scale(mxq::tensor_scale_from(ldexpf(mxq::u2f(0x3F800000u | (m << 16)), e), f ? 114688.0f : 448.0f));
+    printf("tensor_scales_of_bf16_absmax cases=%ld bad=%ld refused=%ld\n", g_n, g_bad, g_refused);
+    g_n = g_bad = g_refused = 0;
+    uint32_t s = 12345u;
+    for (int i = 0; i < 1500; ++i) {
+        s = s * 1664525u + 1013904223u;
+        tensor_scale(mxq::u2f(((67u + (s >> 25)) << 23) | ((s >> 1) & 0x7FFFFFu)));
+        const float td = (1.0f + 0.125f * (s & 7u)) * (1.0f + 0.25f * ((s >> 3) & 3u));      /* and T's with a pair close to a tie */
+        tensor_scale(mxq::u2f(mxq::f2u(mxq::u2f(0x3F800000u | ((s >> 9) & 0x7F0000u)) / td) + ((s >> 5) & 3u) - 1u));
+    }
+    const float edges[7] = {1.0f, 0x1p-60f, 0x1p60f, 0x1p-61f, 0x1.fffffep3f, 3.0f, 0.1f};
+    for (int i = 0; i < 7; ++i) tensor_scale(edges[i]);
+    printf("tensor_scales cases=%ld bad=%ld refused=%ld\n", g_n, g_bad, g_refused);
+}
+
 int main()
 {
     bf16_values();
+    tensor_scales();
     return 0;
 }

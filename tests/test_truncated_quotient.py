@@ -14,15 +14,19 @@ CLANG = shutil.which("amdclang++") or "/opt/rocm/llvm/bin/clang++"
 
 
 def test_decisions_of_the_truncated_quotient_are_exact(tmp_path):
+    if "fma" not in open("/proc/cpuinfo").read():
+        pytest.skip("host CPU has no FMA instruction")
     exe = str(tmp_path / "truncated_quotient_check")
-    subprocess.run([CLANG, "-O2", "-std=c++17", "-ffp-contract=off", "-Wall", "-Werror",
+    subprocess.run([CLANG, "-O2", "-std=c++17", "-ffp-contract=off", "-mfma", "-Wall", "-Werror",
                     os.path.join(HERE, "host", "truncated_quotient_check.cpp"), "-o", exe, "-lm"], check=True)
     out = subprocess.run([exe], capture_output=True, text=True, timeout=300).stdout
     print(out)
     lines = [l for l in out.splitlines() if "cases=" in l]
-    assert [l.split()[0] for l in lines] == ["bf16_values"]
+    assert [l.split()[0] for l in lines] == ["bf16_values", "tensor_scales_of_bf16_absmax", "tensor_scales"]
     for l in lines:
-        assert int(l.split("cases=")[1].split()[0]) > 1_000_000 and int(l.split("bad=")[1]) == 0, l
+        assert int(l.split("cases=")[1].split()[0]) > 1_000_000 and int(l.split("bad=")[1].split()[0]) == 0, l
+    assert int(lines[1].split("refused=")[1]) == 2 * 4 * 4              # four of 128, both formats, four exponents
+    assert int(lines[2].split("refused=")[1]) < 300                     # of 3007
 
 
 def tie_blocks(oracle, fmt, block, seed):
@@ -56,3 +60,39 @@ def test_ties_of_every_scale_code(oracle, fmt, block):
             for g, r in zip(got, want):
                 g = g.cpu().numpy()
                 assert (g.view(np.uint32) == r.view(np.uint32)).all() if g.dtype == np.float32 else (g == r).all(), (recipe, g.dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt", [1, 2])
+@pytest.mark.parametrize("block", [2, 4, 8, 16, 128])
+def test_tensor_scales_of_large_bf16_tensors(oracle, fmt, block):
+    """Four tiles and a rest for every workgroup (n not a multiple of 8 for b = 2 and 4), so that the kernel for
+    scaled bf16 runs: an abs-max whose tensor scale takes reciprocals from above (249), one whose scale is refused (228), an ordinary one, scales
+    by value inside and outside the range that is tried, and one with an all-ones mantissa.  Bits: no tolerance."""
+    from paper_2605_08565_amd import mxq
+
+    rng = np.random.default_rng(7 * block + fmt)
+    cols = 16 * block + (block if block < 8 else 0)
+    rows = (4 * 2048 * 2048 + 5 * 2048) // cols + 1
+    x = (rng.standard_normal(rows * cols, dtype=np.float32) * np.repeat(np.float32([1.0, 40.0]), [rows * cols // 2, rows * cols - rows * cols // 2]))
+    x = W.f32_to_bf16_bits(np.clip(x, -200, 200)).reshape(rows, cols)
+    part = np.r_[0:40, rows // 2 - 40:rows // 2 + 40, rows - 40:rows]   # rows that are compared
+    for top in (249.0, 228.0, 225.0):
+        x[rows // 2, 3] = W.f32_to_bf16_bits(np.float32([-top]))[0]
+        gx = mxq.from_bits(x)
+        T = oracle.tensor_scale(top, fmt)
+        runs = [(T, mxq.quantize_hier(gx, block, fmt, rec, mxq.tensor_absmax(gx)), rec) for rec in (1, 2)]
+        if top == 225.0:
+            for t in (T, 3.0e-7, 0.7, float(np.float32(1.99999988)), 2.0 ** -61):
+                runs.append((t, mxq.quantize(gx, block, fmt, 2, tensor_scale=t), 2))
+            for a in (1.9999999e-15, 3.0e36):                           # T = 2^-61 and less, and beyond 2^60, derived on the device
+                word = torch.full((1,), a, dtype=torch.float32, device="cuda")
+                runs.append((oracle.tensor_scale(a, fmt), mxq.quantize_hier(gx, block, fmt, 2, word), 2))
+        torch.cuda.synchronize()
+        for t, got, rec in runs:
+            want = oracle.quantize(np.ascontiguousarray(x[part]), block, fmt, rec, tensor_scale=t)
+            for g, r in zip(got[:3], want):
+                g = g.cpu().numpy()[part]
+                assert (g.view(np.uint32) == r.view(np.uint32)).all() if g.dtype == np.float32 else (g == r).all(), (top, t, rec, g.dtype)
+            if len(got) == 4:
+                assert float(got[3].cpu()[0]) == t
