@@ -202,6 +202,7 @@ __device__ __forceinline__ bool lean_T(LeanPair pair, float T, float rT, Recip r
 // destination; the inverse one returns the two values times the scale.  Mid-points go to the
 // even code: 0.25->0, 0.75->1, 1.25->1, 1.75->2, 2.5->2, 3.5->4, 5->4.
 using f32x2 = float __attribute__((ext_vector_type(2)));
+using f32x4 = float __attribute__((ext_vector_type(4)));
 using u32x4 = uint32_t __attribute__((ext_vector_type(4)));
 
 template <int SEL>

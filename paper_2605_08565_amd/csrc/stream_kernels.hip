@@ -238,9 +238,29 @@ struct Slices {
     }
 };
 
-// Stores of one slice.
-template <int B>
-__device__ __forceinline__ void store_slice(const TileOut<B>& o, uint32_t s, Slices sl,
+// Flags of a launch (wave-uniform).
+enum : int { kPreventZero = 1, kSsePastCaches = 2 };
+
+// A block SSE is written and not read again here.  With ordinary stores it displaces other lines in the caches;
+// written past them (non-temporal) it does not, but a later reader, or the next call that writes the same
+// buffer, finds nothing there.  (The two asm comments keep the compiler from making one store of both.)
+template <class V>
+__device__ __forceinline__ void store_sse(V* p, V v, int flags)
+{
+    if (flags & kSsePastCaches) {
+        asm volatile("; block SSE, past the caches");
+        __builtin_nontemporal_store(v, p);
+        asm volatile("; block SSE, past the caches, stored");
+    } else {
+        asm volatile("; block SSE");
+        *p = v;
+        asm volatile("; block SSE, stored");
+    }
+}
+
+// Stores of one slice.  (The kernels that output the clipping-only SSE write both ordinarily.)
+template <int B, bool CLIP>
+__device__ __forceinline__ void store_slice(const TileOut<B>& o, uint32_t s, Slices sl, int flags,
                                             uint32_t* __restrict__ codes, uint8_t* __restrict__ scales,
                                             float* __restrict__ sse_out, float* __restrict__ clip_out)
 {
@@ -255,19 +275,19 @@ __device__ __forceinline__ void store_slice(const TileOut<B>& o, uint32_t s, Sli
             if ((tid & (LANES - 1)) == 0) {
                 const uint32_t blk = tid / LANES;
                 (scales + c0 / LANES)[blk] = (uint8_t)o.code[0];
-                if (sse_out) (sse_out + c0 / LANES)[blk] = o.sse[0];
+                if (sse_out) store_sse((sse_out + c0 / LANES) + blk, o.sse[0], CLIP ? 0 : flags);
                 if (clip_out) (clip_out + c0 / LANES)[blk] = o.clip[0];
             }
         } else if constexpr (NBLK == 2) {
             reinterpret_cast<uint16_t*>(scales + c0 * 2)[tid] = (uint16_t)(o.code[0] | (o.code[1] << 8));
-            if (sse_out) reinterpret_cast<float2*>(sse_out + c0 * 2)[tid] = make_float2(o.sse[0], o.sse[1]);
+            if (sse_out) store_sse(reinterpret_cast<f32x2*>(sse_out + c0 * 2) + tid, f32x2{o.sse[0], o.sse[1]}, CLIP ? 0 : flags);
             if (clip_out) reinterpret_cast<float2*>(clip_out + c0 * 2)[tid] = make_float2(o.clip[0], o.clip[1]);
         } else {
             reinterpret_cast<uint32_t*>(scales + c0 * 4)[tid] =
                 o.code[0] | (o.code[1] << 8) | (o.code[2] << 16) | (o.code[3] << 24);
             if (sse_out)
-                reinterpret_cast<float4*>(sse_out + c0 * 4)[tid] =
-                    make_float4(o.sse[0], o.sse[1], o.sse[2], o.sse[3]);
+                store_sse(reinterpret_cast<f32x4*>(sse_out + c0 * 4) + tid, f32x4{o.sse[0], o.sse[1], o.sse[2], o.sse[3]},
+                          CLIP ? 0 : flags);
             if (clip_out)
                 reinterpret_cast<float4*>(clip_out + c0 * 4)[tid] =
                     make_float4(o.clip[0], o.clip[1], o.clip[2], o.clip[3]);
@@ -308,7 +328,7 @@ template <int DT, int B, int FMT, bool FOUR6, int TMODE, bool CLIP, class Entry>
 __device__ __forceinline__ void stream_step(RawChunk<DT> (&cur)[kItems], RawChunk<DT> (&nxt)[kItems],
                                             TileOut<B> (&out)[kItems], bool have_prev, uint32_t s_prev,
                                             const void* __restrict__ x, uint32_t s0, uint32_t stride,
-                                            Slices sl, float T, float rT, int tdyn, bool pz, const Entry* tab,
+                                            Slices sl, float T, float rT, int tdyn, int flags, const Entry* tab,
                                             u32x4* wave_lds, uint32_t* __restrict__ codes, uint8_t* __restrict__ scales,
                                             float* __restrict__ sse_out, float* __restrict__ clip_out)
 {
@@ -320,13 +340,13 @@ __device__ __forceinline__ void stream_step(RawChunk<DT> (&cur)[kItems], RawChun
     if (have_prev) {                                                 // uniform
 #pragma unroll
         for (int i = 0; i < kItems; ++i)
-            store_slice<B>(out[i], s_prev + (uint32_t)i, sl, codes, scales, sse_out, CLIP ? clip_out : nullptr);
+            store_slice<B, CLIP>(out[i], s_prev + (uint32_t)i, sl, flags, codes, scales, sse_out, CLIP ? clip_out : nullptr);
     }
     if (s0 + stride < sl.count) load_tile<DT>(nxt, x, s0 + stride, sl);            // uniform
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < kItems; ++i)
-        process_chunk<B, FMT, FOUR6, TMODE, CLIP>(v[i], T, rT, tdyn, pz, tab, out[i].packed, out[i].code, out[i].sse,
+        process_chunk<B, FMT, FOUR6, TMODE, CLIP>(v[i], T, rT, tdyn, (flags & kPreventZero) != 0, tab, out[i].packed, out[i].code, out[i].sse,
                                                   out[i].clip);
 }
 
@@ -360,7 +380,7 @@ __device__ __forceinline__ void stream_tail(const void* __restrict__ x, uint64_t
 // alternating between "being processed" and "in flight"; bufA holds the first tile's loads.
 template <int DT, int B, int FMT, bool FOUR6, int TMODE, bool CLIP, class Entry>
 __device__ __forceinline__ void stream_tiles(RawChunk<DT> (&bufA)[kItems], const void* __restrict__ x, uint32_t s0,
-                                             uint32_t stride, Slices sl, float T, float rT, int tdyn, bool pz, const Entry* tab,
+                                             uint32_t stride, Slices sl, float T, float rT, int tdyn, int flags, const Entry* tab,
                                              u32x4* wave_lds, uint32_t* __restrict__ codes, uint8_t* __restrict__ scales,
                                              float* __restrict__ sse_out, float* __restrict__ clip_out)
 {
@@ -372,26 +392,26 @@ __device__ __forceinline__ void stream_tiles(RawChunk<DT> (&bufA)[kItems], const
     uint32_t s_prev = s0;
     while (true) {
         stream_step<DT, B, FMT, FOUR6, TMODE, CLIP>(bufA, bufB, out, have_prev, s_prev, x, s0, stride, sl, T, rT, tdyn,
-                                                    pz, tab, wave_lds, codes, scales, sse_out, clip_out);
+                                                    flags, tab, wave_lds, codes, scales, sse_out, clip_out);
         have_prev = true;
         s_prev = s0;
         s0 += stride;
         if (s0 >= sl.count) break;
         stream_step<DT, B, FMT, FOUR6, TMODE, CLIP>(bufB, bufA, out, true, s_prev, x, s0, stride, sl, T, rT, tdyn,
-                                                    pz, tab, wave_lds, codes, scales, sse_out, clip_out);
+                                                    flags, tab, wave_lds, codes, scales, sse_out, clip_out);
         s_prev = s0;
         s0 += stride;
         if (s0 >= sl.count) break;
     }
 #pragma unroll
     for (int i = 0; i < kItems; ++i)
-        store_slice<B>(out[i], s_prev + (uint32_t)i, sl, codes, scales, sse_out, CLIP ? clip_out : nullptr);
+        store_slice<B, CLIP>(out[i], s_prev + (uint32_t)i, sl, flags, codes, scales, sse_out, CLIP ? clip_out : nullptr);
 }
 
 // Main kernel.
 template <int DT, int B, int FMT, bool FOUR6, int TMODE, bool CLIP>
 __global__ void __launch_bounds__(kThreads)
-stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunks, uint32_t tail, float T_arg, int pz,
+stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunks, uint32_t tail, float T_arg, int flags,
               const float* __restrict__ absmax_dev, float* __restrict__ t_out,
               uint32_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ sse_out,
               float* __restrict__ clip_out)
@@ -416,7 +436,7 @@ stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunk
     if constexpr (B < 8) {
         if (tail != 0u && blockIdx.x == workers) {
             if constexpr (FMT != kE8M0) fill_scale_table<FMT>(tab);
-            stream_tail<DT, B, FMT, FOUR6, TMODE, CLIP>(x, sl.elements(), tail, T, rT, tdyn, pz != 0, tab,
+            stream_tail<DT, B, FMT, FOUR6, TMODE, CLIP>(x, sl.elements(), tail, T, rT, tdyn, (flags & kPreventZero) != 0, tab,
                                                         reinterpret_cast<uint8_t*>(codes), scales, sse_out, clip_out);
             return;
         }
@@ -428,7 +448,7 @@ stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunk
     for (int i = 0; i < kItems; ++i) first[i] = RawChunk<DT>{};
     load_tile<DT>(first, x, s0, sl);                                 // in flight while the scale table is built
     if constexpr (FMT != kE8M0) fill_scale_table<FMT>(tab);
-    stream_tiles<DT, B, FMT, FOUR6, TMODE, CLIP>(first, x, s0, stride, sl, T, rT, tdyn, pz != 0, tab, wave_lds, codes, scales,
+    stream_tiles<DT, B, FMT, FOUR6, TMODE, CLIP>(first, x, s0, stride, sl, T, rT, tdyn, flags, tab, wave_lds, codes, scales,
                                                  sse_out, clip_out);
 }
 
@@ -455,7 +475,7 @@ static bool takes_scaled_kernel(const StreamArgs& a, int64_t slices, int64_t wor
 
 template <int B, int FMT, bool FOUR6>
 __global__ void __launch_bounds__(kThreads)
-stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunks, uint32_t tail, float T_arg, int pz,
+stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunks, uint32_t tail, float T_arg, int flags,
                      const float* __restrict__ absmax_dev, float* __restrict__ t_out,
                      uint32_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ sse_out)
 {
@@ -489,7 +509,7 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
             r.hi = u2f((uint32_t)__builtin_amdgcn_readfirstlane((int)f2u(r.hi)));
             r.lo = u2f((uint32_t)__builtin_amdgcn_readfirstlane((int)f2u(r.lo)));
         }
-        stream_tiles<kBF16, B, FMT, FOUR6, kLeanT, false>(first, x, s0, stride, sl, r.hi, r.lo, kLeanT, pz != 0, pairs,
+        stream_tiles<kBF16, B, FMT, FOUR6, kLeanT, false>(first, x, s0, stride, sl, r.hi, r.lo, kLeanT, flags, pairs,
                                                           (u32x4*)nullptr, codes, scales, sse_out, (float*)nullptr);
         return;
     }
@@ -497,14 +517,14 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
     fill_scale_table<FMT>(tab);
     if constexpr (B < 8) {
         if (s0 == stride) {
-            stream_tail<kBF16, B, FMT, FOUR6, kDynT, false>(x, sl.elements(), tail, T, rT, tdyn, pz != 0, tab,
+            stream_tail<kBF16, B, FMT, FOUR6, kDynT, false>(x, sl.elements(), tail, T, rT, tdyn, (flags & kPreventZero) != 0, tab,
                                                             reinterpret_cast<uint8_t*>(codes), scales, sse_out, nullptr);
             return;
         }
     }
     if constexpr (B >= 4) {
         load_tile<kBF16>(first, x, s0, sl);                          // (again: kept from above, it would cost registers)
-        stream_tiles<kBF16, B, FMT, FOUR6, kDynT, false>(first, x, s0, stride, sl, T, rT, tdyn, pz != 0, tab, (u32x4*)nullptr,
+        stream_tiles<kBF16, B, FMT, FOUR6, kDynT, false>(first, x, s0, stride, sl, T, rT, tdyn, flags, tab, (u32x4*)nullptr,
                                                          codes, scales, sse_out, (float*)nullptr);
     } else {
 #pragma unroll 1
@@ -513,8 +533,8 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
             float v[8];
             widen<kBF16>(first[0], v, nullptr);
             TileOut<B> o;
-            process_chunk<B, FMT, FOUR6, kDynT, false>(v, T, rT, tdyn, pz != 0, tab, o.packed, o.code, o.sse, o.clip);
-            store_slice<B>(o, s0, sl, codes, scales, sse_out, nullptr);
+            process_chunk<B, FMT, FOUR6, kDynT, false>(v, T, rT, tdyn, (flags & kPreventZero) != 0, tab, o.packed, o.code, o.sse, o.clip);
+            store_slice<B, false>(o, s0, sl, flags, codes, scales, sse_out, nullptr);
         }
     }
 }
@@ -554,7 +574,7 @@ __device__ __forceinline__ TileRef locate(const BatchArgs& a, uint32_t g)
 template <int DT, int B, int FMT, bool FOUR6, class Entry>
 __device__ __forceinline__ void batch_step(RawChunk<DT> (&cur)[kItems], RawChunk<DT> (&nxt)[kItems],
                                            TileOut<B> (&out)[kItems], bool have_prev, TileRef prev,
-                                           bool have_next, TileRef next, const BatchArgs& a, bool pz,
+                                           bool have_next, TileRef next, const BatchArgs& a, int flags,
                                            const Entry* tab, u32x4* wave_lds)
 {
     static_assert(kItems == 1, "one slice per tile");
@@ -563,10 +583,10 @@ __device__ __forceinline__ void batch_step(RawChunk<DT> (&cur)[kItems], RawChunk
     widen<DT>(cur[0], v, wave_lds);
     __builtin_amdgcn_sched_barrier(0);
     if (have_prev)                                                   // uniform
-        store_slice<B>(out[0], prev.s, prev.sl, a.codes[prev.t], a.scales[prev.t], a.sse[prev.t], nullptr);
+        store_slice<B, false>(out[0], prev.s, prev.sl, flags, a.codes[prev.t], a.scales[prev.t], a.sse[prev.t], nullptr);
     if (have_next) load_tile<DT>(nxt, a.x[next.t], next.s, next.sl); // uniform
     __builtin_amdgcn_sched_barrier(0);
-    process_chunk<B, FMT, FOUR6, kNoT, false>(v, 1.0f, 1.0f, kNoT, pz, tab, out[0].packed, out[0].code, out[0].sse,
+    process_chunk<B, FMT, FOUR6, kNoT, false>(v, 1.0f, 1.0f, kNoT, (flags & kPreventZero) != 0, tab, out[0].packed, out[0].code, out[0].sse,
                                               out[0].clip);
 }
 
@@ -574,7 +594,7 @@ __device__ __forceinline__ void batch_step(RawChunk<DT> (&cur)[kItems], RawChunk
 // and is slower: it keeps three sets of pointers alive in scalar registers.)
 template <int DT, int B, int FMT, bool FOUR6>
 __global__ void __launch_bounds__(kThreads)
-stream_batch_kernel(const BatchArgs a, int pz)
+stream_batch_kernel(const BatchArgs a, int flags)
 {
     using Entry = TableEntry<DT, kNoT>;
     __shared__ Entry tab[(FMT == kE8M0) ? 1 : 256];
@@ -590,7 +610,7 @@ stream_batch_kernel(const BatchArgs a, int pz)
             if (a.tail[t] == 0u) return;
             if constexpr (FMT != kE8M0) fill_scale_table<FMT>(tab);
             stream_tail<DT, B, FMT, FOUR6, kNoT, false>(a.x[t], Slices{a.first[t + 1] - a.first[t], a.last[t]}.elements(),
-                                                        a.tail[t], 1.0f, 1.0f, kNoT, pz != 0, tab,
+                                                        a.tail[t], 1.0f, 1.0f, kNoT, (flags & kPreventZero) != 0, tab,
                                                         reinterpret_cast<uint8_t*>(a.codes[t]), a.scales[t], a.sse[t], nullptr);
             return;
         }
@@ -608,7 +628,7 @@ stream_batch_kernel(const BatchArgs a, int pz)
     while (true) {
         bool have_next = g + stride < total;
         if (have_next) next = locate(a, g + stride);
-        batch_step<DT, B, FMT, FOUR6>(bufA, bufB, out, have_prev, prev, have_next, next, a, pz != 0, tab, wave_lds);
+        batch_step<DT, B, FMT, FOUR6>(bufA, bufB, out, have_prev, prev, have_next, next, a, flags, tab, wave_lds);
         have_prev = true;
         prev = cur;
         if (!have_next) break;
@@ -616,16 +636,31 @@ stream_batch_kernel(const BatchArgs a, int pz)
         g += stride;
         have_next = g + stride < total;
         if (have_next) next = locate(a, g + stride);
-        batch_step<DT, B, FMT, FOUR6>(bufB, bufA, out, true, prev, have_next, next, a, pz != 0, tab, wave_lds);
+        batch_step<DT, B, FMT, FOUR6>(bufB, bufA, out, true, prev, have_next, next, a, flags, tab, wave_lds);
         prev = cur;
         if (!have_next) break;
         cur = next;
         g += stride;
     }
-    store_slice<B>(out[0], prev.s, prev.sl, a.codes[prev.t], a.scales[prev.t], a.sse[prev.t], nullptr);
+    store_slice<B, false>(out[0], prev.s, prev.sl, flags, a.codes[prev.t], a.scales[prev.t], a.sse[prev.t], nullptr);
 }
 
 // ------------------------------------------------------------------------------ dispatch
+
+// Where the block SSEs are written past the caches: up to 15 MiB of them (fp32 input 8) from an input of up to 128 MiB,
+// for fp32 with b <= 32.  Ordinary -> past the caches, E4M3, four tensors in turn, into fresh (re-used) outputs: bf16
+// 4-over-6 b = 16 16 M elements 10.6 -> 9.9 us (10.6 -> 9.9), 32 M 18.7 -> 17.7 (18.5 -> 17.3), 56 M 32.7 -> 31.8
+// (32.9 -> 32.0); b = 8 16 M 11.5 -> 10.4; b = 4 8 M 7.9 -> 7.0; b = 2 8 M 9.4 -> 8.3; fp32 b = 16 16 M 15.5 -> 15.3, b = 8
+// 16.6 -> 15.9.  Beyond the lines: bf16 b = 8 40 M 23.3 -> 23.9, b = 16 128 M 66.8 -> 70.2, fp32 b = 128 32 M 28.3
+// -> 28.8; b <= 4 from 60 M on gains 5 to 13 % in fresh outputs and loses as much in re-used ones.
+template <int DT, int B>
+static int sse_past_caches(int64_t n)
+{
+    constexpr int64_t kMiB = 1 << 20;
+    const int64_t sse_bytes = n / B * 4, in_bytes = n * (DT == kBF16 ? 2 : 4);
+    const bool past = in_bytes <= 128 * kMiB && (DT == kBF16 ? sse_bytes <= 15 * kMiB : B <= 32 && sse_bytes <= 8 * kMiB);
+    return past ? kSsePastCaches : 0;
+}
 
 template <int DT, int B, int FMT, bool FOUR6>
 static hipError_t launch_recipe(const StreamArgs& a, int pz)
@@ -643,16 +678,17 @@ static hipError_t launch_recipe(const StreamArgs& a, int pz)
     const int workers = (n_slices == 0u) ? 0 : stream_grid(((slices + kItems - 1) / kItems) * kThreads);
     const dim3 grid((unsigned)workers + (tail != 0u ? 1u : 0u)), block(kThreads);
     uint32_t* codes = reinterpret_cast<uint32_t*>(a.codes);
+    const int flags = pz | sse_past_caches<DT, B>(a.n);
     if constexpr (DT == kBF16 && FMT != kE8M0) {
         if (takes_scaled_kernel<B, FOUR6>(a, slices, workers)) {
             hipLaunchKernelGGL((stream_scaled_kernel<B, FMT, FOUR6>), grid, block, 0, a.stream, a.x, n_slices, last, tail, a.T,
-                               pz, a.absmax_dev, a.t_out, codes, a.scales, a.sse);
+                               flags, a.absmax_dev, a.t_out, codes, a.scales, a.sse);
             return hipGetLastError();
         }
     }
 #define MXQ_LAUNCH_STREAM(MODE, CLIP)                                                                 \
     hipLaunchKernelGGL((stream_kernel<DT, B, FMT, FOUR6, MODE, CLIP>), grid, block, 0, a.stream, a.x,       \
-                       n_slices, last, tail, a.T, pz, a.absmax_dev, a.t_out, codes, a.scales, a.sse, a.clip)
+                       n_slices, last, tail, a.T, flags, a.absmax_dev, a.t_out, codes, a.scales, a.sse, a.clip)
     if (a.clip) MXQ_LAUNCH_STREAM(kDynT, true);
     else if (tmode == kNoT) MXQ_LAUNCH_STREAM(kNoT, false);
     else if (tmode == kFastT) MXQ_LAUNCH_STREAM(kFastT, false);
@@ -728,7 +764,7 @@ static hipError_t launch_batch_recipe(const StreamArgs* t, int count, int pz, hi
         a.tails = tails ? n_t : 0u;
         const int workers = (total == 0u) ? 0 : stream_grid((int64_t)total * kThreads);
         hipLaunchKernelGGL((stream_batch_kernel<DT, B, FMT, FOUR6>), dim3((unsigned)workers + a.tails), dim3(kThreads), 0,
-                           stream, a, pz);
+                           stream, a, pz | sse_past_caches<DT, B>((int64_t)total * kThreads * 8));
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
