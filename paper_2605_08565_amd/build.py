@@ -1,14 +1,17 @@
-"""Builds libmxq.so (hand-written HIP kernels for gfx950 + the C ABI) in-tree with hipcc."""
+"""Builds libmxq.so (hand-written HIP kernels for gfx950 + the C ABI) in-tree with hipcc, and _mxq_calls.so (the
+native calls of the Python binding, host code on torch's C++ interface) with g++."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libmxq.so")
+CALLS = os.path.join(_HERE, "_mxq_calls.so")
 SOURCES = ["mxq_api.hip", "stream_kernels.hip", "brute_kernels.hip", "aux_kernels.hip", "diag_kernels.hip"]
 
 # No fast-math and no FMA contraction: every rounding in the kernels is written out.
@@ -28,13 +31,25 @@ def _run(cmd, verbose):
         raise RuntimeError("hipcc failed: " + " ".join(cmd))
 
 
+def _calls_command():
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include/torch/csrc/api/include"),
+            "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
+            os.path.join(CSRC, "binding.cpp"), "-o", CALLS, "-L" + os.path.join(root, "lib"),
+            "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+
+
 def build_library(verbose: bool = False, jobs: int = 4) -> str:
-    """Compiles every translation unit (in parallel) and links libmxq.so next to this file."""
+    """Compiles every translation unit (in parallel), links libmxq.so and builds _mxq_calls.so next to this file."""
     with tempfile.TemporaryDirectory(prefix="mxq_build_") as tmp:
         objs = [os.path.join(tmp, s.replace(".hip", ".o")) for s in SOURCES]
         cmds = [["hipcc", *FLAGS, "-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objs)]
         with ThreadPoolExecutor(max_workers=max(1, jobs)) as pool:
-            list(pool.map(lambda c: _run(c, verbose), cmds))
+            list(pool.map(lambda c: _run(c, verbose), cmds + [_calls_command()]))
         _run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-fvisibility=hidden", *objs, "-o", LIB],
              verbose)
     return LIB

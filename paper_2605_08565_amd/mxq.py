@@ -3,10 +3,16 @@
 Argument marshalling only: every function takes torch tensors that already live on the GPU,
 passes their device pointers and the current HIP stream to the library and returns.  Nothing
 is computed here and there is no CPU fallback -- a missing library is an error.
+
+The calls that a program makes often have a native form (csrc/binding.cpp, built as _mxq_calls.so) that is
+asked first.  It declines, before it has done anything, whatever is not plain (it returns None), and
+then the Python form below runs, checks and raises: that is the definition of the call.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -21,6 +27,7 @@ RECIPE_ABSMAX, RECIPE_ABSMAX_PZ, RECIPE_4OVER6, RECIPE_4OVER6_PZ, RECIPE_BRUTE, 
 DT_BF16, DT_F32 = 0, 1
 
 _lib = None
+_calls = None                            # native forms of the calls, once the library is loaded
 
 
 class _Tensor(ctypes.Structure):
@@ -37,7 +44,7 @@ class MxqError(RuntimeError):
 
 def lib() -> ctypes.CDLL:
     """Loads libmxq.so; raises if it has not been built (there is no fallback path)."""
-    global _lib
+    global _lib, _calls
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -79,8 +86,31 @@ def lib() -> ctypes.CDLL:
     L.mxq_num_candidates.argtypes = [i32]
     L.mxq_status_string.restype = ctypes.c_char_p
     L.mxq_status_string.argtypes = [i32]
-    _lib = L
+    _lib, _calls = L, _native_calls(L)
     return L
+
+
+def _native_calls(L: ctypes.CDLL):
+    """The module of native calls on the loaded library; None where it has not been built, or was built for
+    another torch: the Python forms then do all the work, 5 us a call slower."""
+    path = os.path.join(_HERE, "_mxq_calls.so")
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("_mxq_calls", path)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_mxq_calls", path, loader=loader))
+        loader.exec_module(module)
+    except ImportError:
+        return None
+    module.use(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+        L.mxq_quantize, L.mxq_quantize_hier, L.mxq_quantize_batch, L.mxq_tensor_absmax, L.mxq_dequantize,
+        L.mxq_dequantize_hier, L.mxq_clip_sse, L.mxq_histogram)))
+    return module
+
+
+def _done(result):
+    """The result of a native call: a library status other than OK comes back as an int."""
+    if result.__class__ is int:
+        raise MxqError(result)
+    return result
 
 
 def status_string(status: int) -> str:
@@ -139,6 +169,10 @@ def quantize(x: torch.Tensor, block: int, scale_fmt: int, recipe: int, tensor_sc
              elem_fmt: int = ELEM_E2M1, clip_sse_out: torch.Tensor | None = None):
     """mxq_quantize on a 2-D contiguous CUDA tensor. Returns (codes, scales, sse).  With
     `clip_sse_out` (fp32 [rows, cols/block]) mxq_quantize_clip, which also fills that tensor."""
+    if _calls is not None and stream is None and clip_sse_out is None:
+        done = _calls.quantize(x, block, scale_fmt, recipe, tensor_scale, codes_out, scales_out, sse_out, want_sse, elem_fmt)
+        if done is not None:
+            return _done(done)
     if not x.is_cuda or x.dim() != 2 or not x.is_contiguous():
         raise ValueError("x must be a contiguous 2-D tensor on the GPU")
     rows, cols = x.shape
@@ -172,6 +206,10 @@ def quantize_batch(xs, block: int, scale_fmt: int, recipe: int, outs=None, want_
     """mxq_quantize_batch: the 2-D contiguous CUDA tensors `xs` (one dtype) in as few launches as
     possible.  `outs`: optional list of (codes, scales, sse-or-None) per tensor.  Returns that list."""
     xs = list(xs)
+    if _calls is not None and stream is None and outs is None:
+        done = _calls.quantize_batch(xs, block, scale_fmt, recipe, want_sse, elem_fmt)
+        if done is not None:
+            return _done(done)
     if outs is None:
         outs = []
         for x in xs:
@@ -210,6 +248,11 @@ def quantize_hier(x: torch.Tensor, block: int, scale_fmt: int, recipe: int, absm
     """mxq_quantize_hier: T is derived on the device from `absmax` (the one-element tensor that
     tensor_absmax wrote).  Returns (codes, scales, sse, tensor_scale) -- the last a one-element
     fp32 device tensor."""
+    if _calls is not None and stream is None:
+        done = _calls.quantize_hier(x, block, scale_fmt, recipe, absmax, tensor_scale_out, codes_out, scales_out, sse_out,
+                                    want_sse, elem_fmt)
+        if done is not None:
+            return _done(done)
     if not x.is_cuda or x.dim() != 2 or not x.is_contiguous():
         raise ValueError("x must be a contiguous 2-D tensor on the GPU")
     rows, cols = x.shape
@@ -240,6 +283,10 @@ def dequantize(codes: torch.Tensor, scales: torch.Tensor, block: int, scale_fmt:
                out: torch.Tensor | None = None, stream=None, elem_fmt: int = ELEM_E2M1) -> torch.Tensor:
     """mxq_dequantize; with a one-element fp32 device tensor as `tensor_scale` (as returned by
     quantize_hier) mxq_dequantize_hier, which reads the scale on the device."""
+    if _calls is not None and stream is None:
+        done = _calls.dequantize(codes, scales, block, scale_fmt, tensor_scale, out_dtype, out, elem_fmt)
+        if done is not None:
+            return _done(done)
     rows, half = codes.shape
     cols = half * 2
     if out is None:
@@ -285,6 +332,10 @@ def tensor_absmax(x: torch.Tensor, out: torch.Tensor | None = None, stream=None,
                   workspace: torch.Tensor | None = None) -> torch.Tensor:
     """mxq_tensor_absmax: one-element fp32 device tensor holding max |x|.  With a `workspace`
     (from absmax_workspace) mxq_tensor_absmax_ws, the one-launch form."""
+    if _calls is not None and stream is None and workspace is None:
+        done = _calls.tensor_absmax(x, out)
+        if done is not None:
+            return _done(done)
     if not x.is_cuda or not x.is_contiguous():
         raise ValueError("x must be a contiguous tensor on the GPU")
     if out is None:
@@ -319,6 +370,10 @@ def clip_sse(x: torch.Tensor, scales: torch.Tensor, block: int, scale_fmt: int,
              tensor_scale: float = 1.0, out: torch.Tensor | None = None, stream=None,
              elem_fmt: int = ELEM_E2M1) -> torch.Tensor:
     """mxq_clip_sse: clipping-only part of the block SSE for the given scale bytes."""
+    if _calls is not None and stream is None:
+        done = _calls.clip_sse(x, scales, block, scale_fmt, tensor_scale, out, elem_fmt)
+        if done is not None:
+            return _done(done)
     if not x.is_cuda or x.dim() != 2 or not x.is_contiguous():
         raise ValueError("x must be a contiguous 2-D tensor on the GPU")
     rows, cols = x.shape
@@ -335,6 +390,10 @@ def histogram(codes: torch.Tensor, scales: torch.Tensor, block: int, stream=None
               elem_fmt: int = ELEM_E2M1, out=None):
     """mxq_histogram: (int64 [8] magnitude-index counts, int64 [256] scale-byte counts); `out` may
     hold the two result tensors."""
+    if _calls is not None and stream is None and out is None:
+        done = _calls.histogram(codes, scales, block, elem_fmt)
+        if done is not None:
+            return _done(done)
     rows, half = codes.shape
     _need(codes, rows * half, "codes", torch.uint8)
     _need(scales, _nblocks(rows, half * 2, block), "scales", torch.uint8)

@@ -1,0 +1,112 @@
+"""The native forms of the binding's calls (csrc/binding.cpp) against the Python forms, which define them."""
+import os
+
+import pytest
+import torch
+
+from paper_2605_08565_amd import mxq
+
+
+def test_native_calls_are_built_and_decline_what_is_not_plain():
+    """On the CPU: None before anything is done for CPU tensors, other types and active modes."""
+    mxq.lib()
+    assert os.path.exists(os.path.join(os.path.dirname(mxq.__file__), "_mxq_calls.so")) and mxq._calls is not None
+    x = torch.zeros((4, 32), dtype=torch.bfloat16)
+    u = torch.zeros((4, 16), dtype=torch.uint8)
+    for v in (x, None, 3, "x", torch.nn.Parameter(x.float()), x.expand(4, 32)):
+        assert mxq._calls.quantize(v, 16, 1, 0, 1.0, None, None, None, True, 0) is None
+        assert mxq._calls.quantize_hier(v, 16, 1, 0, x, None, None, None, None, True, 0) is None
+        assert mxq._calls.quantize_batch([v], 16, 1, 0, True, 0) is None
+        assert mxq._calls.tensor_absmax(v, None) is None
+        assert mxq._calls.clip_sse(v, u, 16, 1, 1.0, None, 0) is None
+    assert mxq._calls.dequantize(u, u, 16, 1, 1.0, torch.float32, None, 0) is None
+    assert mxq._calls.histogram(u, u, 16, 0) is None
+    assert mxq._calls.quantize_batch([], 16, 1, 0, True, 0) is None
+
+
+def outcome(call):
+    """What a call gives: its tensors (bit patterns), or the type and text of its error."""
+    def flat(r):
+        if isinstance(r, torch.Tensor):
+            return (tuple(r.shape), r.dtype, r.requires_grad, r.cpu().view(torch.uint8).flatten().tolist())
+        return [flat(i) for i in r] if isinstance(r, (list, tuple)) else r
+    try:
+        r = call()
+        torch.cuda.synchronize()
+        return type(r), flat(r)
+    except Exception as e:
+        return type(e), str(e)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("where", ["default stream", "side stream", "default device set"])
+def test_native_and_python_forms_agree(monkeypatch, where):
+    mxq.lib()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    x = torch.randn((6, 64), generator=gen, device="cuda", dtype=torch.float32)
+    xb, n = x.to(torch.bfloat16), x.numel()
+    word = mxq.tensor_absmax(x)
+    codes, scales, sse, _ = mxq.quantize_hier(x, 16, 1, 2, word)
+
+    def new(dtype, size):
+        return torch.full((size,), 7, dtype=dtype, device="cuda")
+
+    calls = {
+        "quantize": lambda: mxq.quantize(xb, 16, 1, 2),
+        "no sse, int scale": lambda: mxq.quantize(x, 2, 2, 0, tensor_scale=2, want_sse=False),
+        "buffers": lambda: mxq.quantize(xb, 4, 1, 5, 0.5, new(torch.uint8, n // 2), new(torch.uint8, n // 4), new(torch.float32, n // 4)),
+        "short buffer": lambda: mxq.quantize(xb, 4, 1, 0, codes_out=new(torch.uint8, n // 2 - 1)),
+        "buffer type": lambda: mxq.quantize(xb, 4, 1, 0, sse_out=new(torch.float64, n)),
+        "misaligned": lambda: mxq.quantize(xb, 4, 1, 0, codes_out=new(torch.uint8, n)[1:]),
+        "block 3": lambda: mxq.quantize(xb[:, :63].contiguous(), 3, 1, 0),
+        "block 0": lambda: mxq.quantize(xb, 0, 1, 0),
+        "block too large": lambda: mxq.quantize(xb, 128, 1, 0),
+        "recipe": lambda: mxq.quantize(xb, 16, 1, 9),
+        "unsupported": lambda: mxq.quantize(xb, 16, 0, 2),
+        "scale": lambda: mxq.quantize(xb, 16, 1, 2, tensor_scale=float("inf")),
+        "type": lambda: mxq.quantize(x.double(), 16, 1, 2),
+        "strided": lambda: mxq.quantize(x.t(), 2, 1, 2),
+        "three dimensions": lambda: mxq.quantize(x.view(2, 3, 64), 16, 1, 2),
+        "empty": lambda: mxq.quantize(xb[:0], 16, 1, 2),
+        "parameter": lambda: mxq.quantize(torch.nn.Parameter(x), 16, 1, 2),
+        "hier": lambda: mxq.quantize_hier(xb, 8, 2, 3, word),
+        "hier empty": lambda: mxq.quantize_hier(xb[:0], 8, 2, 3, word),
+        "hier buffers": lambda: mxq.quantize_hier(x, 8, 1, 0, word, new(torch.float32, 1), want_sse=False),
+        "hier word": lambda: mxq.quantize_hier(x, 8, 1, 0, x.double()),
+        "batch": lambda: mxq.quantize_batch([xb, xb[:2], xb[:0]], 32, 1, 2),
+        "batch types": lambda: mxq.quantize_batch([xb, x], 32, 1, 2),
+        "batch generator": lambda: mxq.quantize_batch((t for t in (x, x)), 32, 1, 2, want_sse=False),
+        "batch recipe": lambda: mxq.quantize_batch([xb], 32, 1, 4),
+        "absmax": lambda: mxq.tensor_absmax(xb),
+        "absmax 3-d, buffer": lambda: mxq.tensor_absmax(x.view(2, 3, 64), out=new(torch.float32, 1)),
+        "absmax empty": lambda: mxq.tensor_absmax(x[:0]),
+        "absmax type": lambda: mxq.tensor_absmax(x.half()),
+        "dequantize": lambda: mxq.dequantize(codes, scales, 16, 1, 0.25, torch.bfloat16),
+        "dequantize hier": lambda: mxq.dequantize(codes, scales, 16, 1, word),
+        "dequantize out": lambda: mxq.dequantize(codes, scales, 16, 1, out=new(torch.bfloat16, n)),
+        "dequantize type": lambda: mxq.dequantize(codes, scales, 16, 1, out_dtype=torch.float16),
+        "dequantize short": lambda: mxq.dequantize(codes, scales[:5], 16, 1),
+        "clip": lambda: mxq.clip_sse(x, scales, 16, 1),
+        "clip out": lambda: mxq.clip_sse(xb, scales, 16, 1, 0.5, out=new(torch.float32, n // 16)),
+        "histogram": lambda: mxq.histogram(codes, scales, 16),
+        "histogram block": lambda: mxq.histogram(codes, scales, 24),
+    }
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+
+    def everything():
+        if where == "side stream":
+            with torch.cuda.stream(side):
+                return {k: outcome(c) for k, c in calls.items()}
+        if where == "default device set":                               # a mode: the native forms decline
+            with torch.device("cuda"):
+                return {k: outcome(c) for k, c in calls.items()}
+        return {k: outcome(c) for k, c in calls.items()}
+
+    native = everything()
+    monkeypatch.setattr(mxq, "_calls", None)
+    python = everything()
+    for k in calls:
+        assert native[k] == python[k], k
+    assert native["quantize"][0] is tuple and native["misaligned"][0] is mxq.MxqError and native["strided"][0] is ValueError
