@@ -221,7 +221,7 @@ MXQ_HD bool fast_division_unsafe_amax(float a)
 }
 
 // bf16 inputs have 128 mantissas only, so for one T it can be SEEN whether shorter sequences are exact:
-//   * the quotient x/T as quot(x, make_recip(T)), two instructions instead of three: tried on every mantissa
+//   * the quotient x/T as quot(x, lean_recip(T)), two instructions instead of three: tried on every mantissa
 //     (lean_division_exact).  About one T in 10^5 fails.
 //   * the quotient of v = fl(x/T) by a scale S as one truncated product with the float nearest to 1/S or the
 //     next one above: it is within 2^-21 of x/(T*S), so it can take a wrong decision only for an x that close
@@ -237,6 +237,16 @@ MXQ_HD bool fast_division_unsafe_amax(float a)
 MXQ_HD bool lean_T_in_range(float T)
 {
     return T >= 0x1p-60f && T <= 0x1p60f && (f2u(T) & 0x7FFFFFu) != 0x7FFFFFu;
+}
+
+// The two parts of 1/T for it.  For a power of two the second part is zero, and an infinite x would give
+// inf*0 = NaN where x/T is infinite; any positive part below half an ulp of every finite quotient mends that
+// (in the range of T all other second parts are above 2^-110).
+MXQ_HD Recip lean_recip(float T)
+{
+    Recip r = make_recip(T);
+    r.lo = __builtin_fmaxf(r.lo, 0x1p-126f);
+    return r;
 }
 
 MXQ_HD bool lean_division_exact(uint32_t mantissa, float T, float rT, Recip r)

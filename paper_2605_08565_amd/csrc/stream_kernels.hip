@@ -497,7 +497,7 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
     if (absmax_dev) T = tensor_scale_of<FMT>(*absmax_dev);
     if (t_out && blockIdx.x == 0 && threadIdx.x == 0) *t_out = T;
     const float rT = 1.0f / T;                                       // correctly rounded
-    Recip r = make_recip(T);
+    Recip r = lean_recip(T);
     uint32_t above = 0u;
     if (s0 < stride && lean_T_in_range(T) && lean_T(pair, T, rT, r, above)) {     // uniform: every wavefront finds the same
         if constexpr (!kEarly) load_tile<kBF16>(first, x, s0, sl);

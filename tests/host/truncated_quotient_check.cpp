@@ -63,7 +63,7 @@ static int lean(float T, mxq::Recip r, uint32_t* above)
 static long g_n, g_bad, g_refused;
 static void tensor_scale(float T)
 {
-    const mxq::Recip r = mxq::make_recip(T);
+    const mxq::Recip r = mxq::lean_recip(T);
     uint32_t above = 0;
     if (!mxq::lean_T_in_range(T) || !lean(T, r, &above)) { ++g_refused; return; }
     for (uint32_t m = 0; m < 128; ++m)
@@ -100,9 +100,25 @@ static void tensor_scales(void)
     printf("tensor_scales cases=%ld bad=%ld refused=%ld\n", g_n, g_bad, g_refused);
 }
 
+/* Powers of two: every bf16 value, zeros, subnormals and infinities among them, bits of the quotient (NaN: a NaN). */
+static void powers_of_two(void)
+{
+    long n = 0, bad = 0;
+    for (int k = -60; k <= 60; ++k) {
+        const float T = ldexpf(1.0f, k);
+        const mxq::Recip r = mxq::lean_recip(T);
+        for (uint32_t u = 0; u < 65536u; ++u, ++n) {
+            const float x = mxq::u2f(u << 16), v = mxq::quot(x, r), w = x / T;
+            bad += (x != x) ? v == v : mxq::f2u(v) != mxq::f2u(w);
+        }
+    }
+    printf("powers_of_two cases=%ld bad=%ld\n", n, bad);
+}
+
 int main()
 {
     bf16_values();
     tensor_scales();
+    powers_of_two();
     return 0;
 }

@@ -22,7 +22,7 @@ def test_decisions_of_the_truncated_quotient_are_exact(tmp_path):
     out = subprocess.run([exe], capture_output=True, text=True, timeout=300).stdout
     print(out)
     lines = [l for l in out.splitlines() if "cases=" in l]
-    assert [l.split()[0] for l in lines] == ["bf16_values", "tensor_scales_of_bf16_absmax", "tensor_scales"]
+    assert [l.split()[0] for l in lines] == ["bf16_values", "tensor_scales_of_bf16_absmax", "tensor_scales", "powers_of_two"]
     for l in lines:
         assert int(l.split("cases=")[1].split()[0]) > 1_000_000 and int(l.split("bad=")[1].split()[0]) == 0, l
     assert int(lines[1].split("refused=")[1]) == 2 * 4 * 4              # four of 128, both formats, four exponents
@@ -96,3 +96,31 @@ def test_tensor_scales_of_large_bf16_tensors(oracle, fmt, block):
                 assert (g.view(np.uint32) == r.view(np.uint32)).all() if g.dtype == np.float32 else (g == r).all(), (top, t, rec, g.dtype)
             if len(got) == 4:
                 assert float(got[3].cpu()[0]) == t
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt", [1, 2])
+@pytest.mark.parametrize("block", [4, 16, 64])
+def test_infinities_of_large_bf16_tensors(fmt, block):
+    """An infinite element gives in the kernel for scaled bf16 what it gives in the general one, which small tensors
+    take: under the tensor scale 1 that an infinite abs-max leads to, and under scales by value beyond 2^+-20.  (Within,
+    the general kernel's refined division makes a NaN of it.)"""
+    from paper_2605_08565_amd import mxq
+
+    cols, rows = 4096, 4 * 2048 * 2048 // 4096 + 3
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(block)
+    x = torch.randn((rows, cols), generator=gen, device="cuda").to(torch.bfloat16)
+    special = (0, rows // 2, rows - 1)
+    for i in special:
+        x[i, 5 + i % 7::97] = float("inf")
+        x[i, 40::131] = -float("inf")
+    small = torch.stack([x[i] for i in special])
+    word = mxq.tensor_absmax(x)
+    assert float(word) == float("inf")
+    for call in (lambda t: mxq.quantize_hier(t, block, fmt, 2, word), lambda t: mxq.quantize_hier(t, block, fmt, 0, word),
+                 *(lambda t, T=T: mxq.quantize(t, block, fmt, 2, tensor_scale=T) for T in (2.0 ** -30, 2.0 ** 21, 3.0e-9))):
+        got, want = call(x), call(small)
+        for g, w in zip(got[:3], want[:3]):
+            g = torch.stack([g[i] for i in special])
+            assert torch.equal(g.view(torch.uint8), w.view(torch.uint8))
