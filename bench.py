@@ -153,8 +153,8 @@ KERNEL_OF_PASS = {
     "4over6_e4m3_b8": "mxq::stream_kernel<0, 8, 1, true, 0, false>",
     "4over6_e4m3_b32": "mxq::stream_kernel<0, 32, 1, true, 0, false>",
     "4over6_e4m3_b64": "mxq::stream_kernel<0, 64, 1, true, 0, false>",
-    "absmax_e4m3_b16_H": "mxq::stream_kernel<0, 16, 1, false, 1, false>",
-    "4over6_e4m3_b16_H": "mxq::stream_kernel<0, 16, 1, true, 1, false>",
+    "absmax_e4m3_b16_H": "mxq::stream_scaled_kernel<16, 1, false>",
+    "4over6_e4m3_b16_H": "mxq::stream_scaled_kernel<16, 1, true>",
     "brute_e4m3_b16": "mxq::brute_kernel<0, 16, 1, false, false>",
     "brute_ue5m3_b16": "mxq::brute_kernel<0, 16, 2, false, false>",
     "brute_e4m3_b4": "mxq::brute_kernel<0, 4, 1, false, false>",
