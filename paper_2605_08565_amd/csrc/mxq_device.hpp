@@ -126,7 +126,9 @@ __device__ __forceinline__ void fill_scale_table(ScalePair* tab, uint32_t above)
 
 // quot_truncated() of the lane's 8 values by NBLK reciprocals: 8 products and two mode switches instead of the
 // 16 instructions of quot().  The rounding mode of the wavefront's fp32 arithmetic is switched inside one asm
-// block, so that no other instruction can get between.  4-over-6 on 4096 x 14336 bf16, with the half as
+// block, so that no other instruction can get between.  Two writes of the mode register have to be two wait states
+// apart, and the compiler, which sees to that between its own, does not look into asm: each block brings them
+// (s_nop 1), whatever write lies before it.  4-over-6 on 4096 x 14336 bf16, with the half as
 // large table entries that go with it: b = 32 31.4 -> 30.4 us, b = 8 32.3 -> 31.6; UE5M3 b = 16 33.2 -> 31.6, b = 2
 // 59.1 -> 56.1.
 template <int NBLK>
@@ -134,7 +136,8 @@ __device__ __forceinline__ void quot8_truncated(const float (&v)[8], const float
 {
     static_assert(NBLK == 1 || NBLK == 2 || NBLK == 4, "blocks inside a lane");
     const float r0 = r[0], r1 = r[2 * NBLK / 8], r2 = r[4 * NBLK / 8], r3 = r[6 * NBLK / 8];
-    asm("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 3\n\t"
+    asm("s_nop 1\n\t"
+        "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 3\n\t"
         "v_mul_f32 %0, %8, %16\n\t"
         "v_mul_f32 %1, %9, %16\n\t"
         "v_mul_f32 %2, %10, %17\n\t"
@@ -175,7 +178,8 @@ __device__ __forceinline__ bool lean_T(LeanPair pair, float T, float rT, Recip r
     float x, y, y_above;
     const bool near = lean_quotient_candidate(pair.td, T, x);
     const float v = div_by_T(x, T, rT);
-    asm("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 3\n\t"
+    asm("s_nop 1\n\t"
+        "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 3\n\t"
         "v_mul_f32 %0, %2, %3\n\t"
         "v_mul_f32 %1, %2, %4\n\t"
         "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 0"
