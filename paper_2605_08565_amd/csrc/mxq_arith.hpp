@@ -241,7 +241,9 @@ MXQ_HD bool lean_T_in_range(float T)
 
 // The two parts of 1/T for it.  For a power of two the second part is zero, and an infinite x would give
 // inf*0 = NaN where x/T is infinite; any positive part below half an ulp of every finite quotient mends that
-// (in the range of T all other second parts are above 2^-110).
+// (in the range of T all other second parts are above 2^-110).  The quotient is the IEEE one for them too; div_by_T,
+// which gives a NaN for every x/T that is infinite, is not, and stream_scaled_kernel follows div_by_T where that is
+// what the general kernel takes.
 MXQ_HD Recip lean_recip(float T)
 {
     Recip r = make_recip(T);

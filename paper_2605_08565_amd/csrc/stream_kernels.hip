@@ -330,7 +330,7 @@ __device__ __forceinline__ void stream_step(RawChunk<DT> (&cur)[kItems], RawChun
                                             const void* __restrict__ x, uint32_t s0, uint32_t stride,
                                             Slices sl, float T, float rT, int tdyn, int flags, const Entry* tab,
                                             u32x4* wave_lds, uint32_t* __restrict__ codes, uint8_t* __restrict__ scales,
-                                            float* __restrict__ sse_out, float* __restrict__ clip_out)
+                                            float* __restrict__ sse_out, float* __restrict__ clip_out, uint32_t& largest_sse)
 {
     float v[kItems][8];
     __builtin_amdgcn_s_waitcnt(0x0F70);                              // vmcnt(0)
@@ -348,6 +348,12 @@ __device__ __forceinline__ void stream_step(RawChunk<DT> (&cur)[kItems], RawChun
     for (int i = 0; i < kItems; ++i)
         process_chunk<B, FMT, FOUR6, TMODE, CLIP>(v[i], T, rT, tdyn, (flags & kPreventZero) != 0, tab, out[i].packed, out[i].code, out[i].sse,
                                                   out[i].clip);
+    if constexpr (TMODE == kLeanT) {
+#pragma unroll
+        for (int i = 0; i < kItems; ++i)
+#pragma unroll
+            for (int k = 0; k < TileOut<B>::NBLK; ++k) largest_sse = max(largest_sse, f2u(out[i].sse[k]));
+    }
 }
 
 // Ragged tail: when n is not a multiple of 8 (only possible for b = 2 or 4) the last `count` < 8
@@ -377,9 +383,10 @@ __device__ __forceinline__ void stream_tail(const void* __restrict__ x, uint64_t
 }
 
 // The complete chunks of one workgroup, grid-stride over workgroup tiles with two register buffers
-// alternating between "being processed" and "in flight"; bufA holds the first tile's loads.
+// alternating between "being processed" and "in flight"; bufA holds the first tile's loads.  With kLeanT the
+// bits of the largest block SSE that the lane has seen come back (a NaN is above all others).
 template <int DT, int B, int FMT, bool FOUR6, int TMODE, bool CLIP, class Entry>
-__device__ __forceinline__ void stream_tiles(RawChunk<DT> (&bufA)[kItems], const void* __restrict__ x, uint32_t s0,
+__device__ __forceinline__ uint32_t stream_tiles(RawChunk<DT> (&bufA)[kItems], const void* __restrict__ x, uint32_t s0,
                                              uint32_t stride, Slices sl, float T, float rT, int tdyn, int flags, const Entry* tab,
                                              u32x4* wave_lds, uint32_t* __restrict__ codes, uint8_t* __restrict__ scales,
                                              float* __restrict__ sse_out, float* __restrict__ clip_out)
@@ -389,16 +396,16 @@ __device__ __forceinline__ void stream_tiles(RawChunk<DT> (&bufA)[kItems], const
     for (int i = 0; i < kItems; ++i) bufB[i] = RawChunk<DT>{};
     TileOut<B> out[kItems];
     bool have_prev = false;
-    uint32_t s_prev = s0;
+    uint32_t s_prev = s0, largest_sse = 0u;
     while (true) {
         stream_step<DT, B, FMT, FOUR6, TMODE, CLIP>(bufA, bufB, out, have_prev, s_prev, x, s0, stride, sl, T, rT, tdyn,
-                                                    flags, tab, wave_lds, codes, scales, sse_out, clip_out);
+                                                    flags, tab, wave_lds, codes, scales, sse_out, clip_out, largest_sse);
         have_prev = true;
         s_prev = s0;
         s0 += stride;
         if (s0 >= sl.count) break;
         stream_step<DT, B, FMT, FOUR6, TMODE, CLIP>(bufB, bufA, out, true, s_prev, x, s0, stride, sl, T, rT, tdyn,
-                                                    flags, tab, wave_lds, codes, scales, sse_out, clip_out);
+                                                    flags, tab, wave_lds, codes, scales, sse_out, clip_out, largest_sse);
         s_prev = s0;
         s0 += stride;
         if (s0 >= sl.count) break;
@@ -406,6 +413,7 @@ __device__ __forceinline__ void stream_tiles(RawChunk<DT> (&bufA)[kItems], const
 #pragma unroll
     for (int i = 0; i < kItems; ++i)
         store_slice<B, CLIP>(out[i], s_prev + (uint32_t)i, sl, flags, codes, scales, sse_out, CLIP ? clip_out : nullptr);
+    return largest_sse;
 }
 
 // Main kernel.
@@ -481,6 +489,7 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
 {
     static_assert(FMT != kE8M0 && kItems == 1, "scales from a table, one slice per tile");
     __shared__ ScaleEntry tab[256];
+    __shared__ uint32_t again;
     const Slices sl{n_slices, last_chunks};
     const uint32_t stride = gridDim.x - ((B < 8 && tail != 0u) ? 1u : 0u);        // the last workgroup takes the tail
     uint32_t s0 = blockIdx.x;
@@ -502,6 +511,7 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
     if (s0 < stride && lean_T_in_range(T) && lean_T(pair, T, rT, r, above)) {     // uniform: every wavefront finds the same
         if constexpr (!kEarly) load_tile<kBF16>(first, x, s0, sl);
         ScalePair* pairs = reinterpret_cast<ScalePair*>(tab);
+        again = 0u;
         fill_scale_table<FMT>(pairs, above);
         if constexpr (kEarly) {
             asm volatile("" : "+v"(r.hi), "+v"(r.lo));
@@ -509,9 +519,15 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
             r.hi = u2f((uint32_t)__builtin_amdgcn_readfirstlane((int)f2u(r.hi)));
             r.lo = u2f((uint32_t)__builtin_amdgcn_readfirstlane((int)f2u(r.lo)));
         }
-        stream_tiles<kBF16, B, FMT, FOUR6, kLeanT, false>(first, x, s0, stride, sl, r.hi, r.lo, kLeanT, flags, pairs,
-                                                          (u32x4*)nullptr, codes, scales, sse_out, (float*)nullptr);
-        return;
+        const uint32_t largest_sse =
+            stream_tiles<kBF16, B, FMT, FOUR6, kLeanT, false>(first, x, s0, stride, sl, r.hi, r.lo, kLeanT, flags, pairs,
+                                                              (u32x4*)nullptr, codes, scales, sse_out, (float*)nullptr);
+        // An element that is not finite, or is not any more after the division, leaves such an SSE, and the general way
+        // may see it otherwise (div_by_T makes a NaN of an infinity, with a sign of its own): the workgroup goes that way
+        // too, so that the outputs of a row do not depend on the size of its tensor.
+        if (largest_sse >= 0x7F800000u) again = 1u;
+        __syncthreads();
+        if (again == 0u) return;                                     // uniform
     }
     const int tdyn = (T == 1.0f) ? kNoT : (fast_division_ok(T) ? kFastT : kSlowT);
     fill_scale_table<FMT>(tab);

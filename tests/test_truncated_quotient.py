@@ -104,7 +104,7 @@ def test_tensor_scales_of_large_bf16_tensors(oracle, fmt, block):
 def test_infinities_of_large_bf16_tensors(fmt, block):
     """An infinite element gives in the kernel for scaled bf16 what it gives in the general one, which small tensors
     take: under the tensor scale 1 that an infinite abs-max leads to, and under scales by value beyond 2^+-20.  (Within,
-    the general kernel's refined division makes a NaN of it.)"""
+    the general kernel's refined division makes a NaN of it: the next test.)"""
     from paper_2605_08565_amd import mxq
 
     cols, rows = 4096, 4 * 2048 * 2048 // 4096 + 3
@@ -124,3 +124,34 @@ def test_infinities_of_large_bf16_tensors(fmt, block):
         for g, w in zip(got[:3], want[:3]):
             g = torch.stack([g[i] for i in special])
             assert torch.equal(g.view(torch.uint8), w.view(torch.uint8))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt", [1, 2])
+@pytest.mark.parametrize("block", [2, 4, 8, 16, 128])
+def test_elements_that_are_not_finite_do_not_depend_on_the_size(fmt, block):
+    """Infinities, NaNs of both signs and finite elements whose quotient by T overflows: the same bytes in a tensor of many
+    tiles (kernel for scaled bf16) as in one of three rows (general kernel).  A row is eight wavefronts in both."""
+    from paper_2605_08565_amd import mxq
+
+    cols, rows = 4096, 4 * 2048 * 2048 // 4096 + 3
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(block)
+    x = torch.randn((rows, cols), generator=gen, device="cuda").to(torch.bfloat16)
+    bits = x.view(torch.int16)
+    special = (0, rows // 2, rows - 1)
+    for i, row in enumerate(special):                                   # one kind alone in a wavefront, and together
+        for j, value in enumerate((0x7F80, 0xFF80, 0x7FC0, 0xFFC1, 0x7F7F, 0xFF7F)):
+            at = bits[row, 512 * j + i:512 * (j + 1):97]
+            at.copy_(torch.full_like(at, value - 65536 if value > 32767 else value))
+            bits[row, 3584 + 61 * j + i] = value - 65536 if value > 32767 else value
+    small = torch.stack([x[i] for i in special])
+    calls = [lambda t, a=a, rec=rec: mxq.quantize_hier(t, block, fmt, rec, torch.full((1,), a, device="cuda"))
+             for rec in (1, 2) for a in (249.0, 0.0, 225.0, 672.0, 1.0e-2, 3.0e-15, 1.0e20, float("inf"))]
+    calls += [lambda t, T=T, rec=rec: mxq.quantize(t, block, fmt, rec, tensor_scale=T)
+              for rec in (0, 3) for T in (0.7, 0.25, 2.0 ** -20, 3.0e-7, 2.0 ** 21)]
+    for i, call in enumerate(calls):
+        got, want = call(x), call(small)
+        for g, w in zip(got[:3], want[:3]):
+            g = torch.stack([g[j] for j in special])
+            assert torch.equal(g.view(torch.uint8), w.view(torch.uint8)), (i, g.dtype, int((g.view(torch.uint8) != w.view(torch.uint8)).sum()))
