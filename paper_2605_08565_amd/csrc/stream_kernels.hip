@@ -462,8 +462,11 @@ stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunk
 
 // bf16 under a tensor scale, T by value or from the abs-max in device memory, for tensors of several tiles a
 // workgroup: 29 vector instructions of 160 a chunk (4-over-6) go where lean_T finds the shorter sequences exact
-// for this T.  Every wavefront finds that out by itself in some 45 instructions.  The other T's go the general way,
-// with b = 2 in a plain loop, whose registers are few, without prefetch.
+// for this T.  Every wavefront finds that out by itself in some 45 instructions.  The other T's (four of the 128 that
+// a bf16 abs-max gives) go the general way, 4-over-6 with b = 2 in a plain loop, whose registers are few, without
+// prefetch.  General kernel -> this one for such a T: 2048 x 4096 4-over-6 b = 16 7.00 -> 7.24 us, b = 64 7.02 -> 7.53;
+// 4096 x 4096 4-over-6 b = 16 12.1 -> 12.1, abs-max 9.9 -> 10.1; 8192 x 4096 4-over-6 b = 16 22.2 -> 21.5, abs-max 17.6
+// -> 17.9; 4-over-6 b = 2 33.9 -> 36.8.  (With the first tile loaded a second time 7.60, 7.87, 12.5, 10.5, 21.8, 18.3.)
 // General kernel -> this one, T from device memory, E4M3: 4096 x 8192 4-over-6 b = 16 23.0 -> 21.1 us, b = 64 22.7
 // -> 20.4, b = 4 27.2 -> 24.8, abs-max b = 16 19.0 -> 18.2.
 // With fewer tiles a workgroup than these the test of T costs what it saves (two tiles, 2048 x 4096: 4-over-6
@@ -528,6 +531,7 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
         if (largest_sse >= 0x7F800000u) again = 1u;
         __syncthreads();
         if (again == 0u) return;                                     // uniform
+        if constexpr (kEarly) load_tile<kBF16>(first, x, s0, sl);
     }
     const int tdyn = (T == 1.0f) ? kNoT : (fast_division_ok(T) ? kFastT : kSlowT);
     fill_scale_table<FMT>(tab);
@@ -538,8 +542,7 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
             return;
         }
     }
-    if constexpr (B >= 4) {
-        load_tile<kBF16>(first, x, s0, sl);                          // (again: kept from above, it would cost registers)
+    if constexpr (kEarly) {
         stream_tiles<kBF16, B, FMT, FOUR6, kDynT, false>(first, x, s0, stride, sl, T, rT, tdyn, flags, tab, (u32x4*)nullptr,
                                                          codes, scales, sse_out, (float*)nullptr);
     } else {
