@@ -666,19 +666,30 @@ stream_batch_kernel(const BatchArgs a, int flags)
 
 // ------------------------------------------------------------------------------ dispatch
 
-// Where the block SSEs are written past the caches: up to 15 MiB of them (fp32 input 8) from an input of up to 128 MiB,
-// for fp32 with b <= 32.  Ordinary -> past the caches, E4M3, four tensors in turn, into fresh (re-used) outputs: bf16
-// 4-over-6 b = 16 16 M elements 10.6 -> 9.9 us (10.6 -> 9.9), 32 M 18.7 -> 17.7 (18.5 -> 17.3), 56 M 32.7 -> 31.8
-// (32.9 -> 32.0); b = 8 16 M 11.5 -> 10.4; b = 4 8 M 7.9 -> 7.0; b = 2 8 M 9.4 -> 8.3; fp32 b = 16 16 M 15.5 -> 15.3, b = 8
-// 16.6 -> 15.9.  Beyond the lines: bf16 b = 8 40 M 23.3 -> 23.9, b = 16 128 M 66.8 -> 70.2, fp32 b = 128 32 M 28.3
-// -> 28.8; b <= 4 from 60 M on gains 5 to 13 % in fresh outputs and loses as much in re-used ones.
-template <int DT, int B>
+// Where the block SSEs are written past the caches: bf16, 4-over-6 or b = 2, 6 to 15 MiB of them from an input of up
+// to 128 MiB.  The line is drawn by the call alone and by the call with a reader of the SSEs behind it (a tensor MSE is
+// usually next), each with four sets of outputs in turn and with one set re-used: the call alone has to gain, and with
+// the reader the two together must not lose.  Ordinary -> past the caches in per cent, E4M3, four inputs in turn, in the
+// order alone, alone re-used, with reader, with reader re-used:
+//   4-over-6 b = 16   2 MiB -3 -3 +5 +5    4 MiB -3 -3 +3 -1    6 MiB -5 -3 +3 -5    8 MiB -5 -3  0 -5   12 MiB -4 -4 -1 -3
+//                    14 MiB -2 -3  0 -1   15 MiB -2 -2  0 +2   18 MiB -1  0 +2 +2   24 MiB +1 +2 +3 +3
+//            b = 8    4 MiB -2 -5 +6 -3    8 MiB -5 -6 +2 -7   12 MiB -2 -2 +4 -7   18 MiB +2 +1 +8 +4
+//            b = 4    6 MiB -13 -15 0 -9   8 MiB -11 -11 0 -11 12 MiB -4 -3 +5 -14  20 MiB +2 +1 +9 +2
+//            b = 2    4 MiB  0  0  0 +9    8 MiB -8 -9 -2 -6   12 MiB -18 -17 -6 -7 24 MiB -2 -1 +6 +10
+//            b = 32   4 MiB -3  0 +1  0    7 MiB -2 -3  0 -1    8 MiB -3 -3 +1 +1
+//   abs-max  b = 16   4 MiB +1  0 +5 +2    8 MiB -4 -4 +1 -3   12 MiB -1 -2 +2 -1   14 MiB  0 -1 +3 +2
+//            b = 8    4 MiB  0  0 +9 +7    8 MiB -2 -3 +5 -5   14 MiB +1  0 +5 -4
+//            b = 2    8 MiB -9 -7 +1 -2   12 MiB -14 -15 0 -3
+//   powers of two b = 16  4 MiB -1 -1 +4 +2   8 MiB -3 -3 +2 -2   14 MiB -1 -2 +2 +2
+//   fp32     b = 16   2 MiB  0  0 +5 +6    8 MiB -1 -1 +2 +2;  b = 8  2 MiB +2 +4 +9 +11   8 MiB -1 -3 +4  0
+// Batches follow their sum (4-over-6 b = 16: 8 MiB -5 -5 -1 -7, 14 MiB -3 -2 0 -1, 20 MiB 0 -2 +2 +1).
+template <int DT, int B, bool FOUR6>
 static int sse_past_caches(int64_t n)
 {
     constexpr int64_t kMiB = 1 << 20;
-    const int64_t sse_bytes = n / B * 4, in_bytes = n * (DT == kBF16 ? 2 : 4);
-    const bool past = in_bytes <= 128 * kMiB && (DT == kBF16 ? sse_bytes <= 15 * kMiB : B <= 32 && sse_bytes <= 8 * kMiB);
-    return past ? kSsePastCaches : 0;
+    if (DT != kBF16 || !(FOUR6 || B == 2) || n > 64 * kMiB) return 0;
+    const int64_t sse_bytes = n / B * 4;
+    return (sse_bytes >= 6 * kMiB && sse_bytes <= 15 * kMiB) ? kSsePastCaches : 0;
 }
 
 template <int DT, int B, int FMT, bool FOUR6>
@@ -697,7 +708,7 @@ static hipError_t launch_recipe(const StreamArgs& a, int pz)
     const int workers = (n_slices == 0u) ? 0 : stream_grid(((slices + kItems - 1) / kItems) * kThreads);
     const dim3 grid((unsigned)workers + (tail != 0u ? 1u : 0u)), block(kThreads);
     uint32_t* codes = reinterpret_cast<uint32_t*>(a.codes);
-    const int flags = pz | sse_past_caches<DT, B>(a.n);
+    const int flags = pz | sse_past_caches<DT, B, FOUR6>(a.n);
     if constexpr (DT == kBF16 && FMT != kE8M0) {
         if (takes_scaled_kernel<B, FOUR6>(a, slices, workers)) {
             hipLaunchKernelGGL((stream_scaled_kernel<B, FMT, FOUR6>), grid, block, 0, a.stream, a.x, n_slices, last, tail, a.T,
@@ -783,7 +794,7 @@ static hipError_t launch_batch_recipe(const StreamArgs* t, int count, int pz, hi
         a.tails = tails ? n_t : 0u;
         const int workers = (total == 0u) ? 0 : stream_grid((int64_t)total * kThreads);
         hipLaunchKernelGGL((stream_batch_kernel<DT, B, FMT, FOUR6>), dim3((unsigned)workers + a.tails), dim3(kThreads), 0,
-                           stream, a, pz | sse_past_caches<DT, B>((int64_t)total * kThreads * 8));
+                           stream, a, pz | sse_past_caches<DT, B, FOUR6>((int64_t)total * kThreads * 8));
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
