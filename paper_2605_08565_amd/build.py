@@ -2,8 +2,10 @@
 native calls of the Python binding, host code on torch's C++ interface) with g++."""
 from __future__ import annotations
 
+import hashlib
 import os
 import subprocess
+import sys
 import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
@@ -31,12 +33,25 @@ def _run(cmd, verbose):
         raise RuntimeError("hipcc failed: " + " ".join(cmd))
 
 
+def header_id() -> str:
+    """Identity of include/mxq.h, compiled into both libraries: the native calls take libmxq's functions by address."""
+    with open(os.path.join(os.path.dirname(_HERE), "include", "mxq.h"), "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:16]
+
+
+def calls_abi() -> str:
+    """The interpreter and the torch, to the commit, whose layouts are compiled into _mxq_calls.so."""
+    import torch
+    return f"{sys.implementation.cache_tag} {torch.__version__} {torch.version.git_version}"
+
+
 def _calls_command():
     import torch
     root = os.path.dirname(torch.__file__)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f'-DMXQ_CALLS_ABI="{calls_abi()}"', f'-DMXQ_HEADER_ID="{header_id()}"',
             "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include/torch/csrc/api/include"),
             "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
             os.path.join(CSRC, "binding.cpp"), "-o", CALLS, "-L" + os.path.join(root, "lib"),
@@ -47,7 +62,8 @@ def build_library(verbose: bool = False, jobs: int = 4) -> str:
     """Compiles every translation unit (in parallel), links libmxq.so and builds _mxq_calls.so next to this file."""
     with tempfile.TemporaryDirectory(prefix="mxq_build_") as tmp:
         objs = [os.path.join(tmp, s.replace(".hip", ".o")) for s in SOURCES]
-        cmds = [["hipcc", *FLAGS, "-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objs)]
+        cmds = [["hipcc", *FLAGS, f'-DMXQ_HEADER_ID="{header_id()}"', "-c", os.path.join(CSRC, s), "-o", o]
+                for s, o in zip(SOURCES, objs)]
         with ThreadPoolExecutor(max_workers=max(1, jobs)) as pool:
             list(pool.map(lambda c: _run(c, verbose), cmds + [_calls_command()]))
         _run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-fvisibility=hidden", *objs, "-o", LIB],

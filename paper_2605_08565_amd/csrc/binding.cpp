@@ -350,6 +350,9 @@ PyObject* histogram(PyObject*, PyObject* const* a, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
+// built_for(): what the layouts and signatures compiled in here belong to; mxq.py compares it before use()
+PyObject* built_for(PyObject*, PyObject*) { return Py_BuildValue("(ss)", MXQ_CALLS_ABI, MXQ_HEADER_ID); }
+
 // use(address, ...): the library's functions in the order of the declarations above
 PyObject* use(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
@@ -373,7 +376,7 @@ PyObject* use(PyObject*, PyObject* const* a, Py_ssize_t n)
 #define MXQ_METHOD(f) {#f, (PyCFunction)(void (*)(void))f, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {MXQ_METHOD(quantize), MXQ_METHOD(quantize_hier), MXQ_METHOD(quantize_batch), MXQ_METHOD(tensor_absmax),
                          MXQ_METHOD(dequantize), MXQ_METHOD(clip_sse), MXQ_METHOD(histogram), MXQ_METHOD(use),
-                         {nullptr, nullptr, 0, nullptr}};
+                         {"built_for", built_for, METH_NOARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_mxq_calls", "The calls of mxq.py in native code.", -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

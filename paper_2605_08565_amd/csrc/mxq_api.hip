@@ -291,6 +291,13 @@ float mxq_tensor_scale_from_absmax(float absmax, int elem_fmt, int scale_fmt)
 
 float mxq_scale_decode(int scale_fmt, uint8_t code) { return host_scale_decode(scale_fmt, code); }
 
+// Which mxq.h this library was built from (for the native calls of the Python binding, which check it).
+#ifndef MXQ_HEADER_ID
+#define MXQ_HEADER_ID "unknown"
+#endif
+MXQ_API extern const char mxq_header_id[];
+const char mxq_header_id[] = MXQ_HEADER_ID;
+
 int mxq_num_candidates(int scale_fmt)
 {
     if (scale_fmt == MXQ_SCALE_E8M0) return 255;

@@ -17,6 +17,8 @@ import os
 
 import torch
 
+from .build import calls_abi
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmxq.so")
 
@@ -92,13 +94,20 @@ def lib() -> ctypes.CDLL:
 
 def _native_calls(L: ctypes.CDLL):
     """The module of native calls on the loaded library; None where it has not been built, or was built for
-    another torch: the Python forms then do all the work, 5 us a call slower."""
+    another interpreter, another torch (whose layouts it has compiled in) or another mxq.h than the library's:
+    the Python forms then do all the work, 5 us a call slower."""
     path = os.path.join(_HERE, "_mxq_calls.so")
     try:
         loader = importlib.machinery.ExtensionFileLoader("_mxq_calls", path)
         module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_mxq_calls", path, loader=loader))
         loader.exec_module(module)
     except ImportError:
+        return None
+    try:
+        header = ctypes.string_at(ctypes.addressof(ctypes.c_char.in_dll(L, "mxq_header_id"))).decode()
+    except ValueError:                   # a library from before the check
+        return None
+    if not hasattr(module, "built_for") or module.built_for() != (calls_abi(), header):
         return None
     module.use(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
         L.mxq_quantize, L.mxq_quantize_hier, L.mxq_quantize_batch, L.mxq_tensor_absmax, L.mxq_dequantize,

@@ -1,5 +1,7 @@
 """The native forms of the binding's calls (csrc/binding.cpp) against the Python forms, which define them."""
+import ctypes
 import os
+import subprocess
 
 import pytest
 import torch
@@ -22,6 +24,22 @@ def test_native_calls_are_built_and_decline_what_is_not_plain():
     assert mxq._calls.dequantize(u, u, 16, 1, 1.0, torch.float32, None, 0) is None
     assert mxq._calls.histogram(u, u, 16, 0) is None
     assert mxq._calls.quantize_batch([], 16, 1, 0, True, 0) is None
+
+
+def test_native_calls_of_another_build_are_not_used(tmp_path, monkeypatch):
+    """Layouts of torch and signatures of mxq.h are compiled into the module: neither may differ from what is loaded."""
+    L = mxq.lib()
+    assert mxq._native_calls(L) is not None
+    assert mxq._native_calls(L).built_for() == (mxq.calls_abi(), ctypes.string_at(ctypes.addressof(
+        ctypes.c_char.in_dll(L, "mxq_header_id"))).decode())
+    assert torch.__version__ in mxq.calls_abi() and torch.version.git_version in mxq.calls_abi()
+    for name, text in (("other", 'const char mxq_header_id[] = "0123456789abcdef";'), ("without", "int mxq_nothing;")):
+        (tmp_path / f"{name}.c").write_text(text)
+        so = str(tmp_path / f"{name}.so")
+        subprocess.run(["gcc", "-shared", "-fPIC", str(tmp_path / f"{name}.c"), "-o", so], check=True)
+        assert mxq._native_calls(ctypes.CDLL(so)) is None, name
+    monkeypatch.setattr(mxq, "calls_abi", lambda: "cpython-310 2.9.1 0")
+    assert mxq._native_calls(L) is None
 
 
 def outcome(call):
