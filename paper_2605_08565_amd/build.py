@@ -25,12 +25,15 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hi
 
 
 def _run(cmd, verbose):
-    res = subprocess.run(cmd, capture_output=True, text=True)
+    try:
+        res = subprocess.run(cmd, capture_output=True, text=True)
+    except FileNotFoundError:
+        raise RuntimeError(f"{cmd[0]} is not installed") from None
     if verbose or res.returncode != 0:
         print(res.stdout)
         print(res.stderr)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed: " + " ".join(cmd))
+        raise RuntimeError(f"{cmd[0]} failed: " + " ".join(cmd))
 
 
 def header_id() -> str:
@@ -58,16 +61,30 @@ def _calls_command():
             "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
 
 
+def build_calls(verbose: bool = False) -> str | None:
+    """Builds _mxq_calls.so; None without torch, whose interface it is for (and without which nothing loads it)."""
+    try:
+        cmd = _calls_command()
+    except ImportError:
+        return None
+    _run(cmd, verbose)
+    return CALLS
+
+
 def build_library(verbose: bool = False, jobs: int = 4) -> str:
-    """Compiles every translation unit (in parallel), links libmxq.so and builds _mxq_calls.so next to this file."""
-    with tempfile.TemporaryDirectory(prefix="mxq_build_") as tmp:
+    """Compiles every translation unit (in parallel), links libmxq.so and builds _mxq_calls.so next to this file.
+    The C library needs hipcc only: it is linked before anything that the native calls lack is reported."""
+    with tempfile.TemporaryDirectory(prefix="mxq_build_") as tmp, ThreadPoolExecutor(max_workers=max(1, jobs)) as pool:
         objs = [os.path.join(tmp, s.replace(".hip", ".o")) for s in SOURCES]
         cmds = [["hipcc", *FLAGS, f'-DMXQ_HEADER_ID="{header_id()}"', "-c", os.path.join(CSRC, s), "-o", o]
                 for s, o in zip(SOURCES, objs)]
-        with ThreadPoolExecutor(max_workers=max(1, jobs)) as pool:
-            list(pool.map(lambda c: _run(c, verbose), cmds + [_calls_command()]))
+        units = [pool.submit(_run, c, verbose) for c in cmds]
+        calls = pool.submit(build_calls, verbose)
+        for u in units:
+            u.result()
         _run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-fvisibility=hidden", *objs, "-o", LIB],
              verbose)
+        calls.result()
     return LIB
 
 

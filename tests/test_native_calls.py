@@ -42,6 +42,38 @@ def test_native_calls_of_another_build_are_not_used(tmp_path, monkeypatch):
     assert mxq._native_calls(L) is None
 
 
+@pytest.mark.parametrize("lacking", ["torch", "g++"])
+def test_c_library_is_linked_without_what_the_native_calls_need(monkeypatch, lacking):
+    from paper_2605_08565_amd import build
+
+    ran = []
+
+    def run(cmd, verbose):
+        ran.append(cmd)
+        if cmd[0] == lacking:
+            raise RuntimeError(f"{cmd[0]} failed")
+
+    def no_torch():
+        raise ImportError("No module named 'torch'")
+
+    monkeypatch.setattr(build, "_run", run)
+    if lacking == "torch":
+        monkeypatch.setattr(build, "_calls_command", no_torch)
+        assert build.build_library() == build.LIB
+    else:
+        with pytest.raises(RuntimeError, match=r"^g\+\+ failed"):
+            build.build_library()
+    assert any("-shared" in c and build.LIB in c and c[0] == "hipcc" for c in ran)
+
+
+def test_a_failing_tool_is_named():
+    from paper_2605_08565_amd import build
+
+    for cmd, text in ((["gcc", "-no-such-option"], "^gcc failed"), (["no-such-compiler-here"], "^no-such-compiler-here is not installed")):
+        with pytest.raises(RuntimeError, match=text):
+            build._run(cmd, False)
+
+
 def outcome(call):
     """What a call gives: its tensors (bit patterns), or the type and text of its error."""
     def flat(r):
