@@ -257,14 +257,47 @@ MXQ_HD bool lean_division_exact(uint32_t mantissa, float T, float rT, Recip r)
     return quot(x, r) == div_by_T(x, T, rT);
 }
 
-// The bf16 value nearest to (t*d)*T, and whether it is close enough to matter.  (What is tried then: the
-// truncated product lies on the same side of t as fl(x/T) does of t*d, a quotient AT t counting as up
-// where the even code lies above.)
+// The bf16 value nearest to (t*d)*T, and whether it is close enough to matter.
 MXQ_HD bool lean_quotient_candidate(float td, float T, float& x)
 {
     const float p = td * T;
     x = u2f((f2u(p) + 0x8000u) & 0xFFFF0000u);
     return __builtin_fabsf(x - p) <= p * 0x1p-20f;
+}
+
+// The 32 pairs of a scale mantissa d (index & 7) and a mid-point mantissa t.  The even code lies above the mid-points
+// .75 and 1.75: a quotient AT them goes up, so they are represented by the float below.
+struct __attribute__((aligned(16))) LeanPair { float td, rd, y_at, v_at; };
+struct LeanPairs { LeanPair of[32]; };
+constexpr LeanPairs make_lean_pairs()
+{
+    LeanPairs p{};
+    for (int i = 0; i < 32; ++i) {
+        const float d = 1.0f + 0.125f * (float)(i & 7), t = 1.0f + 0.25f * (float)(i >> 3);
+        const uint32_t below = (i >> 3) >= 2 ? 1u : 0u;
+        p.of[i] = LeanPair{t * d, 1.0f / d, __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, t) - below),
+                           __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, t * d) - below)};
+    }
+    return p;
+}
+
+MXQ_HD float float_above(float positive) { return u2f(f2u(positive) + 1u); }
+
+// What is tried for a candidate: its truncated product y lies on the same side of t as v = fl(x/T) does of t*d.
+MXQ_HD bool lean_decides(LeanPair pair, float v, float y) { return (y > pair.y_at) == (v > pair.v_at); }
+
+// Bits of the 32 pairs -> of the 8 scale mantissas: the four mid-points of a scale mantissa together.
+MXQ_HD uint32_t lean_of_mantissas(uint32_t pairs)
+{
+    return (pairs | (pairs >> 8) | (pairs >> 16) | (pairs >> 24)) & 0xFFu;
+}
+
+// The reciprocal that scale value S takes: bit i of `above` set, the one above the nearest for the mantissa 1 + i/8.
+// Code 0 (S = 0) keeps its zero.
+MXQ_HD float lean_reciprocal(float S, float nearest, uint32_t above)
+{
+    const uint32_t up = (S == 0.0f) ? 0u : (above >> ((f2u(S) >> 20) & 7u)) & 1u;
+    return u2f(f2u(nearest) + up);
 }
 
 // Per-tensor scale of hierarchical scaling (Section 2, two-stage process) from the tensor

@@ -118,8 +118,7 @@ template <int FMT>
 __device__ __forceinline__ void fill_scale_table(ScalePair* tab, uint32_t above)
 {
     ScalePair e = kScaleTable<FMT, ScalePair>.of[threadIdx.x];
-    const uint32_t up = (threadIdx.x == 0u) ? 0u : (above >> ((f2u(e.S) >> 20) & 7u)) & 1u;
-    e.r = u2f(f2u(e.r) + up);
+    e.r = lean_reciprocal(e.S, e.r, above);
     tab[threadIdx.x] = e;
     __syncthreads();
 }
@@ -152,26 +151,11 @@ __device__ __forceinline__ void quot8_truncated(const float (&v)[8], const float
           "v"(r0), "v"(r1), "v"(r2), "v"(r3));
 }
 
-// One of the 32 pairs of a scale mantissa d and a mid-point mantissa t that lean_T looks at.  The even code lies
-// above the mid-points .75 and 1.75: a quotient AT them goes up, so they are represented by the float below.
-struct __align__(16) LeanPair { float td, rd, y_at, v_at; };
-struct LeanPairs { LeanPair of[32]; };
-constexpr LeanPairs make_lean_pairs()
-{
-    LeanPairs p{};
-    for (int i = 0; i < 32; ++i) {
-        const float d = 1.0f + 0.125f * (float)(i & 7), t = 1.0f + 0.25f * (float)(i >> 3);
-        const uint32_t below = (i >> 3) >= 2 ? 1u : 0u;
-        p.of[i] = LeanPair{t * d, 1.0f / d, __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, t) - below),
-                           __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, t * d) - below)};
-    }
-    return p;
-}
 static __device__ constexpr LeanPairs kLeanPairs = make_lean_pairs();
 
 // Whether both shorter sequences are exact for every bf16 input under this T: two mantissas and one of the 32
 // pairs in every lane, so that no wavefront waits for another.  Bit i of `above`: the scale mantissa 1 + i/8
-// takes the reciprocal above the nearest one.
+// takes the reciprocal above the nearest one.  (All but the rounding mode and the ballots is in mxq_arith.hpp.)
 __device__ __forceinline__ bool lean_T(LeanPair pair, float T, float rT, Recip r, uint32_t& above)
 {
     const uint32_t lane = threadIdx.x & 63u;
@@ -183,15 +167,11 @@ __device__ __forceinline__ bool lean_T(LeanPair pair, float T, float rT, Recip r
         "v_mul_f32 %0, %2, %3\n\t"
         "v_mul_f32 %1, %2, %4\n\t"
         "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 0"
-        : "=&v"(y), "=&v"(y_above) : "v"(v), "v"(pair.rd), "v"(u2f(f2u(pair.rd) + 1u)));
-    const bool up = v > pair.v_at;
+        : "=&v"(y), "=&v"(y_above) : "v"(v), "v"(pair.rd), "v"(float_above(pair.rd)));
     const bool divides = lean_division_exact(lane, T, rT, r) && lean_division_exact(lane + 64u, T, rT, r);
-    auto of_mantissa = [](bool bad) {                                   // the four mid-points of a scale mantissa together
-        const uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64(bad);
-        return (m | (m >> 8) | (m >> 16) | (m >> 24)) & 0xFFu;
-    };
-    above = of_mantissa(near && (y > pair.y_at) != up);
-    return (above & of_mantissa(near && (y_above > pair.y_at) != up)) == 0u && __builtin_amdgcn_ballot_w64(!divides) == 0ull;
+    above = lean_of_mantissas((uint32_t)__builtin_amdgcn_ballot_w64(near && !lean_decides(pair, v, y)));
+    const uint32_t above_fails = lean_of_mantissas((uint32_t)__builtin_amdgcn_ballot_w64(near && !lean_decides(pair, v, y_above)));
+    return (above & above_fails) == 0u && __builtin_amdgcn_ballot_w64(!divides) == 0ull;
 }
 
 // ---------------------------------------------------------------------------------------

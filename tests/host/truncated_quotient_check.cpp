@@ -37,7 +37,9 @@ static void bf16_values(void)
     printf("bf16_values cases=%ld bad=%ld\n", n, bad);
 }
 
-/* lean_T of mxq_device.hpp, lane by lane: 0 no, 1 yes, and which scale mantissas take the reciprocal above */
+/* lean_T of mxq_device.hpp with the ballots and the rounding mode spelt out: 0 no, 1 yes, and which scale mantissas
+ * take the reciprocal above */
+static const mxq::LeanPairs kPairs = mxq::make_lean_pairs();
 static int lean(float T, mxq::Recip r, uint32_t* above)
 {
     const float rT = 1.0f / T;
@@ -45,17 +47,15 @@ static int lean(float T, mxq::Recip r, uint32_t* above)
     for (uint32_t m = 0; m < 128; ++m)
         if (!mxq::lean_division_exact(m, T, rT, r)) return 0;
     for (int i = 0; i < 32; ++i) {
-        const float d = 1.0f + 0.125f * (i & 7), t = 1.0f + 0.25f * (i >> 3), rd = 1.0f / d;
+        const mxq::LeanPair pair = kPairs.of[i];
         float x;
-        if (!mxq::lean_quotient_candidate(t * d, T, x)) continue;
+        if (!mxq::lean_quotient_candidate(pair.td, T, x)) continue;
         const float v = mxq::div_by_T(x, T, rT);
-        const float y = mxq::quot_truncated(v, rd), z = mxq::quot_truncated(v, mxq::u2f(mxq::f2u(rd) + 1u));
-        const bool up = (i >> 3) >= 2 ? v >= t * d : v > t * d;
-        near_bad |= (uint32_t)(((i >> 3) >= 2 ? y >= t : y > t) != up) << (i & 7);
-        above_bad |= (uint32_t)(((i >> 3) >= 2 ? z >= t : z > t) != up) << (i & 7);
+        near_bad |= (uint32_t)!mxq::lean_decides(pair, v, mxq::quot_truncated(v, pair.rd)) << i;
+        above_bad |= (uint32_t)!mxq::lean_decides(pair, v, mxq::quot_truncated(v, mxq::float_above(pair.rd))) << i;
     }
-    *above = near_bad;
-    return (near_bad & above_bad) == 0;
+    *above = mxq::lean_of_mantissas(near_bad);
+    return (*above & mxq::lean_of_mantissas(above_bad)) == 0;
 }
 
 /* For every T that lean() accepts: quotient by T and decision under every scale mantissa, for every bf16
@@ -72,7 +72,7 @@ static void tensor_scale(float T)
             const float v = mxq::quot(x, r), w = x / T;
             g_bad += v != w || mxq::quot(-x, r) != -w;
             for (int i = 0; i < 8; ++i) {
-                const float S = 1.0f + 0.125f * i, rS = mxq::u2f(mxq::f2u(1.0f / S) + ((above >> i) & 1u));
+                const float S = 1.0f + 0.125f * i, rS = mxq::lean_reciprocal(S, 1.0f / S, above);
                 const float y = mxq::quot_truncated(v, rS);
                 ++g_n;
                 g_bad += index_of(y, 1.0) != index_of(v, S) || mxq::quot_truncated(-v, rS) != -y;
