@@ -68,7 +68,8 @@ def test_ties_of_every_scale_code(oracle, fmt, block):
 def test_tensor_scales_of_large_bf16_tensors(oracle, fmt, block):
     """Four tiles and a rest for every workgroup (n not a multiple of 8 for b = 2 and 4), so that the kernel for
     scaled bf16 runs: an abs-max whose tensor scale takes reciprocals from above (249), one whose scale is refused (228), an ordinary one, scales
-    by value inside and outside the range that is tried, and one with an all-ones mantissa.  Bits: no tolerance."""
+    by value inside and outside the range that is tried, and one with an all-ones mantissa.  Rows of every tile against the
+    oracle, the whole tensor against its pieces, which are small enough for the general kernel.  Bits: no tolerance."""
     from paper_2605_08565_amd import mxq
 
     rng = np.random.default_rng(7 * block + fmt)
@@ -76,7 +77,15 @@ def test_tensor_scales_of_large_bf16_tensors(oracle, fmt, block):
     rows = (4 * 2048 * 2048 + 5 * 2048) // cols + 1
     x = (rng.standard_normal(rows * cols, dtype=np.float32) * np.repeat(np.float32([1.0, 40.0]), [rows * cols // 2, rows * cols - rows * cols // 2]))
     x = W.f32_to_bf16_bits(np.clip(x, -200, 200)).reshape(rows, cols)
-    part = np.r_[0:40, rows // 2 - 40:rows // 2 + 40, rows - 40:rows]   # rows that are compared
+    # rows that are compared with the oracle: around the planted abs-max, and those of whole slices of 2048 elements, which
+    # the 2048 workgroups take in turn, from every tile
+    per_slice = -(-2048 // cols) + 1
+    slices = [2048 * k + j for k in range(5) for j in ((0, 700, 2047) if k < 4 else (0, 4))]
+    part = np.unique(np.r_[0:20, rows // 2 - 20:rows // 2 + 20, rows - 20:rows,
+                           np.concatenate([np.arange(per_slice) + s * 2048 // cols for s in slices]).clip(max=rows - 1)])
+    covered = {s for s in slices if set(range(s * 2048 // cols, -(-(s + 1) * 2048 // cols))) <= set(part.tolist())}
+    assert covered == set(slices)
+    cuts = list(range(0, rows, 2048 * 2000 // cols // 16 * 16)) + [rows]             # of at most 2000 slices
     for top in (249.0, 228.0, 225.0):
         x[rows // 2, 3] = W.f32_to_bf16_bits(np.float32([-top]))[0]
         gx = mxq.from_bits(x)
@@ -94,6 +103,9 @@ def test_tensor_scales_of_large_bf16_tensors(oracle, fmt, block):
             for g, r in zip(got[:3], want):
                 g = g.cpu().numpy()[part]
                 assert (g.view(np.uint32) == r.view(np.uint32)).all() if g.dtype == np.float32 else (g == r).all(), (top, t, rec, g.dtype)
+            pieces = [mxq.quantize(gx[a:b], block, fmt, rec, tensor_scale=t) for a, b in zip(cuts, cuts[1:])]
+            for i in range(3):
+                assert torch.equal(got[i].view(torch.uint8), torch.cat([p[i] for p in pieces]).view(torch.uint8)), (top, t, rec, i)
             if len(got) == 4:
                 assert float(got[3].cpu()[0]) == t
 
