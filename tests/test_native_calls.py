@@ -160,3 +160,78 @@ def test_native_and_python_forms_agree(monkeypatch, where):
     for k in calls:
         assert native[k] == python[k], k
     assert native["quantize"][0] is tuple and native["misaligned"][0] is mxq.MxqError and native["strided"][0] is ValueError
+
+
+def native_calls(x, word, codes, scales):
+    """One plain call of each native form, outputs allocated there: name -> (call, the Python call it stands for)."""
+    c = mxq._calls
+    return {
+        "quantize": (lambda: c.quantize(x, 16, 1, 2, 1.0, None, None, None, True, 0), lambda: mxq.quantize(x, 16, 1, 2)),
+        "quantize_hier": (lambda: c.quantize_hier(x, 16, 1, 2, word, None, None, None, None, True, 0),
+                          lambda: mxq.quantize_hier(x, 16, 1, 2, word)),
+        "quantize_batch": (lambda: c.quantize_batch([x, x], 32, 2, 0, True, 0), lambda: mxq.quantize_batch([x, x], 32, 2, 0)),
+        "tensor_absmax": (lambda: c.tensor_absmax(x, None), lambda: mxq.tensor_absmax(x)),
+        "dequantize": (lambda: c.dequantize(codes, scales, 16, 1, 1.0, torch.bfloat16, None, 0),
+                       lambda: mxq.dequantize(codes, scales, 16, 1, 1.0, torch.bfloat16)),
+        "clip_sse": (lambda: c.clip_sse(x, scales, 16, 1, 1.0, None, 0), lambda: mxq.clip_sse(x, scales, 16, 1)),
+        "histogram": (lambda: c.histogram(codes, scales, 16, 0), lambda: mxq.histogram(codes, scales, 16)),
+    }
+
+
+@pytest.mark.gpu
+def test_native_forms_take_plain_calls_and_decline_under_modes():
+    from torch.overrides import TorchFunctionMode
+
+    mxq.lib()
+    x = torch.randn((64, 1024), device="cuda").to(torch.bfloat16)
+    word = mxq.tensor_absmax(x)
+    codes, scales, _ = mxq.quantize(x, 16, 1, 2)
+    calls = native_calls(x, word, codes, scales)
+    for name, (native, _) in calls.items():
+        assert native() is not None, name
+    with TorchFunctionMode():
+        for name, (native, _) in calls.items():
+            assert native() is None, name
+    torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+def test_native_forms_in_a_captured_graph(monkeypatch):
+    """Captured, a call is recorded only if it goes to the current stream; replayed on new contents it must give what the
+    Python form gives on them, with eager work and synchronisation in between."""
+    mxq.lib()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    x = torch.randn((64, 1024), generator=gen, device="cuda").to(torch.bfloat16)
+    word = mxq.tensor_absmax(x)
+    codes, scales, _ = mxq.quantize(x, 16, 1, 2)
+    calls = native_calls(x, word, codes, scales)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):                                       # warm-up outside capture
+        for native, _ in calls.values():
+            native()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        captured = {name: native() for name, (native, _) in calls.items()}
+    assert all(r is not None for r in captured.values())
+    with monkeypatch.context() as m:
+        m.setattr(mxq, "_calls", None)
+
+        def flat(r):
+            return [r] if isinstance(r, torch.Tensor) else [t for i in r for t in flat(i)]
+
+        for seed in range(4):
+            gen.manual_seed(100 + seed)
+            x.copy_(torch.randn(x.shape, generator=gen, device="cuda") * (seed + 1))
+            word.copy_(x.abs().max().reshape(1))
+            for t, new in zip((codes, scales), mxq.quantize(x, 16, 1, 3)):
+                t.copy_(new)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for name, (_, python) in calls.items():
+                for g, w in zip(flat(captured[name]), flat(python())):
+                    assert torch.equal(g.view(torch.uint8), w.view(torch.uint8)), (seed, name)
