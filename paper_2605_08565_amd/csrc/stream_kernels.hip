@@ -300,6 +300,10 @@ __device__ __forceinline__ void store_slice(const TileOut<B>& o, uint32_t s, Sli
 template <int DT, int TMODE>
 using TableEntry = std::conditional_t<DT == kBF16 && TMODE == kNoT, ScalePair, ScaleEntry>;
 
+// Whether a kernel forms its table or copies it (fill_scale_table).
+template <int DT, int TMODE>
+constexpr bool kFormTable = DT == kF32 || TMODE == kNoT;
+
 // A workgroup tile is kItems consecutive slices; every lane owns one chunk of each slice.
 constexpr int kItems = MXQ_STREAM_ITEMS;
 
@@ -445,7 +449,7 @@ stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunk
     const float rT = 1.0f / T;                                       // correctly rounded
     if constexpr (B < 8) {
         if (tail != 0u && blockIdx.x == workers) {
-            if constexpr (FMT != kE8M0) fill_scale_table<FMT>(tab);
+            if constexpr (FMT != kE8M0) fill_scale_table<FMT, kFormTable<DT, TMODE>>(tab);
             stream_tail<DT, B, FMT, FOUR6, TMODE, CLIP>(x, sl.elements(), tail, T, rT, tdyn, (flags & kPreventZero) != 0, tab,
                                                         reinterpret_cast<uint8_t*>(codes), scales, sse_out, clip_out);
             return;
@@ -457,7 +461,7 @@ stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunk
 #pragma unroll
     for (int i = 0; i < kItems; ++i) first[i] = RawChunk<DT>{};
     load_tile<DT>(first, x, s0, sl);                                 // in flight while the scale table is built
-    if constexpr (FMT != kE8M0) fill_scale_table<FMT>(tab);
+    if constexpr (FMT != kE8M0) fill_scale_table<FMT, kFormTable<DT, TMODE>>(tab);
     stream_tiles<DT, B, FMT, FOUR6, TMODE, CLIP>(first, x, s0, stride, sl, T, rT, tdyn, flags, tab, wave_lds, codes, scales,
                                                  sse_out, clip_out);
 }
@@ -535,7 +539,7 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
         if constexpr (kEarly) load_tile<kBF16>(first, x, s0, sl);
     }
     const int tdyn = (T == 1.0f) ? kNoT : (fast_division_ok(T) ? kFastT : kSlowT);
-    fill_scale_table<FMT>(tab);
+    fill_scale_table<FMT, kFormTable<kBF16, kDynT>>(tab);
     if constexpr (B < 8) {
         if (s0 == stride) {
             stream_tail<kBF16, B, FMT, FOUR6, kDynT, false>(x, sl.elements(), tail, T, rT, tdyn, (flags & kPreventZero) != 0, tab,
@@ -628,7 +632,7 @@ stream_batch_kernel(const BatchArgs a, int flags)
         if (g >= stride) {
             const uint32_t t = g - stride;
             if (a.tail[t] == 0u) return;
-            if constexpr (FMT != kE8M0) fill_scale_table<FMT>(tab);
+            if constexpr (FMT != kE8M0) fill_scale_table<FMT, kFormTable<DT, kNoT>>(tab);
             stream_tail<DT, B, FMT, FOUR6, kNoT, false>(a.x[t], Slices{a.first[t + 1] - a.first[t], a.last[t]}.elements(),
                                                         a.tail[t], 1.0f, 1.0f, kNoT, (flags & kPreventZero) != 0, tab,
                                                         reinterpret_cast<uint8_t*>(a.codes[t]), a.scales[t], a.sse[t], nullptr);
@@ -642,7 +646,7 @@ stream_batch_kernel(const BatchArgs a, int flags)
     bufB[0] = RawChunk<DT>{};
     TileRef cur = locate(a, g), prev = cur, next = cur;
     load_tile<DT>(bufA, a.x[cur.t], cur.s, cur.sl);
-    if constexpr (FMT != kE8M0) fill_scale_table<FMT>(tab);
+    if constexpr (FMT != kE8M0) fill_scale_table<FMT, kFormTable<DT, kNoT>>(tab);
     TileOut<B> out[kItems];
     bool have_prev = false;
     while (true) {
