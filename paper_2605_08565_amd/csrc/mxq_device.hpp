@@ -147,9 +147,9 @@ __device__ __forceinline__ void fill_scale_table(ScalePair* tab, uint32_t above)
 // 16 instructions of quot().  The rounding mode of the wavefront's fp32 arithmetic is switched inside one asm
 // block, so that no other instruction can get between.  Two writes of the mode register have to be two wait states
 // apart, and the compiler, which sees to that between its own, does not look into asm: each block brings them
-// (s_nop 1), whatever write lies before it.  4-over-6 on 4096 x 14336 bf16, with the half as
-// large table entries that go with it: b = 32 31.4 -> 30.4 us, b = 8 32.3 -> 31.6; UE5M3 b = 16 33.2 -> 31.6, b = 2
-// 59.1 -> 56.1.
+// (s_nop 1), whatever write lies before it.  Two-part product -> this with its half as large table entries, 4-over-6 on
+// 4096 x 14336 bf16: b = 16 30.9 -> 29.8 us, 32 30.8 -> 28.9, 64 31.5 -> 29.3; UE5M3 b = 16 32.1 -> 29.7, b = 2 58.6 ->
+// 55.6; b = 8 32.2 -> 32.0 (bound by memory).
 template <int NBLK>
 __device__ __forceinline__ void quot8_truncated(const float (&v)[8], const float (&r)[NBLK], float (&y)[8])
 {

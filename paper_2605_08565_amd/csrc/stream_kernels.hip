@@ -479,10 +479,10 @@ stream_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunk
 // prefetch.  General kernel -> this one for such a T: 2048 x 4096 4-over-6 b = 16 7.00 -> 7.24 us, b = 64 7.02 -> 7.53;
 // 4096 x 4096 4-over-6 b = 16 12.1 -> 12.1, abs-max 9.9 -> 10.1; 8192 x 4096 4-over-6 b = 16 22.2 -> 21.5, abs-max 17.6
 // -> 17.9; 4-over-6 b = 2 33.9 -> 36.8.  (With the first tile loaded a second time 7.60, 7.87, 12.5, 10.5, 21.8, 18.3.)
-// General kernel -> this one, T from device memory, E4M3: 4096 x 8192 4-over-6 b = 16 23.0 -> 21.1 us, b = 64 22.7
-// -> 20.4, b = 4 27.2 -> 24.8, abs-max b = 16 19.0 -> 18.2.
+// General kernel -> this one, T from device memory, E4M3: 8192 x 4096 4-over-6 b = 16 22.1 -> 20.5 us, b = 64 22.3
+// -> 20.5, b = 4 26.6 -> 24.2, b = 2 33.2 -> 32.1, abs-max b = 16 18.3 -> 17.9; 14336 x 4096 4-over-6 b = 16 35.6 -> 32.6.
 // With fewer tiles a workgroup than these the test of T costs what it saves (two tiles, 2048 x 4096: 4-over-6
-// b = 16, T from the device 7.5 -> 7.1 us, by value b = 4 8.6 -> 9.2, abs-max b = 16 6.2 -> 6.7).  The abs-max recipes
+// b = 16, T from the device 7.3 -> 7.1 us, by value b = 4 8.6 -> 9.2, abs-max b = 16 6.2 -> 6.7).  The abs-max recipes
 // with b < 16 are bound by memory, and by value, where no wavefront has to derive T, they are 1 to 2 % faster
 // in the general kernel while that has the short division.
 constexpr int64_t kScaledTiles = 4, kScaledTilesFour6 = 2, kScaledTilesFour6ByValue = 3;
