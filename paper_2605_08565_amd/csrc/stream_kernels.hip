@@ -496,6 +496,24 @@ static bool takes_scaled_kernel(const StreamArgs& a, int64_t slices, int64_t wor
     return slices >= (FOUR6 ? kScaledTilesFour6ByValue : kScaledTiles) * workers;
 }
 
+// The wavefront's chunks the general way in a plain loop: few registers, no prefetch, and no barrier with a table in memory.
+template <int B, int FMT, bool FOUR6>
+__device__ __forceinline__ void general_tiles(const void* __restrict__ x, uint32_t s0, uint32_t stride, Slices sl, float T, float rT,
+                                              int tdyn, int flags, const ScaleEntry* tab, uint32_t* __restrict__ codes,
+                                              uint8_t* __restrict__ scales, float* __restrict__ sse_out)
+{
+#pragma unroll 1
+    for (; s0 < sl.count; s0 += stride) {                            // uniform
+        RawChunk<kBF16> raw[kItems];
+        load_tile<kBF16>(raw, x, s0, sl);
+        float v[8];
+        widen<kBF16>(raw[0], v, nullptr);
+        TileOut<B> o;
+        process_chunk<B, FMT, FOUR6, kDynT, false>(v, T, rT, tdyn, (flags & kPreventZero) != 0, tab, o.packed, o.code, o.sse, o.clip);
+        store_slice<B, kMayPass<kBF16, B, FOUR6, false>>(o, s0, sl, flags, codes, scales, sse_out, nullptr);
+    }
+}
+
 template <int B, int FMT, bool FOUR6>
 __global__ void __launch_bounds__(kThreads)
 stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunks, uint32_t tail, float T_arg, int flags,
@@ -506,7 +524,7 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
     __shared__ ScaleEntry tab[256];
     __shared__ uint32_t again;
     const Slices sl{n_slices, last_chunks};
-    uint32_t s0 = blockIdx.x;
+    const uint32_t s0 = blockIdx.x;
     // The first tile's loads are in flight while T is looked at, and both parts of 1/T live in vector registers
     // (an instruction with a scalar operand costs more): not where the 64 registers that eight wavefronts a
     // SIMD leave for each do not hold them.
@@ -520,12 +538,13 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
     if (absmax_dev) T = tensor_scale_of<FMT>(*absmax_dev);
     if (t_out && blockIdx.x == 0 && threadIdx.x == 0) *t_out = T;
     const float rT = 1.0f / T;                                       // correctly rounded
+    const int tdyn = (T == 1.0f) ? kNoT : (fast_division_ok(T) ? kFastT : kSlowT);
     Recip r = lean_recip(T);
     uint32_t above = 0u;
     if (s0 < stride && lean_T_in_range(T) && lean_T(pair, T, rT, r, above)) {     // uniform: every wavefront finds the same
         if constexpr (!kEarly) load_tile<kBF16>(first, x, s0, sl);
         ScalePair* pairs = reinterpret_cast<ScalePair*>(tab);
-        again = 0u;
+        if constexpr (!kEarly) again = 0u;
         fill_scale_table<FMT>(pairs, above);
         if constexpr (kEarly) {
             asm volatile("" : "+v"(r.hi), "+v"(r.lo));
@@ -537,14 +556,20 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
             stream_tiles<kBF16, B, FMT, FOUR6, kLeanT, false>(first, x, s0, stride, sl, r.hi, r.lo, kLeanT, flags, pairs,
                                                               (u32x4*)nullptr, codes, scales, sse_out, (float*)nullptr);
         // An element that is not finite, or is not any more after the division, leaves such an SSE, and the general way
-        // may see it otherwise (div_by_T makes a NaN of an infinity, with a sign of its own): the workgroup goes that way
-        // too, so that the outputs of a row do not depend on the size of its tensor.
-        if (largest_sse >= 0x7F800000u) again = 1u;
+        // may see it otherwise (div_by_T makes a NaN of an infinity, with a sign of its own): the wavefront goes that way
+        // too, so that the outputs of a row do not depend on the size of its tensor.  (The whole workgroup, with a
+        // barrier, takes 1 to 2 % longer on all tensors: 8192 x 4096 4-over-6 b = 16 20.1 us against 19.7, 14336 x 4096 32.5
+        // against 31.7.  With b = 2 it saves the registers of a second copy of the code.)
+        const bool bad = __builtin_amdgcn_ballot_w64(largest_sse >= 0x7F800000u) != 0ull;
+        if constexpr (kEarly) {
+            if (bad)                                                 // rare
+                general_tiles<B, FMT, FOUR6>(x, s0, stride, sl, T, rT, tdyn, flags, kScaleTable<FMT, ScaleEntry>.of, codes, scales, sse_out);
+            return;
+        }
+        if (bad) again = 1u;
         __syncthreads();
         if (again == 0u) return;                                     // uniform
-        if constexpr (kEarly) load_tile<kBF16>(first, x, s0, sl);
     }
-    const int tdyn = (T == 1.0f) ? kNoT : (fast_division_ok(T) ? kFastT : kSlowT);
     fill_scale_table<FMT, kFormTable<kBF16, kDynT>>(tab);
     if constexpr (B < 8) {
         if (s0 == stride) {
@@ -553,20 +578,11 @@ stream_scaled_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t las
             return;
         }
     }
-    if constexpr (kEarly) {
+    if constexpr (kEarly)
         stream_tiles<kBF16, B, FMT, FOUR6, kDynT, false>(first, x, s0, stride, sl, T, rT, tdyn, flags, tab, (u32x4*)nullptr,
                                                          codes, scales, sse_out, (float*)nullptr);
-    } else {
-#pragma unroll 1
-        for (; s0 < sl.count; s0 += stride) {                        // uniform
-            load_tile<kBF16>(first, x, s0, sl);
-            float v[8];
-            widen<kBF16>(first[0], v, nullptr);
-            TileOut<B> o;
-            process_chunk<B, FMT, FOUR6, kDynT, false>(v, T, rT, tdyn, (flags & kPreventZero) != 0, tab, o.packed, o.code, o.sse, o.clip);
-            store_slice<B, kMayPass<kBF16, B, FOUR6, false>>(o, s0, sl, flags, codes, scales, sse_out, nullptr);
-        }
-    }
+    else
+        general_tiles<B, FMT, FOUR6>(x, s0, stride, sl, T, rT, tdyn, flags, tab, codes, scales, sse_out);
 }
 
 // ---------------------------------------------------------------------------------------

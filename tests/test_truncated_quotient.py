@@ -143,7 +143,9 @@ def test_infinities_of_large_bf16_tensors(fmt, block):
 @pytest.mark.parametrize("block", [2, 4, 8, 16, 128])
 def test_elements_that_are_not_finite_do_not_depend_on_the_size(fmt, block):
     """Infinities, NaNs of both signs and finite elements whose quotient by T overflows: the same bytes in a tensor of many
-    tiles (kernel for scaled bf16) as in one of three rows (general kernel).  A row is eight wavefronts in both."""
+    tiles (kernel for scaled bf16) as in one of three rows (general kernel).  A row is eight wavefronts in both.  (An SSE
+    that is a NaN need only be one: which of two NaNs their sum is depends on the order of its operands, which the
+    compiler is free to choose.)"""
     from paper_2605_08565_amd import mxq
 
     cols, rows = 4096, 4 * 2048 * 2048 // 4096 + 3
@@ -166,4 +168,7 @@ def test_elements_that_are_not_finite_do_not_depend_on_the_size(fmt, block):
         got, want = call(x), call(small)
         for g, w in zip(got[:3], want[:3]):
             g = torch.stack([g[j] for j in special])
-            assert torch.equal(g.view(torch.uint8), w.view(torch.uint8)), (i, g.dtype, int((g.view(torch.uint8) != w.view(torch.uint8)).sum()))
+            same = g == w
+            if g.dtype == torch.float32:
+                same = (g.view(torch.int32) == w.view(torch.int32)) | (g.isnan() & w.isnan())
+            assert bool(same.all()), (i, g.dtype, int((~same).sum()))
