@@ -246,8 +246,8 @@ enum : int { kPreventZero = 1, kSsePastCaches = 2 };
 // buffer, finds nothing there.  (The two asm comments keep the compiler from making one store of both.)
 // Only the kernels that sse_past_caches may send there have the choice (kMayPass): it costs the others 1 % (fp32
 // b = 16 1024 x 4096 5.04 -> 4.92 us, 4096 x 14336 50.4 -> 50.2; bf16 abs-max b = 16 512 x 4096 2.98 -> 2.91).
-template <int DT, int B, bool FOUR6, bool CLIP>
-constexpr bool kMayPass = DT == kBF16 && (FOUR6 || B == 2) && !CLIP;
+template <int DT, int B, bool FOUR6, int TMODE, bool CLIP>
+constexpr bool kMayPass = DT == kBF16 && (FOUR6 || B == 2 || TMODE == kDynT || TMODE == kLeanT) && !CLIP;
 
 template <bool MAY_PASS, class V>
 __device__ __forceinline__ void store_sse(V* p, V v, int flags)
@@ -350,7 +350,7 @@ __device__ __forceinline__ void stream_step(RawChunk<DT> (&cur)[kItems], RawChun
     if (have_prev) {                                                 // uniform
 #pragma unroll
         for (int i = 0; i < kItems; ++i)
-            store_slice<B, kMayPass<DT, B, FOUR6, CLIP>>(out[i], s_prev + (uint32_t)i, sl, flags, codes, scales, sse_out, CLIP ? clip_out : nullptr);
+            store_slice<B, kMayPass<DT, B, FOUR6, TMODE, CLIP>>(out[i], s_prev + (uint32_t)i, sl, flags, codes, scales, sse_out, CLIP ? clip_out : nullptr);
     }
     if (s0 + stride < sl.count) load_tile<DT>(nxt, x, s0 + stride, sl);            // uniform
     __builtin_amdgcn_sched_barrier(0);
@@ -422,7 +422,7 @@ __device__ __forceinline__ uint32_t stream_tiles(RawChunk<DT> (&bufA)[kItems], c
     }
 #pragma unroll
     for (int i = 0; i < kItems; ++i)
-        store_slice<B, kMayPass<DT, B, FOUR6, CLIP>>(out[i], s_prev + (uint32_t)i, sl, flags, codes, scales, sse_out, CLIP ? clip_out : nullptr);
+        store_slice<B, kMayPass<DT, B, FOUR6, TMODE, CLIP>>(out[i], s_prev + (uint32_t)i, sl, flags, codes, scales, sse_out, CLIP ? clip_out : nullptr);
     return largest_sse;
 }
 
@@ -510,7 +510,7 @@ __device__ __forceinline__ void general_tiles(const void* __restrict__ x, uint32
         widen<kBF16>(raw[0], v, nullptr);
         TileOut<B> o;
         process_chunk<B, FMT, FOUR6, kDynT, false>(v, T, rT, tdyn, (flags & kPreventZero) != 0, tab, o.packed, o.code, o.sse, o.clip);
-        store_slice<B, kMayPass<kBF16, B, FOUR6, false>>(o, s0, sl, flags, codes, scales, sse_out, nullptr);
+        store_slice<B, kMayPass<kBF16, B, FOUR6, kDynT, false>>(o, s0, sl, flags, codes, scales, sse_out, nullptr);
     }
 }
 
@@ -629,7 +629,7 @@ __device__ __forceinline__ void batch_step(RawChunk<DT> (&cur)[kItems], RawChunk
     widen<DT>(cur[0], v, wave_lds);
     __builtin_amdgcn_sched_barrier(0);
     if (have_prev)                                                   // uniform
-        store_slice<B, kMayPass<DT, B, FOUR6, false>>(out[0], prev.s, prev.sl, flags, a.codes[prev.t], a.scales[prev.t], a.sse[prev.t], nullptr);
+        store_slice<B, kMayPass<DT, B, FOUR6, kNoT, false>>(out[0], prev.s, prev.sl, flags, a.codes[prev.t], a.scales[prev.t], a.sse[prev.t], nullptr);
     if (have_next) load_tile<DT>(nxt, a.x[next.t], next.s, next.sl); // uniform
     __builtin_amdgcn_sched_barrier(0);
     process_chunk<B, FMT, FOUR6, kNoT, false>(v, 1.0f, 1.0f, kNoT, (flags & kPreventZero) != 0, tab, out[0].packed, out[0].code, out[0].sse,
@@ -688,16 +688,17 @@ stream_batch_kernel(const BatchArgs a, int flags)
         cur = next;
         g += stride;
     }
-    store_slice<B, kMayPass<DT, B, FOUR6, false>>(out[0], prev.s, prev.sl, flags, a.codes[prev.t], a.scales[prev.t], a.sse[prev.t], nullptr);
+    store_slice<B, kMayPass<DT, B, FOUR6, kNoT, false>>(out[0], prev.s, prev.sl, flags, a.codes[prev.t], a.scales[prev.t], a.sse[prev.t], nullptr);
 }
 
 // ------------------------------------------------------------------------------ dispatch
 
-// Where the block SSEs are written past the caches: bf16, 4-over-6 or b = 2, 6 to 15 MiB of them from an input of up
-// to 128 MiB.  The line is drawn by the call alone and by the call with a reader of the SSEs behind it (a tensor MSE is
-// usually next), each with four sets of outputs in turn and with one set re-used: the call alone has to gain, and with
-// the reader the two together must not lose.  Ordinary -> past the caches in per cent, E4M3, four inputs in turn, in the
-// order alone, alone re-used, with reader, with reader re-used:
+// Where the block SSEs are written past the caches: bf16, up to 15 MiB of them from an input of up to 128 MiB; with 4-over-6 or
+// b = 2 from 6 MiB on; where T comes from the abs-max in device memory, from 8 MiB on (4-over-6 4).  The lines are drawn
+// by the call alone and by the call with a reader of the SSEs behind it (a tensor MSE is usually next), each with four
+// sets of outputs in turn and with one set re-used; a hierarchical call has its abs-max pass in front each time.  Without
+// the reader it has to gain, and with it the whole must not lose.  Ordinary -> past the caches in per cent, E4M3, four
+// inputs in turn, in the order alone, alone re-used, with reader, with reader re-used:
 //   4-over-6 b = 16   2 MiB -3 -3 +5 +5    4 MiB -3 -3 +3 -1    6 MiB -5 -3 +3 -5    8 MiB -5 -3  0 -5   12 MiB -4 -4 -1 -3
 //                    14 MiB -2 -3  0 -1   15 MiB -2 -2  0 +2   18 MiB -1  0 +2 +2   24 MiB +1 +2 +3 +3
 //            b = 8    4 MiB -2 -5 +6 -3    8 MiB -5 -6 +2 -7   12 MiB -2 -2 +4 -7   18 MiB +2 +1 +8 +4
@@ -710,13 +711,20 @@ stream_batch_kernel(const BatchArgs a, int flags)
 //   powers of two b = 16  4 MiB -1 -1 +4 +2   8 MiB -3 -3 +2 -2   14 MiB -1 -2 +2 +2
 //   fp32     b = 16   2 MiB  0  0 +5 +6    8 MiB -1 -1 +2 +2;  b = 8  2 MiB +2 +4 +9 +11   8 MiB -1 -3 +4  0
 // Batches follow their sum (4-over-6 b = 16: 8 MiB -5 -5 -1 -7, 14 MiB -3 -2 0 -1, 20 MiB 0 -2 +2 +1).
+// With the abs-max pass, T from device memory:
+//   abs-max  b = 4    8 MiB -7 -7 -2 -9    b = 8    4 MiB -4 -4 +3  0    8 MiB -5 -5 -1 -2
+//            b = 16   2 MiB -2 -2 +3 +2    4 MiB -2 -2 +3 +2    8 MiB -1 -1 +1 +1   14 MiB -2 -2  0  0
+//            b = 32   4 MiB  0 -1 +2 +3    7 MiB +1  0 +2 +2
+//   4-over-6 b = 4    8 MiB -6 -5 -2 -11   b = 8    4 MiB -2 -4 +2 -2    8 MiB -5 -5  0 -2
+//            b = 16   2 MiB -1 -1 +3 +4    4 MiB -2 -2  0 +2    8 MiB -3 -3 -1 -1   14 MiB -2 -2 -1 -1
+//            b = 32   4 MiB -1 -1 +1  0    7 MiB -2 -2  0  0;  b = 64  2 MiB 0 0 +2 +1
 template <int DT, int B, bool FOUR6>
-static int sse_past_caches(int64_t n)
+static int sse_past_caches(int64_t n, bool behind_absmax)
 {
     constexpr int64_t kMiB = 1 << 20;
-    if (!kMayPass<DT, B, FOUR6, false> || n > 64 * kMiB) return 0;
-    const int64_t sse_bytes = n / B * 4;
-    return (sse_bytes >= 6 * kMiB && sse_bytes <= 15 * kMiB) ? kSsePastCaches : 0;
+    if (DT != kBF16 || n > 64 * kMiB || !(FOUR6 || B == 2 || behind_absmax)) return 0;
+    const int64_t sse_bytes = n / B * 4, from = behind_absmax ? (FOUR6 ? 4 : 8) : 6;
+    return (sse_bytes >= from * kMiB && sse_bytes <= 15 * kMiB) ? kSsePastCaches : 0;
 }
 
 template <int DT, int B, int FMT, bool FOUR6>
@@ -735,7 +743,7 @@ static hipError_t launch_recipe(const StreamArgs& a, int pz)
     const int workers = (n_slices == 0u) ? 0 : stream_grid(((slices + kItems - 1) / kItems) * kThreads);
     const dim3 grid((unsigned)workers + (tail != 0u ? 1u : 0u)), block(kThreads);
     uint32_t* codes = reinterpret_cast<uint32_t*>(a.codes);
-    const int flags = pz | sse_past_caches<DT, B, FOUR6>(a.n);
+    const int flags = pz | sse_past_caches<DT, B, FOUR6>(a.n, a.absmax_dev != nullptr);
     if constexpr (DT == kBF16 && FMT != kE8M0) {
         if (takes_scaled_kernel<B, FOUR6>(a, slices, workers)) {
             hipLaunchKernelGGL((stream_scaled_kernel<B, FMT, FOUR6>), grid, block, 0, a.stream, a.x, n_slices, last, tail, a.T,
@@ -821,7 +829,7 @@ static hipError_t launch_batch_recipe(const StreamArgs* t, int count, int pz, hi
         const int workers = (total == 0u) ? 0 : stream_grid((int64_t)total * kThreads);
         a.workers = (uint32_t)workers;
         hipLaunchKernelGGL((stream_batch_kernel<DT, B, FMT, FOUR6>), dim3((unsigned)workers + (tails ? n_t : 0u)), dim3(kThreads), 0,
-                           stream, a, pz | sse_past_caches<DT, B, FOUR6>((int64_t)total * kThreads * 8));
+                           stream, a, pz | sse_past_caches<DT, B, FOUR6>((int64_t)total * kThreads * 8, false));
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
