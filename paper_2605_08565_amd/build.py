@@ -43,7 +43,7 @@ def header_id() -> str:
 
 
 def calls_abi() -> str:
-    """The interpreter and the torch, to the commit, whose layouts are compiled into _mxq_calls.so."""
+    """The interpreter and the torch, to the commit, whose layouts are compiled into _mxq_calls.so (mxq.py compares it)."""
     import torch
     return f"{sys.implementation.cache_tag} {torch.__version__} {torch.version.git_version}"
 

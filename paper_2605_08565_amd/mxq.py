@@ -14,10 +14,9 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import sys
 
 import torch
-
-from .build import calls_abi
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmxq.so")
@@ -90,6 +89,12 @@ def lib() -> ctypes.CDLL:
     L.mxq_status_string.argtypes = [i32]
     _lib, _calls = L, _native_calls(L)
     return L
+
+
+def calls_abi() -> str:
+    """The interpreter and the torch, to the commit, whose layouts _mxq_calls.so has compiled in (build.py writes the
+    same text into it; this file loads without its package)."""
+    return f"{sys.implementation.cache_tag} {torch.__version__} {torch.version.git_version}"
 
 
 def _native_calls(L: ctypes.CDLL):

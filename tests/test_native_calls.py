@@ -28,8 +28,10 @@ def test_native_calls_are_built_and_decline_what_is_not_plain():
 
 def test_native_calls_of_another_build_are_not_used(tmp_path, monkeypatch):
     """Layouts of torch and signatures of mxq.h are compiled into the module: neither may differ from what is loaded."""
+    from paper_2605_08565_amd import build
+
     L = mxq.lib()
-    assert mxq._native_calls(L) is not None
+    assert mxq._native_calls(L) is not None and mxq.calls_abi() == build.calls_abi()
     assert mxq._native_calls(L).built_for() == (mxq.calls_abi(), ctypes.string_at(ctypes.addressof(
         ctypes.c_char.in_dll(L, "mxq_header_id"))).decode())
     assert torch.__version__ in mxq.calls_abi() and torch.version.git_version in mxq.calls_abi()
