@@ -301,6 +301,36 @@ __device__ __forceinline__ void store_slice(const TileOut<B>& o, uint32_t s, Sli
     }
 }
 
+// Where the block SSEs of a complete slice go.
+enum : int { kNoSse = 0, kSseCached = 1, kSsePast = 2 };
+
+// Stores of one slice of 256 complete chunks.  Every lane of a block stores the block's scale byte and SSE, the same
+// values to the same place: without masks and branches the compiler can count the stores that lie behind a load.
+template <int B, int SSE>
+__device__ __forceinline__ void store_complete_slice(const TileOut<B>& o, uint32_t s, uint32_t* __restrict__ codes,
+                                                     uint8_t* __restrict__ scales, float* __restrict__ sse_out)
+{
+    constexpr int NBLK = TileOut<B>::NBLK;
+    constexpr int LANES = (B < 8) ? 1 : B / 8;
+    const uint32_t tid = threadIdx.x;
+    const uint64_t c0 = (uint64_t)s * kThreads;                      // first chunk of the slice
+    const auto store = [](auto* p, auto v) {
+        if constexpr (SSE == kSsePast) __builtin_nontemporal_store(v, p);
+        else if constexpr (SSE == kSseCached) *p = v;
+    };
+    __builtin_nontemporal_store(o.packed, codes + c0 + tid);
+    if constexpr (B >= 8) {
+        (scales + c0 / LANES)[tid / LANES] = (uint8_t)o.code[0];
+        store((sse_out + c0 / LANES) + tid / LANES, o.sse[0]);
+    } else if constexpr (NBLK == 2) {
+        reinterpret_cast<uint16_t*>(scales + c0 * 2)[tid] = (uint16_t)(o.code[0] | (o.code[1] << 8));
+        store(reinterpret_cast<f32x2*>(sse_out + c0 * 2) + tid, f32x2{o.sse[0], o.sse[1]});
+    } else {
+        reinterpret_cast<uint32_t*>(scales + c0 * 4)[tid] = o.code[0] | (o.code[1] << 8) | (o.code[2] << 16) | (o.code[3] << 24);
+        store(reinterpret_cast<f32x4*>(sse_out + c0 * 4) + tid, f32x4{o.sse[0], o.sse[1], o.sse[2], o.sse[3]});
+    }
+}
+
 // Scale table of a kernel.  One truncated product does for bf16 values that nothing has divided (8 significant
 // bits); fp32 values and quotients by a tensor scale have 24 and need both parts.
 template <int DT, int TMODE>
@@ -424,6 +454,90 @@ __device__ __forceinline__ uint32_t stream_tiles(RawChunk<DT> (&bufA)[kItems], c
     for (int i = 0; i < kItems; ++i)
         store_slice<B, kMayPass<DT, B, FOUR6, TMODE, CLIP>>(out[i], s_prev + (uint32_t)i, sl, flags, codes, scales, sse_out, CLIP ? clip_out : nullptr);
     return largest_sse;
+}
+
+// ---------------------------------------------------------------------------------------
+// Large tensors without a per-tensor scale in device memory: a workgroup takes kOnce consecutive slices and ends.  All
+// its loads are in flight before the first slice is quantised, a slice waits for its own load only, and the next
+// workgroup's loads start when this one's last stores do.  Bound by HBM (4-over-6: vector issue beside it).  In the loop
+// of stream_kernel a wavefront has one tile's loads in flight, and none while it waits for them and the stores before.
+// Loop -> two / three / four slices: 4096 x 14336 bf16 abs-max b = 16 28.4 -> 27.3 / 26.6 / 27.6 us, 4-over-6 b = 8 31.3 -> 29.7
+// / 29.4 / 30.6, b = 32 28.6 -> 26.2 / 26.0 / 26.7, b = 2 48.1 -> 46.0 / 46.2 / 46.3; fp32 b = 16 49.5 -> 46.0 / 46.2 / 47.3;
+// a batch of 218 M elements, 4-over-6 b = 32 112.8 -> 103.4 / 97.8 / 96.7 (5.1 -> 5.9 TB/s).  A tensor of fewer slices has too
+// few workgroups for their phases to overlap: 4096 x 4096 (8192 slices) bf16 abs-max b = 16 8.3 -> 8.9, 2563 x 4110 b = 2 12.1 ->
+// 12.5; 6000 x 4096 (11719) 13.4 -> 13.5; 8192 x 4096 (16384) 4-over-6 b = 16 16.6 -> 16.5, b = 4 22.8 -> 21.4, abs-max 16.7 ->
+// 16.2.  Behind an abs-max pass (T in device memory) the loop's order of the slices finds more in the caches: 8192 x 4096
+// abs-max and quantise, b = 16, 26.2 -> 29.7.
+// ---------------------------------------------------------------------------------------
+constexpr int kOnce = 3;
+constexpr int64_t kOnceFrom = 16384;                                 // slices
+constexpr int64_t kOnceMost = (int64_t)1 << 25;                      // a grid counts fewer than 2^32 threads
+
+// The kOnce slices from s0 on; slices beyond the last are read as the last.
+template <int DT>
+__device__ __forceinline__ void load_once(RawChunk<DT> (&raw)[kOnce], const void* __restrict__ x, uint32_t s0, Slices sl)
+{
+    constexpr uint64_t kVecPerChunk = (DT == kBF16) ? 1 : 2;
+#pragma unroll
+    for (int i = 0; i < kOnce; ++i) {
+        const uint32_t s = min(s0 + (uint32_t)i, sl.count - 1u);     // uniform
+        raw[i] = load_raw<DT>(static_cast<const u32x4*>(x) + (uint64_t)s * kThreads * kVecPerChunk, (uint32_t)threadIdx.x, sl.chunks(s));
+    }
+}
+
+template <int DT, int B, int FMT, bool FOUR6, int TMODE, class Entry>
+__device__ __forceinline__ void once_slices(const RawChunk<DT> (&raw)[kOnce], uint32_t s0, Slices sl, float T, float rT, int flags,
+                                            const Entry* tab, u32x4* wave_lds, uint32_t* __restrict__ codes,
+                                            uint8_t* __restrict__ scales, float* __restrict__ sse_out)
+{
+    constexpr bool kPass = kMayPass<DT, B, FOUR6, TMODE, false>;
+    const auto slices = [&](auto store) {
+#pragma unroll
+        for (int i = 0; i < kOnce; ++i) {
+            float v[8];
+            widen<DT>(raw[i], v, wave_lds);
+            TileOut<B> o;
+            process_chunk<B, FMT, FOUR6, TMODE, false>(v, T, rT, TMODE, (flags & kPreventZero) != 0, tab, o.packed, o.code, o.sse, o.clip);
+            store(o, s0 + (uint32_t)i);
+            __builtin_amdgcn_sched_barrier(0);                       // one slice at a time: registers
+        }
+    };
+    if (s0 + (uint32_t)kOnce >= sl.count)                            // uniform; the last slices of the tensor
+        slices([&](const TileOut<B>& o, uint32_t s) { store_slice<B, kPass>(o, s, sl, flags, codes, scales, sse_out, nullptr); });
+    else if (!sse_out)
+        slices([&](const TileOut<B>& o, uint32_t s) { store_complete_slice<B, kNoSse>(o, s, codes, scales, nullptr); });
+    else if (kPass && (flags & kSsePastCaches))
+        slices([&](const TileOut<B>& o, uint32_t s) { store_complete_slice<B, kPass ? kSsePast : kSseCached>(o, s, codes, scales, sse_out); });
+    else
+        slices([&](const TileOut<B>& o, uint32_t s) { store_complete_slice<B, kSseCached>(o, s, codes, scales, sse_out); });
+}
+
+// The first `tiles` workgroups take the slices; one more, where there is one, takes the ragged tail.
+template <int DT, int B, int FMT, bool FOUR6, int TMODE>
+__global__ void __launch_bounds__(kThreads)
+stream_once_kernel(const void* __restrict__ x, uint32_t n_slices, uint32_t last_chunks, uint32_t tail, float T, int flags,
+                   uint32_t tiles, uint32_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ sse_out)
+{
+    static_assert(TMODE == kNoT || TMODE == kFastT, "T by value");
+    using Entry = TableEntry<DT, TMODE>;
+    __shared__ Entry tab[(FMT == kE8M0) ? 1 : 256];
+    __shared__ u32x4 xpose[(DT == kF32) ? 2 * kThreads : 1];        // 2 KiB per wavefront, fp32 input only
+    u32x4* wave_lds = xpose + ((DT == kF32) ? 2u * (threadIdx.x & ~63u) : 0u);
+
+    const Slices sl{n_slices, last_chunks};
+    const uint32_t s0 = blockIdx.x * (uint32_t)kOnce;
+    RawChunk<DT> raw[kOnce];
+    load_once<DT>(raw, x, s0, sl);                                   // in flight while the scale table is built
+    const float rT = 1.0f / T;                                       // correctly rounded
+    if constexpr (FMT != kE8M0) fill_scale_table<FMT, kFormTable<DT, TMODE>>(tab);
+    if constexpr (B < 8) {
+        if (blockIdx.x == tiles) {
+            stream_tail<DT, B, FMT, FOUR6, TMODE, false>(x, sl.elements(), tail, T, rT, TMODE, (flags & kPreventZero) != 0, tab,
+                                                         reinterpret_cast<uint8_t*>(codes), scales, sse_out, nullptr);
+            return;
+        }
+    }
+    once_slices<DT, B, FMT, FOUR6, TMODE>(raw, s0, sl, T, rT, flags, tab, wave_lds, codes, scales, sse_out);
 }
 
 // Main kernel.  The number of workgroups without the one for the tail is an argument: the launch's own count lies in
@@ -597,7 +711,8 @@ struct BatchArgs {
     uint32_t* codes[kMaxBatch];
     uint8_t* scales[kMaxBatch];
     float* sse[kMaxBatch];
-    uint32_t first[kMaxBatch + 1];        // first global slice of tensor t; first[count] = total
+    uint32_t first[kMaxBatch + 1];        // first global slice (tile of kOnce slices) of tensor t; first[count] = total
+    uint32_t slices[kMaxBatch];
     uint32_t last[kMaxBatch];             // chunks in tensor t's last slice, 1 .. 256
     uint32_t tail[kMaxBatch];             // elements behind the complete chunks, 0 .. 7 (b = 2, 4)
     uint32_t count;
@@ -691,6 +806,40 @@ stream_batch_kernel(const BatchArgs a, int flags)
     store_slice<B, kMayPass<DT, B, FOUR6, kNoT, false>>(out[0], prev.s, prev.sl, flags, a.codes[prev.t], a.scales[prev.t], a.sse[prev.t], nullptr);
 }
 
+// The same with kOnce consecutive slices of one tensor to a workgroup: first[] counts such tiles, and the slices of a
+// tensor follow from its own count.
+template <int DT, int B, int FMT, bool FOUR6>
+__global__ void __launch_bounds__(kThreads)
+stream_batch_once_kernel(const BatchArgs a, int flags)
+{
+    using Entry = TableEntry<DT, kNoT>;
+    __shared__ Entry tab[(FMT == kE8M0) ? 1 : 256];
+    __shared__ u32x4 xpose[(DT == kF32) ? 2 * kThreads : 1];
+    u32x4* wave_lds = xpose + ((DT == kF32) ? 2u * (threadIdx.x & ~63u) : 0u);
+
+    const uint32_t g = blockIdx.x;
+    if constexpr (B < 8) {
+        if (g >= a.workers) {
+            const uint32_t t = g - a.workers;
+            if (a.tail[t] == 0u) return;
+            if constexpr (FMT != kE8M0) fill_scale_table<FMT, kFormTable<DT, kNoT>>(tab);
+            stream_tail<DT, B, FMT, FOUR6, kNoT, false>(a.x[t], Slices{a.slices[t], a.last[t]}.elements(), a.tail[t], 1.0f, 1.0f, kNoT,
+                                                        (flags & kPreventZero) != 0, tab, reinterpret_cast<uint8_t*>(a.codes[t]),
+                                                        a.scales[t], a.sse[t], nullptr);
+            return;
+        }
+    }
+    uint32_t t = 0u;
+#pragma unroll
+    for (int k = 1; k < kMaxBatch; ++k) t += ((uint32_t)k < a.count && g >= a.first[k]) ? 1u : 0u;
+    const Slices sl{a.slices[t], a.last[t]};
+    const uint32_t s0 = (g - a.first[t]) * (uint32_t)kOnce;
+    RawChunk<DT> raw[kOnce];
+    load_once<DT>(raw, a.x[t], s0, sl);
+    if constexpr (FMT != kE8M0) fill_scale_table<FMT, kFormTable<DT, kNoT>>(tab);
+    once_slices<DT, B, FMT, FOUR6, kNoT>(raw, s0, sl, 1.0f, 1.0f, flags, tab, wave_lds, a.codes[t], a.scales[t], a.sse[t]);
+}
+
 // ------------------------------------------------------------------------------ dispatch
 
 // Where the block SSEs are written past the caches: bf16, up to 15 MiB of them from an input of up to 128 MiB; with 4-over-6 or
@@ -751,6 +900,17 @@ static hipError_t launch_recipe(const StreamArgs& a, int pz)
             return hipGetLastError();
         }
     }
+    if (slices >= kOnceFrom && slices <= kOnceMost && (tmode == kNoT || tmode == kFastT)) {
+        const uint32_t tiles = (n_slices + (uint32_t)kOnce - 1u) / (uint32_t)kOnce;
+        const dim3 once(tiles + (tail != 0u ? 1u : 0u));
+#define MXQ_LAUNCH_ONCE(MODE)                                                                                                  \
+    hipLaunchKernelGGL((stream_once_kernel<DT, B, FMT, FOUR6, MODE>), once, block, 0, a.stream, a.x, n_slices, last, tail,     \
+                       a.T, flags, tiles, codes, a.scales, a.sse)
+        if (tmode == kNoT) MXQ_LAUNCH_ONCE(kNoT);
+        else MXQ_LAUNCH_ONCE(kFastT);
+#undef MXQ_LAUNCH_ONCE
+        return hipGetLastError();
+    }
 #define MXQ_LAUNCH_STREAM(MODE, CLIP)                                                                 \
     hipLaunchKernelGGL((stream_kernel<DT, B, FMT, FOUR6, MODE, CLIP>), grid, block, 0, a.stream, a.x,       \
                        n_slices, last, tail, a.T, flags, (uint32_t)workers, a.absmax_dev, a.t_out, codes, a.scales, a.sse, a.clip)
@@ -807,8 +967,12 @@ static hipError_t launch_batch_recipe(const StreamArgs* t, int count, int pz, hi
     // up to kMaxBatch tensors per launch, ragged tails (b = 2, 4) included
     for (int i0 = 0; i0 < count; i0 += kMaxBatch) {
         BatchArgs a{};
+        int64_t sum = 0;
+        for (int i = i0; i < count && i < i0 + kMaxBatch; ++i) sum += (t[i].n / 8 + kThreads - 1) / kThreads;
+        const bool once = sum >= kOnceFrom && sum <= kOnceMost;
+        const int64_t per = once ? kOnce : 1;
         uint32_t n_t = 0u;
-        uint64_t total = 0u;
+        int64_t total = 0;
         bool tails = false;
         for (int i = i0; i < count && i < i0 + kMaxBatch; ++i) {
             const int64_t n_full = t[i].n / 8;
@@ -817,19 +981,24 @@ static hipError_t launch_batch_recipe(const StreamArgs* t, int count, int pz, hi
             a.codes[n_t] = reinterpret_cast<uint32_t*>(t[i].codes);
             a.scales[n_t] = t[i].scales;
             a.sse[n_t] = t[i].sse;
-            a.first[n_t] = (uint32_t)total;
+            a.first[n_t] = (uint32_t)total;                      // the host has bounded the sum below 2^32
+            a.slices[n_t] = (uint32_t)slices;
             a.last[n_t] = (uint32_t)(n_full - (slices - 1) * kThreads);
             a.tail[n_t] = (uint32_t)(t[i].n - n_full * 8);
             tails |= a.tail[n_t] != 0u;
-            total += (uint64_t)slices;
+            total += (slices + per - 1) / per;
             ++n_t;
         }
-        a.first[n_t] = (uint32_t)total;                          // the host has bounded the sum below 2^32
+        a.first[n_t] = (uint32_t)total;
         a.count = n_t;
-        const int workers = (total == 0u) ? 0 : stream_grid((int64_t)total * kThreads);
+        const int flags = pz | sse_past_caches<DT, B, FOUR6>(sum * kThreads * 8, false);
+        const int workers = (total == 0) ? 0 : once ? (int)total : stream_grid(total * kThreads);
         a.workers = (uint32_t)workers;
-        hipLaunchKernelGGL((stream_batch_kernel<DT, B, FMT, FOUR6>), dim3((unsigned)workers + (tails ? n_t : 0u)), dim3(kThreads), 0,
-                           stream, a, pz | sse_past_caches<DT, B, FOUR6>((int64_t)total * kThreads * 8, false));
+        const dim3 grid((unsigned)workers + (tails ? n_t : 0u));
+        if (once)
+            hipLaunchKernelGGL((stream_batch_once_kernel<DT, B, FMT, FOUR6>), grid, dim3(kThreads), 0, stream, a, flags);
+        else
+            hipLaunchKernelGGL((stream_batch_kernel<DT, B, FMT, FOUR6>), grid, dim3(kThreads), 0, stream, a, flags);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

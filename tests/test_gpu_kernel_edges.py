@@ -245,3 +245,34 @@ def test_dequantize_at_tile_edges(oracle, mxq, block, dtype):
             got = out.float().cpu().numpy()
             ref = want if dtype == "f32" else torch.from_numpy(want).to(torch.bfloat16).float().numpy()
             assert (got[:, :n] == ref).all() and (got[:, n:] == 7.0).all()
+
+
+@pytest.mark.parametrize("block", [2, 4, 8, 16, 128])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_quantize_where_a_workgroup_takes_three_slices(oracle, mxq, block, dtype):
+    """From 16384 slices of 2048 elements on: one slice below the line, tiles of three that end full, one and two slices
+    short, a part-filled last slice, a ragged tail.  Whole tensors against the quantisation of their pieces (below the
+    line, where a workgroup loops), which no tile boundary shares, and the last elements against the oracle."""
+    rng = np.random.default_rng(block)
+    per, line = 2048, 16384
+    period = (rng.standard_normal(block * 40009) * 0.05).astype(np.float32)
+    big = torch.from_numpy(np.resize(period, (line + 3) * per)).cuda().to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    ends = [(line - 1) * per, line * per, (line + 1) * per, (line + 1) * per + 1000 // block * block]
+    if block < 8:
+        ends.append((line + 2) * per + 6 // block * block)
+    for n in ends:
+        x = big[:n].reshape(1, n)
+        for fmt, rec, T, want in [(1, 2, 1.0, True), (2, 1, 1.0, False), (0, 0, 1.0, True), (1, 0, 0.7, True)]:
+            print(f"[edges] large b={block} {dtype} n={n} fmt={fmt} recipe={rec} T={T}", flush=True)
+            for got in (mxq.quantize(x, block, fmt, rec, tensor_scale=T, want_sse=want),
+                        *(mxq.quantize_batch([x], block, fmt, rec, want_sse=want) if T == 1.0 else ())):
+                cut = n // 3 // block * block
+                pieces = [mxq.quantize(x[:, i:j].clone(), block, fmt, rec, tensor_scale=T, want_sse=want)
+                          for i, j in ((0, cut), (cut, 2 * cut), (2 * cut, n))]
+                assert (got[2] is not None) == want
+                for g, *p in zip(got if want else got[:2], *pieces):
+                    assert torch.equal(g.view(torch.uint8), torch.cat(p, 1).view(torch.uint8))
+                end = x[:, n - 5 * per - n % per:].contiguous()
+                end = end.cpu().numpy() if dtype == "f32" else end.view(torch.int16).cpu().numpy().view(np.uint16)
+                ref = oracle.quantize(end, block, fmt, rec, tensor_scale=T)
+                same([g[:, -r.shape[1]:].contiguous() for g, r in zip(got, ref) if g is not None], ref)
