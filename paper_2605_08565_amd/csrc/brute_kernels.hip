@@ -82,56 +82,85 @@ struct GroupArgMin {
     }
 };
 
-// SSE of the lane's blocks under S = mant_value(MI) * scale2 (scale2 a power of two), entered
-// into the group at position POS.  w holds the lane's quotients v / mant_value(MI).
-template <int B, int MI, int POS, class G>
-__device__ __forceinline__ void try_candidate(const float (&v)[8], const float (&w)[8], float scale2, G& g)
+// Block SSE of the lane's residuals: separately rounded squares in a balanced tree.  FUSED: every square is exact
+// (squares_exact), so the first level of the tree may take one of the two squares by a fused multiply-add with the
+// same bits, and four of the 15 instructions go.
+template <int B, bool FUSED>
+__device__ __forceinline__ void residual_sse(const float (&e)[8], float (&sse)[4])
 {
-    const uint32_t packed = e2m1_pack8(w, scale2);
-    float q2[8], sq[8];
-    e2m1_unpack8(packed, scale2, q2);                                  // q * 2^e
+    if constexpr (FUSED) {
+        const float s0 = e[0] * e[0], s2 = e[2] * e[2], s4 = e[4] * e[4], s6 = e[6] * e[6];
+        const float p0 = __builtin_fmaf(e[1], e[1], s0), p1 = __builtin_fmaf(e[3], e[3], s2);
+        const float p2 = __builtin_fmaf(e[5], e[5], s4), p3 = __builtin_fmaf(e[7], e[7], s6);
+        if constexpr (B == 2) { sse[0] = p0; sse[1] = p1; sse[2] = p2; sse[3] = p3; }
+        else if constexpr (B == 4) { sse[0] = p0 + p1; sse[1] = p2 + p3; }
+        else sse[0] = group_sum<B / 8>((p0 + p1) + (p2 + p3));
+    } else {
+        float sq[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sq[j] = e[j] * e[j];
+        block_sse<B>(sq, sse);
+    }
+}
+
+// SSE of the lane's blocks under S = mant_value(MI) * scale2.  Of scale2 only the exponent counts, one for each
+// block (scale2[k]).  w holds the lane's quotients v / mant_value(MI).
+template <int B, int MI, bool FUSED>
+__device__ __forceinline__ void mantissa_sse(const float (&v)[8], const float (&w)[8], const float (&scale2)[BruteState<B>::NBLK],
+                                             float (&sse)[4])
+{
+    constexpr int EPB = (B < 8) ? B : 8;
+    const uint32_t packed = e2m1_pack8_scales<EPB>(w, scale2);
+    float q2[8], e[8];                                                 // q * 2^e
+    e2m1_unpack2<0>(packed, scale2[0 / EPB], q2[0], q2[1]);
+    e2m1_unpack2<1>(packed, scale2[2 / EPB], q2[2], q2[3]);
+    e2m1_unpack2<2>(packed, scale2[4 / EPB], q2[4], q2[5]);
+    e2m1_unpack2<3>(packed, scale2[6 / EPB], q2[6], q2[7]);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        float e;
-        if constexpr (MI == 0) e = v[j] - q2[j];
-        else e = __builtin_fmaf(-q2[j], mant_value(MI), v[j]);
-        sq[j] = e * e;
+        if constexpr (MI == 0) e[j] = v[j] - q2[j];
+        else e[j] = __builtin_fmaf(-q2[j], mant_value(MI), v[j]);
     }
-    const float p0 = sq[0] + sq[1], p1 = sq[2] + sq[3], p2 = sq[4] + sq[5], p3 = sq[6] + sq[7];
-    if constexpr (B == 2) {
-        g.template put<POS>(0, p0); g.template put<POS>(1, p1);
-        g.template put<POS>(2, p2); g.template put<POS>(3, p3);
-    } else if constexpr (B == 4) {
-        g.template put<POS>(0, p0 + p1); g.template put<POS>(1, p2 + p3);
-    } else {
-        g.template put<POS>(0, group_sum<B / 8>((p0 + p1) + (p2 + p3)));
-    }
+    residual_sse<B, FUSED>(e, sse);
+}
+
+// The same under one scale for all blocks, entered into the group at position POS.
+template <int B, int MI, int POS, bool FUSED, class G>
+__device__ __forceinline__ void try_candidate(const float (&v)[8], const float (&w)[8], float scale2, G& g)
+{
+    constexpr int NBLK = BruteState<B>::NBLK;
+    float scales[NBLK], sse[4];
+#pragma unroll
+    for (int k = 0; k < NBLK; ++k) scales[k] = scale2;
+    mantissa_sse<B, MI, FUSED>(v, w, scales, sse);
+#pragma unroll
+    for (int k = 0; k < NBLK; ++k) g.template put<POS>(k, sse[k]);
     // One candidate at a time: left alone, the instruction scheduler interleaves several
     // candidates, which costs registers and 10 % of the kernel's speed (measured).
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int B, int FMT, int MI, class G>
+template <int B, int FMT, int MI, bool FUSED, class G>
 __device__ __forceinline__ void try_binade_from(const float (&v)[8], const float (&w)[8][8], float scale2,
                                                 uint32_t code0, G& g)
 {
     if constexpr (MI < 7) {
-        try_candidate<B, MI, MI>(v, w[MI], scale2, g);
-        try_binade_from<B, FMT, MI + 1>(v, w, scale2, code0, g);
+        try_candidate<B, MI, MI, FUSED>(v, w[MI], scale2, g);
+        try_binade_from<B, FMT, MI + 1, FUSED>(v, w, scale2, code0, g);
     } else {
         if (code0 + 7u <= (uint32_t)ScaleFmt<FMT>::kMaxCode)            // skips the NaN code only
-            try_candidate<B, 7, 7>(v, w[7], scale2, g);
+            try_candidate<B, 7, 7, FUSED>(v, w[7], scale2, g);
     }
 }
 
 // The 8 codes code0 .. code0 + 7 of one binade: (1 + mi/8) * scale2.
-template <int B, int FMT>
+template <int B, int FMT, bool FUSED>
 __device__ __forceinline__ void try_binade(const float (&v)[8], const float (&w)[8][8], float scale2,
                                            uint32_t code0, BruteState<B>& st)
 {
     GroupArgMin<B> g;
     g.begin();
-    try_binade_from<B, FMT, 0>(v, w, scale2, code0, g);
+    try_binade_from<B, FMT, 0, FUSED>(v, w, scale2, code0, g);
     g.end(st, code0);
 }
 
@@ -169,6 +198,15 @@ __device__ __forceinline__ void try_binade(const float (&v)[8], const float (&w)
 
 template <int FMT>
 __device__ __forceinline__ float walk_scale(uint32_t code) { return walk_scale_bias<ScaleFmt<FMT>::kBias>(code); }
+
+// The smallest |v| of the lane.
+__device__ __forceinline__ float smallest_of(const float (&v)[8])
+{
+    float m = __builtin_fabsf(v[0]);
+#pragma unroll
+    for (int j = 1; j < 8; ++j) m = __builtin_fminf(m, __builtin_fabsf(v[j]));
+    return m;
+}
 
 // SSE of the lane's blocks under the scales S.  ONE_MUL (bf16 input, no per-tensor scale): the
 // quotient is one product with the hardware reciprocal.  With 8 significant bits in v and 4 in S an
@@ -416,13 +454,29 @@ template <int B, int POS, class G>
 __device__ __forceinline__ void try_pow2_from(const float (&v)[8], uint32_t code0, G& g)
 {
     if constexpr (POS < 8) {
-        if (POS < 7 || code0 + 7u <= 254u) try_candidate<B, 0, POS>(v, v, pow2_scale(code0 + POS), g);
+        if (POS < 7 || code0 + 7u <= 254u) try_candidate<B, 0, POS, false>(v, v, pow2_scale(code0 + POS), g);
         try_pow2_from<B, POS + 1>(v, code0, g);
     }
 }
 
+// The sub-normal codes 1 .. 7 = j * s1: 1, 2, 3 = 1.5 * 2, 4, 5 = 1.25 * 4, 6 = 1.5 * 4, 7 = 1.75 * 4.
+template <int B, bool FUSED = false>
+__device__ __forceinline__ void try_subnormals(const float (&v)[8], const float (&w)[8][8], float s1, float s2, float s4, BruteState<B>& st)
+{
+    GroupArgMin<B> g;
+    g.begin();
+    try_candidate<B, 0, 0, FUSED>(v, w[0], s1, g);
+    try_candidate<B, 0, 1, FUSED>(v, w[0], s2, g);
+    try_candidate<B, 4, 2, FUSED>(v, w[4], s2, g);
+    try_candidate<B, 0, 3, FUSED>(v, w[0], s4, g);
+    try_candidate<B, 2, 4, FUSED>(v, w[2], s4, g);
+    try_candidate<B, 4, 5, FUSED>(v, w[4], s4, g);
+    try_candidate<B, 6, 6, FUSED>(v, w[6], s4, g);
+    g.end(st, 1u);
+}
+
 // Search for the lane's 8 values (already divided by T): winner codes, packed nibbles, SSE.
-template <int B, int FMT>
+template <int B, int FMT, bool SHORT>
 __device__ __forceinline__ void brute_search(const float (&v)[8], uint32_t& packed, BruteState<B>& st)
 {
     constexpr int NBLK = BruteState<B>::NBLK;
@@ -441,27 +495,34 @@ __device__ __forceinline__ void brute_search(const float (&v)[8], uint32_t& pack
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) { st.best_sse[k] = __builtin_inff(); st.best_code[k] = 1u; }
 
-    // sub-normal codes 1..7 = j * 2^(emin-3): 1, 2, 3 = 1.5*2, 4, 5 = 1.25*4, 6 = 1.5*4, 7 = 1.75*4
     const float s1 = u2f((uint32_t)(127 + emin - 3) << 23);
     const float s2 = u2f((uint32_t)(127 + emin - 2) << 23);
     const float s4 = u2f((uint32_t)(127 + emin - 1) << 23);
-    {
-        GroupArgMin<B> g;
-        g.begin();
-        try_candidate<B, 0, 0>(v, w[0], s1, g);
-        try_candidate<B, 0, 1>(v, w[0], s2, g);
-        try_candidate<B, 4, 2>(v, w[4], s2, g);
-        try_candidate<B, 0, 3>(v, w[0], s4, g);
-        try_candidate<B, 2, 4>(v, w[2], s4, g);
-        try_candidate<B, 4, 5>(v, w[4], s4, g);
-        try_candidate<B, 6, 6>(v, w[6], s4, g);
-        g.end(st, 1u);
+    // SHORT (bf16 that nothing has divided): from the first binade on whose squares are all exact, four of a candidate's
+    // instructions go.  (Two loops: with both kinds in one, more registers and 2 % slower.)  4096 x 14336 E4M3 b = 16 801 ->
+    // 746 us; 4096 x 4096 b = 32 245 -> 235, b = 128 254 -> 240, b = 4 227 -> 224; b = 2, of whose sums too little is left, not.
+    float largest = 0.0f;
+    bool regular = false;
+    if constexpr (SHORT) {
+        regular = __builtin_amdgcn_ballot_w64(!(smallest_of(v) >= kSmallestSquared)) == 0ull;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) largest = __builtin_fmaxf(largest, __builtin_fabsf(v[j]));
     }
+    const auto exact = [&](float lowest) {
+        return SHORT && regular && __builtin_amdgcn_ballot_w64(!(largest < kExactScales * lowest)) == 0ull;
+    };
+    try_subnormals<B, false>(v, w, s1, s2, s4, st);
 
     // normal codes: exponent field ef = 1 .. kMaxCode >> 3, value (1 + mi/8) * 2^(ef - bias)
-    for (uint32_t ef = 1u; ef <= (uint32_t)(ScaleFmt<FMT>::kMaxCode >> 3); ++ef) {
+    constexpr uint32_t last = (uint32_t)(ScaleFmt<FMT>::kMaxCode >> 3);
+    uint32_t ef = 1u;
+    for (; ef <= last; ++ef) {
         const float scale2 = u2f((ef + (uint32_t)(127 - bias)) << 23);
-        try_binade<B, FMT>(v, w, scale2, ef << 3, st);
+        if (exact(scale2)) break;                                       // and all above it
+        try_binade<B, FMT, false>(v, w, scale2, ef << 3, st);
+    }
+    if constexpr (SHORT) {
+        for (; ef <= last; ++ef) try_binade<B, FMT, true>(v, w, u2f((ef + (uint32_t)(127 - bias)) << 23), ef << 3, st);
     }
 
     // codes of the winners
@@ -564,7 +625,7 @@ brute_kernel(const void* __restrict__ x, int64_t n_full, int tail, float T_arg,
         BruteState<B> st;
         if constexpr (FMT == kE8M0) brute_search_pow2<B>(v, packed, st);
         else if constexpr (PRUNE) brute_search_pruned<B, FMT, DT == kBF16 && !HAS_T>(v, packed, st);
-        else brute_search<B, FMT>(v, packed, st);
+        else brute_search<B, FMT, DT == kBF16 && !HAS_T && B != 2>(v, packed, st);
         float clip[4];
         if (clip_out) {                                                 // uniform
             float S_best[NBLK];

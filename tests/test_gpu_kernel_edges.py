@@ -276,3 +276,27 @@ def test_quantize_where_a_workgroup_takes_three_slices(oracle, mxq, block, dtype
                 end = end.cpu().numpy() if dtype == "f32" else end.view(torch.int16).cpu().numpy().view(np.uint16)
                 ref = oracle.quantize(end, block, fmt, rec, tensor_scale=T)
                 same([g[:, -r.shape[1]:].contiguous() for g, r in zip(got, ref) if g is not None], ref)
+
+
+@pytest.mark.parametrize("fmt", [1, 2])
+@pytest.mark.parametrize("block", [4, 8, 32])
+def test_search_where_squares_are_exact_and_where_not(oracle, mxq, fmt, block):
+    """bf16 wavefronts on both sides of what lets a search sum exact squares: elements on and beside 128 times every power of
+    two of the scales, on and beside 2^-67, zeros; both searches."""
+    rng = np.random.default_rng(block + fmt)
+    rows = 512 // block
+    waves = []
+    for e in range(-20, 20):
+        for m in (1.0, 0.99609375, 1.9921875):
+            v = rng.standard_normal((rows, block)) * 2.0 ** (e - 9)
+            v[0, 0] = m * 2.0 ** e
+            if e % 4 == 1:
+                v[-1, -1] = 2.0 ** rng.integers(-70, -64) * m
+            if e % 4 == 2:
+                v[-1, -1] = 0.0
+            waves.append(v)
+    x = W.f32_to_bf16_bits(np.concatenate(waves).astype(np.float32))
+    print(f"[edges] squares fmt={fmt} b={block}", flush=True)
+    ref = oracle.quantize(x, block, fmt, 4)
+    for recipe in (mxq.RECIPE_BRUTE, mxq.RECIPE_BRUTE_PRUNED):
+        same(mxq.quantize(mxq.from_bits(x), block, fmt, recipe), ref)

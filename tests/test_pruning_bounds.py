@@ -60,3 +60,32 @@ def test_bounds_of_the_way_down_hold_for_every_code(oracle, fmt, b, kind):
             assert not (every[winner] > best)
             ruled_out += int((every[:start] > best).sum())
     assert ruled_out > 0 or kind == "normal_small"       # the bounds do bite
+
+
+def test_squares_of_residuals_are_exact_below_128_scales():
+    """A bf16 value v with |v| < 128 S leaves, under every E2M1 value q that is nearest to v / S, a residual v - q S of at
+    most 12 significant bits: all 128 mantissas, all scale mantissas (four bits and the shorter ones of sub-normal codes),
+    all distances of the exponents, in integers.  Some way beyond 128 S 13 bits occur."""
+    grid = (0, 1, 2, 3, 4, 6, 8, 12)                                       # 2 q
+
+    def most_bits(v, s):                                                   # v and s in units of 2^-24
+        y2, nearest = 2 * v / s, []
+        for g in grid:
+            nearest.append((abs(y2 - g), g))
+        best = min(nearest)[0]
+        r = [abs(2 * v - g * s) for d, g in nearest if d == best]          # both sides of a tie
+        return max((x // (x & -x)).bit_length() if x else 0 for x in r)
+
+    beyond = 0
+    for s_mant in list(range(8, 16)) + [1, 2, 3, 4, 5, 6, 7]:
+        s = s_mant << 21                                                   # 2^24 .. for 8 .. 15
+        for shift in range(-16, 13):
+            for mant in range(128, 256):
+                v = (mant << 17) << shift if shift >= 0 else (mant << 17) >> -shift
+                if shift < 0 and (mant << 17) & ((1 << -shift) - 1):
+                    continue
+                if v < 128 * s:
+                    assert most_bits(v, s) <= 12, (s_mant, shift, mant)
+                else:
+                    beyond = max(beyond, most_bits(v, s))
+    assert beyond > 12
