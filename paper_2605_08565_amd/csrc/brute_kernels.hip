@@ -17,6 +17,8 @@
 #include "mxq_device.hpp"
 #include "mxq_launch.hpp"
 
+#include <type_traits>
+
 namespace mxq {
 
 // hi/lo split of 1/m for m = 1 + i/8 (see "Quotients whose rounding decisions are exact").
@@ -180,20 +182,25 @@ __device__ __forceinline__ void try_binade(const float (&v)[8], const float (&w)
 //        fp32 sums of non-negative terms never fall below a term, so that is a lower bound of the
 //        candidate's SSE.  Once it exceeds the best SSE found so far, this code loses and, because the
 //        bound grows as S falls, so do all lower ones.
-// So the scan starts at the abs-max code (Eq. 2), walks up to amax / 3.5 (five to seven codes; odd
-// codes to 15 beyond that where the scales are that small), then down until (lo) stops it (one to
-// three codes a block of up to 16, four to seven a wavefront at b = 64 and 128; blocks beyond the format
-// see walk_saturated).  Every block walks from its OWN code: scale and reciprocal are per-lane registers,
-// the wavefront takes as many steps as its longest block, and blocks of very different magnitude
-// cost each other nothing.  A block that is done goes on trying codes: a code that cannot win changes
-// nothing, and masking it out would cost more.  Where every block of a wavefront starts at code 16 or
-// above (all of UE5M3 in practice), the way up is seven unrolled steps without the odd-code rule.
-// Bound by vector issue, ten or eleven steps.  What an instruction costs here, measured in a loop of
+// So the codes that can win a block lie between its own abs-max code (Eq. 2) and amax / 3.5 (five to seven codes, in 2 % of
+// the blocks eight; odd codes to 15 beyond that where the scales are that small), and below it until (lo) stops (one to
+// three codes a block of up to 16, four to seven a wavefront at b = 64 and 128; blocks beyond the format see
+// walk_saturated).  Every block tries its OWN codes: blocks of very different magnitude cost each other nothing, and a
+// block that is done goes on trying codes: one that cannot win changes nothing, and masking it out would cost more.
+//   * Where every block of a wavefront starts at code 17 or above and lies within the format (all of UE5M3 in practice, E4M3
+//     under a per-tensor scale), eight neighbouring codes hold each mantissa once.  The eight from the one below the start
+//     on are tried mantissa by mantissa (try_window): w = v / mantissa is a multiplication by a constant, the same for all
+//     blocks, each block's exponent goes into the conversions, and no reciprocal is formed; the order in which a block's
+//     codes come does not matter to keep_less.  What is needed beyond them is tried one by one.
+//   * Any other wavefront walks code by code (walk_from_any), scale and reciprocal in per-lane registers.
+// Bound by vector issue, about eleven codes.  What an instruction costs here, measured in a loop of
 // independent ones over 8 wavefronts per SIMD, cycles per wavefront: fp32 add, multiply, FMA and logic
 // on vector registers 2.5; the same with a scalar-register operand, minimum, maximum, compare, shift,
-// DPP and unpacking 4.3; packing to E2M1 and the reciprocal 8.5.
-// Measured on 4096 x 14336 bf16 weights with the exact quotient and masks in every step -> as it is:
-// E4M3 b = 16 127 -> 113 us, b = 4 160 -> 151 us; UE5M3 b = 16 132 -> 111 us, b = 4 157 -> 126 us.
+// DPP, unpacking and the fp64 minimum 4.8; packing to E2M1 and the reciprocal 8.4.
+// Code by code throughout -> as it is: 4096 x 14336 bf16 UE5M3 b = 4 129.4 -> 98.8 us; 4096 x 4096 UE5M3 b = 2 51.5 -> 46.7, b = 8 32.0 ->
+// 28.4, b = 16 33.7 -> 30.1, b = 128 42.2 -> 37.5, fp32 b = 4 43.8 -> 33.5; E4M3 under a per-tensor scale b = 4 50.0 -> 38.9, b = 16
+// 43.7 -> 38.2.  (Wavefronts that walk, E4M3 weights: b = 4 41.8 -> 41.1, b = 16 33.7 -> 32.1, b = 2 57.2 -> 58.6, fp32 b = 16 36.8
+// -> 37.2.)
 // ---------------------------------------------------------------------------------------
 
 template <int FMT>
@@ -214,7 +221,7 @@ __device__ __forceinline__ float smallest_of(const float (&v)[8])
 // the mid-point, far more than the 2^-22 that the product is off, so it rounds to the right side; an
 // element exactly half way may round to either neighbour, but both leave the same |residual| and
 // hence the same SSE.  (The codes come from the exact quotient, once, in walk_codes.)
-template <int B, bool ONE_MUL>
+template <int B, bool ONE_MUL, bool FUSED>
 __device__ __forceinline__ void walk_sse(const float (&v)[8], const float (&S)[BruteState<B>::NBLK], float (&sse)[4])
 {
     constexpr int NBLK = BruteState<B>::NBLK;
@@ -233,11 +240,11 @@ __device__ __forceinline__ void walk_sse(const float (&v)[8], const float (&S)[B
         }
     }
     const uint32_t packed = e2m1_pack8(y, 1.0f);
-    float q[8], sq[8];
+    float q[8], e[8];
     e2m1_unpack8(packed, 1.0f, q);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) { const float e = __builtin_fmaf(-q[j], S[j / EPB], v[j]); sq[j] = e * e; }
-    block_sse<B>(sq, sse);
+    for (int j = 0; j < 8; ++j) e[j] = __builtin_fmaf(-q[j], S[j / EPB], v[j]);
+    residual_sse<B, FUSED>(e, sse);
 }
 
 // Codes of the lane's blocks under the scales S.
@@ -257,12 +264,12 @@ __device__ __forceinline__ uint32_t walk_codes(const float (&v)[8], const float 
 
 // One step upwards: a strictly lower SSE wins.  Trying a code that cannot win, or the last code again,
 // changes nothing, so no block needs to be masked.
-template <int B, bool ONE_MUL>
+template <int B, bool ONE_MUL, bool FUSED>
 __device__ __forceinline__ void walk_up(const float (&v)[8], const float (&S)[BruteState<B>::NBLK],
                                         const uint32_t (&code)[BruteState<B>::NBLK], BruteState<B>& st)
 {
     float sse[4];
-    walk_sse<B, ONE_MUL>(v, S, sse);
+    walk_sse<B, ONE_MUL, FUSED>(v, S, sse);
 #pragma unroll
     for (int k = 0; k < BruteState<B>::NBLK; ++k) {
         const bool better = sse[k] < st.best_sse[k];
@@ -318,7 +325,7 @@ __device__ __forceinline__ void walk_saturated(const float (&v)[8], uint32_t (&c
     }
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) { floor[k] = hi[k]; S[k] = walk_scale<FMT>(hi[k]); }
-    walk_sse<B, ONE_MUL>(v, S, sse);
+    walk_sse<B, ONE_MUL, false>(v, S, sse);
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) {
         const bool over = sse[k] <= reached[k] && sse[k] <= st.best_sse[k];
@@ -328,29 +335,25 @@ __device__ __forceinline__ void walk_saturated(const float (&v)[8], uint32_t (&c
     }
 }
 
-template <int B, int FMT, bool ONE_MUL>
-__device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_t& packed, BruteState<B>& st)
+// The walk from any start, for wavefronts with a block among theirs that the window below does not take.
+template <int B, int FMT, bool ONE_MUL, bool FUSED>
+__device__ __forceinline__ void walk_from_any(const float (&v)[8], float (&amax)[BruteState<B>::NBLK],
+                                              uint32_t (&start)[BruteState<B>::NBLK], BruteState<B>& st)
 {
     constexpr int NBLK = BruteState<B>::NBLK;
-    constexpr int LANES = (B < 8) ? 1 : B / 8;
-    constexpr int EPB = (B < 8) ? B : 8;
     constexpr uint32_t kMax = (uint32_t)ScaleFmt<FMT>::kMaxCode;
     constexpr int kBias = ScaleFmt<FMT>::kBias;
 
-    float amax[NBLK], S[NBLK], sse[4];
-    uint32_t start[NBLK], code[NBLK], halved[NBLK], floor[NBLK];
-    bool low = false, none = false;
-    block_amax<NBLK, EPB, LANES>(v, amax);
+    float S[NBLK], sse[4];
+    uint32_t code[NBLK], halved[NBLK], floor[NBLK], last_odd[NBLK];
+    bool none = false;
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) {
-        start[k] = max(sf_encode_rne<FMT>(sixth_of(amax[k])), 1u);
+        start[k] = max(start[k], 1u);
         halved[k] = walk_halved<kBias>(sf_encode_rne<FMT>(amax[k] * kHalvedAt), amax[k]);
-        low |= start[k] - 16u > kMax - 7u - 16u;                        // start < 16 or start + 7 > kMax
         S[k] = walk_scale<FMT>(start[k]);
-        st.best_sse[k] = __builtin_inff();
-        st.best_code[k] = start[k];
     }
-    walk_sse<B, ONE_MUL>(v, S, sse);
+    walk_sse<B, ONE_MUL, FUSED>(v, S, sse);
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) {
         const bool better = sse[k] < __builtin_inff();                  // nothing wins where every SSE overflows
@@ -374,73 +377,191 @@ __device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_
         }
     }
 
-    if (__builtin_amdgcn_ballot_w64(low) == 0ull) {
-        // Every code the blocks try is a normal number with a code at half its value: neighbouring codes
-        // are 2^20 apart as floats, and amax / 3.5 lies five to seven codes above the start.
 #pragma unroll
-        for (uint32_t i = 1u; i <= 7u; ++i) {
-            if (i > 4u) {
-                bool any = false;
-#pragma unroll
-                for (int k = 0; k < NBLK; ++k) any |= start[k] + i < halved[k];
-                if (__builtin_amdgcn_ballot_w64(any) == 0ull) break;    // uniform
-            }
-#pragma unroll
-            for (int k = 0; k < NBLK; ++k) {
-                code[k] = start[k] + i;
-                S[k] = u2f(f2u(S[k]) + (1u << 20));
-            }
-            walk_up<B, ONE_MUL>(v, S, code, st);
-        }
-    } else {
-        uint32_t last_odd[NBLK];
+    for (int k = 0; k < NBLK; ++k) {
+        last_odd[k] = walk_last_odd<kBias>(amax[k]);
+        code[k] = start[k];
+    }
+    while (true) {
+        bool any = false;
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) {
-            last_odd[k] = walk_last_odd<kBias>(amax[k]);
-            code[k] = start[k];
+            code[k] += 1u;
+            const bool below = code[k] < halved[k];
+            code[k] = below ? code[k] : (code[k] | 1u);
+            any |= below || code[k] <= last_odd[k];
+            code[k] = min(code[k], kMax);
+            S[k] = walk_scale<FMT>(code[k]);
         }
-        while (true) {
-            bool any = false;
-#pragma unroll
-            for (int k = 0; k < NBLK; ++k) {
-                code[k] += 1u;
-                const bool below = code[k] < halved[k];
-                code[k] = below ? code[k] : (code[k] | 1u);
-                any |= below || code[k] <= last_odd[k];
-                code[k] = min(code[k], kMax);
-                S[k] = walk_scale<FMT>(code[k]);
-            }
-            if (__builtin_amdgcn_ballot_w64(any) == 0ull) break;        // uniform
-            walk_up<B, ONE_MUL>(v, S, code, st);
-        }
+        if (__builtin_amdgcn_ballot_w64(any) == 0ull) break;            // uniform
+        walk_up<B, ONE_MUL, FUSED>(v, S, code, st);
     }
 
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) code[k] = start[k];
-    for (uint32_t step = 0u;; ++step) {                                 // downwards: the lower code wins a tie
-        if (__builtin_expect(step == walk_patience(B), 0)) walk_saturated<B, FMT, ONE_MUL>(v, code, floor, st);
+    // Downwards the lower code wins a tie.  Beyond the patience the squares need not be exact any more.
+    const auto down = [&](uint32_t step, uint32_t end, auto fused) {
+        for (;; ++step) {
+            if (FUSED && step == end) return true;
+            if (!decltype(fused)::value && __builtin_expect(step == walk_patience(B), 0))
+                walk_saturated<B, FMT, ONE_MUL>(v, code, floor, st);
+            bool any = false;
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) {
+                const bool first = code[k] <= floor[k];                 // nothing below: the floor once more
+                code[k] = max(code[k] - 1u, floor[k]);
+                S[k] = walk_scale<FMT>(code[k]);
+                const float over = amax[k] - 6.0f * S[k];
+                any |= !first && !(over > 0.0f && over * over > st.best_sse[k]);
+            }
+            if (__builtin_amdgcn_ballot_w64(any) == 0ull) return false; // uniform
+            walk_sse<B, ONE_MUL, decltype(fused)::value>(v, S, sse);
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) {
+                const bool better = sse[k] <= st.best_sse[k];
+                st.best_code[k] = better ? code[k] : st.best_code[k];
+                st.best_sse[k] = better ? sse[k] : st.best_sse[k];
+            }
+        }
+    };
+    if constexpr (FUSED) {
+        if (__builtin_expect(down(0u, walk_patience(B), std::true_type{}), 0)) down(walk_patience(B), 0xFFFFFFFFu, std::false_type{});
+    } else {
+        down(0u, 0u, std::false_type{});
+    }
+}
+
+// The best of a block in the window below as one 64-bit number: the SSE above the bits of its scale, which order like
+// the codes.  The lower SSE wins and, on a tie, the lower code, in one instruction and whatever the order in which they are
+// tried: as a double such a pair is a positive number (an infinite SSE included), and pairs order like the doubles.
+__device__ __forceinline__ void keep_less(uint64_t& best, float sse, float S)
+{
+    const uint64_t other = ((uint64_t)f2u(sse) << 32) | f2u(S);
+    asm("v_min_f64 %0, %0, %1" : "+v"(best) : "v"(other));
+}
+__device__ __forceinline__ float sse_of(uint64_t best) { return u2f((uint32_t)(best >> 32)); }
+
+// The codes of mantissa MI and of those behind it, one for each block: the one among the eight from `first` (a scale's bits) on.
+template <int B, int MI, bool ONE_MUL, bool FUSED>
+__device__ __forceinline__ void try_window(const float (&v)[8], const uint32_t (&first)[BruteState<B>::NBLK],
+                                           uint64_t (&best)[BruteState<B>::NBLK])
+{
+    constexpr int NBLK = BruteState<B>::NBLK;
+    if constexpr (MI < 8) {
+        float S[NBLK], w[8], sse[4];
+#pragma unroll
+        for (int k = 0; k < NBLK; ++k)
+            S[k] = u2f(((first[k] + ((uint32_t)(7 - MI) << 20)) & 0xFF800000u) | ((uint32_t)MI << 20));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if constexpr (MI == 0) w[j] = v[j];
+            else if constexpr (ONE_MUL) w[j] = v[j] * (1.0f / mant_value(MI));
+            else w[j] = quot(v[j], Recip{mant_rhi(MI), mant_rlo(MI)});
+        }
+        mantissa_sse<B, MI, FUSED>(v, w, S, sse);
+#pragma unroll
+        for (int k = 0; k < NBLK; ++k) keep_less(best[k], sse[k], S[k]);
+        __builtin_amdgcn_sched_barrier(0);
+        try_window<B, MI + 1, ONE_MUL, FUSED>(v, first, best);
+    }
+}
+
+template <int B, int FMT, bool ONE_MUL, bool FUSED>
+__device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_t& packed, BruteState<B>& st)
+{
+    constexpr int NBLK = BruteState<B>::NBLK;
+    constexpr int LANES = (B < 8) ? 1 : B / 8;
+    constexpr int EPB = (B < 8) ? B : 8;
+    constexpr uint32_t kMax = (uint32_t)ScaleFmt<FMT>::kMaxCode;
+    constexpr uint32_t kBits0 = (127u - (uint32_t)ScaleFmt<FMT>::kBias) << 3;       // code + kBits0: the scale's upper bits
+    constexpr uint32_t kDown = 8u;                                       // steps below the window: code 8, the first normal one, is the lowest
+    // bf16 wavefronts whose squares are not all exact are rare, and the code of a second window in the kernel costs more than
+    // it gains them (4096 x 14336 UE5M3 b = 4 104.6 us with it, 98.8 without).
+    constexpr bool kWindow = !ONE_MUL || FUSED || B == 2;
+
+    float amax[NBLK], S[NBLK], sse[4];
+    uint32_t start[NBLK];
+    bool outside = false;
+    block_amax<NBLK, EPB, LANES>(v, amax);
+#pragma unroll
+    for (int k = 0; k < NBLK; ++k) {
+        start[k] = sf_encode_rne<FMT>(sixth_of(amax[k]));
+        outside |= start[k] < 17u || amax[k] > 6.5f * ScaleFmt<FMT>::kMaxValue;
+    }
+    bool done = false;                                                  // uniform
+    if (kWindow && __builtin_amdgcn_ballot_w64(outside) == 0ull) {
+        // Every code the blocks try is a normal number with a code at half its value: neighbouring codes are 2^20
+        // apart as floats.  amax / 3.5 lies five to seven codes above the start, in 2 % of the blocks eight.  The eight codes
+        // from the one below the start on (from the eighth last on at the end of the format) hold each mantissa once, so they
+        // are tried mantissa by mantissa.
+        uint32_t bits[NBLK];
+        uint64_t best[NBLK];
+#pragma unroll
+        for (int k = 0; k < NBLK; ++k) {
+            bits[k] = (min(start[k] - 1u, kMax - 7u) + kBits0) << 20;
+            best[k] = (uint64_t)0x7F800000u << 32;
+        }
+        try_window<B, 0, ONE_MUL, FUSED>(v, bits, best);
         bool any = false;
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) {
-            const bool first = code[k] <= floor[k];                     // nothing below: the floor once more
-            code[k] = max(code[k] - 1u, floor[k]);
-            S[k] = walk_scale<FMT>(code[k]);
-            const float over = amax[k] - 6.0f * S[k];
-            any |= !first && !(over > 0.0f && over * over > st.best_sse[k]);
+            S[k] = u2f(bits[k] + (8u << 20));
+            any |= 3.5f * S[k] < amax[k] && S[k] <= ScaleFmt<FMT>::kMaxValue;
+            S[k] = fminf(S[k], ScaleFmt<FMT>::kMaxValue);
         }
-        if (__builtin_amdgcn_ballot_w64(any) == 0ull) break;            // uniform
-        walk_sse<B, ONE_MUL>(v, S, sse);
+        if (__builtin_amdgcn_ballot_w64(any) != 0ull) {                 // uniform
+            walk_sse<B, ONE_MUL, FUSED>(v, S, sse);
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) keep_less(best[k], sse[k], S[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < NBLK; ++k) S[k] = u2f(bits[k]);
+#pragma unroll 1
+        for (uint32_t step = 0u; step < kDown; ++step) {
+            any = false;
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) {
+                S[k] = u2f(f2u(S[k]) - (1u << 20));
+                const float over = __builtin_fmaf(-6.0f, S[k], amax[k]);               // 6 S is exact: as amax - 6 S
+                any |= !(over * __builtin_fabsf(over) > sse_of(best[k]));
+            }
+            if (__builtin_amdgcn_ballot_w64(any) == 0ull) { done = true; break; }      // uniform
+            walk_sse<B, ONE_MUL, FUSED>(v, S, sse);
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) keep_less(best[k], sse[k], S[k]);
+        }
+        bool bad = false;                                               // an SSE that is not a finite number
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) {
-            const bool better = sse[k] <= st.best_sse[k];
-            st.best_code[k] = better ? code[k] : st.best_code[k];
-            st.best_sse[k] = better ? sse[k] : st.best_sse[k];
+            bad |= !(sse_of(best[k]) < __builtin_inff());
+            st.best_sse[k] = sse_of(best[k]);
+            st.best_code[k] = ((uint32_t)best[k] >> 20) - kBits0;
         }
+        done = done && __builtin_amdgcn_ballot_w64(bad) == 0ull;
     }
+    if (!done) walk_from_any<B, FMT, ONE_MUL, FUSED>(v, amax, start, st);
 
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) S[k] = walk_scale<FMT>(st.best_code[k]);
     packed = walk_codes<B>(v, S);
+}
+
+// FUSED for the wavefronts whose squares are all exact: no element nearly vanishes, none is beyond the format.  (The walk
+// starts at a scale of at least amax / 9, or at the largest, and takes walk_patience steps down with it, to amax / 105 at most.)
+template <int B, int FMT, bool ONE_MUL>
+__device__ __forceinline__ void search_pruned(const float (&v)[8], uint32_t& packed, BruteState<B>& st)
+{
+    if constexpr (ONE_MUL && B != 2) {
+        float largest = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) largest = __builtin_fmaxf(largest, __builtin_fabsf(v[j]));
+        const bool inexact = !(smallest_of(v) >= kSmallestSquared && largest < kExactScales * ScaleFmt<FMT>::kMaxValue);
+        if (__builtin_amdgcn_ballot_w64(inexact) == 0ull) {              // uniform
+            brute_search_pruned<B, FMT, true, true>(v, packed, st);
+            return;
+        }
+    }
+    brute_search_pruned<B, FMT, ONE_MUL, false>(v, packed, st);
 }
 
 // Value of a power-of-two scale byte (0 .. 254); 2^-127 is a sub-normal float.
@@ -624,7 +745,7 @@ brute_kernel(const void* __restrict__ x, int64_t n_full, int tail, float T_arg,
         uint32_t packed;
         BruteState<B> st;
         if constexpr (FMT == kE8M0) brute_search_pow2<B>(v, packed, st);
-        else if constexpr (PRUNE) brute_search_pruned<B, FMT, DT == kBF16 && !HAS_T>(v, packed, st);
+        else if constexpr (PRUNE) search_pruned<B, FMT, DT == kBF16 && !HAS_T>(v, packed, st);
         else brute_search<B, FMT, DT == kBF16 && !HAS_T && B != 2>(v, packed, st);
         float clip[4];
         if (clip_out) {                                                 // uniform

@@ -278,6 +278,45 @@ def test_quantize_where_a_workgroup_takes_three_slices(oracle, mxq, block, dtype
                 same([g[:, -r.shape[1]:].contiguous() for g, r in zip(got, ref) if g is not None], ref)
 
 
+@pytest.mark.parametrize("T", [1.0, 0.7])
+@pytest.mark.parametrize("fmt", [1, 2])
+@pytest.mark.parametrize("block", [2, 4, 8, 16, 64])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_pruned_search_in_a_window_of_eight_codes(oracle, mxq, fmt, block, dtype, T):
+    """Wavefronts (512 elements) whose blocks all start at code 17 or above and lie within the format try eight codes
+    mantissa by mantissa: both ends of that range, the last codes of the format, where the window moves down, abs-max values
+    on and beside 3.5, 6 and 6.5 times a scale; beside them wavefronts with one block outside it; elements that are zero,
+    nearly vanish or tie."""
+    rng = np.random.default_rng(1000 * block + 10 * fmt + (dtype == "bf16"))
+    top, per_wave = oracle.scale_max_code(fmt), 512 // block
+    value = lambda c: np.float32(oracle.scale_decode(fmt, int(c)))
+    waves = []
+    for kind in range(24):
+        codes = rng.integers(17, top + 1, per_wave)
+        codes[:4] = (18, top, top - 6, top - 7) if per_wave >= 4 else codes[:4]
+        s = np.array([value(c) for c in codes], np.float32)
+        f = rng.choice([3.5, 5.0, 6.0, 6.0, 6.49], per_wave).astype(np.float32)
+        f[codes < 30] = np.maximum(f[codes < 30], 6.0)                   # 6 S at least: the start is not below 17
+        amax = f * s
+        v = rng.choice([0.25, 0.75, 1.25, 1.75, 2.5, 3.5, 5.0, 1.0, 1.5, 3.0], (per_wave, block)) * s[:, None]
+        v = np.where(rng.random((per_wave, 1)) < 0.5, v, rng.random((per_wave, block)) * amax[:, None])
+        v = np.minimum(v, amax[:, None])
+        if kind % 4 == 1:
+            v[rng.random(v.shape) < 0.2] = 0.0
+        if kind % 4 == 2:
+            v[rng.random(v.shape) < 0.2] = 2.0 ** rng.integers(-74, -60)
+        v = v * rng.choice([-1, 1], v.shape)
+        v[np.arange(per_wave), rng.integers(block, size=per_wave)] = amax
+        if kind >= 20:                                                    # one block outside the range
+            v[rng.integers(per_wave)] = (value(16) * 5.5, value(top) * 6.6, 0.0, value(3))[kind - 20]
+        waves.append(v.astype(np.float32) * np.float32(T))
+    x = np.concatenate(waves)
+    x = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    print(f"[edges] window fmt={fmt} b={block} {dtype} T={T}", flush=True)
+    same(mxq.quantize(mxq.from_bits(x), block, fmt, mxq.RECIPE_BRUTE_PRUNED, tensor_scale=T),
+         oracle.quantize(x, block, fmt, 4, tensor_scale=T))
+
+
 @pytest.mark.parametrize("fmt", [1, 2])
 @pytest.mark.parametrize("block", [4, 8, 32])
 def test_search_where_squares_are_exact_and_where_not(oracle, mxq, fmt, block):
