@@ -339,3 +339,53 @@ def test_search_where_squares_are_exact_and_where_not(oracle, mxq, fmt, block):
     ref = oracle.quantize(x, block, fmt, 4)
     for recipe in (mxq.RECIPE_BRUTE, mxq.RECIPE_BRUTE_PRUNED):
         same(mxq.quantize(mxq.from_bits(x), block, fmt, recipe), ref)
+
+
+@pytest.mark.parametrize("block", [2, 4, 16, 128])
+def test_histogram_at_the_edges_of_its_workgroups(oracle, mxq, block):
+    """A workgroup counts 64 KiB of codes or 32 KiB of scales: one for each array (which stores its counts), one for one and
+    two for the other, several; vectors that begin up to three dwords into the arrays, bytes outside them."""
+    rng = np.random.default_rng(block)
+    kib = 2048                                             # elements in a KiB of codes
+    sizes = {block, 8, 32, 40, kib, 64 * kib - 8, 64 * kib, 64 * kib + 8, 128 * kib, 128 * kib + 8, 200 * kib + 24}
+    sizes |= {(32 << 10) * block + d for d in (-8, 0, 8)} if block <= 16 else set()
+    for n in sorted(max(block, n // block * block) for n in sizes):
+        codes = rng.integers(0, 256, n // 2, dtype=np.uint8)
+        scales = (rng.integers(0, 256, n // block) if n % 3 else rng.integers(40, 44, n // block)).astype(np.uint8)
+        want = [np.bincount((np.stack([codes, codes >> 4]) & 7).ravel(), minlength=8), np.bincount(scales, minlength=256)]
+        for off in (0, 4, 12):
+            print(f"[edges] histogram b={block} n={n} offset={off}", flush=True)
+            c = torch.zeros(n // 2 + 16, dtype=torch.uint8, device="cuda")[off:off + n // 2]
+            s = torch.zeros(n // block + 16, dtype=torch.uint8, device="cuda")[off:off + n // block]
+            c.copy_(torch.from_numpy(codes)); s.copy_(torch.from_numpy(scales))
+            got = mxq.histogram(c.reshape(1, -1), s.reshape(1, -1), block)
+            assert all((g.cpu().numpy() == w).all() for g, w in zip(got, want))
+
+
+@pytest.mark.parametrize("block", [2, 4, 8, 32, 128])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_clip_sse_at_tile_edges(oracle, mxq, block, dtype):
+    """A loop over chunks of 256 lanes below 16384 of them, three at once from there on: part-filled last chunks, ragged tails;
+    small tensors and the ends of large ones against the oracle, large ones against their pieces."""
+    rng = np.random.default_rng(block)
+    line = 16384 * 2048
+    period = (rng.standard_normal(block * 40009) * 0.05).astype(np.float32)
+    x = torch.from_numpy(np.resize(period, line + 4 * 2048)).cuda().to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    last = 6 // block * block
+    for n in (block, 2048, 2048 + 8 * block + last, 2048 * 2048 + 2048 + last, line - 2048, line, line + 2048 + last, line + 3 * 2048 - block):
+        n = n // block * block
+        print(f"[edges] clip b={block} {dtype} n={n}", flush=True)
+        v = x[:n].reshape(1, n)
+        for fmt, T in ((1, 1.0), (0, 0.7)):
+            scales = torch.from_numpy(np.resize(rng.integers(0x10 if fmt else 0x70, 0x38 if fmt else 0x7C, 997), n // block).astype(np.uint8)).cuda().reshape(1, -1)
+            got = mxq.clip_sse(v, scales, block, fmt, tensor_scale=T)
+            end = min(n, 4 * 2048 + n % 2048)
+            bits = v[:, n - end:].contiguous()
+            bits = bits.cpu().numpy() if dtype == "f32" else bits.view(torch.int16).cpu().numpy().view(np.uint16)
+            ref = oracle.clip_sse(bits, scales[:, (n - end) // block:].cpu().numpy(), block, fmt, tensor_scale=T)
+            assert (got[:, (n - end) // block:].cpu().numpy().view(np.uint32) == ref.view(np.uint32)).all()
+            if n >= line - 2048:
+                cut = n // 3 // (4 * block) * (4 * block)
+                pieces = [mxq.clip_sse(v[:, i:j].clone(), scales[:, i // block:j // block].clone(), block, fmt, tensor_scale=T)
+                          for i, j in ((0, cut), (cut, 2 * cut), (2 * cut, n))]
+                assert torch.equal(got.view(torch.int32), torch.cat(pieces, 1).view(torch.int32))
