@@ -707,11 +707,10 @@ __device__ __forceinline__ void brute_clip_sse(const float (&v)[8], const float 
 }
 
 template <int DT, int B, int FMT, bool HAS_T, bool PRUNE>
-__global__ void __launch_bounds__(kThreads)
-brute_kernel(const void* __restrict__ x, int64_t n_full, int tail, float T_arg,
-             const float* __restrict__ absmax_dev, float* __restrict__ t_out,
-             uint32_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ sse_out,
-             float* __restrict__ clip_out)
+__device__ __forceinline__ void brute_body(const void* __restrict__ x, int64_t n_full, int tail, float T_arg,
+                                           const float* __restrict__ absmax_dev, float* __restrict__ t_out,
+                                           uint32_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ sse_out,
+                                           float* __restrict__ clip_out)
 {
     constexpr int NBLK = BruteState<B>::NBLK;
     constexpr int LANES = (B < 8) ? 1 : B / 8;
@@ -787,6 +786,27 @@ brute_kernel(const void* __restrict__ x, int64_t n_full, int tail, float T_arg,
     }
 }
 
+// One argument costs the host less than ten (see StreamKernelArgs).
+struct BruteKernelArgs {
+    const void* x;
+    int64_t n_full;
+    int tail;
+    float T;
+    const float* absmax_dev;
+    float* t_out;
+    uint32_t* codes;
+    uint8_t* scales;
+    float* sse;
+    float* clip;
+};
+
+template <int DT, int B, int FMT, bool HAS_T, bool PRUNE>
+__global__ void __launch_bounds__(kThreads)
+brute_kernel(const BruteKernelArgs a)
+{
+    brute_body<DT, B, FMT, HAS_T, PRUNE>(a.x, a.n_full, a.tail, a.T, a.absmax_dev, a.t_out, a.codes, a.scales, a.sse, a.clip);
+}
+
 template <int DT, int B, int FMT, bool PRUNE>
 static hipError_t launch_f(const StreamArgs& a)
 {
@@ -795,12 +815,9 @@ static hipError_t launch_f(const StreamArgs& a)
     const bool has_t = (a.absmax_dev != nullptr) || (a.T != 1.0f);
     const int64_t need = (n_full + (count != 0 ? 1 : 0) + kThreads - 1) / kThreads;
     const dim3 grid((unsigned)(need < 256 * 8 ? need : 256 * 8)), block(kThreads);
-    if (has_t)
-        hipLaunchKernelGGL((brute_kernel<DT, B, FMT, true, PRUNE>), grid, block, 0, a.stream, a.x, n_full, count, a.T,
-                           a.absmax_dev, a.t_out, (uint32_t*)a.codes, a.scales, a.sse, a.clip);
-    else
-        hipLaunchKernelGGL((brute_kernel<DT, B, FMT, false, PRUNE>), grid, block, 0, a.stream, a.x, n_full, count, a.T,
-                           a.absmax_dev, a.t_out, (uint32_t*)a.codes, a.scales, a.sse, a.clip);
+    const BruteKernelArgs args{a.x, n_full, count, a.T, a.absmax_dev, a.t_out, (uint32_t*)a.codes, a.scales, a.sse, a.clip};
+    if (has_t) hipLaunchKernelGGL((brute_kernel<DT, B, FMT, true, PRUNE>), grid, block, 0, a.stream, args);
+    else hipLaunchKernelGGL((brute_kernel<DT, B, FMT, false, PRUNE>), grid, block, 0, a.stream, args);
     return hipGetLastError();
 }
 
