@@ -58,7 +58,7 @@ def _calls_command():
             "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include/torch/csrc/api/include"),
             "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
             os.path.join(CSRC, "binding.cpp"), "-o", CALLS, "-L" + os.path.join(root, "lib"),
-            "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+            "-ltorch_python", "-ltorch_hip", "-ltorch_cpu", "-lc10_hip", "-lc10"]
 
 
 def build_calls(verbose: bool = False) -> str | None:

@@ -8,7 +8,9 @@
 #include <Python.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <ATen/hip/EmptyTensor.h>
 #include <ATen/ops/empty.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
@@ -85,8 +87,13 @@ void* ptr(const at::Tensor& t) { return t.data_ptr(); }
 
 void* stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
 
+// What at::empty ends at for a GPU, without its two dispatches (0.70 -> 0.47 us, three of them in a small call of 6 us), where
+// nothing has asked to see them: a tracer or a transform adds its key to the thread's.
 at::Tensor new_empty(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like)
 {
+    const c10::DispatchKeySet added = c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set;
+    if (added.empty() && !at::globalContext().deterministicAlgorithms())       // those have new memory filled
+        return at::detail::empty_cuda(shape, type, like.device(), std::nullopt);
     return at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
 }
 

@@ -237,3 +237,43 @@ def test_native_forms_in_a_captured_graph(monkeypatch):
             for name, (_, python) in calls.items():
                 for g, w in zip(flat(captured[name]), flat(python())):
                     assert torch.equal(g.view(torch.uint8), w.view(torch.uint8)), (seed, name)
+
+
+@pytest.mark.gpu
+def test_new_outputs_of_the_native_calls_are_those_of_torch_empty():
+    """Allocated without torch's dispatcher where nothing watches it: the same kind of tensor in inference mode, on the
+    inputs' device and in the caching allocator's books, and through the dispatcher where deterministic mode fills new memory
+    or a transform is active."""
+    x = torch.randn((64, 64), device="cuda")
+    want = mxq.quantize(x, 16, 1, 0)
+
+    def same(got):
+        torch.cuda.synchronize()
+        for g, w in zip(got, want):
+            assert g.dtype == w.dtype and g.shape == w.shape and g.stride() == w.stride() and g.device == w.device
+            assert torch.equal(g, w) and not g.requires_grad and g.is_contiguous()
+
+    before = torch.cuda.memory_allocated()
+    got = mxq.quantize(x, 16, 1, 0)
+    assert torch.cuda.memory_allocated() - before == sum(-(-t.numel() * t.element_size() // 512) * 512 for t in got)
+    same(got)
+    with torch.inference_mode():
+        got = mxq.quantize(x, 16, 1, 0)
+        assert all(t.is_inference() for t in got)
+    same(got)
+    assert not any(t.is_inference() for t in mxq.quantize(x, 16, 1, 0))
+    torch.use_deterministic_algorithms(True)
+    try:
+        same(mxq.quantize(x, 16, 1, 0))
+    finally:
+        torch.use_deterministic_algorithms(False)
+    seen = []
+
+    def f(y):
+        seen.append(mxq.quantize(x, 16, 1, 0))
+        return y + 1
+
+    torch.func.vmap(f)(torch.zeros(3, device="cuda"))
+    same(seen[0])
+    with torch.no_grad():
+        same(mxq.quantize(x, 16, 1, 0))
