@@ -147,12 +147,12 @@ def algorithmic_bytes(kind, block, n, in_bytes):
 
 # pass name -> kernel instantiation as rocprofv3 prints it (for the recorded counter figures)
 KERNEL_OF_PASS = {
-    "absmax_e4m3_b16": "mxq::stream_kernel<0, 16, 1, false, 0, false>",
-    "absmax_pz_e4m3_b16": "mxq::stream_kernel<0, 16, 1, false, 0, false>",
-    "4over6_e4m3_b16": "mxq::stream_kernel<0, 16, 1, true, 0, false>",
-    "4over6_e4m3_b8": "mxq::stream_kernel<0, 8, 1, true, 0, false>",
-    "4over6_e4m3_b32": "mxq::stream_kernel<0, 32, 1, true, 0, false>",
-    "4over6_e4m3_b64": "mxq::stream_kernel<0, 64, 1, true, 0, false>",
+    "absmax_e4m3_b16": "mxq::stream_once_kernel<0, 16, 1, false, 0>",
+    "absmax_pz_e4m3_b16": "mxq::stream_once_kernel<0, 16, 1, false, 0>",
+    "4over6_e4m3_b16": "mxq::stream_once_kernel<0, 16, 1, true, 0>",
+    "4over6_e4m3_b8": "mxq::stream_once_kernel<0, 8, 1, true, 0>",
+    "4over6_e4m3_b32": "mxq::stream_once_kernel<0, 32, 1, true, 0>",
+    "4over6_e4m3_b64": "mxq::stream_once_kernel<0, 64, 1, true, 0>",
     "absmax_e4m3_b16_H": "mxq::stream_scaled_kernel<16, 1, false>",
     "4over6_e4m3_b16_H": "mxq::stream_scaled_kernel<16, 1, true>",
     "brute_e4m3_b16": "mxq::brute_kernel<0, 16, 1, false, false>",
