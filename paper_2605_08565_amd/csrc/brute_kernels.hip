@@ -546,8 +546,9 @@ __device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_
     packed = walk_codes<B>(v, S);
 }
 
-// FUSED for the wavefronts whose squares are all exact: no element nearly vanishes, none is beyond the format.  (The walk
-// starts at a scale of at least amax / 9, or at the largest, and takes walk_patience steps down with it, to amax / 105 at most.)
+// FUSED for the wavefronts whose squares are all exact: no element nearly vanishes, none is far beyond the format.  (The walk
+// starts at a scale of at least amax / 9, or at the largest, above amax / 128, and takes up to 16 steps (walk_patience) down with
+// it: from a normal code to a quarter of its value, amax / 512, or among the lowest codes to amax / 105.)
 template <int B, int FMT, bool ONE_MUL>
 __device__ __forceinline__ void search_pruned(const float (&v)[8], uint32_t& packed, BruteState<B>& st)
 {

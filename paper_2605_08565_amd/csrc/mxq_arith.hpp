@@ -167,18 +167,19 @@ MXQ_HD constexpr uint32_t walk_patience(int b) { return b <= 4 ? 3u : b == 8 ? 4
 
 // ---------------------------------------------------------------------------------------
 // Residuals whose squares are exact.  v a bf16 value (8 significant bits), S a scale of 4 bits with 2^e <= S < 2^(e+1),
-// r = v - q*S its residual under the E2M1 value q.  Where |v| < 128 S, r has at most 12 significant bits, so r*r has at
+// r = v - q*S its residual under the E2M1 value q.  Where |v| < 512 S, r has at most 12 significant bits, so r*r has at
 // most 24:
 //   q = 0:             r = v, 8 bits.
 //   |v| <= 6 S, q > 0: |v| >= S/4, so v is a multiple of 2^(e-9) and q*S of 2^(e-4); |r| <= S < 2^(e+1): 10 bits.
-//   |v| > 6 S:         with 2^k <= |v| < 2^(k+1), e+2 <= k <= e+7, v is a multiple of 2^(k-7) and q*S of 2^(e-4);
-//                      |r| < 2^(k+1): 8 bits for k = e+2, k-e+5 <= 12 beyond.
+//   |v| > 6 S:         q*S = 6 S is a multiple of 2^(e-2).  With 2^k <= |v| < 2^(k+1), e+2 <= k <= e+9, v is one of 2^(k-7);
+//                      |r| < 2^(k+1): 8 bits for k <= e+5, k-e+3 <= 12 beyond.
 // And r*r does not underflow below the fp32 grid where r is a multiple of 2^-74: a bf16 value from 2^-67 on is, and so
 // is q*S (S >= 2^-17).  So a square and its sum with another are one fused multiply-add with the bits of the two
 // separately rounded operations.
 // ---------------------------------------------------------------------------------------
 constexpr float kSmallestSquared = 0x1p-67f;     // every |v| of the wavefront is at least this (a zero is not)
-constexpr float kExactScales = 128.0f;           // and below this many times the scale
+// Below this many times a scale the squares are exact under it and, for the steps of a walk, down to a quarter of it.
+constexpr float kExactScales = 128.0f;
 
 // amax / 6 and amax / 4 in front of Round_SF (Eq. 2, M = 6; Eq. 4, M = 4): the first by the
 // two-part reciprocal above (6 has 2 significant bits), the second is exact.

@@ -4,9 +4,9 @@
 // Mapping: every lane owns 8 consecutive elements (one 128-bit load for bf16, two for fp32),
 // so a block of b >= 8 elements is b/8 neighbouring lanes of one DPP row and a block of
 // b < 8 sits inside a lane.  Per lane the kernel emits one dword of packed codes; the first
-// lane of a block emits the scale byte and the block SSE.  The next chunk's load is issued
-// before the current chunk is processed.  HBM-bound by design: algorithmic traffic is
-// sizeof(in) + 0.5 + 5/b bytes per element.
+// lane of a block emits the scale byte and the block SSE.  Loads are issued before what is processed
+// meanwhile: the next chunk's in a loop, or three chunks' at once in workgroups that end (large tensors).
+// HBM-bound by design: algorithmic traffic is sizeof(in) + 0.5 + 5/b bytes per element.
 #include "mxq_device.hpp"
 #include "mxq_launch.hpp"
 
