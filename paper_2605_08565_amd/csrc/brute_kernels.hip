@@ -191,7 +191,8 @@ __device__ __forceinline__ void try_binade(const float (&v)[8], const float (&w)
 //     under a per-tensor scale), eight neighbouring codes hold each mantissa once.  The eight from the one below the start
 //     on are tried mantissa by mantissa (try_window): w = v / mantissa is a multiplication by a constant, the same for all
 //     blocks, each block's exponent goes into the conversions, and no reciprocal is formed; the order in which a block's
-//     codes come does not matter to keep_less.  What is needed beyond them is tried one by one.
+//     codes come does not matter to keep_less.  What is needed beyond them is tried one by one, after eight steps down
+//     as in the walk, from where they ended.
 //   * Any other wavefront walks code by code (walk_from_any), scale and reciprocal in per-lane registers.
 // Bound by vector issue, about eleven codes.  What an instruction costs here, measured in a loop of
 // independent ones over 8 wavefronts per SIMD, cycles per wavefront: fp32 add, multiply, FMA and logic
@@ -335,7 +336,7 @@ __device__ __forceinline__ void walk_saturated(const float (&v)[8], uint32_t (&c
     }
 }
 
-// The walk from any start, for wavefronts with a block among theirs that the window below does not take.
+// The way up from any start, for wavefronts with a block among theirs that the window below does not take.
 template <int B, int FMT, bool ONE_MUL, bool FUSED>
 __device__ __forceinline__ void walk_from_any(const float (&v)[8], float (&amax)[BruteState<B>::NBLK],
                                               uint32_t (&start)[BruteState<B>::NBLK], BruteState<B>& st)
@@ -345,7 +346,7 @@ __device__ __forceinline__ void walk_from_any(const float (&v)[8], float (&amax)
     constexpr int kBias = ScaleFmt<FMT>::kBias;
 
     float S[NBLK], sse[4];
-    uint32_t code[NBLK], halved[NBLK], floor[NBLK], last_odd[NBLK];
+    uint32_t code[NBLK], halved[NBLK], last_odd[NBLK];
     bool none = false;
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) {
@@ -359,7 +360,6 @@ __device__ __forceinline__ void walk_from_any(const float (&v)[8], float (&amax)
         const bool better = sse[k] < __builtin_inff();                  // nothing wins where every SSE overflows
         st.best_code[k] = better ? start[k] : 1u;
         st.best_sse[k] = better ? sse[k] : __builtin_inff();
-        floor[k] = 1u;
         none |= !better;
     }
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(none) != 0ull, 0)) {                    // uniform
@@ -396,11 +396,20 @@ __device__ __forceinline__ void walk_from_any(const float (&v)[8], float (&amax)
         if (__builtin_amdgcn_ballot_w64(any) == 0ull) break;            // uniform
         walk_up<B, ONE_MUL, FUSED>(v, S, code, st);
     }
+}
 
+// The way down from `code`, `step` steps of which have been taken: the lower code wins a tie.  Beyond the patience the
+// squares need not be exact any more.
+template <int B, int FMT, bool ONE_MUL, bool FUSED>
+__device__ __forceinline__ void walk_down(const float (&v)[8], const float (&amax)[BruteState<B>::NBLK],
+                                          uint32_t (&code)[BruteState<B>::NBLK], uint32_t step, BruteState<B>& st)
+{
+    constexpr int NBLK = BruteState<B>::NBLK;
+    float S[NBLK], sse[4];
+    uint32_t floor[NBLK];
 #pragma unroll
-    for (int k = 0; k < NBLK; ++k) code[k] = start[k];
-    // Downwards the lower code wins a tie.  Beyond the patience the squares need not be exact any more.
-    const auto down = [&](uint32_t step, uint32_t end, auto fused) {
+    for (int k = 0; k < NBLK; ++k) floor[k] = 1u;
+    const auto down = [&](uint32_t end, auto fused) {
         for (;; ++step) {
             if (FUSED && step == end) return true;
             if (!decltype(fused)::value && __builtin_expect(step == walk_patience(B), 0))
@@ -425,9 +434,9 @@ __device__ __forceinline__ void walk_from_any(const float (&v)[8], float (&amax)
         }
     };
     if constexpr (FUSED) {
-        if (__builtin_expect(down(0u, walk_patience(B), std::true_type{}), 0)) down(walk_patience(B), 0xFFFFFFFFu, std::false_type{});
+        if (__builtin_expect(down(walk_patience(B), std::true_type{}), 0)) down(0xFFFFFFFFu, std::false_type{});
     } else {
-        down(0u, 0u, std::false_type{});
+        down(0u, std::false_type{});
     }
 }
 
@@ -474,7 +483,6 @@ __device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_
     constexpr int EPB = (B < 8) ? B : 8;
     constexpr uint32_t kMax = (uint32_t)ScaleFmt<FMT>::kMaxCode;
     constexpr uint32_t kBits0 = (127u - (uint32_t)ScaleFmt<FMT>::kBias) << 3;       // code + kBits0: the scale's upper bits
-    constexpr uint32_t kDown = 8u;                                       // steps below the window: code 8, the first normal one, is the lowest
     // bf16 wavefronts whose squares are not all exact are rare, and the code of a second window in the kernel costs more than
     // it gains them (4096 x 14336 UE5M3 b = 4 104.6 us with it, 98.8 without).
     constexpr bool kWindow = !ONE_MUL || FUSED || B == 2;
@@ -488,7 +496,8 @@ __device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_
         start[k] = sf_encode_rne<FMT>(sixth_of(amax[k]));
         outside |= start[k] < 17u || amax[k] > 6.5f * ScaleFmt<FMT>::kMaxValue;
     }
-    bool done = false;                                                  // uniform
+    uint32_t step = 0u;                                                  // uniform: steps down so far
+    bool done = false, whole = true;                                    // uniform: over, all codes are still to be tried
     if (kWindow && __builtin_amdgcn_ballot_w64(outside) == 0ull) {
         // Every code the blocks try is a normal number with a code at half its value: neighbouring codes are 2^20
         // apart as floats.  amax / 3.5 lies five to seven codes above the start, in 2 % of the blocks eight.  The eight codes
@@ -498,7 +507,7 @@ __device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_
         uint64_t best[NBLK];
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) {
-            bits[k] = (min(start[k] - 1u, kMax - 7u) + kBits0) << 20;
+            bits[k] = (window_first(start[k], kMax) + kBits0) << 20;
             best[k] = (uint64_t)0x7F800000u << 32;
         }
         try_window<B, 0, ONE_MUL, FUSED>(v, bits, best);
@@ -517,7 +526,7 @@ __device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) S[k] = u2f(bits[k]);
 #pragma unroll 1
-        for (uint32_t step = 0u; step < kDown; ++step) {
+        for (uint32_t i = 0u; i < kWindowDown; ++i) {
             any = false;
 #pragma unroll
             for (int k = 0; k < NBLK; ++k) {
@@ -537,9 +546,18 @@ __device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_
             st.best_sse[k] = sse_of(best[k]);
             st.best_code[k] = ((uint32_t)best[k] >> 20) - kBits0;
         }
-        done = done && __builtin_amdgcn_ballot_w64(bad) == 0ull;
+        whole = __builtin_amdgcn_ballot_w64(bad) != 0ull;
+        done = done && !whole;
+        if (!done && !whole) {
+            step = window_steps(B);
+#pragma unroll
+            for (int k = 0; k < NBLK; ++k) start[k] = (f2u(S[k]) >> 20) - kBits0;
+        }
     }
-    if (!done) walk_from_any<B, FMT, ONE_MUL, FUSED>(v, amax, start, st);
+    if (!done) {
+        if (whole) walk_from_any<B, FMT, ONE_MUL, FUSED>(v, amax, start, st);
+        walk_down<B, FMT, ONE_MUL, FUSED>(v, amax, start, step, st);
+    }
 
 #pragma unroll
     for (int k = 0; k < NBLK; ++k) S[k] = walk_scale<FMT>(st.best_code[k]);

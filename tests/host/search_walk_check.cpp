@@ -1,17 +1,21 @@
 /*
  * The pruned scale search on the CPU, one block at a time, with the scalar rules of mxq_arith.hpp that
- * the kernel uses (walk_scale_bias, walk_halved, walk_last_odd, saturation_loss, walk_patience, the
- * quotients) and the kernel's order of steps: abs-max code, up, down, with a floor for long ways down.  The winner and its
+ * the kernel uses (walk_scale_bias, walk_halved, walk_last_odd, saturation_loss, walk_patience, window_first, window_steps,
+ * the quotients) and the kernel's order of steps: blocks that the window takes try its eight codes mantissa by mantissa, the
+ * one above where it is needed and up to kWindowDown below, the best kept by the order of (SSE, scale) pairs as doubles;
+ * the others the abs-max code, up; both go on down from there, with a floor for long ways.  The winner and its
  * SSE must be those of the full enumeration, and no block may cost many candidates.
  *
  * Blocks: every scale code times the factors at which the rules switch and their neighbours, over grid
  * points and ties; random blocks of every magnitude from 2^-40 to overflow; NaN and infinity.
- * Prints "<name> cases=<n> bad=<m> most=<candidates of the costliest block>".
+ * Prints "<name> cases=<n> bad=<m> most=<candidates of the costliest block> window=<blocks that it decided> on=<blocks that
+ * went on down behind it>".
  */
 #include <math.h>
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
+#include <string.h>
 
 #include <vector>
 
@@ -40,6 +44,7 @@ static float tree(std::vector<float> s)
 template <int BIAS, int MAX, bool ONE_MUL> struct Search {
     std::vector<float> v;
     int tried = 0;
+    bool in_window = false, went_on = false;
 
     float sse(uint32_t code, bool exact = false)
     {
@@ -49,6 +54,21 @@ template <int BIAS, int MAX, bool ONE_MUL> struct Search {
         for (size_t i = 0; i < v.size(); ++i) {
             const float y = (ONE_MUL && !exact) ? v[i] * (1.0f / S) : quot(v[i], r);
             const float e = fmaf(-e2m1(y), S, v[i]);
+            sq[i] = e * e;
+        }
+        return tree(sq);
+    }
+    /* Under the same code from quotients by its mantissa alone, as in the window. */
+    float sse_by_mantissa(uint32_t code)
+    {
+        const float m = 1.0f + 0.125f * (float)(code & 7u), pow2 = walk_scale_bias<BIAS>(code) / m;
+        const double inverse = 1.0 / (double)m;
+        const float hi = (double)(float)inverse > inverse ? u2f(f2u((float)inverse) - 1u) : (float)inverse;
+        const Recip r{hi, (float)(inverse - (double)hi)};
+        std::vector<float> sq(v.size());
+        for (size_t i = 0; i < v.size(); ++i) {
+            const float w = (code & 7u) == 0u ? v[i] : ONE_MUL ? v[i] * (1.0f / m) : quot(v[i], r);
+            const float e = fmaf(-(e2m1(w / pow2) * pow2), m, v[i]);
             sq[i] = e * e;
         }
         return tree(sq);
@@ -70,40 +90,86 @@ template <int BIAS, int MAX, bool ONE_MUL> struct Search {
         }
     }
 
+    /* The window and the codes below it.  False: all codes are still to be tried.  `done`: over; else the walk goes on down
+       from `code`. */
+    bool window(uint32_t& best, float& best_sse, float amax, uint32_t start, uint32_t& code, bool& done)
+    {
+        if (start < 17u || amax > 6.5f * walk_scale_bias<BIAS>(MAX)) return false;
+        const uint32_t first = window_first(start, (uint32_t)MAX), above = first + 8u;
+        uint64_t least = (uint64_t)0x7F800000u << 32;
+        auto keep = [&](uint32_t c, float s) {
+            ++tried;
+            const uint64_t other = ((uint64_t)f2u(s) << 32) | c;
+            double x, y;
+            memcpy(&x, &least, 8);
+            memcpy(&y, &other, 8);
+            x = fmin(x, y);
+            memcpy(&least, &x, 8);
+        };
+        for (uint32_t m = 0u; m < 8u; ++m) {
+            const uint32_t c = ((first + 7u - m) & ~7u) | m;
+            keep(c, sse_by_mantissa(c));
+        }
+        if (above <= (uint32_t)MAX && 3.5f * walk_scale_bias<BIAS>(above) < amax) keep(above, sse(above));
+        done = false;
+        code = first;
+        for (uint32_t i = 0u; i < kWindowDown; ++i) {
+            code -= 1u;
+            const float over = fmaf(-6.0f, walk_scale_bias<BIAS>(code), amax);
+            if (over * fabsf(over) > u2f((uint32_t)(least >> 32))) { done = true; break; }
+            keep(code, sse(code));
+        }
+        best = (uint32_t)least;
+        best_sse = u2f((uint32_t)(least >> 32));
+        return best_sse < INFINITY;
+    }
+
     void walk(uint32_t& best, float& best_sse)
     {
         float amax = 0.0f;
         for (float x : v) amax = fmaxf(amax, fabsf(x));
         const float top = walk_scale_bias<BIAS>(MAX);
-        uint32_t start = sf_encode_bits<BIAS>(fminf(sixth_of(amax), top));
-        if (start < 1u) start = 1u;
-        uint32_t halved = walk_halved<BIAS>(sf_encode_bits<BIAS>(fminf(amax * kHalvedAt, top)), amax), floor = 1u;
-        const bool low = start < 16u || start + 7u > (uint32_t)MAX;
-        auto up = [&](uint32_t c) { ++tried; const float s = sse(c); if (s < best_sse) { best = c; best_sse = s; } };
+        uint32_t start = sf_encode_bits<BIAS>(fminf(sixth_of(amax), top)), code = 0u, step = 0u;
+        bool done = false;
+        if (window(best, best_sse, amax, start, code, done)) {
+            in_window = true;
+            if (done) return;
+            went_on = true;
+            step = window_steps((int)v.size());
+        } else {
+            up_from(best, best_sse, amax, start, top);
+            code = start;
+        }
+        down_from(best, best_sse, amax, code, step);
+    }
 
+    void up_from(uint32_t& best, float& best_sse, float& amax, uint32_t& start, float top)
+    {
+        if (start < 1u) start = 1u;
+        uint32_t halved = walk_halved<BIAS>(sf_encode_bits<BIAS>(fminf(amax * kHalvedAt, top)), amax);
         const float first = sse(start);
         ++tried;
         best = first < INFINITY ? start : 1u;
         best_sse = first < INFINITY ? first : INFINITY;
         if (!(first < INFINITY) && (first != first || loss(start) == INFINITY)) { start = 1u; halved = 1u; amax = 0.0f; }
-        if (!low) {
-            for (uint32_t i = 1u; i <= 7u; ++i) {
-                if (i > 4u && start + i >= halved) break;
-                up(start + i);
-            }
-        } else {
-            const uint32_t last_odd = walk_last_odd<BIAS>(amax);
-            for (uint32_t c = start;;) {
-                c += 1u;
-                const bool below = c < halved;
-                c = below ? c : (c | 1u);
-                const bool go = below || c <= last_odd;
-                c = c < (uint32_t)MAX ? c : (uint32_t)MAX;
-                if (!go) break;
-                up(c);
-            }
+        const uint32_t last_odd = walk_last_odd<BIAS>(amax);
+        for (uint32_t c = start;;) {
+            c += 1u;
+            const bool below = c < halved;
+            c = below ? c : (c | 1u);
+            const bool go = below || c <= last_odd;
+            c = c < (uint32_t)MAX ? c : (uint32_t)MAX;
+            if (!go) break;
+            ++tried;
+            const float s = sse(c);
+            if (s < best_sse) { best = c; best_sse = s; }
         }
-        for (uint32_t c = start, step = 0u;; ++step) {
+    }
+
+    void down_from(uint32_t& best, float& best_sse, float amax, uint32_t c, uint32_t step)
+    {
+        uint32_t floor = 1u;
+        for (;; ++step) {
             if (step == walk_patience((int)v.size())) {
                 uint32_t hi = c;
                 const float reached = loss(c);
@@ -136,7 +202,7 @@ static double uniform()
 static double normal() { return sqrt(-2.0 * log(uniform() + 1e-300)) * cos(6.283185307179586 * uniform()); }
 static float as_bf16(float f) { return u2f(f2u(f) & 0xFFFF0000u); }
 
-struct Count { long n = 0, bad = 0; int most = 0; };
+struct Count { long n = 0, bad = 0, window = 0, on = 0; int most = 0; };
 
 template <int BIAS, int MAX, bool BF16>
 static void one(Count& c, std::vector<float> v)
@@ -153,12 +219,14 @@ static void one(Count& c, std::vector<float> v)
         if (c.bad++ < 5) printf("  bias %d b %zu: code %u sse %g, full search %u %g; v0 = %a\n", BIAS, v.size(), b, y, a, x, v[0]);
     }
     if (s.tried > c.most) c.most = s.tried;
+    c.window += s.in_window;
+    c.on += s.went_on;
 }
 
 template <int BIAS, int MAX, bool BF16>
 static void run(const char* fmt)
 {
-    const int sizes[4] = {2, 4, 16, 128};
+    const int sizes[5] = {2, 4, 16, 32, 128};
     Count edges, inside, beyond, special;
     /* the factors of a scale at which a rule switches, and the neighbours of the abs-max there */
     for (uint32_t code = 1u; code <= (uint32_t)MAX; ++code) {
@@ -175,8 +243,8 @@ static void run(const char* fmt)
     }
     for (int e = -40; e <= 126; e += 3)
         for (int b : sizes)
-            for (int kind = 0; kind < 6; ++kind)
-                for (int rep = 0; rep < (b == 128 ? 2 : 8); ++rep) {
+            for (int kind = 0; kind < 8; ++kind)
+                for (int rep = 0; rep < (b >= 32 ? 2 : 8); ++rep) {
                     std::vector<float> v(b);
                     for (int i = 0; i < b; ++i) {
                         double z = normal();
@@ -185,6 +253,8 @@ static void run(const char* fmt)
                         if (kind == 3 && i == 0) z = 50.0;                                /* one outlier */
                         if (kind == 4) z *= pow(2.0, -20.0 * uniform());                  /* magnitudes mixed */
                         if (kind == 5) z *= (i & 1) ? 1.0 : 0x1p-12;
+                        if (kind == 6) z = 2.0 * uniform() - 1.0;                         /* light tails: a long way down */
+                        if (kind == 7) z = i == 0 ? 6.0 : uniform() < 0.5 ? 5.0 : -2.5;   /* on ties under the abs-max code */
                         v[i] = (float)ldexp(z, e);
                         if (!isfinite(v[i])) v[i] = 3e38f;
                     }
@@ -201,7 +271,8 @@ static void run(const char* fmt)
                 one<BIAS, MAX, BF16>(special, v);
             }
     const struct { const char* name; Count* c; } all[4] = {{"edges", &edges}, {"inside", &inside}, {"beyond", &beyond}, {"special", &special}};
-    for (auto& a : all) printf("%s_%s_%s cases=%ld bad=%ld most=%d\n", fmt, BF16 ? "bf16" : "f32", a.name, a.c->n, a.c->bad, a.c->most);
+    for (auto& a : all) 
+        printf("%s_%s_%s cases=%ld bad=%ld most=%d window=%ld on=%ld\n", fmt, BF16 ? "bf16" : "f32", a.name, a.c->n, a.c->bad, a.c->most, a.c->window, a.c->on);
 }
 
 int main()

@@ -317,6 +317,31 @@ def test_pruned_search_in_a_window_of_eight_codes(oracle, mxq, fmt, block, dtype
          oracle.quantize(x, block, fmt, 4, tensor_scale=T))
 
 
+@pytest.mark.parametrize("T", [1.0, 0.7])
+@pytest.mark.parametrize("fmt", [1, 2])
+@pytest.mark.parametrize("block", [2, 16, 32, 64, 128])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_pruned_search_goes_on_down_behind_its_window(oracle, mxq, fmt, block, dtype, T):
+    """Blocks that the window takes and whose best code may lie more than eight below it: values spread evenly over their
+    range (b = 128: some 15 steps down), and two-valued blocks, in wavefronts of their own, mixed with ordinary blocks and
+    with a NaN among them (for which all codes are tried again)."""
+    rng = np.random.default_rng(7 * block + fmt)
+    per_wave = 512 // block
+    even = rng.uniform(-1, 1, (12 * per_wave, block)) * 2.0 ** rng.integers(-1, 6, (12 * per_wave, 1))
+    two = np.where(rng.random((6 * per_wave, block)) < 0.5, 1.0, rng.uniform(0.05, 0.6, (6 * per_wave, 1))) * rng.choice([-1, 1], (6 * per_wave, block))
+    mixed = rng.standard_normal((6 * per_wave, block))
+    mixed[::3] = rng.uniform(-1, 1, mixed[::3].shape)
+    x = (np.concatenate([even, two, mixed]) * T).astype(np.float32)
+    x[-per_wave * 2, 0] = np.nan
+    x = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    print(f"[edges] behind the window fmt={fmt} b={block} {dtype} T={T}", flush=True)
+    got = mxq.quantize(mxq.from_bits(x), block, fmt, mxq.RECIPE_BRUTE_PRUNED, tensor_scale=T)
+    ref = oracle.quantize(x, block, fmt, 4, tensor_scale=T)
+    rows = np.arange(x.shape[0]) != x.shape[0] - per_wave * 2
+    assert (got[1].cpu().numpy() == ref[1]).all()                          # the block of the NaN too: code 1
+    same([g.cpu()[torch.from_numpy(rows)].cuda() for g in got], [r[rows] for r in ref])
+
+
 @pytest.mark.parametrize("fmt", [1, 2])
 @pytest.mark.parametrize("block", [4, 8, 32])
 def test_search_where_squares_are_exact_and_where_not(oracle, mxq, fmt, block):
