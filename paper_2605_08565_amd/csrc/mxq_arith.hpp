@@ -186,7 +186,11 @@ MXQ_HD constexpr uint32_t window_steps(int b) { return walk_patience(b) < kWindo
 // is q*S (S >= 2^-17).  So a square and its sum with another are one fused multiply-add with the bits of the two
 // separately rounded operations.
 // ---------------------------------------------------------------------------------------
-constexpr float kSmallestSquared = 0x1p-67f;     // every |v| of the wavefront is at least this (a zero is not)
+// A zero leaves a residual of zero: only other elements below kSmallestSquared are too small.  Their magnitudes by rank, a
+// zero's above all, so that a minimum over many tells whether one of them is.
+constexpr float kSmallestSquared = 0x1p-67f;
+MXQ_HD constexpr uint32_t square_rank(uint32_t float_bits) { return (float_bits << 1) - 1u; }
+constexpr uint32_t kSmallestSquareRank = square_rank(__builtin_bit_cast(uint32_t, kSmallestSquared));
 // Below this many times a scale the squares are exact under it and, for the steps of a walk, down to a quarter of it.
 constexpr float kExactScales = 128.0f;
 

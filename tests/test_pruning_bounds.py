@@ -9,8 +9,15 @@ against the oracle's own block SSE (pinned fp32 arithmetic) for every scale code
 Both must be lower bounds of the SSE under S and must not fall as S falls, so that they rule out every
 lower code as well; and the lowest code of minimal SSE must survive them whatever the best SSE so far
 is.  (The bound of the way up is in test_search_walk.py.)"""
+import os
+import shutil
+import subprocess
+
 import numpy as np
 import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CLANG = shutil.which("amdclang++") or "/opt/rocm/llvm/bin/clang++"
 
 E4M3, UE5M3 = 1, 2
 
@@ -89,3 +96,21 @@ def test_squares_of_residuals_are_exact_below_512_scales():
                 else:
                     beyond = max(beyond, most_bits(v, s))
     assert beyond > 12
+
+
+def test_fused_sums_of_squares_where_the_rules_allow_them(tmp_path):
+    """The kernels' own rules (mxq_arith.hpp) over every bf16 magnitude and scale code: a zero passes them, the sums of what
+    passes have the bits of separate roundings, and on either side beyond them they do not all."""
+    if "fma" not in open("/proc/cpuinfo").read():
+        pytest.skip("host CPU has no FMA instruction")
+    exe = str(tmp_path / "squares_check")
+    subprocess.run([CLANG, "-O2", "-std=c++17", "-ffp-contract=off", "-mfma", "-Wall", "-Werror",
+                    os.path.join(HERE, "host", "squares_check.cpp"), "-o", exe, "-lm"], check=True)
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    print(res.stdout)
+    rows = {l.split()[0]: [int(t.split("=")[1]) for t in l.split()[1:]] for l in res.stdout.splitlines()}
+    assert res.returncode == 0 and len(rows) == 8
+    assert rows["zeros"] == [2, 0] and rows["edge"] == [3, 0]
+    for fmt in ("e4m3", "ue5m3"):
+        assert rows[fmt + "_inside"][0] > 1_000_000 and rows[fmt + "_inside"][1] == 0
+        assert rows[fmt + "_too_small"][1] > 1000 and rows[fmt + "_too_large"][1] > 1000
