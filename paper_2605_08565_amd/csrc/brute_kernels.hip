@@ -207,8 +207,8 @@ template <int FMT>
 __device__ __forceinline__ float walk_scale(uint32_t code) { return walk_scale_bias<ScaleFmt<FMT>::kBias>(code); }
 
 // Whether no element of the wavefront is too small for an exact square.  Wavefronts without a zero are through with the
-// first test.  (Where a zero counted as too small: 4096 x 4096 bf16 with 1 % zeros, pruned UE5M3 b = 4 49.2 us instead of 37.3, all codes of E4M3
-// 246 instead of 225.)
+// first test.  (Where a zero counted as too small: 4096 x 4096 bf16 with 1 % zeros, b = 4, pruned UE5M3 49.2 us instead of 37.3,
+// all codes of E4M3 246 instead of 225.)
 __device__ __forceinline__ bool none_vanishes(const float (&v)[8])
 {
     float m = __builtin_fabsf(v[0]);
@@ -455,9 +455,19 @@ __device__ __forceinline__ void keep_less(uint64_t& best, float sse, float S)
 }
 __device__ __forceinline__ float sse_of(uint64_t best) { return u2f((uint32_t)(best >> 32)); }
 
+// What is formed from v behind this is not formed before it.  Left alone, the compiler formed the quotients of all mantissas
+// before the second: with blocks of two 112 to 114 vector registers for UE5M3, four wavefronts a SIMD.  Halved once it is 80
+// to 82 and five or six: 4096 x 4096 bf16 with every other element zero, whose wavefronts walk, 64.7 -> 62.2 us, random values,
+// in the window, 42.9 -> 43.8.  (At every mantissa, seven wavefronts, 61.6 and 44.2.)  Blocks of four hold them back at every
+// mantissa: 36.1 -> 35.6.
+__device__ __forceinline__ void formed_below(float (&v)[8])
+{
+    asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]));
+}
+
 // The codes of mantissa MI and of those behind it, one for each block: the one among the eight from `first` (a scale's bits) on.
 template <int B, int MI, bool ONE_MUL, bool FUSED>
-__device__ __forceinline__ void try_window(const float (&v)[8], const uint32_t (&first)[BruteState<B>::NBLK],
+__device__ __forceinline__ void try_window(float (&v)[8], const uint32_t (&first)[BruteState<B>::NBLK],
                                            uint64_t (&best)[BruteState<B>::NBLK])
 {
     constexpr int NBLK = BruteState<B>::NBLK;
@@ -476,12 +486,13 @@ __device__ __forceinline__ void try_window(const float (&v)[8], const uint32_t (
 #pragma unroll
         for (int k = 0; k < NBLK; ++k) keep_less(best[k], sse[k], S[k]);
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (B == 2 ? MI == 3 : B == 4) formed_below(v);
         try_window<B, MI + 1, ONE_MUL, FUSED>(v, first, best);
     }
 }
 
 template <int B, int FMT, bool ONE_MUL, bool FUSED>
-__device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_t& packed, BruteState<B>& st)
+__device__ __forceinline__ void brute_search_pruned(float (&v)[8], uint32_t& packed, BruteState<B>& st)
 {
     constexpr int NBLK = BruteState<B>::NBLK;
     constexpr int LANES = (B < 8) ? 1 : B / 8;
@@ -552,12 +563,12 @@ __device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_
             st.best_sse[k] = sse_of(best[k]);
             st.best_code[k] = ((uint32_t)best[k] >> 20) - kBits0;
         }
-        whole = __builtin_amdgcn_ballot_w64(bad) != 0ull;
-        done = done && !whole;
-        if (!done && !whole) {
-            step = window_steps(B);
+        done = done && __builtin_amdgcn_ballot_w64(bad) == 0ull;
+        if (__builtin_expect(!done, 0)) {                               // on down from here, unless all is to be tried again
+            whole = __builtin_amdgcn_ballot_w64(bad) != 0ull;
+            step = whole ? 0u : window_steps(B);
 #pragma unroll
-            for (int k = 0; k < NBLK; ++k) start[k] = (f2u(S[k]) >> 20) - kBits0;
+            for (int k = 0; k < NBLK; ++k) start[k] = whole ? start[k] : (bits[k] >> 20) - kBits0 - kWindowDown;
         }
     }
     if (!done) {
@@ -574,7 +585,7 @@ __device__ __forceinline__ void brute_search_pruned(const float (&v)[8], uint32_
 // starts at a scale of at least amax / 9, or at the largest, above amax / 128, and takes up to 16 steps (walk_patience) down with
 // it: from a normal code to a quarter of its value, amax / 512, or among the lowest codes to amax / 105.)
 template <int B, int FMT, bool ONE_MUL>
-__device__ __forceinline__ void search_pruned(const float (&v)[8], uint32_t& packed, BruteState<B>& st)
+__device__ __forceinline__ void search_pruned(float (&v)[8], uint32_t& packed, BruteState<B>& st)
 {
     if constexpr (ONE_MUL && B != 2) {
         float largest = 0.0f;

@@ -6,11 +6,14 @@ oracle's SSE of every code, in its pinned fp32 arithmetic, together with the set
 visits: the lowest code of minimal SSE must always be among them.  And the element quotient the search
 forms from the hardware reciprocal."""
 import os
+import re
 import shutil
 import subprocess
 
 import numpy as np
 import pytest
+
+from paper_2605_08565_amd import build
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CLANG = shutil.which("amdclang++") or "/opt/rocm/llvm/bin/clang++"
@@ -119,3 +122,20 @@ def test_search_rules_are_defined_once():
     for f in os.listdir(csrc):
         text = open(os.path.join(csrc, f)).read()
         assert all((n in text) == (f == "mxq_arith.hpp") for n in names), f
+
+
+def test_pruned_search_kernels_leave_room_for_wavefronts(tmp_path):
+    """The search waits for its own instructions' results, so it lives on wavefronts in flight: five a SIMD with blocks of
+    two, eight else (the compiler may form the quotients of all mantissas at once, which takes the registers of two), and
+    nothing spilled."""
+    out = str(tmp_path / "brute.s")
+    subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, "brute_kernels.hip"), "-o", out],
+                   check=True, capture_output=True)
+    found = 0
+    for part in open(out).read().split("; -- Begin function ")[1:]:        # figures stand behind each kernel's end
+        kernel = re.match(r"_ZN3mxq12brute_kernelILi[01]ELi(\d+)ELi[12]ELb[01]ELb1E", part)    # <type, block, format, scaled, pruned>
+        if kernel:
+            found += 1
+            room, spilled = (int(re.search(rf"; {k}: (\d+)", part).group(1)) for k in ("Occupancy", "ScratchSize"))
+            assert spilled == 0 and room >= (5 if kernel.group(1) == "2" else 8), (kernel.group(), room, spilled)
+    assert found == 2 * 7 * 2 * 2
