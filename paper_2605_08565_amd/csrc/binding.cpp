@@ -10,6 +10,7 @@
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <ATen/ops/empty.h>
+#include <ATen/record_function.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
@@ -87,13 +88,18 @@ void* ptr(const at::Tensor& t) { return t.data_ptr(); }
 
 void* stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
 
-// What at::empty ends at for a GPU, without its two dispatches (0.70 -> 0.47 us, three of them in a small call of 6 us), where
-// nothing has asked to see them: a tracer or a transform adds its key to the thread's.
-at::Tensor new_empty(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like)
+// Nothing has asked to see a new tensor made, or to fill it: a tracer or a transform adds its key to the thread's, a profiler
+// its callbacks, deterministic mode has new memory filled.
+bool nothing_watches()
 {
     const c10::DispatchKeySet added = c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set;
-    if (added.empty() && !at::globalContext().deterministicAlgorithms())       // those have new memory filled
-        return at::detail::empty_cuda(shape, type, like.device(), std::nullopt);
+    return added.empty() && !at::globalContext().deterministicAlgorithms() && !at::hasCallbacks();
+}
+
+// What at::empty ends at for a GPU, without its two dispatches (0.70 -> 0.47 us, three of them in a small call of 6 us).
+at::Tensor new_empty(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like)
+{
+    if (nothing_watches()) return at::detail::empty_cuda(shape, type, like.device(), std::nullopt);
     return at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
 }
 
@@ -357,6 +363,9 @@ PyObject* histogram(PyObject*, PyObject* const* a, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
+// new_outputs_direct(): whether outputs made now would be allocated past the dispatcher
+PyObject* new_outputs_direct(PyObject*, PyObject*) { return PyBool_FromLong(nothing_watches()); }
+
 // built_for(): what the layouts and signatures compiled in here belong to; mxq.py compares it before use()
 PyObject* built_for(PyObject*, PyObject*) { return Py_BuildValue("(ss)", MXQ_CALLS_ABI, MXQ_HEADER_ID); }
 
@@ -383,6 +392,7 @@ PyObject* use(PyObject*, PyObject* const* a, Py_ssize_t n)
 #define MXQ_METHOD(f) {#f, (PyCFunction)(void (*)(void))f, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {MXQ_METHOD(quantize), MXQ_METHOD(quantize_hier), MXQ_METHOD(quantize_batch), MXQ_METHOD(tensor_absmax),
                          MXQ_METHOD(dequantize), MXQ_METHOD(clip_sse), MXQ_METHOD(histogram), MXQ_METHOD(use),
+                         {"new_outputs_direct", new_outputs_direct, METH_NOARGS, nullptr},
                          {"built_for", built_for, METH_NOARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_mxq_calls", "The calls of mxq.py in native code.", -1, methods, nullptr, nullptr, nullptr, nullptr};
 

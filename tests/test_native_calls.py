@@ -239,11 +239,49 @@ def test_native_forms_in_a_captured_graph(monkeypatch):
                     assert torch.equal(g.view(torch.uint8), w.view(torch.uint8)), (seed, name)
 
 
+def test_new_outputs_go_past_the_dispatcher_only_where_nothing_watches_it():
+    mxq.lib()
+    direct = mxq._calls.new_outputs_direct
+    assert direct()
+    with torch.inference_mode():
+        assert direct()
+    with torch.no_grad():
+        assert direct()
+    torch.use_deterministic_algorithms(True)                   # has new memory filled
+    try:
+        assert not direct()
+    finally:
+        torch.use_deterministic_algorithms(False)
+    seen = []
+    torch.func.vmap(lambda y: seen.append(direct()) or y + 1)(torch.zeros(3))
+    torch.func.grad(lambda y: seen.append(direct()) or y.sum())(torch.zeros(3))
+    torch.jit.trace(lambda y: seen.append(direct()) or y + 1, torch.zeros(3), check_trace=False)
+    assert len(seen) >= 3 and not any(seen)
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]):
+        assert not direct()
+    with torch.autograd.profiler.profile(use_device=None):
+        assert not direct()
+    assert direct()
+
+
+@pytest.mark.gpu
+def test_a_profiler_sees_the_outputs_of_the_native_calls_made():
+    x = torch.randn((64, 64), device="cuda")
+    mxq.quantize(x, 16, 1, 0)
+    torch.cuda.synchronize()
+    counts = []
+    for call in (lambda: mxq.quantize(x, 16, 1, 0), lambda: mxq.quantize(x, 16, 1, 0, want_sse=False)):
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]) as p:
+            call()
+        counts.append(sum(e.count for e in p.key_averages() if e.key == "aten::empty"))
+    assert counts == [3, 2]
+
+
 @pytest.mark.gpu
 def test_new_outputs_of_the_native_calls_are_those_of_torch_empty():
-    """Allocated without torch's dispatcher where nothing watches it: the same kind of tensor in inference mode, on the
-    inputs' device and in the caching allocator's books, and through the dispatcher where deterministic mode fills new memory
-    or a transform is active."""
+    """The same kind of tensor in inference mode, on the inputs' device and in the caching allocator's books, and the same
+    results where new memory is filled or a transform is active (which way they are allocated there is the test of
+    new_outputs_direct)."""
     x = torch.randn((64, 64), device="cuda")
     want = mxq.quantize(x, 16, 1, 0)
 
