@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2605_08565_amd import workloads as W
+from test_pruning_bounds import bf16_bits, guard_blocks
 
 pytestmark = pytest.mark.gpu
 
@@ -278,6 +279,41 @@ def test_quantize_where_a_workgroup_takes_three_slices(oracle, mxq, block, dtype
                 same([g[:, -r.shape[1]:].contiguous() for g, r in zip(got, ref) if g is not None], ref)
 
 
+@pytest.mark.parametrize("block", [2, 4, 16, 128])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_batch_where_a_workgroup_takes_three_slices_of_one_tensor(oracle, mxq, block, dtype):
+    """Eleven tensors: the first eight that are not empty, more than 16384 slices together, in one launch of workgroups that
+    take three slices of a tensor and end, the rest in one of workgroups that loop.  A large tensor among the eight, one and two
+    slices more than a multiple of three, part-filled last slices, a tensor of one block, an empty one, ragged tails (b = 2, 4);
+    with and without SSEs.  Small tensors whole and the large one's end against the oracle, the whole of
+    it against single calls on its pieces."""
+    rng = np.random.default_rng(block)
+    per, tail = 2048, 6 // block * block
+    sizes = [per, 2 * per + 8 * block + tail, block, 16390 * per + 1000 // block * block + tail, 0, 4 * per + tail, 5 * per, 3 * per + 128 + tail,
+             7 * per + tail, block, 10 * per]
+    period = (rng.standard_normal(block * 40009) * 0.05).astype(np.float32)
+    kind = torch.float32 if dtype == "f32" else torch.bfloat16
+    xs = [torch.from_numpy(np.resize(np.roll(period, 977 * i), n)).cuda().to(kind).reshape(1, n) for i, n in enumerate(sizes)]
+    assert all(n % block == 0 for n in sizes) and sum(-(-n // per) for n in sizes[:8]) >= 16384
+    for fmt, rec, want in ((1, 2, True), (2, 1, False), (0, 0, True)):
+        print(f"[edges] large batch b={block} {dtype} fmt={fmt} recipe={rec} sse={want}", flush=True)
+        outs = mxq.quantize_batch(xs, block, fmt, rec, want_sse=want)
+        for i, (x, got) in enumerate(zip(xs, outs)):
+            n = sizes[i]
+            assert (got[2] is not None) == want and got[0].numel() == n // 2 and got[1].numel() == n // block
+            if n == 0:
+                continue
+            if n > 16384 * per:
+                cut = n // 3 // block * block
+                pieces = [mxq.quantize(x[:, a:b].clone(), block, fmt, rec, want_sse=want) for a, b in ((0, cut), (cut, 2 * cut), (2 * cut, n))]
+                for g, *p in zip(got if want else got[:2], *pieces):
+                    assert torch.equal(g.view(torch.uint8), torch.cat(p, 1).view(torch.uint8)), i
+            end = x[:, max(0, n - 6 * per - n % per):].contiguous()
+            end = end.cpu().numpy() if dtype == "f32" else end.view(torch.int16).cpu().numpy().view(np.uint16)
+            ref = oracle.quantize(end, block, fmt, rec)
+            same([g[:, -r.shape[1]:].contiguous() for g, r in zip(got, ref) if g is not None], ref)
+
+
 @pytest.mark.parametrize("T", [1.0, 0.7])
 @pytest.mark.parametrize("fmt", [1, 2])
 @pytest.mark.parametrize("block", [2, 4, 8, 16, 64])
@@ -364,6 +400,20 @@ def test_search_where_squares_are_exact_and_where_not(oracle, mxq, fmt, block):
     ref = oracle.quantize(x, block, fmt, 4)
     for recipe in (mxq.RECIPE_BRUTE, mxq.RECIPE_BRUTE_PRUNED):
         same(mxq.quantize(mxq.from_bits(x), block, fmt, recipe), ref)
+
+
+@pytest.mark.parametrize("fmt", [1, 2])
+@pytest.mark.parametrize("block", [4, 8, 16, 64])
+def test_search_beyond_the_rules_for_exact_squares(oracle, mxq, fmt, block):
+    """Blocks whose SSEs come out otherwise where a rule is missing (shown in test_pruning_bounds.py), each kind in wavefronts
+    of its own: both searches against the oracle."""
+    top = float(oracle.scale_decode(fmt, oracle.scale_max_code(fmt)))
+    for name, v in guard_blocks(block, top).items():
+        x = bf16_bits(v)
+        ref = oracle.quantize(x, block, fmt, 4)
+        for recipe in (mxq.RECIPE_BRUTE, mxq.RECIPE_BRUTE_PRUNED):
+            print(f"[edges] rules fmt={fmt} b={block} {name} recipe={recipe}", flush=True)
+            same(mxq.quantize(mxq.from_bits(x), block, fmt, recipe), ref)
 
 
 @pytest.mark.parametrize("block", [2, 4, 16, 128])

@@ -114,3 +114,50 @@ def test_fused_sums_of_squares_where_the_rules_allow_them(tmp_path):
     for fmt in ("e4m3", "ue5m3"):
         assert rows[fmt + "_inside"][0] > 1_000_000 and rows[fmt + "_inside"][1] == 0
         assert rows[fmt + "_too_small"][1] > 1000 and rows[fmt + "_too_large"][1] > 1000
+
+
+def bf16_bits(v):
+    return (np.asarray(v, np.float32).view(np.uint32) >> 16).astype(np.uint16)       # truncated: full mantissas stay full
+
+
+def guard_blocks(block, top):
+    """bf16 blocks (as fp32) on both sides of the two rules for exact squares, in wavefronts of 512 elements: {name: blocks}.
+    small: every element around 2^-72 .. 2^-64, no zeros; zeros: the same with some; far: every element 64 to 4096 times the
+    largest power of two up to the largest scale `top`; low: every element 64 to 4096 times some lower scale."""
+    rng = np.random.default_rng(block)
+    waves = 16
+    shape = (waves, 512 // block, block)
+    mantissa = rng.choice([-1, 1], shape) * (1 + rng.integers(0, 128, shape) / 128)
+    small = mantissa * 2.0 ** (np.linspace(-72, -64, waves).round()[:, None, None] + rng.integers(-1, 2, shape))
+    zeros = np.where(rng.random(shape) < 0.1, 0.0, small)
+    many = 2.0 ** rng.integers(6, 13, shape)
+    far = mantissa * many * 2.0 ** np.floor(np.log2(top))
+    low = mantissa * many * 2.0 ** -rng.integers(4, 12, waves)[:, None, None]
+    return {k: v.reshape(-1, block).astype(np.float32) for k, v in dict(small=small, zeros=zeros, far=far, low=low).items()}
+
+
+@pytest.mark.parametrize("fmt", [E4M3, UE5M3])
+@pytest.mark.parametrize("block", [4, 8, 16, 64])
+def test_blocks_beyond_the_rules_tell_fused_sums_apart(oracle, fmt, block):
+    """What a search with a rule missing would return for these blocks is not what it has to: SSEs with the odd squares of
+    each lane fused, under the scales that the rule keeps from it, against separately rounded ones.  (The searches themselves
+    are compared with the oracle on these blocks in test_gpu_kernel_edges.py.)"""
+    def sums(v, S, fused):
+        q = np.array([0, .5, 1, 1.5, 2, 3, 4, 6], np.float32)
+        y = np.abs(v.astype(np.float64) / S)
+        e = (np.abs(v) - q[np.abs(y[..., None] - q).argmin(-1)] * S).astype(np.float32)
+        even, odd = (e[:, 0::2] * e[:, 0::2]).astype(np.float32), e[:, 1::2]
+        if fused:
+            first = (odd.astype(np.longdouble) ** 2 + even.astype(np.longdouble)).astype(np.float32)
+        else:
+            first = ((odd * odd).astype(np.float32) + even).astype(np.float32)
+        return tree_sum32(first)
+
+    top = np.float32(oracle.scale_decode(fmt, oracle.scale_max_code(fmt)))
+    data = guard_blocks(block, float(top))
+    assert all((bf16_bits(v).astype(np.uint32) << 16 == v.view(np.uint32)).all() for v in data.values())
+    # under the scales that win: any for elements that vanish, the largest beyond the format (the lower scales of "low" never
+    # win, its wavefronts only go from one kind of sum to the other)
+    for name, S in (("small", np.float32(2.0 ** -6)), ("zeros", np.float32(2.0 ** -6)), ("far", top)):
+        apart = int((sums(data[name], S, True) != sums(data[name], S, False)).sum())
+        assert apart >= 5, (name, apart)
