@@ -71,8 +71,8 @@ typedef enum { MXQ_SCALE_E8M0 = 0, MXQ_SCALE_E4M3 = 1, MXQ_SCALE_UE5M3 = 2 } mxq
  *              or of all saturated elements, costs more than the best candidate so far.  A step
  *              toward cheaper near-optimal selection (Conclusion).  Time of BRUTE over time of
  *              BRUTE_PRUNED, 16 M elements, both dtypes, all block sizes, with and without the
- *              per-tensor scale: E4M3 3.4 to 6.4, UE5M3 6.5 to 15 (b = 2 and values beyond the
- *              format the least); up to 17 where the scales are tiny.
+ *              per-tensor scale: E4M3 3.2 to 6.4, UE5M3 6.6 to 12.7 (b = 2 the least); values beyond
+ *              the format from 2.6 and 5.4, tiny scales up to 14.
  * 4OVER6* and BRUTE_PRUNED with E8M0 return MXQ_ERR_UNSUPPORTED (Eq. 4 rounds amax / M to the
  * scale format, which the floor rule of Eq. 1 does not define). */
 typedef enum {

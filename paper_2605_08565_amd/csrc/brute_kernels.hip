@@ -85,8 +85,8 @@ struct GroupArgMin {
 };
 
 // Block SSE of the lane's residuals: separately rounded squares in a balanced tree.  FUSED: every square is exact
-// (squares_exact), so the first level of the tree may take one of the two squares by a fused multiply-add with the
-// same bits, and four of the 15 instructions go.
+// ("Residuals whose squares are exact" in mxq_arith.hpp), so the first level of the tree may take one of the two squares by
+// a fused multiply-add with the same bits, and four of the 15 instructions go.
 template <int B, bool FUSED>
 __device__ __forceinline__ void residual_sse(const float (&e)[8], float (&sse)[4])
 {
@@ -197,10 +197,11 @@ __device__ __forceinline__ void try_binade(const float (&v)[8], const float (&w)
 // independent ones over 8 wavefronts per SIMD, cycles per wavefront: fp32 add, multiply, FMA and logic
 // on vector registers 2.5; the same with a scalar-register operand, minimum, maximum, compare, shift,
 // DPP, unpacking and the fp64 minimum 4.8; packing to E2M1 and the reciprocal 8.4.
-// Code by code throughout -> as it is: 4096 x 14336 bf16 UE5M3 b = 4 129.4 -> 98.8 us; 4096 x 4096 UE5M3 b = 2 51.5 -> 46.7, b = 8 32.0 ->
-// 28.4, b = 16 33.7 -> 30.1, b = 128 42.2 -> 37.5, fp32 b = 4 43.8 -> 33.5; E4M3 under a per-tensor scale b = 4 50.0 -> 38.9, b = 16
-// 43.7 -> 38.2.  (Wavefronts that walk, E4M3 weights: b = 4 41.8 -> 41.1, b = 16 33.7 -> 32.1, b = 2 57.2 -> 58.6, fp32 b = 16 36.8
-// -> 37.2.)
+// Code by code throughout -> as it is, 4096 x 4096 bf16: UE5M3 b = 2 57.7 -> 52.3 us, b = 4 44.6 -> 35.5, b = 8 36.9 -> 33.3, b = 16
+// 38.5 -> 34.7, b = 128 46.3 -> 41.2, with 1 % zeros b = 4 44.7 -> 35.9, with half zeros b = 16 37.0 -> 33.9, values spread evenly b = 128
+// 59.5 -> 54.6; fp32 b = 4 50.5 -> 39.7; E4M3 under a per-tensor scale b = 4 57.4 -> 45.6, b = 16 50.2 -> 45.4; 4096 x 14336 UE5M3
+// b = 4 129 -> 100.  Wavefronts that walk, E4M3 weights: b = 4 47.3 -> 46.3, b = 16 38.7 -> 37.5, b = 2 64.3 -> 63.7, fp32 b = 16 42.8 -> 43.1,
+// b = 8 44.4 -> 45.7; UE5M3 with half zeros, b = 2 62.8 -> 62.6.
 // ---------------------------------------------------------------------------------------
 
 template <int FMT>
@@ -583,7 +584,7 @@ __device__ __forceinline__ void brute_search_pruned(float (&v)[8], uint32_t& pac
 
 // FUSED for the wavefronts whose squares are all exact: no element but zeros nearly vanishes, none is far beyond the format.  (The walk
 // starts at a scale of at least amax / 9, or at the largest, above amax / 128, and takes up to 16 steps (walk_patience) down with
-// it: from a normal code to a quarter of its value, amax / 512, or among the lowest codes to amax / 105.)
+// it: from a normal code to a quarter of its value, amax / 512, or from code 17 and below to code 1, amax / 114 at most.)
 template <int B, int FMT, bool ONE_MUL>
 __device__ __forceinline__ void search_pruned(float (&v)[8], uint32_t& packed, BruteState<B>& st)
 {
@@ -656,8 +657,9 @@ __device__ __forceinline__ void brute_search(const float (&v)[8], uint32_t& pack
     const float s2 = u2f((uint32_t)(127 + emin - 2) << 23);
     const float s4 = u2f((uint32_t)(127 + emin - 1) << 23);
     // SHORT (bf16 that nothing has divided): from the first binade on whose squares are all exact, four of a candidate's
-    // instructions go.  (Two loops: with both kinds in one, more registers and 2 % slower.)  4096 x 14336 E4M3 b = 16 801 ->
-    // 746 us; 4096 x 4096 b = 32 245 -> 235, b = 128 254 -> 240, b = 4 227 -> 224; b = 2, of whose sums too little is left, not.
+    // instructions go.  (Two loops: with both kinds in one, more registers and 2 % slower.)  4096 x 4096 E4M3, separate roundings ->
+    // as it is: b = 4 247 -> 224 us, b = 16 237 -> 216, b = 32 243 -> 221, b = 128 259 -> 239; UE5M3 b = 16 460 -> 423; 4096 x 14336 E4M3 b = 16
+    // 801 -> 739.  b = 2, of whose sums too little is left, not.
     float largest = 0.0f;
     bool regular = false;
     if constexpr (SHORT) {

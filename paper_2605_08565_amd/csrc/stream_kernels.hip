@@ -304,8 +304,9 @@ __device__ __forceinline__ void store_slice(const TileOut<B>& o, uint32_t s, Sli
 // Where the block SSEs of a complete slice go.
 enum : int { kNoSse = 0, kSseCached = 1, kSsePast = 2 };
 
-// Stores of one slice of 256 complete chunks.  Every lane of a block stores the block's scale byte and SSE, the same
-// values to the same place: without masks and branches the compiler can count the stores that lie behind a load.
+// Stores of one slice of 256 complete chunks.  Every lane of a block stores the block's scale byte and SSE to the same
+// place: without masks and branches the compiler can count the stores that lie behind a load.  They are the same values
+// but for an SSE that is NaN (a block with a NaN or an infinity), of which each lane may hold another sign and payload.
 template <int B, int SSE>
 __device__ __forceinline__ void store_complete_slice(const TileOut<B>& o, uint32_t s, uint32_t* __restrict__ codes,
                                                      uint8_t* __restrict__ scales, float* __restrict__ sse_out)
@@ -466,7 +467,10 @@ __device__ __forceinline__ uint32_t stream_tiles(RawChunk<DT> (&bufA)[kItems], c
 // a batch of 218 M elements, 4-over-6 b = 32 112.8 -> 103.4 / 97.8 / 96.7 (5.1 -> 5.9 TB/s).  A tensor of fewer slices has too
 // few workgroups for their phases to overlap: 4096 x 4096 (8192 slices) bf16 abs-max b = 16 8.3 -> 8.9, 2563 x 4110 b = 2 12.1 ->
 // 12.5; 6000 x 4096 (11719) 13.4 -> 13.5; 8192 x 4096 (16384) 4-over-6 b = 16 16.6 -> 16.5, b = 4 22.8 -> 21.4, abs-max 16.7 ->
-// 16.2.  Behind an abs-max pass (T in device memory) the loop's order of the slices finds more in the caches: 8192 x 4096
+// 16.2.  fp32 has its line there too, and T by value (four recipes and formats, b = 2 .. 128, three slices against the loop):
+// 4096 slices 0.93 to 1.08 of the loop's time, 1.03 in the mean; 8192 0.92 to 1.06, 1.01; 12288 0.96 to 1.03, 0.99; 16383 0.91 to
+// 0.99, 0.96.  58.7 M elements, fp32 abs-max b = 16 T = 1 51.8 -> 48.0, T by value 51.7 -> 48.4, 4-over-6 b = 8 T by value 55.8 ->
+// 51.9; bf16 abs-max T by value b = 8 33.8 -> 32.1, b = 2 58.3 -> 55.1.  Behind an abs-max pass (T in device memory) the loop's order of the slices finds more in the caches: 8192 x 4096
 // abs-max and quantise, b = 16, 26.2 -> 29.7.
 // ---------------------------------------------------------------------------------------
 constexpr int kOnce = 3;

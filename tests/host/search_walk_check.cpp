@@ -9,7 +9,7 @@
  * Blocks: every scale code times the factors at which the rules switch and their neighbours, over grid
  * points and ties; random blocks of every magnitude from 2^-40 to overflow; NaN and infinity.
  * Prints "<name> cases=<n> bad=<m> most=<candidates of the costliest block> window=<blocks that it decided> on=<blocks that
- * went on down behind it>".
+ * went on down behind it> far=<abs-max over the lowest scale tried where squares count as exact>".
  */
 #include <math.h>
 #include <stdint.h>
@@ -45,6 +45,7 @@ template <int BIAS, int MAX, bool ONE_MUL> struct Search {
     std::vector<float> v;
     int tried = 0;
     bool in_window = false, went_on = false;
+    float far = 0.0f;                                       /* amax over the lowest scale tried before the patience is out */
 
     float sse(uint32_t code, bool exact = false)
     {
@@ -117,6 +118,7 @@ template <int BIAS, int MAX, bool ONE_MUL> struct Search {
             code -= 1u;
             const float over = fmaf(-6.0f, walk_scale_bias<BIAS>(code), amax);
             if (over * fabsf(over) > u2f((uint32_t)(least >> 32))) { done = true; break; }
+            far = fmaxf(far, amax / walk_scale_bias<BIAS>(code));
             keep(code, sse(code));
         }
         best = (uint32_t)least;
@@ -186,6 +188,7 @@ template <int BIAS, int MAX, bool ONE_MUL> struct Search {
             c -= 1u;
             const float over = amax - 6.0f * walk_scale_bias<BIAS>(c);
             if (over > 0.0f && over * over > best_sse) break;
+            if (step < walk_patience((int)v.size())) far = fmaxf(far, amax / walk_scale_bias<BIAS>(c));
             ++tried;
             const float s = sse(c);
             if (s <= best_sse) { best = c; best_sse = s; }
@@ -202,7 +205,7 @@ static double uniform()
 static double normal() { return sqrt(-2.0 * log(uniform() + 1e-300)) * cos(6.283185307179586 * uniform()); }
 static float as_bf16(float f) { return u2f(f2u(f) & 0xFFFF0000u); }
 
-struct Count { long n = 0, bad = 0, window = 0, on = 0; int most = 0; };
+struct Count { long n = 0, bad = 0, window = 0, on = 0; int most = 0; float far = 0.0f; };
 
 template <int BIAS, int MAX, bool BF16>
 static void one(Count& c, std::vector<float> v)
@@ -221,6 +224,9 @@ static void one(Count& c, std::vector<float> v)
     if (s.tried > c.most) c.most = s.tried;
     c.window += s.in_window;
     c.on += s.went_on;
+    float amax = 0.0f;
+    for (float x : v) amax = fmaxf(amax, fabsf(x));
+    if (amax < kExactScales * walk_scale_bias<BIAS>(MAX)) c.far = fmaxf(c.far, s.far);
 }
 
 template <int BIAS, int MAX, bool BF16>
@@ -272,7 +278,7 @@ static void run(const char* fmt)
             }
     const struct { const char* name; Count* c; } all[4] = {{"edges", &edges}, {"inside", &inside}, {"beyond", &beyond}, {"special", &special}};
     for (auto& a : all) 
-        printf("%s_%s_%s cases=%ld bad=%ld most=%d window=%ld on=%ld\n", fmt, BF16 ? "bf16" : "f32", a.name, a.c->n, a.c->bad, a.c->most, a.c->window, a.c->on);
+        printf("%s_%s_%s cases=%ld bad=%ld most=%d window=%ld on=%ld far=%.9g\n", fmt, BF16 ? "bf16" : "f32", a.name, a.c->n, a.c->bad, a.c->most, a.c->window, a.c->on, a.c->far);
 }
 
 int main()

@@ -100,7 +100,8 @@ def test_walk_over_single_blocks_with_the_kernels_rules(tmp_path):
     infinity.  The longest way down before a floor is looked for is 16 steps; with the start and the floor
     itself that is 18 candidates; ordinary blocks end well before (15 on these inputs).  A block that the window takes
     tries eight codes, one above, the 15 of the 16 steps down that are not among the eight, and the floor: 25 at most,
-    where it goes on down behind the window (33 to 35 if it walked from its start again)."""
+    where it goes on down behind the window (33 to 35 if it walked from its start again).  And the scales under which the
+    kernel takes squares for exact are above 1/512 of the abs-max, as exact squares need."""
     if "fma" not in open("/proc/cpuinfo").read():
         pytest.skip("host CPU has no FMA instruction")
     exe = str(tmp_path / "search_walk_check")
@@ -112,6 +113,7 @@ def test_walk_over_single_blocks_with_the_kernels_rules(tmp_path):
     assert res.returncode == 0 and len(rows) == 16
     for r in rows:
         assert int(r["cases"]) > 100 and int(r["bad"]) == 0 and int(r["most"]) <= (25 if int(r["on"]) else 18), r
+        assert float(r["far"]) < 512.0, r
     assert sum(int(r["on"]) for r in rows) > 40 and sum(int(r["window"]) for r in rows) > 20000
 
 
