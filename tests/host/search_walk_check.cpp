@@ -8,8 +8,8 @@
  *
  * Blocks: every scale code times the factors at which the rules switch and their neighbours, over grid
  * points and ties; random blocks of every magnitude from 2^-40 to overflow; NaN and infinity.
- * Prints "<name> cases=<n> bad=<m> most=<candidates of the costliest block> window=<blocks that it decided> on=<blocks that
- * went on down behind it> far=<abs-max over the lowest scale tried where squares count as exact>".
+ * Prints "<name> cases=<n> bad=<m> most=<candidates of the costliest block that does not go on down behind its
+ * window> window=<blocks that it decided> on=<blocks that went on down behind it> most_on=<candidates of the costliest of these> far=<abs-max over the lowest scale tried where squares count as exact>".
  */
 #include <math.h>
 #include <stdint.h>
@@ -205,7 +205,7 @@ static double uniform()
 static double normal() { return sqrt(-2.0 * log(uniform() + 1e-300)) * cos(6.283185307179586 * uniform()); }
 static float as_bf16(float f) { return u2f(f2u(f) & 0xFFFF0000u); }
 
-struct Count { long n = 0, bad = 0, window = 0, on = 0; int most = 0; float far = 0.0f; };
+struct Count { long n = 0, bad = 0, window = 0, on = 0; int most = 0, most_on = 0; float far = 0.0f; };
 
 template <int BIAS, int MAX, bool BF16>
 static void one(Count& c, std::vector<float> v)
@@ -221,7 +221,8 @@ static void one(Count& c, std::vector<float> v)
     if (a != b || f2u(x) != f2u(y)) {
         if (c.bad++ < 5) printf("  bias %d b %zu: code %u sse %g, full search %u %g; v0 = %a\n", BIAS, v.size(), b, y, a, x, v[0]);
     }
-    if (s.tried > c.most) c.most = s.tried;
+    int& most = s.went_on ? c.most_on : c.most;
+    if (s.tried > most) most = s.tried;
     c.window += s.in_window;
     c.on += s.went_on;
     float amax = 0.0f;
@@ -277,8 +278,9 @@ static void run(const char* fmt)
                 one<BIAS, MAX, BF16>(special, v);
             }
     const struct { const char* name; Count* c; } all[4] = {{"edges", &edges}, {"inside", &inside}, {"beyond", &beyond}, {"special", &special}};
-    for (auto& a : all) 
-        printf("%s_%s_%s cases=%ld bad=%ld most=%d window=%ld on=%ld far=%.9g\n", fmt, BF16 ? "bf16" : "f32", a.name, a.c->n, a.c->bad, a.c->most, a.c->window, a.c->on, a.c->far);
+    for (auto& a : all)
+        printf("%s_%s_%s cases=%ld bad=%ld most=%d window=%ld on=%ld most_on=%d far=%.9g\n", fmt, BF16 ? "bf16" : "f32", a.name, a.c->n, a.c->bad,
+               a.c->most, a.c->window, a.c->on, a.c->most_on, a.c->far);
 }
 
 int main()

@@ -98,10 +98,7 @@ def test_walk_over_single_blocks_with_the_kernels_rules(tmp_path):
     SSE bits as all codes tried, and never many candidates -- also for blocks beyond the format, which
     the clipping bound of one element alone would send through every code (126 and 254), and for NaN and
     infinity.  The longest way down before a floor is looked for is 16 steps; with the start and the floor
-    itself that is 18 candidates; ordinary blocks end well before (15 on these inputs).  A block that the window takes
-    tries eight codes, one above, the 15 of the 16 steps down that are not among the eight, and the floor: 25 at most,
-    where it goes on down behind the window (33 to 35 if it walked from its start again).  And the scales under which the
-    kernel takes squares for exact are above 1/512 of the abs-max, as exact squares need."""
+    itself that is 18 candidates; ordinary blocks end well before (15 on these inputs)."""
     if "fma" not in open("/proc/cpuinfo").read():
         pytest.skip("host CPU has no FMA instruction")
     exe = str(tmp_path / "search_walk_check")
@@ -112,18 +109,42 @@ def test_walk_over_single_blocks_with_the_kernels_rules(tmp_path):
     rows = [dict(t.split("=") for t in l.split()[1:]) for l in res.stdout.splitlines() if "cases=" in l]
     assert res.returncode == 0 and len(rows) == 16
     for r in rows:
-        assert int(r["cases"]) > 100 and int(r["bad"]) == 0 and int(r["most"]) <= (25 if int(r["on"]) else 18), r
-        assert float(r["far"]) < 512.0, r
+        assert int(r["cases"]) > 100 and int(r["bad"]) == 0 and int(r["most"]) <= 18, r
+
+
+def test_window_over_single_blocks_with_the_kernels_rules(tmp_path):
+    """Of the same blocks, those that the window takes: it tries eight codes, one above, the 15 of the 16 steps down that
+    are not among the eight, and the floor, 25 at most, where it goes on down behind the window (33 to 35 if it walked from
+    its start again).  And the scales under which the kernel takes squares for exact are above 1/512 of the abs-max, as
+    exact squares need."""
+    if "fma" not in open("/proc/cpuinfo").read():
+        pytest.skip("host CPU has no FMA instruction")
+    exe = str(tmp_path / "search_walk_check")
+    subprocess.run([CLANG, "-O2", "-std=c++17", "-ffp-contract=off", "-mfma", "-Wall", "-Werror",
+                    os.path.join(HERE, "host", "search_walk_check.cpp"), "-o", exe, "-lm"], check=True)
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    print(res.stdout)
+    rows = [dict(t.split("=") for t in l.split()[1:]) for l in res.stdout.splitlines() if "cases=" in l]
+    assert res.returncode == 0 and len(rows) == 16
+    for r in rows:
+        assert int(r["bad"]) == 0 and int(r["most_on"]) <= 25 and float(r["far"]) < 512.0, r
     assert sum(int(r["on"]) for r in rows) > 40 and sum(int(r["window"]) for r in rows) > 20000
 
 
 def test_search_rules_are_defined_once():
     """In the header that the host check compiles, not a second time in a kernel file."""
     csrc = os.path.join(os.path.dirname(HERE), "paper_2605_08565_amd", "csrc")
-    names = ("walk_scale_bias(uint32_t", "walk_halved(uint32_t", "walk_last_odd(float", "saturation_loss(float", "walk_patience(int", "window_first(uint32_t start, uint32_t", "window_steps(int", "make_recip_from(float")
+    names = ("walk_scale_bias(uint32_t", "walk_halved(uint32_t", "walk_last_odd(float", "saturation_loss(float", "walk_patience(int", "make_recip_from(float")
     for f in os.listdir(csrc):
         text = open(os.path.join(csrc, f)).read()
         assert all((n in text) == (f == "mxq_arith.hpp") for n in names), f
+
+
+def test_window_rules_are_defined_once():
+    csrc = os.path.join(os.path.dirname(HERE), "paper_2605_08565_amd", "csrc")
+    for f in os.listdir(csrc):
+        text = open(os.path.join(csrc, f)).read()
+        assert all((n in text) == (f == "mxq_arith.hpp") for n in ("window_first(uint32_t start, uint32_t", "window_steps(int")), f
 
 
 def test_pruned_search_kernels_leave_room_for_wavefronts(tmp_path):
