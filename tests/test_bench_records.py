@@ -45,3 +45,16 @@ def test_every_profile_summary_names_its_commit_and_command():
         assert re.search(r"Taken at commit `[0-9a-f]{7,40}`", text), f
         assert "bench.py" in text, f
         assert len(text) < 20000, f
+
+
+def test_vector_issue_time_is_that_of_the_counted_instructions():
+    """One wavefront instruction serves 64 chunks and occupies one of 1024 SIMDs for four cycles: the column `issue (us)` of the
+    committed summary follows from its instructions per chunk."""
+    import bench
+    rows, _ = bench.profile_rows(bench.PROFILE_VALU)
+    assert len(rows) > 20
+    for kern, cells in rows.items():
+        # instructions per chunk are printed to 0.1 and the time to 0.01 us
+        want, per_chunk = float(cells[6]), float(cells[2])
+        slack = 0.005 + 0.05 / per_chunk * want
+        assert abs(bench.valu_issue_ms(per_chunk, bench.N_ELEM) * 1e3 - want) <= slack + 1e-6, kern
